@@ -78,7 +78,8 @@ struct infmllm_stream {
     float* Wb;           // [Hkv][cap]
     int32_t* I;          // [Hkv][B]
     FwdScratch fwd;      // scratch of the row-split scoring launch
-    float* dec_part;     // partials of the decoding step
+    float* dec_part;     // partials of the decoding step (plain-arithmetic kernels)
+    RowsScratch rows{nullptr, nullptr, nullptr, 0};   // partials of attention launches with a cut key range (bf16 on the matrix cores)
     // optional per-kernel timing: one event pair per kernel per step, up to prof_cap steps
     std::vector<hipEvent_t> prof_ev;   // [prof_cap][INFMLLM_K_COUNT][2]
     std::vector<char> prof_used;       // [prof_cap][INFMLLM_K_COUNT]
@@ -100,9 +101,12 @@ struct infmllm_stream {
         prof_ev.clear(); prof_used.clear(); prof_cap = 0; prof_steps = 0;
     }
 
+    bool mfma() const { return dtype == INFMLLM_BF16 && impl == 0; }
+
     struct Layout {
-        size_t K, V, pos, score, rank, row, lse, Wb, I, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, dec_part, K_rot,
-            kc_rot, q_rot, rope_tab, total;
+        size_t K, V, pos, score, rank, row, lse, Wb, I, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, dec_part, rows_o,
+            rows_ml, rows_arrived, K_rot, kc_rot, q_rot, rope_tab, total;
+        long rows_cap;
     };
     Layout layout() const
     {
@@ -127,7 +131,17 @@ struct infmllm_stream {
         L.mv_count = off; off += up((size_t)g.Hkv * 4);
         // row-split scoring (bf16 streams): partial column sums and arrival counters
         L.score_part = off; off += up(g.elt == 2 ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
-        L.dec_part = off; off += up(g.max_decode > 0 ? (size_t)g.Hq * DECODE_MAX_SPLIT * (g.d + 2) * 4 + (size_t)g.Hkv * 4 : 0);
+        L.dec_part = off; off += up(g.max_decode > 0 && !mfma() ? (size_t)g.Hq * DECODE_MAX_SPLIT * (g.d + 2) * 4 + (size_t)g.Hkv * 4 : 0);
+        // (query row, piece) pairs of a launch with a cut key range: at most ROWS_MAX_PARTS, at least one token's
+        L.rows_cap = 0;
+        if (mfma()) {
+            const long most = (long)g.Hq * std::max(g.max_chunk, g.max_decode) * ((g.cap + 127) / 128);
+            const int ksd = rows_decode_keys_per_piece(g);
+            L.rows_cap = std::max(std::min(most, ROWS_MAX_PARTS), (long)g.Hq * ((g.B + g.max_decode + ksd - 1) / ksd));
+        }
+        L.rows_o = off; off += up((size_t)L.rows_cap * g.d * 4);
+        L.rows_ml = off; off += up((size_t)L.rows_cap * 8);
+        L.rows_arrived = off; off += up(mfma() ? (size_t)g.Hkv * 4 : 0);
         const bool rope = rope_base > 0.0;
         L.K_rot = off; off += rope ? kv : 0;
         L.kc_rot = off; off += up(rope ? (size_t)g.max_chunk * g.Hkv * g.d * g.elt : 0);
@@ -273,6 +287,10 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     s->I = (int32_t*)(base + L.I);
     s->fwd.score_part = (float*)(base + L.score_part);
     s->dec_part = (float*)(base + L.dec_part);
+    s->rows.o = (float*)(base + L.rows_o);
+    s->rows.ml = (float2*)(base + L.rows_ml);
+    s->rows.arrived = (int*)(base + L.rows_arrived);
+    s->rows.cap_rows = L.rows_cap;
     s->K_rot = base + L.K_rot;
     s->kc_rot = base + L.kc_rot;
     s->q_rot = base + L.q_rot;
@@ -366,7 +384,7 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
     const Geometry& g = s->g;
     const CacheView& cur = s->cache;
     const int t = s->len, n = t + L;
-    const bool mfma = (s->dtype == INFMLLM_BF16 && s->impl == 0);
+    const bool mfma = s->mfma();
     hipError_t e;
 
     // An evicting step on the matrix-core path never appends: attention and scoring read the chunk's
@@ -396,7 +414,7 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
         s->rot_rows = in_place ? t : n;
     }
     s->mark(INFMLLM_K_ATTN, 0);
-    e = mfma ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->st)
+    e = mfma ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, s->st)
              : launch_attn_simple(g, att, q_att, t, L, out, s->lse, s->st);
     if (e != hipSuccess) return fail_hip(e, "attention");
     s->mark(INFMLLM_K_ATTN, 1);
@@ -575,34 +593,45 @@ int infmllm_stream_profile_read(infmllm_stream_t* s, float* ms, int* launches)
     return INFMLLM_OK;
 }
 
-// One decoding step on a stream whose state has been checked: launches, then the host-side counters.
-static int decode_one(infmllm_stream* s, const void* q, const void* k, const void* v, void* out)
+// Decoding steps of T tokens on a stream whose state has been checked: launches, then the host-side counters.  On the
+// matrix cores the T tokens share one launch (decode_tokens_per_launch says how many may), else T is 1.
+static int decode_some(infmllm_stream* s, const void* q, const void* k, const void* v, void* out, int T)
 {
     s->mark(INFMLLM_K_DECODE, 0);
+    const int t = s->len;
     hipError_t e;
+    CacheView att = s->cache;
     if (s->rope_base > 0.0) {
-        // the token's row enters the cache as given; the decoding kernels see the turned copies (and put the
-        // turned key at row t of K_rot themselves)
-        const CacheView& cur = s->cache;
-        const int t = s->len;
-        if ((e = launch_append(s->g, cur, k, v, t, 1, s->streamed, s->st)) != hipSuccess) return fail_hip(e, "decode: append");
-        e = launch_rope(s->g, cur.K, s->K_rot, cur.rank, s->rot_rows < t ? s->rot_rows : t, t, k, s->kc_rot, q, s->q_rot,
-                        t, 1, s->rope_tab, s->st);
+        // the tokens' rows enter the cache as given; the decoding kernels see the turned copies (and put the
+        // turned keys at rows t.. of K_rot themselves)
+        if ((e = launch_append(s->g, s->cache, k, v, t, T, s->streamed, s->st)) != hipSuccess) return fail_hip(e, "decode: append");
+        e = launch_rope(s->g, s->cache.K, s->K_rot, s->cache.rank, s->rot_rows < t ? s->rot_rows : t, t, k, s->kc_rot, q,
+                        s->q_rot, t, T, s->rope_tab, s->st);
         if (e != hipSuccess) return fail_hip(e, "decode: position encoding");
-        CacheView att = cur;
         att.K = s->K_rot;
-        e = launch_decode(s->g, att, s->q_rot, s->kc_rot, v, t, s->streamed, out, s->dec_part, DECODE_MAX_SPLIT, s->st);
-        s->rot_rows = t + 1;
-    } else {
-        e = launch_decode(s->g, s->cache, q, k, v, s->len, s->streamed, out, s->dec_part, DECODE_MAX_SPLIT, s->st);
+        q = s->q_rot;
+        k = s->kc_rot;
+        s->rot_rows = t + T;
     }
+    e = s->mfma() ? launch_rows_decode(s->g, att, q, k, v, t, T, s->streamed, out, s->rows, s->st)
+                  : launch_decode(s->g, att, q, k, v, t, s->streamed, out, s->dec_part, DECODE_MAX_SPLIT, s->st);
     if (e != hipSuccess) return fail_hip(e, "decode");
     s->mark(INFMLLM_K_DECODE, 1);
-    s->len += 1;
-    s->streamed += 1;
+    s->len += T;
+    s->streamed += T;
     s->last_cnd = 0;
     if (s->prof_steps < s->prof_cap) ++s->prof_steps;
     return INFMLLM_OK;
+}
+
+static int decode_tokens_per_launch(const infmllm_stream* s, int left)
+{
+    if (!s->mfma()) return 1;
+    int T = left < DECODE_MAX_TOKENS ? left : DECODE_MAX_TOKENS;
+    if (s->rope_base > 0.0 && T > s->g.max_chunk) T = s->g.max_chunk;      // what the turned copies hold
+    const int ks = rows_decode_keys_per_piece(s->g);
+    while (T > 1 && (long)s->g.Hq * T * ((s->len + T + ks - 1) / ks) > s->rows.cap_rows) --T;
+    return T;
 }
 
 int infmllm_decode_n(infmllm_stream_t* s, const void* q, const void* k, const void* v, void* out, int n_tokens)
@@ -618,10 +647,12 @@ int infmllm_decode_n(infmllm_stream_t* s, const void* q, const void* k, const vo
     if (s->streamed + n_tokens > (int64_t)INT32_MAX)
         return fail(INFMLLM_ECAPACITY, "decode: stream positions would exceed 2^31-1");
     const size_t qrow = (size_t)s->g.Hq * s->g.d * s->g.elt, krow = (size_t)s->g.Hkv * s->g.d * s->g.elt;
-    for (int i = 0; i < n_tokens; ++i) {
-        const int rc = decode_one(s, (const char*)q + i * qrow, (const char*)k + i * krow, (const char*)v + i * krow,
-                                  (char*)out + i * qrow);
+    for (int i = 0; i < n_tokens;) {
+        const int T = decode_tokens_per_launch(s, n_tokens - i);
+        const int rc = decode_some(s, (const char*)q + i * qrow, (const char*)k + i * krow, (const char*)v + i * krow,
+                                   (char*)out + i * qrow, T);
         if (rc != INFMLLM_OK) return rc;
+        i += T;
     }
     return INFMLLM_OK;
 }

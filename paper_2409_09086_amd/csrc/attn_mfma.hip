@@ -691,10 +691,25 @@ hipError_t launch_fwd_cfg(const Geometry& g, const CacheView& c, const KeySource
 }
 
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                            void* out, float* lse, hipStream_t st)
+                            void* out, float* lse, const RowsScratch& sc, hipStream_t st)
 {
+    if (g.d != 64 && g.d != 128) return hipErrorInvalidValue;
+    if (g.attn_tile == 0) {
+        // Few query rows: attn_rows, which cuts the key range over the workgroups.  Examples, measured, attn_rows against
+        // the kernels below: 32 x 128 heads, 4096 keys: 24 / 49 us with 37 rows, 22 / 50 with 64; 16 heads on 4 of 128,
+        // 5000 keys, 320 rows: 37 / 61; 8 x 64 heads, 4000 keys, 320 rows: 19 / 72.  The time of the kernels below, fitted
+        // to measurements like that of rows_chunk_plan: per round of workgroups over the 256 CUs, and the more the
+        // fuller the chip; at head_dim 64 several workgroups share a CU.
+        const int n = t + L, wgs = g.d == 128 ? g.Hq * ((L + 63) / 64) : g.Hq * ((L + 127) / 128);
+        const int wgs2 = g.Hq * ((L + 31) / 32) / 4;             // of 128 rows, head_dim 128 (see below)
+        const float rounds = (float)(((g.d == 128 && wgs2 >= 140 ? wgs2 : wgs) + 255) / 256), fill = wgs < 256 ? (float)wgs / 256.f : 1.f;
+        const float other = g.d == 64 ? (7.f + 0.0136f * (float)n) * (1.f + 0.35f * (rounds - 1.f))
+                            : wgs2 >= 140 ? rounds * (10.f + 0.0148f * (float)n)
+                                          : rounds * (9.f + 0.0096f * (float)n) * (1.f + 0.15f * fill);
+        RowsPlan plan{};
+        if (rows_chunk_plan(g, n, L, sc.cap_rows, plan) < other) return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, plan, st);
+    }
     if (g.d == 64) return launch_fwd_cfg<64, 4, 1, 2>(g, c, ks, q, t, L, out, lse, st);
-    if (g.d != 128) return hipErrorInvalidValue;
     // 128 query rows x 64 keys per wavefront-tile is the efficient shape; when that grid would cover
     // only about half of the chip (128 workgroups at 32 heads x 512 rows), 64-row workgroups with four
     // key ways inside the workgroup are faster.  g.attn_tile > 0 (a test hook) forces one shape.

@@ -1,4 +1,5 @@
-// Decoding step for gfx950 (Sec. 3.2, last paragraph): one new token per call, its query attends
+// Decoding step for gfx950 in plain fp32 arithmetic (Sec. 3.2, last paragraph; bf16 streams decode in attn_rows.hip
+// unless they were created with the plain-arithmetic override): one new token per call, its query attends
 // all t cached keys plus its own, nothing is evicted.
 //
 // One query row against n keys is a matrix-vector product: every K and V byte is used once, so the

@@ -92,14 +92,37 @@ struct KeySource {
     const void* v;
 };
 
+// Partial results of attention launches whose key range is cut into pieces (attn_rows.hip): for every
+// (query row, piece) the un-normalised output, the softmax reference and the sum.
+struct RowsScratch {
+    float* o;           // [cap_rows][d]
+    float2* ml;         // [cap_rows]
+    int* arrived;       // [Hkv] tickets, zero between launches
+    long cap_rows;      // most (query row, piece) pairs of a launch
+};
+
 // a2 on bf16 MFMA (bf16 streams only): out and the row log-sum-exp (base 2).
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                            void* out, float* lse, hipStream_t st);
+                            void* out, float* lse, const RowsScratch& sc, hipStream_t st);
 
 // The same for head_dim 128 with 64 query rows per wavefront (one wavefront per SIMD, 256-row workgroups):
 // the shape for long key ranges and grids that fill the chip; launch_attn_mfma picks it by itself.
 hipError_t launch_attn_mfma64(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
                               void* out, float* lse, hipStream_t st);
+
+constexpr long ROWS_MAX_PARTS = 16384;
+constexpr int DECODE_MAX_TOKENS = 64;    // most tokens a launch decodes
+// Decoding on bf16 MFMA: T tokens in one launch (and a merging one where there are many rows); the tokens' keys and
+// values become cache rows t .. t+T-1 (stream positions pos ..).  Needs Hq * T * pieces <= sc.cap_rows.
+int rows_decode_keys_per_piece(const Geometry& g);
+hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void* q, const void* k, const void* v, int t,
+                              int T, int64_t pos, void* out, const RowsScratch& sc, hipStream_t st);
+// Chunk attention (a2) with few query rows, the key range cut into pieces of plan.keys keys, workgroups of 16 * plan.nrb
+// query rows.  rows_chunk_plan fills the plan in and returns the time it should take, in us.
+struct RowsPlan { int nrb, keys; };
+float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, RowsPlan& plan);
+hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
+                             void* out, float* lse, const RowsScratch& sc, const RowsPlan& plan, hipStream_t st);
 
 // a3+a4 on bf16 MFMA (bf16 streams only).
 hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q,
@@ -160,7 +183,8 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 // warm-up: I[h][j] = j for j < n.
 hipError_t launch_iota(const Geometry& g, int n, int32_t* user_I, int32_t* user_count, hipStream_t st);
 
-// Decoding step: appends the token's k, v as cache row t and attends all t + 1 keys with q (one
+// Decoding step in plain fp32 arithmetic (fp32 streams, bf16 ones with the plain-arithmetic override): appends the
+// token's k, v as cache row t and attends all t + 1 keys with q (one
 // row per query head).  part is scratch of [Hq][max_split][d + 2] floats followed by Hkv ints that are zero
 // between launches (ticket counters; the last workgroup of a kv-head to finish merges its splits).
 constexpr int DECODE_MAX_SPLIT = 64;

@@ -1,0 +1,59 @@
+"""attn_rows: attention of few query rows with the key range cut into pieces, against the fp64 oracle.  Chunks whose
+rows, pieces and key runs end in every way the kernel distinguishes, decoding of several tokens per launch, and that
+a token's output does not depend on how many tokens share the call."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import OracleStream
+from paper_2409_09086_amd import binding as B
+from paper_2409_09086_amd.workloads import random_chunk
+from _parity import LockStep
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads,kv,d,budget,recent,chunks", [
+    (4, 4, 128, 900, 200, [900, 1, 16, 17, 33, 300]),     # four pieces; 1, 16 and 17 rows (tickets, then a merging launch)
+    (8, 2, 128, 1500, 300, [800, 700, 5, 37, 64]),        # grouped heads: a row group holds several tokens
+    (6, 2, 64, 777, 100, [777, 3, 11, 50]),               # three heads per group, runs that straddle the cache's end
+    (2, 1, 64, 5000, 500, [2500, 2500, 2, 40]),           # more than sixteen pieces' worth of keys
+    (16, 16, 64, 600, 150, [300, 300, 128, 31]),          # many heads: few pieces or one
+    (1, 1, 128, 31, 8, [31, 7, 20]),                      # fewer keys than a run
+])
+def test_short_chunks_match_oracle(heads, kv, d, budget, recent, chunks):
+    gpu = B.Stream(budget, recent, heads, kv, d, dtype=torch.bfloat16, bias=1e-3, max_chunk=max(chunks))
+    ls = LockStep(gpu, OracleStream(budget, recent, heads, kv, d, bias=1e-3))
+    for step, L in enumerate(chunks):
+        print("rows", (heads, kv, d, budget), "step", step, "L", L, flush=True)
+        ls.step(*random_chunk(3100 + step, L, heads, kv, d, "bf16"), check_state=True)
+
+
+@pytest.mark.parametrize("heads,kv,d,budget,rope", [(4, 4, 128, 1300, None), (8, 2, 128, 1300, None), (6, 2, 64, 700, None),
+                                                    (4, 1, 64, 5000, None), (8, 2, 128, 600, 10000.0)])
+def test_tokens_do_not_depend_on_how_many_share_a_call(heads, kv, d, budget, rope):
+    """decode_n in calls of 1, 2, 17 and 40 tokens against a twin that decodes one at a time: outputs and cache bit for
+    bit; and against the oracle with the error of one rounding to bf16 (eight significant bits: at most 2^-8 relative) plus 2e-5 for the fp32 sums of
+    a few thousand terms of size |v| <= 5 (2^-24 * 5 * sqrt(5000)): the weights enter the product unrounded."""
+    max_chunk, nd = 64, 60
+    mk = lambda: B.Stream(budget, budget // 4, heads, kv, d, dtype=torch.bfloat16, max_chunk=max_chunk, max_decode=nd,
+                          rope_base=rope)
+    a, b = mk(), mk()
+    orc = OracleStream(budget, budget // 4, heads, kv, d, rope_base=rope or 0.0, rope_round="bf16" if rope else None)
+    g = torch.Generator().manual_seed(17)
+    K, V = torch.randn((kv, budget, d), generator=g).bfloat16(), torch.randn((kv, budget, d), generator=g).bfloat16()
+    pos = torch.arange(budget, dtype=torch.int32).repeat(kv, 1).contiguous()
+    for s in (a, b):
+        s.load(K.cuda(), V.cuda(), pos.cuda(), budget)
+    orc.load(K.double().numpy(), V.double().numpy(), pos.numpy(), budget)
+    for key, n in enumerate((1, 2, 17, 40)):
+        print("tokens", (heads, kv, d, budget, rope), "n", n, flush=True)
+        q, k, v = random_chunk(3200 + key, n, heads, kv, d, "bf16")
+        out = a.decode_n(q.cuda(), k.cuda(), v.cuda())
+        one = torch.cat([b.decode(*(x[i:i + 1].contiguous().cuda() for x in (q, k, v))) for i in range(n)])
+        assert torch.equal(out.view(torch.int16), one.view(torch.int16)), "%d tokens per call" % n
+        ref = np.concatenate([orc.decode(*(x[i:i + 1].double().numpy() for x in (q, k, v))) for i in range(n)])
+        err = np.abs(out.double().cpu().numpy() - ref)
+        assert (err <= 2.0 ** -8 * np.abs(ref) + 2e-5).all(), err.max()
+    for x, y in zip(a.export(), b.export()):
+        assert torch.equal(x, y)
