@@ -1,0 +1,304 @@
+// Device helpers shared by the attention kernels that cut the key range into pieces (attn_rows.hip, attn_rows64.hip).
+#pragma once
+#include "launch.h"
+#include "mfma_common.h"
+
+namespace infmllm {
+
+struct RowsArgs {
+    const uint16_t* q;         // [L][Hq][D]
+    uint16_t* K;               // cache
+    uint16_t* V;
+    const uint16_t* kc;        // keys and values from row tc on: chunk tensors [L][Hkv][D]
+    const uint16_t* vc;
+    uint16_t* out;             // [L][Hq][D]
+    float* lse2;               // [Hq][max_chunk], or null (decoding)
+    float* part_o;             // [Hkv][M][nsplit][D]
+    float2* part_ml;           // [Hkv][M][nsplit]
+    int* arrived;              // [Hkv] tickets, zero between launches; null: a second launch merges
+    // decoding: the tokens become cache rows t .. t+L-1
+    int32_t* pos;              // null: nothing is appended
+    float* score;
+    int32_t* rank;
+    int32_t* row;
+    int pos0;
+    int t, L, tc, Hq, Hkv, G, cap, max_chunk, ks, nsplit;
+    uint32_t inv_g;            // floor(2^32 / G) + 1
+    float c;                   // scale * log2(e)
+};
+
+void launch_rows64(const RowsArgs& a, hipStream_t st);
+
+namespace {
+
+constexpr int RW_NW = 8, RW_NT = 64 * RW_NW;        // wavefronts, threads
+constexpr int RW_RUN = 32;                         // keys of a wavefront's run
+constexpr int RW_PASS = RW_NW * RW_RUN;            // keys of a workgroup's pass
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef const __attribute__((address_space(1))) void global_void;
+
+template <int D, int NRB>
+struct RowsCfg {
+    static constexpr int ROWB = D * 2;             // bytes of a K or V row
+    static constexpr int RUN = RW_RUN * ROWB;      // bytes of a run of K or of V
+    static constexpr int STAGE = 2 * RUN;          // ... of both
+    static constexpr int NS = D / 32;              // MFMAs along head_dim of one 16-key block of S
+    static constexpr int NC = D / 16;              // 16-column blocks of O
+    static constexpr int NL = RUN / 1024;          // direct loads per run of K or V (1 KB each)
+    static constexpr int RPL = 1024 / ROWB;        // rows per direct load
+    static constexpr int ROWS = 16 * NRB;
+    static constexpr int MB = ROWS * D * 4;        // bytes a wavefront leaves for the merge, in its own buffers
+    static_assert(MB <= STAGE, "the merge reuses the buffers of the tiles");
+};
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// maximum / sum over the four 16-lane groups of a wavefront (lanes l, l ^ 16, l ^ 32, l ^ 48), in every lane
+__device__ __forceinline__ float groups_max(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return xhalf_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float groups_sum(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return xhalf_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+
+// 16 bytes per lane, memory -> 1 KB of LDS at dst: lane's address base + off + soff, base and soff uniform, `bytes` =
+// the extent of what base points at.  (A buffer load: the compiler counts it like any other load.  It takes global_load_lds for one
+// that may also be an LDS access, and drains every load in flight at the next wait.)
+// THROUGH: from where every XCD's agent-scope stores go (see part_load2).
+template <bool THROUGH = false>
+__device__ __forceinline__ void buffer_to_lds(const void* base, int bytes, char* dst, int off, int soff = 0)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000),
+                                             (lds_void*)dst, 16, off, soff, 0, THROUGH ? 16 /* sc1 */ : 0);
+}
+
+// sum / maximum over N = 8 or 16 consecutive lanes, the same bits in all of them: neighbours, pairs, quads, eights
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ float lanes_sum(float x)
+{
+    x += dpp<0xB1>(x);                             // quad_perm [1,0,3,2]
+    x += dpp<0x4E>(x);                             // quad_perm [2,3,0,1]
+    x += dpp<0x141>(x);                            // row_half_mirror
+    if (N == 16) x += dpp<0x140>(x);               // row_mirror
+    return x;
+}
+template <int N>
+__device__ __forceinline__ float lanes_max(float x)
+{
+    x = fmaxf(x, dpp<0xB1>(x));
+    x = fmaxf(x, dpp<0x4E>(x));
+    x = fmaxf(x, dpp<0x141>(x));
+    if (N == 16) x = fmaxf(x, dpp<0x140>(x));
+    return x;
+}
+
+template <int OFF>
+__device__ __forceinline__ bf16x4 rw_read_tr16(uint32_t addr)
+{
+    bf16x4 v;
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+    return v;
+}
+template <int OFF>
+__device__ __forceinline__ bf16x8 rw_read_b128(uint32_t addr)
+{
+    bf16x8 v;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+    return v;
+}
+template <int N>
+__device__ __forceinline__ void wait_loads()       // all but the N newest
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Partial results of a piece: un-normalised o[D], reference maximum and sum, per (kv-head, row, piece).
+// THROUGH: read and written where every XCD sees them (the last workgroup of a launch merges), else plainly.
+template <bool THROUGH>
+__device__ __forceinline__ float2 part_load2(const float2* p)
+{
+    if constexpr (THROUGH) {
+        const uint64_t a = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return float2{__uint_as_float((uint32_t)a), __uint_as_float((uint32_t)(a >> 32))};
+    } else {
+        return *p;
+    }
+}
+
+__device__ __forceinline__ void part_store2(float2* p, float2 v)
+{
+    __hip_atomic_store((uint64_t*)p, (uint64_t)__float_as_uint(v.x) | ((uint64_t)__float_as_uint(v.y) << 32), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// How the shares of a row are added, those of a workgroup's wavefronts as well as those of its pieces, and the same bits
+// whoever does it: under their largest reference, products rounded before they are added, neighbours first, then pairs,
+// and so on (a binary tree over the index; missing shares weigh 0).  Piece s belongs to class s % 16, and a class absorbs
+// its pieces in ascending order before the tree.  A share in which the row saw no key has m = -inf and weight 0, so pieces
+// past the row's last key change nothing.
+constexpr int RW_CLASSES = 16;
+constexpr int RW_TICKET_PARTS = 256;               // most (row, piece) pairs of a kv-head that its last workgroup merges
+struct PieceSum {
+    float m, l;
+    f32x4 o;                   // four of the row's columns
+    __device__ __forceinline__ void absorb(float2 ml, f32x4 x)
+    {
+        const float mn = fmaxf(m, ml.x), mz = (mn == -__builtin_inff()) ? 0.f : mn;
+        const float wa = fast_exp2(m - mz), wb = fast_exp2(ml.x - mz);
+        m = mn;
+        l = __builtin_fmaf(wa, l, wb * ml.y);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(wa, o[e], wb * x[e]);
+    }
+    // the tree over N consecutive lanes: few instructions, for few rows
+    template <int N>
+    __device__ __forceinline__ void add_lanes()
+    {
+#pragma clang fp contract(off)
+        const float mt = lanes_max<N>(m), mz = (mt == -__builtin_inff()) ? 0.f : mt;
+        const float w = fast_exp2(m - mz);
+        m = mt;
+        l = lanes_sum<N>(w * l);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = lanes_sum<N>(w * o[e]);
+    }
+    __device__ __forceinline__ f32x4 out() const
+    {
+        const float inv = 1.0f / l;
+        return f32x4{o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
+    }
+    __device__ __forceinline__ float lse() const { return m + __builtin_log2f(l); }
+};
+// the tree in one thread: no lane does another one's work, for many rows
+template <int N>
+__device__ __forceinline__ PieceSum add_tree(PieceSum (&p)[N])
+{
+#pragma clang fp contract(off)
+    float mt = p[0].m;
+#pragma unroll
+    for (int i = 1; i < N; ++i) mt = fmaxf(mt, p[i].m);
+    const float mz = (mt == -__builtin_inff()) ? 0.f : mt;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float w = fast_exp2(p[i].m - mz);
+        p[i].l = w * p[i].l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[i].o[e] = w * p[i].o[e];
+    }
+#pragma unroll
+    for (int st = 1; st < N; st *= 2)
+#pragma unroll
+        for (int i = 0; i < N; i += 2 * st) {
+            p[i].l = p[i].l + p[i + st].l;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[i].o[e] = p[i].o[e] + p[i + st].o[e];
+        }
+    p[0].m = mt;
+    return p[0];
+}
+
+__device__ __forceinline__ void store_out4(uint16_t* p, f32x4 v)
+{
+    bf16x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = (__bf16)v[e];
+    *(bf16x4*)p = w;
+}
+
+
+
+// token of a row (row = token * G + head in group): row / G; inv_g = floor(2^32 / G) + 1 is exact for the at most 2^20
+// rows of a kv-head
+__device__ __forceinline__ int rows_token(const RowsArgs& a, int rho) { return a.G == 1 ? rho : (int)__umulhi((uint32_t)rho, a.inv_g); }
+
+// Tiles in LDS: rows are not padded; the 16-byte pieces of a row are permuted at load time instead (by choosing which
+// piece of its row a lane fetches), so that sixteen rows of K (or Q) at one piece, and the sixteen rows of a transpose
+// read of V (32 bytes of each), spread over the banks.  Piece p of row r lies in slot p ^ swz(r).
+template <int D> __device__ __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+template <int D> __device__ __forceinline__ int swz_v(int r) { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); }
+
+// A wavefront's direct loads of a run: 32 rows of K and / or V from row k0 on, to `dst` (K) and `dst` + RUN (V).
+template <int D>
+struct RunLoader {
+    static constexpr int ROWB = D * 2, RUN = RW_RUN * ROWB, NL = RUN / 1024, RPL = 1024 / ROWB;
+    const uint16_t *Kh, *Vh, *kch, *vch;
+    int tc, n, cap, L, crs;                        // crs: row stride of the chunk tensors
+    int lrow, lpos;                                // this lane's row and slot of a load
+    __device__ __forceinline__ RunLoader(const RowsArgs& a, int h, int lane)
+        : Kh(a.K + (size_t)h * a.cap * D), Vh(a.V + (size_t)h * a.cap * D), kch(a.kc + (size_t)h * D), vch(a.vc + (size_t)h * D),
+          tc(a.tc), n(a.t + a.L), cap(a.cap), L(a.L), crs(a.Hkv * D), lrow(lane / (ROWB / 16)), lpos(lane % (ROWB / 16))
+    {
+    }
+    template <bool K, bool V>
+    __device__ __forceinline__ void load(int k0, char* dst) const
+    {
+        // (past the last key the rows of a warm-up step's cache are read as they are: finite, and masked)
+        const bool in_cache = k0 + RW_RUN <= (tc == n ? cap : tc), in_chunk = k0 >= tc && k0 + RW_RUN <= n;
+        if (in_cache || in_chunk) {                // rows a fixed stride apart
+            const int stride = in_cache ? ROWB : crs * 2, at = (in_cache ? k0 : k0 - tc) * stride;
+            const int bytes = (in_cache ? cap : L) * stride - at;
+            const uint16_t *k_cache = Kh, *k_chunk = kch, *v_cache = Vh, *v_chunk = vch;
+            const char* kp = (const char*)(in_cache ? k_cache : k_chunk) + at;
+            const char* vp = (const char*)(in_cache ? v_cache : v_chunk) + at;
+            if (K) {
+#pragma unroll
+                for (int u = 0; u < NL; ++u)
+                    buffer_to_lds(kp, bytes, dst + u * 1024, lrow * stride + ((lpos ^ swz_k<D>(u * RPL + lrow)) * 16), u * RPL * stride);
+            }
+            if (V) {
+#pragma unroll
+                for (int u = 0; u < NL; ++u)
+                    buffer_to_lds(vp, bytes, dst + RUN + u * 1024, lrow * stride + ((lpos ^ swz_v<D>(u * RPL + lrow)) * 16), u * RPL * stride);
+            }
+        } else {                                   // where the cache or the chunk ends: row by row
+#pragma nounroll
+            for (int u = 0; u < NL; ++u) {
+                const int r = u * RPL + lrow, key = min(k0 + r, n - 1);
+                const bool cached = key < tc;
+                const size_t off = cached ? (size_t)key * D : (size_t)(key - tc) * crs;
+                const uint16_t *ka = Kh + off, *kb = kch + off, *va = Vh + off, *vb = vch + off;
+                if (K) __builtin_amdgcn_global_load_lds((global_void*)((cached ? ka : kb) + (lpos ^ swz_k<D>(r)) * 8), (lds_void*)(dst + u * 1024), 16, 0, 0);
+                if (V) __builtin_amdgcn_global_load_lds((global_void*)((cached ? va : vb) + (lpos ^ swz_v<D>(r)) * 8), (lds_void*)(dst + RUN + u * 1024), 16, 0, 0);
+            }
+        }
+    }
+};
+
+// Four columns of a row, merged over the workgroup's wavefronts: the finished output, or this piece's share of it.
+template <int D>
+__device__ __forceinline__ void leave_row(const RowsArgs& a, int h, int sp, int rho, int d, const PieceSum& ps)
+{
+    if (a.nsplit == 1) {
+        const int tok = rows_token(a, rho), gq = h * a.G + rho - tok * a.G;
+        store_out4(a.out + ((size_t)tok * a.Hq + gq) * D + d, ps.out());
+        if (a.lse2 && d == 0) a.lse2[(size_t)gq * a.max_chunk + tok] = ps.lse();
+        return;
+    }
+    const size_t at = ((size_t)h * a.L * a.G + rho) * a.nsplit + sp;
+    float* po = a.part_o + at * D + d;
+    if (a.arrived) {
+        part_store2((float2*)po, float2{ps.o[0], ps.o[1]});
+        part_store2((float2*)po + 1, float2{ps.o[2], ps.o[3]});
+        if (d == 0) part_store2(a.part_ml + at, float2{ps.m, ps.l});
+    } else {
+        *(f32x4*)po = ps.o;
+        if (d == 0) a.part_ml[at] = float2{ps.m, ps.l};
+    }
+}
+
+}  // namespace
+}  // namespace infmllm

@@ -25,222 +25,11 @@
 // launch where there are many rows.
 #include <algorithm>
 
-#include "launch.h"
-#include "mfma_common.h"
+#include "attn_rows.h"
 
 namespace infmllm {
 
 namespace {
-
-constexpr int RW_NW = 8, RW_NT = 64 * RW_NW;        // wavefronts, threads
-constexpr int RW_RUN = 32;                         // keys of a wavefront's run
-constexpr int RW_PASS = RW_NW * RW_RUN;            // keys of a workgroup's pass
-
-typedef __attribute__((address_space(3))) void lds_void;
-typedef const __attribute__((address_space(1))) void global_void;
-
-template <int D, int NRB>
-struct RowsCfg {
-    static constexpr int ROWB = D * 2;             // bytes of a K or V row
-    static constexpr int RUN = RW_RUN * ROWB;      // bytes of a run of K or of V
-    static constexpr int STAGE = 2 * RUN;          // ... of both
-    static constexpr int NS = D / 32;              // MFMAs along head_dim of one 16-key block of S
-    static constexpr int NC = D / 16;              // 16-column blocks of O
-    static constexpr int NL = RUN / 1024;          // direct loads per run of K or V (1 KB each)
-    static constexpr int RPL = 1024 / ROWB;        // rows per direct load
-    static constexpr int ROWS = 16 * NRB;
-    static constexpr int MB = ROWS * D * 4;        // bytes a wavefront leaves for the merge, in its own buffers
-    static_assert(MB <= STAGE, "the merge reuses the buffers of the tiles");
-};
-
-__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// maximum / sum over the four 16-lane groups of a wavefront (lanes l, l ^ 16, l ^ 32, l ^ 48), in every lane
-__device__ __forceinline__ float groups_max(float x)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return xhalf_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
-}
-__device__ __forceinline__ float groups_sum(float x)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return xhalf_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-}
-
-
-// 16 bytes per lane, memory -> 1 KB of LDS at dst: lane's address base + off, base uniform, `bytes` = the extent of
-// what base points at.  (A buffer load: the compiler counts it like any other load.  It takes global_load_lds for one
-// that may also be an LDS access, and drains every load in flight at the next wait.)
-// THROUGH: from where every XCD's agent-scope stores go (see part_load2).
-template <bool THROUGH = false>
-__device__ __forceinline__ void buffer_to_lds(const void* base, int bytes, char* dst, int off)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000),
-                                             (lds_void*)dst, 16, off, 0, 0, THROUGH ? 16 /* sc1 */ : 0);
-}
-
-// sum / maximum over N = 8 or 16 consecutive lanes, the same bits in all of them: neighbours, pairs, quads, eights
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x)
-{
-    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
-}
-template <int N>
-__device__ __forceinline__ float lanes_sum(float x)
-{
-    x += dpp<0xB1>(x);                             // quad_perm [1,0,3,2]
-    x += dpp<0x4E>(x);                             // quad_perm [2,3,0,1]
-    x += dpp<0x141>(x);                            // row_half_mirror
-    if (N == 16) x += dpp<0x140>(x);               // row_mirror
-    return x;
-}
-template <int N>
-__device__ __forceinline__ float lanes_max(float x)
-{
-    x = fmaxf(x, dpp<0xB1>(x));
-    x = fmaxf(x, dpp<0x4E>(x));
-    x = fmaxf(x, dpp<0x141>(x));
-    if (N == 16) x = fmaxf(x, dpp<0x140>(x));
-    return x;
-}
-
-template <int OFF>
-__device__ __forceinline__ bf16x4 rw_read_tr16(uint32_t addr)
-{
-    bf16x4 v;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
-template <int OFF>
-__device__ __forceinline__ bf16x8 rw_read_b128(uint32_t addr)
-{
-    bf16x8 v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
-template <int N>
-__device__ __forceinline__ void wait_loads()       // all but the N newest
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Partial results of a piece: un-normalised o[D], reference maximum and sum, per (kv-head, row, piece).
-// THROUGH: read and written where every XCD sees them (the last workgroup of a launch merges), else plainly.
-template <bool THROUGH>
-__device__ __forceinline__ float2 part_load2(const float2* p)
-{
-    if constexpr (THROUGH) {
-        const uint64_t a = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return float2{__uint_as_float((uint32_t)a), __uint_as_float((uint32_t)(a >> 32))};
-    } else {
-        return *p;
-    }
-}
-
-__device__ __forceinline__ void part_store2(float2* p, float2 v)
-{
-    __hip_atomic_store((uint64_t*)p, (uint64_t)__float_as_uint(v.x) | ((uint64_t)__float_as_uint(v.y) << 32), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// How the shares of a row are added, those of a workgroup's wavefronts as well as those of its pieces, and the same bits
-// whoever does it: under their largest reference, products rounded before they are added, neighbours first, then pairs,
-// and so on (a binary tree over the index; missing shares weigh 0).  Piece s belongs to class s % 16, and a class absorbs
-// its pieces in ascending order before the tree.  A share in which the row saw no key has m = -inf and weight 0, so pieces
-// past the row's last key change nothing.
-constexpr int RW_CLASSES = 16;
-constexpr int RW_TICKET_PARTS = 256;               // most (row, piece) pairs of a kv-head that its last workgroup merges
-struct PieceSum {
-    float m, l;
-    f32x4 o;                   // four of the row's columns
-    __device__ __forceinline__ void absorb(float2 ml, f32x4 x)
-    {
-        const float mn = fmaxf(m, ml.x), mz = (mn == -__builtin_inff()) ? 0.f : mn;
-        const float wa = fast_exp2(m - mz), wb = fast_exp2(ml.x - mz);
-        m = mn;
-        l = __builtin_fmaf(wa, l, wb * ml.y);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(wa, o[e], wb * x[e]);
-    }
-    // the tree over N consecutive lanes: few instructions, for few rows
-    template <int N>
-    __device__ __forceinline__ void add_lanes()
-    {
-#pragma clang fp contract(off)
-        const float mt = lanes_max<N>(m), mz = (mt == -__builtin_inff()) ? 0.f : mt;
-        const float w = fast_exp2(m - mz);
-        m = mt;
-        l = lanes_sum<N>(w * l);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = lanes_sum<N>(w * o[e]);
-    }
-    __device__ __forceinline__ f32x4 out() const
-    {
-        const float inv = 1.0f / l;
-        return f32x4{o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
-    }
-    __device__ __forceinline__ float lse() const { return m + __builtin_log2f(l); }
-};
-// the tree in one thread: no lane does another one's work, for many rows
-template <int N>
-__device__ __forceinline__ PieceSum add_tree(PieceSum (&p)[N])
-{
-#pragma clang fp contract(off)
-    float mt = p[0].m;
-#pragma unroll
-    for (int i = 1; i < N; ++i) mt = fmaxf(mt, p[i].m);
-    const float mz = (mt == -__builtin_inff()) ? 0.f : mt;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const float w = fast_exp2(p[i].m - mz);
-        p[i].l = w * p[i].l;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[i].o[e] = w * p[i].o[e];
-    }
-#pragma unroll
-    for (int st = 1; st < N; st *= 2)
-#pragma unroll
-        for (int i = 0; i < N; i += 2 * st) {
-            p[i].l = p[i].l + p[i + st].l;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) p[i].o[e] = p[i].o[e] + p[i + st].o[e];
-        }
-    p[0].m = mt;
-    return p[0];
-}
-
-__device__ __forceinline__ void store_out4(uint16_t* p, f32x4 v)
-{
-    bf16x4 w;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w[e] = (__bf16)v[e];
-    *(bf16x4*)p = w;
-}
-
-struct RowsArgs {
-    const uint16_t* q;         // [L][Hq][D]
-    uint16_t* K;               // cache
-    uint16_t* V;
-    const uint16_t* kc;        // keys and values from row tc on: chunk tensors [L][Hkv][D]
-    const uint16_t* vc;
-    uint16_t* out;             // [L][Hq][D]
-    float* lse2;               // [Hq][max_chunk], or null (decoding)
-    float* part_o;             // [Hkv][M][nsplit][D]
-    float2* part_ml;           // [Hkv][M][nsplit]
-    int* arrived;              // [Hkv] tickets, zero between launches; null: a second launch merges
-    // decoding: the tokens become cache rows t .. t+L-1
-    int32_t* pos;              // null: nothing is appended
-    float* score;
-    int32_t* rank;
-    int32_t* row;
-    int pos0;
-    int t, L, tc, Hq, Hkv, G, cap, max_chunk, ks, nsplit;
-    uint32_t inv_g;            // floor(2^32 / G) + 1
-    float c;                   // scale * log2(e)
-};
 
 template <int D, int NRB, bool EXACT>
 __global__ void __launch_bounds__(RW_NT)
@@ -258,57 +47,15 @@ attn_rows_kernel(RowsArgs a)
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.L * a.G, row0 = rg * C::ROWS;
-    const int t = a.t, tc = a.tc, n = t + a.L;
-    // token of a row: row / G (inv_g = floor(2^32 / G) + 1 is exact for the at most 2^20 rows of a kv-head)
-    auto token = [&](int rho) -> int { return a.G == 1 ? rho : (int)__umulhi((uint32_t)rho, a.inv_g); };
+    const int t = a.t;
+    auto token = [&](int rho) -> int { return rows_token(a, rho); };
     const int first_lim = t + token(row0);                     // last key the group's first row sees
     const int n_end = t + token(min(row0 + C::ROWS, M) - 1) + 1;
     const int k_end = min((sp + 1) * a.ks, n_end);
 
-    const uint16_t* Kh = a.K + (size_t)h * a.cap * D;
-    const uint16_t* Vh = a.V + (size_t)h * a.cap * D;
-    const uint16_t* kch = a.kc + (size_t)h * D;
-    const uint16_t* vch = a.vc + (size_t)h * D;
-    const size_t crs = (size_t)a.Hkv * D;                      // row stride of the chunk tensors
-
-    // Tiles in LDS: rows are not padded; the 16-byte pieces of a row are permuted at load time instead (by choosing
-    // which piece of its row a lane fetches), so that sixteen rows of K at one piece, and the sixteen rows of a
-    // transpose read of V (32 bytes of each), spread over the banks.  Piece p of row r lies in slot p ^ swz(r).
-    auto swz_k = [](int r) -> int { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
-    auto swz_v = [](int r) -> int { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); };
+    const RunLoader<D> runs(a, h, lane);
     char* const mine = smem + wave * C::STAGE;
-    const int lrow = lane / (C::ROWB / 16), lpos = lane % (C::ROWB / 16);   // this lane's row and slot of a direct load
-    auto load_run = [&](int k0, char* dst) {
-        // (past the last key the rows of a warm-up step's cache are read as they are: finite, and masked)
-        const bool in_cache = k0 + RW_RUN <= (tc == n ? a.cap : tc), in_chunk = k0 >= tc && k0 + RW_RUN <= n;
-        if (in_cache || in_chunk) {                            // rows a fixed stride apart
-            const int stride = in_cache ? C::ROWB : (int)crs * 2, at = (in_cache ? k0 : k0 - tc) * stride;
-            const int bytes = (in_cache ? a.cap : a.L) * stride - at;
-            const char* kp = (const char*)(in_cache ? Kh : kch) + at;
-            const char* vp = (const char*)(in_cache ? Vh : vch) + at;
-#pragma unroll
-            for (int u = 0; u < C::NL; ++u) {
-                const int r = u * C::RPL + lrow;
-                buffer_to_lds(kp, bytes, dst + u * 1024, r * stride + (lpos ^ swz_k(r)) * 16);
-            }
-#pragma unroll
-            for (int u = 0; u < C::NL; ++u) {
-                const int r = u * C::RPL + lrow;
-                buffer_to_lds(vp, bytes, dst + C::RUN + u * 1024, r * stride + (lpos ^ swz_v(r)) * 16);
-            }
-        } else {                                               // where the cache or the chunk ends: row by row
-#pragma nounroll
-            for (int u = 0; u < C::NL; ++u) {
-                const int r = u * C::RPL + lrow, key = min(k0 + r, n - 1);
-                const bool cached = key < tc;
-                const size_t off = cached ? (size_t)key * D : (size_t)(key - tc) * crs;
-                const uint16_t* ks = (cached ? Kh : kch) + off;
-                const uint16_t* vs = (cached ? Vh : vch) + off;
-                __builtin_amdgcn_global_load_lds((global_void*)(ks + (lpos ^ swz_k(r)) * 8), (lds_void*)(dst + u * 1024), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((global_void*)(vs + (lpos ^ swz_v(r)) * 8), (lds_void*)(dst + C::RUN + u * 1024), 16, 0, 0);
-            }
-        }
-    };
+    auto load_run = [&](int k0, char* dst) { runs.template load<true, true>(k0, dst); };
     const int k_first = sp * a.ks + wave * RW_RUN;
     const int np = k_end > k_first ? (k_end - k_first + RW_PASS - 1) / RW_PASS : 0;
     // wavefront 0, which has a run more than the others if any has, has a second stage for its odd runs
@@ -344,10 +91,10 @@ attn_rows_kernel(RowsArgs a)
         const uint32_t base = (uint32_t)(uintptr_t)(lds_void*)mine;
         const int vkey = 4 * g4 + (c16 >> 2), q4 = c16 & 3;    // swz(key + 16) = swz(key)
 #pragma unroll
-        for (int s = 0; s < C::NS; ++s) kaddr[s] = base + c16 * C::ROWB + (((4 * s + g4) ^ swz_k(c16)) * 16);
+        for (int s = 0; s < C::NS; ++s) kaddr[s] = base + c16 * C::ROWB + (((4 * s + g4) ^ swz_k<D>(c16)) * 16);
 #pragma unroll
         for (int b = 0; b < C::NC; ++b)
-            vaddr[b] = base + C::RUN + vkey * C::ROWB + (((2 * b + (q4 >> 1)) ^ swz_v(vkey)) * 16) + 8 * (q4 & 1);
+            vaddr[b] = base + C::RUN + vkey * C::ROWB + (((2 * b + (q4 >> 1)) ^ swz_v<D>(vkey)) * 16) + 8 * (q4 & 1);
     }
 
     for (int p = 0; p < np; ++p) {
@@ -446,9 +193,9 @@ attn_rows_kernel(RowsArgs a)
         constexpr int VPR = D / 8;
         for (int i = sp + a.nsplit * (tid / VPR); i < a.L; i += a.nsplit * (RW_NT / VPR)) {
             const int x = tid % VPR;
-            const size_t dst = ((size_t)h * a.cap + t + i) * D + x * 8, src = (size_t)i * crs + x * 8;
-            *(u32x4*)(a.K + dst) = *(const u32x4*)(kch + src);
-            *(u32x4*)(a.V + dst) = *(const u32x4*)(vch + src);
+            const size_t dst = ((size_t)h * a.cap + t + i) * D + x * 8, src = (size_t)i * runs.crs + x * 8;
+            *(u32x4*)(a.K + dst) = *(const u32x4*)(runs.kch + src);
+            *(u32x4*)(a.V + dst) = *(const u32x4*)(runs.vch + src);
             if (x == 0) {
                 const size_t at = (size_t)h * a.cap + t + i;
                 a.pos[at] = a.pos0 + i;
@@ -479,30 +226,12 @@ attn_rows_kernel(RowsArgs a)
         }
     __syncthreads();
     const bool single = a.nsplit == 1;
-    auto leave = [&](const PieceSum& ps, int rho, int d) {     // a row's four columns: finished, or this piece's share
-        if (single) {
-            const int tok = token(rho), gq = h * a.G + rho - tok * a.G;
-            store_out4(a.out + ((size_t)tok * a.Hq + gq) * D + d, ps.out());
-            if (a.lse2 && d == 0) a.lse2[(size_t)gq * a.max_chunk + tok] = ps.lse();
-        } else {
-            const size_t at = ((size_t)h * M + rho) * a.nsplit + sp;
-            float* po = a.part_o + at * D + d;
-            if (a.arrived) {
-                part_store2((float2*)po, float2{ps.o[0], ps.o[1]});
-                part_store2((float2*)po + 1, float2{ps.o[2], ps.o[3]});
-                if (d == 0) part_store2(a.part_ml + at, float2{ps.m, ps.l});
-            } else {
-                *(f32x4*)po = ps.o;
-                if (d == 0) a.part_ml[at] = float2{ps.m, ps.l};
-            }
-        }
-    };
     if (NRB == 1 && rows <= 4) {                               // eight lanes, one wavefront's share each
         for (int x = tid / RW_NW; x < rows * (D / 4); x += RW_NT / RW_NW) {
             const int r = x / (D / 4), d = 4 * (x % (D / 4)), w = tid % RW_NW;
             PieceSum ps{s_m[w][r], s_l[w][r], *(const f32x4*)merged(w, r, d / 4)};
             ps.add_lanes<RW_NW>();
-            if (w == 0) leave(ps, row0 + r, d);
+            if (w == 0) leave_row<D>(a, h, sp, row0 + r, d, ps);
         }
     } else {
         for (int x = tid; x < rows * (D / 4); x += RW_NT) {
@@ -510,7 +239,7 @@ attn_rows_kernel(RowsArgs a)
             PieceSum ps[RW_NW];
 #pragma unroll
             for (int w = 0; w < RW_NW; ++w) ps[w] = PieceSum{s_m[w][r], s_l[w][r], *(const f32x4*)merged(w, r, d / 4)};
-            leave(add_tree(ps), row0 + r, d);
+            leave_row<D>(a, h, sp, row0 + r, d, add_tree(ps));
         }
     }
     if (single || !a.arrived) return;
@@ -590,7 +319,8 @@ hipError_t launch_rows_d(const RowsArgs& args, int nrb, hipStream_t st)
     RowsArgs a = args;
     a.inv_g = (uint32_t)((1ull << 32) / (unsigned)a.G + 1);
     if (nrb == 1) launch_rows_cfg<D, 1, EXACT>(a, st);
-    else launch_rows_cfg<D, 2, EXACT>(a, st);
+    else if (EXACT || nrb == 2) launch_rows_cfg<D, 2, EXACT>(a, st);
+    else if constexpr (D == 128) launch_rows64(a, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.nsplit == 1 || a.arrived) return e;
     const int M = a.L * a.G;
@@ -644,21 +374,25 @@ hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void*
 // keys, a pass of 256 keys per round of 256 workgroups, the partials and the merging launch of a cut key range, and
 // never less than the cache takes to come in.  (32 heads of 128 on 4 kv-heads, measured / this: 16 rows per workgroup,
 // 128 workgroups, 2064 keys 16.4 / 18.3; 256 workgroups, 8128 keys 45.4 / 44.0; 32 rows, 256 workgroups, 4256 keys
-// 34.1 / 34.0; 512 workgroups, 4512 keys 63.7 / 63.3; four pieces, 256 workgroups, 8064 keys 25.2 / 25.0.)
+// 34.1 / 34.0; 512 workgroups, 4512 keys 63.7 / 63.3; four pieces, 256 workgroups, 8064 keys 25.2 / 25.0; 64 rows,
+// 256 workgroups, 4608 keys 51.7 / 49.3, 2560 keys 36.6 / 34.3; at head_dim 64 rows of 64 gain nothing over 32: 24.9 and
+// 24.8 us for 32 heads, 512 rows, 2560 keys.)
 float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, RowsPlan& plan)
 {
     struct Cost { float fixed, more_rounds, pass; };
-    static constexpr Cost COST[2][2] = {{{6.5f, 1.f, 0.66f}, {8.7f, 1.f, 0.85f}},       // head_dim 64: 16, 32 rows
-                                        {{8.2f, 4.f, 1.12f}, {11.4f, 4.f, 1.33f}}};     // 128
+    static constexpr Cost COST[2][3] = {{{6.5f, 1.f, 0.66f}, {8.7f, 1.f, 0.85f}, {}},                      // head_dim 64: 16, 32 rows
+                                        {{8.2f, 4.f, 1.12f}, {11.4f, 4.f, 1.33f}, {15.5f, 8.f, 1.88f}}};   // 128: 16, 32, 64
     const float floor_us = 6.f + (float)n * g.Hkv * g.d * 4.f / 5.5e6f;
     float best = 1e30f;
-    for (int nrb = 1; nrb <= 2; ++nrb) {
-        const Cost& c = COST[g.d == 128][nrb - 1];
+    for (int i = 0; i < (g.d == 128 ? 3 : 2); ++i) {
+        const int nrb = 1 << i;
+        const Cost& c = COST[g.d == 128][i];
         const long units = (long)g.Hkv * ((L * g.G + 16 * nrb - 1) / (16 * nrb));       // workgroups per piece
         const long most = std::min<long>(std::min<long>(256 / units, (n + 255) / 256), cap_rows / ((long)g.Hq * L));
         for (int pieces = 1; pieces == 1 || pieces <= std::min<long>(most, RW_CLASSES); ++pieces) {
             const int keys = ((n + pieces - 1) / pieces + RW_RUN - 1) / RW_RUN * RW_RUN;
             const float rounds = (float)((units * pieces + 255) / 256);
+            if (nrb == 4 && rounds > 1.f) continue;            // attn_fwd is as good or better: 100 / 109 us at 4 x 8 heads, 1077 rows
             float us = c.fixed + c.more_rounds * (rounds - 1.f) + rounds * c.pass * (float)((keys + RW_PASS - 1) / RW_PASS);
             if (us < floor_us) us = floor_us;
             if (pieces > 1) us += 1.2f + 0.45f * (float)pieces;

@@ -1,0 +1,228 @@
+// Attention of up to a few hundred query rows per kv-head on bf16 MFMA for gfx950, head_dim 128: attn_rows
+// (attn_rows.hip) with 64 query rows per workgroup.
+//
+// What bounds attn_rows with 32 rows is the way of K and V into the CU: 128 KB per pass of 256 keys take 1.1 us (64 bytes
+// per cycle), its products half of that.  Twice the rows per byte need twice the output accumulators (128 registers of
+// a wavefront's 256, eight wavefronts on a CU); the query fragments then have no place in registers and are read from
+// LDS, which all wavefronts share, beside the K fragments.  K and V have one buffer each per wavefront: a run's K
+// buffer is refilled as soon as S has its fragments, its V buffer as soon as O has.  A pass of 256 keys takes 1.9 us (LDS:
+// 384 KB, 1.5 us; products 1.0), two workgroups of 32 rows 2.7.
+#include "attn_rows.h"
+
+namespace infmllm {
+
+namespace {
+
+template <int D>
+struct Rows64Cfg {
+    static constexpr int ROWB = D * 2, RUN = RW_RUN * ROWB, STAGE = 2 * RUN;
+    static constexpr int NS = D / 32, NC = D / 16, NL = RUN / 1024, RPL = 1024 / ROWB;
+    static constexpr int NX = 4, ROWS = 16 * NX;               // blocks of sixteen query rows
+    static constexpr int QL = ROWS * ROWB / 1024 / RW_NW;      // direct loads of queries per wavefront
+    static constexpr int MC = D / 2;                           // columns merged at once: a wavefront's share fits its stage
+    static_assert(ROWS * MC * 4 <= STAGE, "the merge reuses the buffers of the tiles");
+};
+
+template <int D>
+__global__ void __launch_bounds__(RW_NT)
+attn_rows64_kernel(RowsArgs a)
+{
+    using C = Rows64Cfg<D>;
+    __shared__ __attribute__((aligned(1024))) char smem[RW_NW * C::STAGE];
+    __shared__ __attribute__((aligned(1024))) char qmem[C::ROWS * C::ROWB];
+    __shared__ float s_m[RW_NW][C::ROWS], s_l[RW_NW][C::ROWS];
+
+    const int sp = blockIdx.x, h = blockIdx.y, rg = blockIdx.z;    // piece, kv-head, row group (see attn_rows_kernel)
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int M = a.L * a.G, row0 = rg * C::ROWS, t = a.t;
+    const int first_lim = t + rows_token(a, row0);             // last key the group's first row sees
+    const int n_end = t + rows_token(a, min(row0 + C::ROWS, M) - 1) + 1;
+    const int k_end = min((sp + 1) * a.ks, n_end);
+
+    const RunLoader<D> runs(a, h, lane);
+    char* const mine = smem + wave * C::STAGE;
+    // queries: row r of the group in LDS row r, swizzled like K
+#pragma unroll
+    for (int u = 0; u < C::QL; ++u) {
+        const int r = (wave * C::QL + u) * C::RPL + runs.lrow, rho = min(row0 + r, M - 1), tok = rows_token(a, rho);
+        const uint16_t* src = a.q + ((size_t)tok * a.Hq + h * a.G + (rho - tok * a.G)) * D + (runs.lpos ^ swz_k<D>(r)) * 8;
+        __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)(qmem + (wave * C::QL + u) * 1024), 16, 0, 0);
+    }
+    const int k_first = sp * a.ks + wave * RW_RUN;
+    const int np = k_end > k_first ? (k_end - k_first + RW_PASS - 1) / RW_PASS : 0;
+    if (np > 0) {
+        runs.template load<true, false>(k_first, mine);
+        runs.template load<false, true>(k_first, mine);
+        wait_loads<2 * C::NL>();                               // the queries have landed ...
+    } else {
+        wait_loads<0>();
+    }
+
+    f32x4 o[C::NX][C::NC];
+    float m_ref[C::NX], m_use[C::NX], lsum[C::NX];
+#pragma unroll
+    for (int x = 0; x < C::NX; ++x) {
+#pragma unroll
+        for (int b = 0; b < C::NC; ++b) o[x][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m_ref[x] = -__builtin_inff(); m_use[x] = 0.f; lsum[x] = 0.f;
+    }
+    // Fragment addresses: K and Q as in attn_rows (lane (row c16, group g4), piece 4s + g4), V by the transpose read.  The
+    // step or column block only flips address bits that are clear in the rest, so one address each is kept, in a form
+    // that the compiler does not see through (it would keep all sixteen, and run out of registers).
+    uint32_t k0addr, q0addr, v0addr;
+    {
+        const uint32_t base = (uint32_t)(uintptr_t)(lds_void*)mine, qbase = (uint32_t)(uintptr_t)(lds_void*)qmem;
+        const int vkey = 4 * g4 + (c16 >> 2), q4 = c16 & 3;
+        const uint32_t rel = c16 * C::ROWB + ((g4 ^ swz_k<D>(c16)) * 16);
+        k0addr = base + rel;
+        q0addr = qbase + rel;
+        v0addr = base + C::RUN + vkey * C::ROWB + (((q4 >> 1) ^ swz_v<D>(vkey)) * 16) + 8 * (q4 & 1);
+    }
+    __builtin_amdgcn_s_barrier();                              // ... everybody's
+
+    for (int p = 0; p < np; ++p) {
+        const int k0 = k_first + p * RW_PASS;
+        const bool more = p + 1 < np;
+        asm volatile("" : "+v"(k0addr), "+v"(q0addr), "+v"(v0addr));
+        wait_loads<C::NL>();                                   // this run's K has landed, its V may be on its way
+        // ---- S^T = K.Q^T, the fragments of a step requested a step ahead
+        bf16x8 kf[2][2], qf[2][C::NX];
+        f32x4 S[C::NX][2];
+        auto request = [&](auto step) {
+            constexpr int s = decltype(step)::value, b = s & 1;
+            const uint32_t ka = k0addr ^ (64 * s), qa = q0addr ^ (64 * s);
+            kf[b][0] = rw_read_b128<0>(ka);
+            kf[b][1] = rw_read_b128<16 * C::ROWB>(ka);
+            qf[b][0] = rw_read_b128<0>(qa);
+            qf[b][1] = rw_read_b128<16 * C::ROWB>(qa);
+            qf[b][2] = rw_read_b128<32 * C::ROWB>(qa);
+            qf[b][3] = rw_read_b128<48 * C::ROWB>(qa);
+        };
+        request(std::integral_constant<int, 0>{});
+        static_for<0, C::NS>([&](auto step) {
+            constexpr int s = decltype(step)::value, b = s & 1;
+            if constexpr (s + 1 < C::NS) request(std::integral_constant<int, s + 1>{});
+            asm volatile("s_waitcnt lgkmcnt(%6)"
+                         : "+v"(kf[b][0]), "+v"(kf[b][1]), "+v"(qf[b][0]), "+v"(qf[b][1]), "+v"(qf[b][2]), "+v"(qf[b][3])
+                         : "n"(s + 1 < C::NS ? 6 : 0));
+            if constexpr (s + 1 == C::NS)
+                if (more) runs.template load<true, false>(k0 + RW_PASS, mine);
+#pragma unroll
+            for (int x = 0; x < C::NX; ++x)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    S[x][kb] = mfma16(kf[b][kb], qf[b][x], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : S[x][kb]);
+        });
+        if (more) wait_loads<C::NL>();                         // this run's V has landed, the next one's K may be on its way
+        else wait_loads<0>();
+        // ---- V fragments of the lower columns, behind them mask and softmax
+        constexpr int HC = C::NC / 2;
+        bf16x4 vlo[2][HC], vhi[2][HC];
+        auto request_v = [&](auto half) {
+            constexpr int hf = decltype(half)::value;
+#pragma unroll
+            for (int b = 0; b < HC; ++b) {
+                const uint32_t va = v0addr ^ (32 * (hf * HC + b));
+                vlo[hf][b] = rw_read_tr16<0>(va);
+                vhi[hf][b] = rw_read_tr16<16 * C::ROWB>(va);
+            }
+        };
+        auto await_v = [&](auto half) {
+            constexpr int hf = decltype(half)::value;
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vlo[hf][0]), "+v"(vhi[hf][0]), "+v"(vlo[hf][1]), "+v"(vhi[hf][1]));
+            if constexpr (HC == 4) asm volatile("" : "+v"(vlo[hf][2]), "+v"(vhi[hf][2]), "+v"(vlo[hf][3]), "+v"(vhi[hf][3]));
+        };
+        using I0 = std::integral_constant<int, 0>;
+        using I1 = std::integral_constant<int, 1>;
+        bf16x8 pf[C::NX];
+        const bool masked = k0 + RW_RUN - 1 > first_lim;
+#pragma unroll
+        for (int x = 0; x < C::NX; ++x) {
+            if (masked) {
+                const int lim = t + rows_token(a, min(row0 + 16 * x + c16, M - 1));
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (k0 + 16 * kb + 4 * g4 + i > lim) S[x][kb][i] = -__builtin_inff();
+            }
+            float mx = fmaxf(fmaxf(fmaxf(S[x][0][0], S[x][0][1]), fmaxf(S[x][0][2], S[x][0][3])),
+                             fmaxf(fmaxf(S[x][1][0], S[x][1][1]), fmaxf(S[x][1][2], S[x][1][3])));
+            mx = groups_max(mx) * a.c;
+            if (__any(mx > m_ref[x] + RESCALE_TAU)) {
+                const float m_new = fmaxf(m_ref[x], mx);
+                const float mu = (m_new == -__builtin_inff()) ? 0.f : m_new;
+                const float alpha = fast_exp2(m_ref[x] - mu);  // m_ref = -inf gives 0
+                m_ref[x] = m_new;
+                m_use[x] = mu;
+                lsum[x] *= alpha;
+#pragma unroll
+                for (int b = 0; b < C::NC; ++b) o[x][b] *= alpha;
+            }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float w = fast_exp2(__builtin_fmaf(S[x][kb][i], a.c, -m_use[x]));
+                    lsum[x] += w;
+                    pf[x][4 * kb + i] = (__bf16)w;
+                }
+        }
+        // ---- O^T += V^T.P^T
+        request_v(I0{});
+        await_v(I0{});
+        request_v(I1{});
+        auto products = [&](auto half) {
+            constexpr int hf = decltype(half)::value;
+#pragma unroll
+            for (int b = 0; b < HC; ++b) {
+                const bf16x8 vf = __builtin_shufflevector(vlo[hf][b], vhi[hf][b], 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+                for (int x = 0; x < C::NX; ++x) o[x][hf * HC + b] = mfma16(vf, pf[x], o[x][hf * HC + b]);
+            }
+        };
+        products(I0{});
+        await_v(I1{});
+        if (more) runs.template load<false, true>(k0 + RW_PASS, mine);
+        products(I1{});
+    }
+
+    // ---- merge the wavefronts (see attn_rows_kernel), half of the columns at a time
+#pragma unroll
+    for (int x = 0; x < C::NX; ++x) {
+        const float l = groups_sum(lsum[x]);
+        if (g4 == 0) { s_m[wave][16 * x + c16] = m_ref[x]; s_l[wave][16 * x + c16] = l; }
+    }
+    auto merged = [&](int w, int r, int p) -> char* {
+        return smem + w * C::STAGE + r * (C::MC * 4) + ((p ^ ((r ^ w) & 7)) * 16);
+    };
+    const int rows = min(C::ROWS, M - row0);
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+        if (hf > 0) __syncthreads();
+        constexpr int CBH = C::NC / 2;
+#pragma unroll
+        for (int x = 0; x < C::NX; ++x)
+#pragma unroll
+            for (int b = 0; b < CBH; ++b) *(f32x4*)merged(wave, 16 * x + c16, 4 * b + g4) = o[x][hf * CBH + b];
+        __syncthreads();
+        for (int i = tid; i < rows * (C::MC / 4); i += RW_NT) {
+            const int r = i / (C::MC / 4), d4 = i % (C::MC / 4);
+            PieceSum ps[RW_NW];
+#pragma unroll
+            for (int w = 0; w < RW_NW; ++w) ps[w] = PieceSum{s_m[w][r], s_l[w][r], *(const f32x4*)merged(w, r, d4)};
+            leave_row<D>(a, h, sp, row0 + r, hf * C::MC + 4 * d4, add_tree(ps));
+        }
+    }
+}
+
+}  // namespace
+
+void launch_rows64(const RowsArgs& a, hipStream_t st)
+{
+    const dim3 grid((unsigned)a.nsplit, (unsigned)a.Hkv, (unsigned)((a.L * a.G + Rows64Cfg<128>::ROWS - 1) / Rows64Cfg<128>::ROWS));
+    hipLaunchKernelGGL(attn_rows64_kernel<128>, grid, dim3(RW_NT), 0, st, a);
+}
+
+}  // namespace infmllm
