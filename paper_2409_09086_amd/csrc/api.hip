@@ -102,6 +102,7 @@ struct infmllm_stream {
     }
 
     bool mfma() const { return dtype == INFMLLM_BF16 && impl == 0; }
+    bool f32() const { return dtype == INFMLLM_FP32; }
 
     struct Layout {
         size_t K, V, pos, score, rank, row, lse, Wb, I, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, dec_part, rows_o,
@@ -129,8 +130,8 @@ struct infmllm_stream {
         L.mv_x = off; off += ml;
         L.mv_score = off; off += ml;
         L.mv_count = off; off += up((size_t)g.Hkv * 4);
-        // row-split scoring (bf16 streams): partial column sums and arrival counters
-        L.score_part = off; off += up(g.elt == 2 ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
+        // row-split scoring: partial column sums and arrival counters
+        L.score_part = off; off += up(mfma() || f32() ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
         L.dec_part = off; off += up(g.max_decode > 0 && !mfma() ? (size_t)g.Hq * DECODE_MAX_SPLIT * (g.d + 2) * 4 + (size_t)g.Hkv * 4 : 0);
         // (query row, piece) pairs of a launch with a cut key range: at most ROWS_MAX_PARTS, at least one token's
         L.rows_cap = 0;
@@ -138,6 +139,8 @@ struct infmllm_stream {
             const long most = (long)g.Hq * std::max(g.max_chunk, g.max_decode) * ((g.cap + 127) / 128);
             const int ksd = rows_decode_keys_per_piece(g);
             L.rows_cap = std::max(std::min(most, ROWS_MAX_PARTS), (long)g.Hq * ((g.B + g.max_decode + ksd - 1) / ksd));
+        } else if (f32()) {
+            L.rows_cap = std::min((long)g.Hq * g.max_chunk * ((g.cap + 127) / 128), ROWS_MAX_PARTS);
         }
         L.rows_o = off; off += up((size_t)L.rows_cap * g.d * 4);
         L.rows_ml = off; off += up((size_t)L.rows_cap * 8);
@@ -384,12 +387,12 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
     const Geometry& g = s->g;
     const CacheView& cur = s->cache;
     const int t = s->len, n = t + L;
-    const bool mfma = s->mfma();
+    const bool mfma = s->mfma(), f32 = s->f32();
     hipError_t e;
 
-    // An evicting step on the matrix-core path never appends: attention and scoring read the chunk's
+    // An evicting step on the matrix cores never appends: attention and scoring read the chunk's
     // rows in place and the placement writes the survivors into the rows the eviction frees.
-    const bool in_place = mfma && n > g.B;
+    const bool in_place = (mfma || f32) && n > g.B;
     const KeySource ks = in_place ? KeySource{t, k, v} : KeySource{n, nullptr, nullptr};
     if (!in_place) {
         s->mark(INFMLLM_K_APPEND, 0);
@@ -414,8 +417,9 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
         s->rot_rows = in_place ? t : n;
     }
     s->mark(INFMLLM_K_ATTN, 0);
-    e = mfma ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, s->st)
-             : launch_attn_simple(g, att, q_att, t, L, out, s->lse, s->st);
+    e = mfma  ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, s->st)
+        : f32 ? launch_attn_f32(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, s->st)
+              : launch_attn_simple(g, att, q_att, t, L, out, s->lse, s->st);
     if (e != hipSuccess) return fail_hip(e, "attention");
     s->mark(INFMLLM_K_ATTN, 1);
 
@@ -434,8 +438,9 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
     if (g.policy == POLICY_WINDOW || g.policy == POLICY_INITIAL_RECENT)
         e = launch_rank_scores(g, s->Wb, n - g.R, g.policy == POLICY_WINDOW ? 1.f : -1.f, s->st);
     else
-        e = mfma ? launch_score_mfma(g, att, ks_att, q_att, s->lse, s->fwd, t, L, s->Wb, s->st)
-                 : launch_score_simple(g, att, q_att, s->lse, t, L, s->Wb, s->st);
+        e = mfma  ? launch_score_mfma(g, att, ks_att, q_att, s->lse, s->fwd, t, L, s->Wb, s->st)
+            : f32 ? launch_score_f32(g, att, ks_att, q_att, s->lse, s->fwd, t, L, s->Wb, s->st)
+                  : launch_score_simple(g, att, q_att, s->lse, t, L, s->Wb, s->st);
     if (e != hipSuccess) return fail_hip(e, "score");
     s->mark(INFMLLM_K_SCORE, 1);
     return INFMLLM_OK;

@@ -5,14 +5,15 @@
 
 namespace infmllm {
 
-struct RowsArgs {
-    const uint16_t* q;         // [L][Hq][D]
-    uint16_t* K;               // cache
-    uint16_t* V;
-    const uint16_t* kc;        // keys and values from row tc on: chunk tensors [L][Hkv][D]
-    const uint16_t* vc;
-    uint16_t* out;             // [L][Hq][D]
-    float* lse2;               // [Hq][max_chunk], or null (decoding)
+template <typename T>
+struct RowsArgsT {
+    const T* q;                // [L][Hq][D]
+    T* K;                      // cache
+    T* V;
+    const T* kc;               // keys and values from row tc on: chunk tensors [L][Hkv][D]
+    const T* vc;
+    T* out;                    // [L][Hq][D]
+    float* lse;                // [Hq][max_chunk] row log-sum-exp (base 2; natural for fp32), or null (decoding)
     float* part_o;             // [Hkv][M][nsplit][D]
     float2* part_ml;           // [Hkv][M][nsplit]
     int* arrived;              // [Hkv] tickets, zero between launches; null: a second launch merges
@@ -24,19 +25,21 @@ struct RowsArgs {
     int pos0;
     int t, L, tc, Hq, Hkv, G, cap, max_chunk, ks, nsplit;
     uint32_t inv_g;            // floor(2^32 / G) + 1
-    float c;                   // scale * log2(e)
+    float c;                   // scale * log2(e); fp32: scale
 };
+typedef RowsArgsT<uint16_t> RowsArgs;
 
 void launch_rows64(const RowsArgs& a, hipStream_t st);
 
 namespace {
 
+typedef __attribute__((address_space(3))) void lds_void;
+typedef const __attribute__((address_space(1))) void global_void;
+
 constexpr int RW_NW = 8, RW_NT = 64 * RW_NW;        // wavefronts, threads
 constexpr int RW_RUN = 32;                         // keys of a wavefront's run
 constexpr int RW_PASS = RW_NW * RW_RUN;            // keys of a workgroup's pass
 
-typedef __attribute__((address_space(3))) void lds_void;
-typedef const __attribute__((address_space(1))) void global_void;
 
 template <int D, int NRB>
 struct RowsCfg {
@@ -106,6 +109,9 @@ __device__ __forceinline__ float lanes_max(float x)
     return x;
 }
 
+// LDS reads as statements of their own: the compiler, which cannot tell one buffer from the other, would wait for
+// every direct load in flight before each read it knows of.  They are waited for by hand, and the registers are
+// first touched after that wait.
 template <int OFF>
 __device__ __forceinline__ bf16x4 rw_read_tr16(uint32_t addr)
 {
@@ -117,6 +123,13 @@ template <int OFF>
 __device__ __forceinline__ bf16x8 rw_read_b128(uint32_t addr)
 {
     bf16x8 v;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+    return v;
+}
+template <int OFF>
+__device__ __forceinline__ f32x4 rw_read_f32x4(uint32_t addr)
+{
+    f32x4 v;
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
     return v;
 }
@@ -152,13 +165,16 @@ __device__ __forceinline__ void part_store2(float2* p, float2 v)
 // past the row's last key change nothing.
 constexpr int RW_CLASSES = 16;
 constexpr int RW_TICKET_PARTS = 256;               // most (row, piece) pairs of a kv-head that its last workgroup merges
-struct PieceSum {
+// NAT: references are natural logarithms (fp32 streams), else base 2
+template <bool NAT>
+struct PieceSumT {
     float m, l;
     f32x4 o;                   // four of the row's columns
+    static __device__ __forceinline__ float power(float x) { return NAT ? expf(x) : fast_exp2(x); }
     __device__ __forceinline__ void absorb(float2 ml, f32x4 x)
     {
         const float mn = fmaxf(m, ml.x), mz = (mn == -__builtin_inff()) ? 0.f : mn;
-        const float wa = fast_exp2(m - mz), wb = fast_exp2(ml.x - mz);
+        const float wa = power(m - mz), wb = power(ml.x - mz);
         m = mn;
         l = __builtin_fmaf(wa, l, wb * ml.y);
 #pragma unroll
@@ -170,7 +186,7 @@ struct PieceSum {
     {
 #pragma clang fp contract(off)
         const float mt = lanes_max<N>(m), mz = (mt == -__builtin_inff()) ? 0.f : mt;
-        const float w = fast_exp2(m - mz);
+        const float w = power(m - mz);
         m = mt;
         l = lanes_sum<N>(w * l);
 #pragma unroll
@@ -181,11 +197,12 @@ struct PieceSum {
         const float inv = 1.0f / l;
         return f32x4{o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
     }
-    __device__ __forceinline__ float lse() const { return m + __builtin_log2f(l); }
+    __device__ __forceinline__ float lse() const { return m + (NAT ? logf(l) : __builtin_log2f(l)); }
 };
+typedef PieceSumT<false> PieceSum;
 // the tree in one thread: no lane does another one's work, for many rows
-template <int N>
-__device__ __forceinline__ PieceSum add_tree(PieceSum (&p)[N])
+template <int N, bool NAT>
+__device__ __forceinline__ PieceSumT<NAT> add_tree(PieceSumT<NAT> (&p)[N])
 {
 #pragma clang fp contract(off)
     float mt = p[0].m;
@@ -194,7 +211,7 @@ __device__ __forceinline__ PieceSum add_tree(PieceSum (&p)[N])
     const float mz = (mt == -__builtin_inff()) ? 0.f : mt;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const float w = fast_exp2(p[i].m - mz);
+        const float w = PieceSumT<NAT>::power(p[i].m - mz);
         p[i].l = w * p[i].l;
 #pragma unroll
         for (int e = 0; e < 4; ++e) p[i].o[e] = w * p[i].o[e];
@@ -218,27 +235,39 @@ __device__ __forceinline__ void store_out4(uint16_t* p, f32x4 v)
     for (int e = 0; e < 4; ++e) w[e] = (__bf16)v[e];
     *(bf16x4*)p = w;
 }
+__device__ __forceinline__ void store_out4(float* p, f32x4 v) { *(f32x4*)p = v; }
 
 
 
 // token of a row (row = token * G + head in group): row / G; inv_g = floor(2^32 / G) + 1 is exact for the at most 2^20
 // rows of a kv-head
-__device__ __forceinline__ int rows_token(const RowsArgs& a, int rho) { return a.G == 1 ? rho : (int)__umulhi((uint32_t)rho, a.inv_g); }
+template <typename T>
+__device__ __forceinline__ int rows_token(const RowsArgsT<T>& a, int rho) { return a.G == 1 ? rho : (int)__umulhi((uint32_t)rho, a.inv_g); }
 
 // Tiles in LDS: rows are not padded; the 16-byte pieces of a row are permuted at load time instead (by choosing which
 // piece of its row a lane fetches), so that sixteen rows of K (or Q) at one piece, and the sixteen rows of a transpose
 // read of V (32 bytes of each), spread over the banks.  Piece p of row r lies in slot p ^ swz(r).
 template <int D> __device__ __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
 template <int D> __device__ __forceinline__ int swz_v(int r) { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); }
+template <typename T, int D> struct Tile {
+    static __device__ __forceinline__ int k(int r, int p) { return p ^ swz_k<D>(r); }      // slot of piece p; its own inverse
+    static __device__ __forceinline__ int v(int r, int p) { return p ^ swz_v<D>(r); }
+};
+// fp32: sixteen rows of K at one piece; of V a row's pieces 2l (then 2l + 1) for the sixteen lanes l of a group
+template <int D> struct Tile<float, D> {
+    static __device__ __forceinline__ int k(int r, int p) { return p ^ (r & 15); }
+    static __device__ __forceinline__ int v(int, int p) { return D == 128 ? p ^ ((p >> 4) & 1) : p; }
+};
 
-// A wavefront's direct loads of a run: 32 rows of K and / or V from row k0 on, to `dst` (K) and `dst` + RUN (V).
-template <int D>
+// A wavefront's direct loads of a run: KEYS rows of K and / or V from row k0 on, to `dst` (K) and `dst` + RUN (V).
+template <typename T, int D, int KEYS>
 struct RunLoader {
-    static constexpr int ROWB = D * 2, RUN = RW_RUN * ROWB, NL = RUN / 1024, RPL = 1024 / ROWB;
-    const uint16_t *Kh, *Vh, *kch, *vch;
+    static constexpr int ROWB = D * (int)sizeof(T), RUN = KEYS * ROWB, NL = RUN / 1024, RPL = 1024 / ROWB;
+    typedef Tile<T, D> Swz;
+    const T *Kh, *Vh, *kch, *vch;
     int tc, n, cap, L, crs;                        // crs: row stride of the chunk tensors
     int lrow, lpos;                                // this lane's row and slot of a load
-    __device__ __forceinline__ RunLoader(const RowsArgs& a, int h, int lane)
+    __device__ __forceinline__ RunLoader(const RowsArgsT<T>& a, int h, int lane)
         : Kh(a.K + (size_t)h * a.cap * D), Vh(a.V + (size_t)h * a.cap * D), kch(a.kc + (size_t)h * D), vch(a.vc + (size_t)h * D),
           tc(a.tc), n(a.t + a.L), cap(a.cap), L(a.L), crs(a.Hkv * D), lrow(lane / (ROWB / 16)), lpos(lane % (ROWB / 16))
     {
@@ -247,22 +276,22 @@ struct RunLoader {
     __device__ __forceinline__ void load(int k0, char* dst) const
     {
         // (past the last key the rows of a warm-up step's cache are read as they are: finite, and masked)
-        const bool in_cache = k0 + RW_RUN <= (tc == n ? cap : tc), in_chunk = k0 >= tc && k0 + RW_RUN <= n;
+        const bool in_cache = k0 + KEYS <= (tc == n ? cap : tc), in_chunk = k0 >= tc && k0 + KEYS <= n;
         if (in_cache || in_chunk) {                // rows a fixed stride apart
-            const int stride = in_cache ? ROWB : crs * 2, at = (in_cache ? k0 : k0 - tc) * stride;
+            const int stride = in_cache ? ROWB : crs * (int)sizeof(T), at = (in_cache ? k0 : k0 - tc) * stride;
             const int bytes = (in_cache ? cap : L) * stride - at;
-            const uint16_t *k_cache = Kh, *k_chunk = kch, *v_cache = Vh, *v_chunk = vch;
+            const T *k_cache = Kh, *k_chunk = kch, *v_cache = Vh, *v_chunk = vch;
             const char* kp = (const char*)(in_cache ? k_cache : k_chunk) + at;
             const char* vp = (const char*)(in_cache ? v_cache : v_chunk) + at;
             if (K) {
 #pragma unroll
                 for (int u = 0; u < NL; ++u)
-                    buffer_to_lds(kp, bytes, dst + u * 1024, lrow * stride + ((lpos ^ swz_k<D>(u * RPL + lrow)) * 16), u * RPL * stride);
+                    buffer_to_lds(kp, bytes, dst + u * 1024, lrow * stride + (Swz::k(u * RPL + lrow, lpos) * 16), u * RPL * stride);
             }
             if (V) {
 #pragma unroll
                 for (int u = 0; u < NL; ++u)
-                    buffer_to_lds(vp, bytes, dst + RUN + u * 1024, lrow * stride + ((lpos ^ swz_v<D>(u * RPL + lrow)) * 16), u * RPL * stride);
+                    buffer_to_lds(vp, bytes, dst + RUN + u * 1024, lrow * stride + (Swz::v(u * RPL + lrow, lpos) * 16), u * RPL * stride);
             }
         } else {                                   // where the cache or the chunk ends: row by row
 #pragma nounroll
@@ -270,22 +299,22 @@ struct RunLoader {
                 const int r = u * RPL + lrow, key = min(k0 + r, n - 1);
                 const bool cached = key < tc;
                 const size_t off = cached ? (size_t)key * D : (size_t)(key - tc) * crs;
-                const uint16_t *ka = Kh + off, *kb = kch + off, *va = Vh + off, *vb = vch + off;
-                if (K) __builtin_amdgcn_global_load_lds((global_void*)((cached ? ka : kb) + (lpos ^ swz_k<D>(r)) * 8), (lds_void*)(dst + u * 1024), 16, 0, 0);
-                if (V) __builtin_amdgcn_global_load_lds((global_void*)((cached ? va : vb) + (lpos ^ swz_v<D>(r)) * 8), (lds_void*)(dst + RUN + u * 1024), 16, 0, 0);
+                const T *ka = Kh + off, *kb = kch + off, *va = Vh + off, *vb = vch + off;
+                if (K) __builtin_amdgcn_global_load_lds((global_void*)((cached ? ka : kb) + Swz::k(r, lpos) * (16 / (int)sizeof(T))), (lds_void*)(dst + u * 1024), 16, 0, 0);
+                if (V) __builtin_amdgcn_global_load_lds((global_void*)((cached ? va : vb) + Swz::v(r, lpos) * (16 / (int)sizeof(T))), (lds_void*)(dst + RUN + u * 1024), 16, 0, 0);
             }
         }
     }
 };
 
 // Four columns of a row, merged over the workgroup's wavefronts: the finished output, or this piece's share of it.
-template <int D>
-__device__ __forceinline__ void leave_row(const RowsArgs& a, int h, int sp, int rho, int d, const PieceSum& ps)
+template <int D, typename T, bool NAT>
+__device__ __forceinline__ void leave_row(const RowsArgsT<T>& a, int h, int sp, int rho, int d, const PieceSumT<NAT>& ps)
 {
     if (a.nsplit == 1) {
         const int tok = rows_token(a, rho), gq = h * a.G + rho - tok * a.G;
         store_out4(a.out + ((size_t)tok * a.Hq + gq) * D + d, ps.out());
-        if (a.lse2 && d == 0) a.lse2[(size_t)gq * a.max_chunk + tok] = ps.lse();
+        if (a.lse && d == 0) a.lse[(size_t)gq * a.max_chunk + tok] = ps.lse();
         return;
     }
     const size_t at = ((size_t)h * a.L * a.G + rho) * a.nsplit + sp;
@@ -298,6 +327,48 @@ __device__ __forceinline__ void leave_row(const RowsArgs& a, int h, int sp, int 
         *(f32x4*)po = ps.o;
         if (d == 0) a.part_ml[at] = float2{ps.m, ps.l};
     }
+}
+
+// The second launch: one thread per four columns of a row.  N = classes that can have a piece (4, 8 or 16).
+template <typename T, int D, int N, bool NAT>
+__global__ void __launch_bounds__(256)
+merge_rows_kernel(const float* __restrict__ part_o, const float2* __restrict__ part_ml, T* __restrict__ out,
+                  float* __restrict__ lse, int M, int Hq, int G, int max_chunk, int nsplit)
+{
+    const int h = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= M * (D / 4)) return;
+    const int rho = i / (D / 4), d = 4 * (i % (D / 4)), tok = rho / G, gq = h * G + rho - tok * G;
+    const float2* pml = part_ml + ((size_t)h * M + rho) * nsplit;
+    const float* po = part_o + ((size_t)h * M + rho) * nsplit * D + d;
+    PieceSumT<NAT> ps[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) {                              // all requested before any is used
+        const int s = min(c, nsplit - 1);
+        const float2 ml = pml[s];
+        ps[c] = PieceSumT<NAT>{c < nsplit ? ml.x : -__builtin_inff(), ml.y, *(const f32x4*)(po + (size_t)s * D)};
+    }
+    if (N == RW_CLASSES)
+        for (int s0 = RW_CLASSES; s0 < nsplit; s0 += RW_CLASSES)
+#pragma unroll
+            for (int c = 0; c < N; ++c)
+                if (s0 + c < nsplit) ps[c].absorb(pml[s0 + c], *(const f32x4*)(po + (size_t)(s0 + c) * D));
+    const PieceSumT<NAT> tot = add_tree(ps);
+    store_out4(out + ((size_t)tok * Hq + gq) * D + d, tot.out());
+    if (lse && d == 0) lse[(size_t)gq * max_chunk + tok] = tot.lse();
+}
+
+template <typename T, int D, bool NAT>
+void launch_merge_rows(const RowsArgsT<T>& a, hipStream_t st)
+{
+    const int M = a.L * a.G;
+    const dim3 grid((unsigned)((M * (D / 4) + 255) / 256), (unsigned)a.Hkv), block(256);
+#define INFMLLM_MERGE(N)                                                                                                    \
+    hipLaunchKernelGGL((merge_rows_kernel<T, D, N, NAT>), grid, block, 0, st, a.part_o, a.part_ml, a.out, a.lse, M, a.Hq, a.G, \
+                       a.max_chunk, a.nsplit)
+    if (a.nsplit <= 4) INFMLLM_MERGE(4);
+    else if (a.nsplit <= 8) INFMLLM_MERGE(8);
+    else INFMLLM_MERGE(16);
+#undef INFMLLM_MERGE
 }
 
 }  // namespace

@@ -53,7 +53,7 @@ attn_rows_kernel(RowsArgs a)
     const int n_end = t + token(min(row0 + C::ROWS, M) - 1) + 1;
     const int k_end = min((sp + 1) * a.ks, n_end);
 
-    const RunLoader<D> runs(a, h, lane);
+    const RunLoader<uint16_t, D, RW_RUN> runs(a, h, lane);
     char* const mine = smem + wave * C::STAGE;
     auto load_run = [&](int k0, char* dst) { runs.template load<true, true>(k0, dst); };
     const int k_first = sp * a.ks + wave * RW_RUN;
@@ -271,38 +271,10 @@ attn_rows_kernel(RowsArgs a)
             if (c == 0) {
                 const int tok = token(r), gq = h * a.G + r - tok * a.G;
                 store_out4(a.out + ((size_t)tok * a.Hq + gq) * D + d, ps.out());
-                if (a.lse2 && d == 0) a.lse2[(size_t)gq * a.max_chunk + tok] = ps.lse();
+                if (a.lse && d == 0) a.lse[(size_t)gq * a.max_chunk + tok] = ps.lse();
             }
         }
     }
-}
-
-// The second launch: one thread per four columns of a row.  N = classes that can have a piece (4, 8 or 16).
-template <int D, int N>
-__global__ void __launch_bounds__(256)
-merge_rows_kernel(const float* __restrict__ part_o, const float2* __restrict__ part_ml, uint16_t* __restrict__ out,
-                  float* __restrict__ lse2, int M, int Hq, int G, int max_chunk, int nsplit)
-{
-    const int h = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * (D / 4)) return;
-    const int rho = i / (D / 4), d = 4 * (i % (D / 4)), tok = rho / G, gq = h * G + rho - tok * G;
-    const float2* pml = part_ml + ((size_t)h * M + rho) * nsplit;
-    const float* po = part_o + ((size_t)h * M + rho) * nsplit * D + d;
-    PieceSum ps[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) {                              // all requested before any is used
-        const int s = min(c, nsplit - 1);
-        const float2 ml = pml[s];
-        ps[c] = PieceSum{c < nsplit ? ml.x : -__builtin_inff(), ml.y, *(const f32x4*)(po + (size_t)s * D)};
-    }
-    if (N == RW_CLASSES)
-        for (int s0 = RW_CLASSES; s0 < nsplit; s0 += RW_CLASSES)
-#pragma unroll
-            for (int c = 0; c < N; ++c)
-                if (s0 + c < nsplit) ps[c].absorb(pml[s0 + c], *(const f32x4*)(po + (size_t)(s0 + c) * D));
-    const PieceSum tot = add_tree(ps);
-    store_out4(out + ((size_t)tok * Hq + gq) * D + d, tot.out());
-    if (lse2 && d == 0) lse2[(size_t)gq * max_chunk + tok] = tot.lse();
 }
 
 template <int D, int NRB, bool EXACT>
@@ -323,15 +295,7 @@ hipError_t launch_rows_d(const RowsArgs& args, int nrb, hipStream_t st)
     else if constexpr (D == 128) launch_rows64(a, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.nsplit == 1 || a.arrived) return e;
-    const int M = a.L * a.G;
-    const dim3 grid((unsigned)((M * (D / 4) + 255) / 256), (unsigned)a.Hkv), block(256);
-#define INFMLLM_MERGE(N)                                                                                                \
-    hipLaunchKernelGGL((merge_rows_kernel<D, N>), grid, block, 0, st, a.part_o, a.part_ml, a.out, a.lse2, M, a.Hq, a.G, \
-                       a.max_chunk, a.nsplit)
-    if (a.nsplit <= 4) INFMLLM_MERGE(4);
-    else if (a.nsplit <= 8) INFMLLM_MERGE(8);
-    else INFMLLM_MERGE(16);
-#undef INFMLLM_MERGE
+    launch_merge_rows<uint16_t, D, false>(a, st);
     return hipGetLastError();
 }
 
@@ -354,7 +318,7 @@ hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void*
 {
     RowsArgs a{};
     a.q = (const uint16_t*)q; a.K = (uint16_t*)c.K; a.V = (uint16_t*)c.V;
-    a.kc = (const uint16_t*)k; a.vc = (const uint16_t*)v; a.out = (uint16_t*)out; a.lse2 = nullptr;
+    a.kc = (const uint16_t*)k; a.vc = (const uint16_t*)v; a.out = (uint16_t*)out; a.lse = nullptr;
     a.part_o = sc.o; a.part_ml = sc.ml;
     a.pos = c.pos; a.score = c.score; a.rank = c.rank; a.row = c.row; a.pos0 = (int)pos;
     a.t = t; a.L = T; a.tc = t; a.Hq = g.Hq; a.Hkv = g.Hkv; a.G = g.G; a.cap = g.cap; a.max_chunk = g.max_chunk;
@@ -407,7 +371,7 @@ hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySou
 {
     RowsArgs a{};
     a.q = (const uint16_t*)q; a.K = (uint16_t*)c.K; a.V = (uint16_t*)c.V;
-    a.kc = (const uint16_t*)ks.k; a.vc = (const uint16_t*)ks.v; a.out = (uint16_t*)out; a.lse2 = lse;
+    a.kc = (const uint16_t*)ks.k; a.vc = (const uint16_t*)ks.v; a.out = (uint16_t*)out; a.lse = lse;
     a.part_o = sc.o; a.part_ml = sc.ml;
     a.t = t; a.L = L; a.tc = ks.rows; a.Hq = g.Hq; a.Hkv = g.Hkv; a.G = g.G; a.cap = g.cap; a.max_chunk = g.max_chunk;
     a.ks = plan.keys;

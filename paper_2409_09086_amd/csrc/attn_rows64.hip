@@ -40,7 +40,7 @@ attn_rows64_kernel(RowsArgs a)
     const int n_end = t + rows_token(a, min(row0 + C::ROWS, M) - 1) + 1;
     const int k_end = min((sp + 1) * a.ks, n_end);
 
-    const RunLoader<D> runs(a, h, lane);
+    const RunLoader<uint16_t, D, RW_RUN> runs(a, h, lane);
     char* const mine = smem + wave * C::STAGE;
     // queries: row r of the group in LDS row r, swizzled like K
 #pragma unroll

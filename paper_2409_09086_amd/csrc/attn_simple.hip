@@ -1,8 +1,5 @@
-// Plain fp32-arithmetic chunk attention and column scoring for gfx950.
-//
-// This is the path of fp32 streams (an fp32 contraction cannot go through the bf16 matrix
-// cores within the 1e-4 output tolerance); bf16 streams use the MFMA kernels instead and
-// reach this file only when the stream was created with the plain-arithmetic override.
+// Plain fp32-arithmetic chunk attention and column scoring for gfx950: the path of bf16 streams that were created with
+// the plain-arithmetic override.  (bf16 streams otherwise use the bf16 matrix cores, fp32 streams attn_f32.hip.)
 //
 //   attn_simple  : Sec. 3.2 -- the L new queries attend the t cached keys and, causally, the
 //                  chunk's own keys.  One workgroup per (query row, query head): logits into
@@ -24,11 +21,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 template <typename T> struct Elt;
-template <> struct Elt<float> {
-    static __device__ __forceinline__ float load(const float* p) { return *p; }
-    static __device__ __forceinline__ f32x4 load4(const float* p) { return *(const f32x4*)p; }   // p 16-byte aligned
-    static __device__ __forceinline__ void store(float* p, float x) { *p = x; }
-};
 template <> struct Elt<uint16_t> {   // bf16 held as raw bits
     static __device__ __forceinline__ float load(const uint16_t* p) { return __uint_as_float((uint32_t)(*p) << 16); }
     static __device__ __forceinline__ f32x4 load4(const uint16_t* p)                              // p 8-byte aligned
@@ -248,9 +240,7 @@ hipError_t launch_attn_simple(const Geometry& g, const CacheView& c, const void*
                            (const TT*)c.K, (const TT*)c.V, (TT*)out, lse, t, L, g.Hq, g.G, g.cap,       \
                            g.max_chunk, (float)g.scale);                                                       \
     } while (0)
-    if (g.elt == 4 && g.d == 64) INFMLLM_ATTN(float, 64);
-    else if (g.elt == 4 && g.d == 128) INFMLLM_ATTN(float, 128);
-    else if (g.elt == 2 && g.d == 64) INFMLLM_ATTN(uint16_t, 64);
+    if (g.elt == 2 && g.d == 64) INFMLLM_ATTN(uint16_t, 64);
     else if (g.elt == 2 && g.d == 128) INFMLLM_ATTN(uint16_t, 128);
     else return hipErrorInvalidValue;
 #undef INFMLLM_ATTN
@@ -267,9 +257,7 @@ hipError_t launch_score_simple(const Geometry& g, const CacheView& c, const void
     hipLaunchKernelGGL((score_simple_kernel<TT, DD>), grid, block, 0, st, (const TT*)q, (const TT*)c.K, \
                        lse, g.policy == POLICY_CUMULATIVE ? c.score : nullptr, c.rank, Wb, L, lq, g.Hq, g.G, g.cap, \
                        g.max_chunk, cnd, n, (float)g.scale, (float)(g.bias / (double)cnd))
-    if (g.elt == 4 && g.d == 64) INFMLLM_SCORE(float, 64);
-    else if (g.elt == 4 && g.d == 128) INFMLLM_SCORE(float, 128);
-    else if (g.elt == 2 && g.d == 64) INFMLLM_SCORE(uint16_t, 64);
+    if (g.elt == 2 && g.d == 64) INFMLLM_SCORE(uint16_t, 64);
     else if (g.elt == 2 && g.d == 128) INFMLLM_SCORE(uint16_t, 128);
     else return hipErrorInvalidValue;
 #undef INFMLLM_SCORE

@@ -63,20 +63,20 @@ struct MoveList {
 hipError_t launch_append(const Geometry& g, const CacheView& c, const void* k, const void* v,
                          int t, int L, int64_t T, hipStream_t st);
 
-// a2 (plain fp32 arithmetic, any dtype): out and per-row log-sum-exp.
+// a2 (plain fp32 arithmetic on bf16 streams, the debug override): out and per-row log-sum-exp (natural).
 hipError_t launch_attn_simple(const Geometry& g, const CacheView& c, const void* q, int t, int L,
                               void* out, float* lse, hipStream_t st);
 
-// a3+a4 (plain fp32 arithmetic, any dtype): W'[h][j] for j < cnd = n - R, j = the stream-order index of a
+// a3+a4 (plain fp32 arithmetic on bf16 streams, the debug override): W'[h][j] for j < cnd = n - R, j = the stream-order index of a
 // column (c.rank of its physical row); all n rows are in the cache here.
 // With g.policy == POLICY_CUMULATIVE the score is S plus the score the row carries in c.score
 // (a row never ranked carries +inf there and counts as 0) and no bias is applied.
 hipError_t launch_score_simple(const Geometry& g, const CacheView& c, const void* q, const float* lse,
                                int t, int L, float* Wb, hipStream_t st);
 
-// Scratch of the matrix-core scoring launch.
+// Scratch of the matrix-core scoring launches.
 struct FwdScratch {
-    // Row-split scoring: raw column sums of each split, [SCORE_SPLIT_WGS][256] fp32, followed by one
+    // Row-split scoring: raw column sums of each split, [SCORE_SPLIT_WGS][256] fp32 (at most), followed by one
     // arrival counter per (kv-head, column block), [SCORE_SPLIT_WGS] int32, zero between launches.
     float* score_part;
 };
@@ -104,6 +104,12 @@ struct RowsScratch {
 // a2 on bf16 MFMA (bf16 streams only): out and the row log-sum-exp (base 2).
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
                             void* out, float* lse, const RowsScratch& sc, hipStream_t st);
+
+// a2 and a3+a4 of fp32 streams, on the fp32 matrix cores; lse is the natural log-sum-exp.
+hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
+                           void* out, float* lse, const RowsScratch& sc, hipStream_t st);
+hipError_t launch_score_f32(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, const float* lse,
+                            const FwdScratch& sc, int t, int L, float* Wb, hipStream_t st);
 
 // The same for head_dim 128 with 64 query rows per wavefront (one wavefront per SIMD, 256-row workgroups):
 // the shape for long key ranges and grids that fill the chip; launch_attn_mfma picks it by itself.
