@@ -390,14 +390,25 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
     const bool mfma = s->mfma(), f32 = s->f32();
     hipError_t e;
 
-    // An evicting step on the matrix cores never appends: attention and scoring read the chunk's
-    // rows in place and the placement writes the survivors into the rows the eviction frees.
-    const bool in_place = (mfma || f32) && n > g.B;
+    // On the matrix cores attention and scoring read the chunk's rows in place.  An evicting step never appends: the
+    // placement writes the survivors into the rows the eviction frees; in one that evicts nothing the attention launch
+    // writes the chunk into the cache as well.  The position encoding turns rows of the cache, so with it (and where out
+    // overwrites the chunk's tensors) a step that evicts nothing appends first.
+    const bool warm = n <= g.B;
+    const size_t kv_bytes = (size_t)L * g.Hkv * g.d * g.elt, out_bytes = (size_t)L * g.Hq * g.d * g.elt;
+    auto overwritten = [&](const void* x) {
+        return (uintptr_t)out < (uintptr_t)x + kv_bytes && (uintptr_t)x < (uintptr_t)out + out_bytes;
+    };
+    const bool in_place = (mfma || f32) && !(warm && (s->rope_base > 0.0 || overwritten(k) || overwritten(v)));
     const KeySource ks = in_place ? KeySource{t, k, v} : KeySource{n, nullptr, nullptr};
+    AppendJob job{};
+    if (warm || !in_place)
+        job = append_job(g, cur, k, v, t, L, s->streamed, warm ? retained : nullptr, warm ? n_retained : nullptr);
     if (!in_place) {
         s->mark(INFMLLM_K_APPEND, 0);
-        if ((e = launch_append(g, cur, k, v, t, L, s->streamed, s->st)) != hipSuccess) return fail_hip(e, "append");
+        if ((e = launch_append(job, s->st)) != hipSuccess) return fail_hip(e, "append");
         s->mark(INFMLLM_K_APPEND, 1);
+        job.k = nullptr;                                       // done
     }
     // With the position encoding on, attention and scoring read turned copies of the keys and queries;
     // selection and compaction go on working with the rows as given (ks).
@@ -417,17 +428,16 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
         s->rot_rows = in_place ? t : n;
     }
     s->mark(INFMLLM_K_ATTN, 0);
-    e = mfma  ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, s->st)
-        : f32 ? launch_attn_f32(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, s->st)
+    e = mfma  ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, job, s->st)
+        : f32 ? launch_attn_f32(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, job, s->st)
               : launch_attn_simple(g, att, q_att, t, L, out, s->lse, s->st);
     if (e != hipSuccess) return fail_hip(e, "attention");
     s->mark(INFMLLM_K_ATTN, 1);
 
-    *evict = n > g.B;
+    *evict = !warm;
     *ks_out = ks;
-    if (n <= g.B) {
+    if (warm) {
         // the chunk fits: nothing is evicted
-        if ((e = launch_iota(g, n, retained, n_retained, s->st)) != hipSuccess) return fail_hip(e, "index list");
         s->len = n;
         s->last_cnd = 0;
         s->streamed += L;
@@ -609,7 +619,7 @@ static int decode_some(infmllm_stream* s, const void* q, const void* k, const vo
     if (s->rope_base > 0.0) {
         // the tokens' rows enter the cache as given; the decoding kernels see the turned copies (and put the
         // turned keys at rows t.. of K_rot themselves)
-        if ((e = launch_append(s->g, s->cache, k, v, t, T, s->streamed, s->st)) != hipSuccess) return fail_hip(e, "decode: append");
+        if ((e = launch_append(append_job(s->g, s->cache, k, v, t, T, s->streamed, nullptr, nullptr), s->st)) != hipSuccess) return fail_hip(e, "decode: append");
         e = launch_rope(s->g, s->cache.K, s->K_rot, s->cache.rank, s->rot_rows < t ? s->rot_rows : t, t, k, s->kc_rot, q,
                         s->q_rot, t, T, s->rope_tab, s->st);
         if (e != hipSuccess) return fail_hip(e, "decode: position encoding");

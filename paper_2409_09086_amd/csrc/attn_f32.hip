@@ -17,6 +17,7 @@
 // 256 rows over 1024 keys, 8 heads of 128.
 #include <algorithm>
 
+#include "append_body.h"
 #include "attn_rows.h"
 
 namespace infmllm {
@@ -31,9 +32,9 @@ __device__ __forceinline__ f32x4 mfma16_f32(float a, float b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <int D>
+template <int D, bool APPEND>
 __global__ void __launch_bounds__(RW_NT)
-attn_f32_kernel(RowsArgsT<float> a)
+attn_f32_kernel(RowsArgsT<float> a, AppendJob ap)
 {
     typedef RunLoader<float, D, F32_RUN> Runs;
     constexpr int ROWB = Runs::ROWB, RUN = Runs::RUN, STAGE = 2 * RUN;
@@ -62,6 +63,8 @@ attn_f32_kernel(RowsArgsT<float> a)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) qf[j] = *(const f32x4*)(qp + 16 * j);
     }
+    if constexpr (APPEND)
+        append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     f32x4 o[NJ];                                               // block b: lane (row c16, group g4) holds columns VW (4 g4 + i) + b
 #pragma unroll
     for (int b = 0; b < NJ; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -254,7 +257,7 @@ score_f32_kernel(const float* __restrict__ q, const float* __restrict__ K, const
 }  // namespace
 
 hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                           void* out, float* lse, const RowsScratch& sc, hipStream_t st)
+                           void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st)
 {
     RowsArgsT<float> a{};
     a.q = (const float*)q; a.K = (float*)c.K; a.V = (float*)c.V; a.kc = (const float*)ks.k; a.vc = (const float*)ks.v;
@@ -271,10 +274,12 @@ hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySourc
     a.nsplit = (n + a.ks - 1) / a.ks;
     const dim3 grid((unsigned)a.nsplit, (unsigned)g.Hkv, (unsigned)((L * g.G + 15) / 16)), block(RW_NT);
     if (g.d == 128) {
-        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, st, a);
+        if (ap.k) hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, block, 0, st, a, ap);
+        else hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, block, 0, st, a, ap);
         if (a.nsplit > 1) launch_merge_rows<float, 128, true>(a, st);
     } else if (g.d == 64) {
-        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, st, a);
+        if (ap.k) hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, block, 0, st, a, ap);
+        else hipLaunchKernelGGL((attn_f32_kernel<64, false>), grid, block, 0, st, a, ap);
         if (a.nsplit > 1) launch_merge_rows<float, 64, true>(a, st);
     } else {
         return hipErrorInvalidValue;

@@ -20,6 +20,7 @@
 //
 // fp32 is kept from the MFMA accumulators to the score: the bf16 rounding of P is applied only
 // to the copy that feeds the P.V product.
+#include "append_body.h"
 #include "launch.h"
 #include "mfma_common.h"
 
@@ -135,7 +136,7 @@ __global__ void __launch_bounds__(64 * RB * KW)
 attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                 const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, int tc,
                 uint16_t* __restrict__ out, float* __restrict__ lse2, int t, int L, int Hq, int G, int cap,
-                int max_chunk, int hpw, int ntile, int ny, float c /* scale * log2(e) */)
+                int max_chunk, int hpw, int ntile, int ny, float c /* scale * log2(e) */, AppendJob ap)
 {
     using C = FwdCfg<D, RB, KW, KVB>;
     __shared__ __attribute__((aligned(16))) char smem[C::LDS];
@@ -259,6 +260,7 @@ attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, 
     const int ntiles = (n_end + C::TILE - 1) / C::TILE;
     constexpr int tile_lo = 0;
     if (tile_lo < ntiles) fetch(tile_lo * C::TILE);
+    if (ap.k) append_share(ap, blockIdx.x, gridDim.x, tid, C::NT);
     if (C::NBUF == 2) {
         if (tile_lo < ntiles) stash(tile_lo & 1);
         if (tile_lo + 1 < ntiles) fetch((tile_lo + 1) * C::TILE);
@@ -678,7 +680,7 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
 
 template <int D, int RB, int KW, int KVB>
 hipError_t launch_fwd_cfg(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                          void* out, float* lse, hipStream_t st)
+                          void* out, float* lse, const AppendJob& ap, hipStream_t st)
 {
     const int hpw = (RB % g.G == 0) ? g.G : ((g.G % RB == 0) ? RB : 1);
     const int rbph = RB / hpw;
@@ -686,12 +688,12 @@ hipError_t launch_fwd_cfg(const Geometry& g, const CacheView& c, const KeySource
     const dim3 grid(ntile * ny), block(64 * RB * KW);
     hipLaunchKernelGGL((attn_fwd_kernel<D, RB, KW, KVB>), grid, block, 0, st, (const uint16_t*)q, (const uint16_t*)c.K, (const uint16_t*)c.V,
                        (const uint16_t*)ks.k, (const uint16_t*)ks.v, ks.rows, (uint16_t*)out, lse, t, L, g.Hq, g.G,
-                       g.cap, g.max_chunk, hpw, ntile, ny, (float)(g.scale * (double)LOG2E));
+                       g.cap, g.max_chunk, hpw, ntile, ny, (float)(g.scale * (double)LOG2E), ap);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                            void* out, float* lse, const RowsScratch& sc, hipStream_t st)
+                            void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st)
 {
     if (g.d != 64 && g.d != 128) return hipErrorInvalidValue;
     if (g.attn_tile == 0) {
@@ -707,9 +709,9 @@ hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySour
                             : wgs2 >= 140 ? rounds * (10.f + 0.0148f * (float)n)
                                           : rounds * (9.f + 0.0096f * (float)n) * (1.f + 0.15f * fill);
         RowsPlan plan{};
-        if (rows_chunk_plan(g, n, L, sc.cap_rows, plan) < other) return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, plan, st);
+        if (rows_chunk_plan(g, n, L, sc.cap_rows, plan) < other) return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, plan, ap, st);
     }
-    if (g.d == 64) return launch_fwd_cfg<64, 4, 1, 2>(g, c, ks, q, t, L, out, lse, st);
+    if (g.d == 64) return launch_fwd_cfg<64, 4, 1, 2>(g, c, ks, q, t, L, out, lse, ap, st);
     // 128 query rows x 64 keys per wavefront-tile is the efficient shape; when that grid would cover
     // only about half of the chip (128 workgroups at 32 heads x 512 rows), 64-row workgroups with four
     // key ways inside the workgroup are faster.  g.attn_tile > 0 (a test hook) forces one shape.
@@ -722,11 +724,15 @@ hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySour
     const bool fills = wgs64 * 5 >= rounds64 * 256 * 4;
     const int v = g.attn_tile > 0 ? g.attn_tile : (fills && t + L >= 1024 ? 5 : (wgs128 >= 140 ? 1 : 2));
     switch (v) {
-        case 5: return launch_attn_mfma64(g, c, ks, q, t, L, out, lse, st);
-        case 1: return launch_fwd_cfg<128, 4, 2, 2>(g, c, ks, q, t, L, out, lse, st);
-        case 2: return launch_fwd_cfg<128, 2, 4, 1>(g, c, ks, q, t, L, out, lse, st);
-        case 3: return launch_fwd_cfg<128, 4, 2, 1>(g, c, ks, q, t, L, out, lse, st);
-        default: return launch_fwd_cfg<128, 4, 1, 2>(g, c, ks, q, t, L, out, lse, st);
+        case 5: {
+            // no share of the job here: the kernel has its SIMDs to itself and no register to spare
+            const hipError_t e = ap.k ? launch_append(ap, st) : hipSuccess;
+            return e != hipSuccess ? e : launch_attn_mfma64(g, c, ks, q, t, L, out, lse, st);
+        }
+        case 1: return launch_fwd_cfg<128, 4, 2, 2>(g, c, ks, q, t, L, out, lse, ap, st);
+        case 2: return launch_fwd_cfg<128, 2, 4, 1>(g, c, ks, q, t, L, out, lse, ap, st);
+        case 3: return launch_fwd_cfg<128, 4, 2, 1>(g, c, ks, q, t, L, out, lse, ap, st);
+        default: return launch_fwd_cfg<128, 4, 1, 2>(g, c, ks, q, t, L, out, lse, ap, st);
     }
 }
 

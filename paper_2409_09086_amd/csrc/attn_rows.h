@@ -29,7 +29,7 @@ struct RowsArgsT {
 };
 typedef RowsArgsT<uint16_t> RowsArgs;
 
-void launch_rows64(const RowsArgs& a, hipStream_t st);
+void launch_rows64(const RowsArgs& a, const AppendJob& ap, hipStream_t st);
 
 namespace {
 

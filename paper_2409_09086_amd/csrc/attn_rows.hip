@@ -25,15 +25,16 @@
 // launch where there are many rows.
 #include <algorithm>
 
+#include "append_body.h"
 #include "attn_rows.h"
 
 namespace infmllm {
 
 namespace {
 
-template <int D, int NRB, bool EXACT>
+template <int D, int NRB, bool EXACT, bool APPEND>
 __global__ void __launch_bounds__(RW_NT)
-attn_rows_kernel(RowsArgs a)
+attn_rows_kernel(RowsArgs a, AppendJob ap)
 {
     using C = RowsCfg<D, NRB>;
     __shared__ __attribute__((aligned(1024))) char smem[(RW_NW + 1) * C::STAGE];   // a run of K and V per wavefront, two for the first one
@@ -75,6 +76,8 @@ attn_rows_kernel(RowsArgs a)
         for (int s = 0; s < C::NS; ++s) qf[x][s] = as_bf16x8(*(const u32x4*)(qp + 32 * s));
     }
 
+    if constexpr (APPEND)
+        append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     f32x4 o[NRB][C::NC];
     float m_ref[NRB], m_use[NRB], lsum[NRB];
 #pragma unroll
@@ -278,21 +281,26 @@ attn_rows_kernel(RowsArgs a)
 }
 
 template <int D, int NRB, bool EXACT>
-void launch_rows_cfg(const RowsArgs& a, hipStream_t st)
+void launch_rows_cfg(const RowsArgs& a, const AppendJob& ap, hipStream_t st)
 {
     constexpr int ROWS = 16 * NRB;
     const dim3 grid((unsigned)a.nsplit, (unsigned)a.Hkv, (unsigned)((a.L * a.G + ROWS - 1) / ROWS));
-    hipLaunchKernelGGL((attn_rows_kernel<D, NRB, EXACT>), grid, dim3(RW_NT), 0, st, a);
+    if constexpr (!EXACT)
+        if (ap.k) {
+            hipLaunchKernelGGL((attn_rows_kernel<D, NRB, false, true>), grid, dim3(RW_NT), 0, st, a, ap);
+            return;
+        }
+    hipLaunchKernelGGL((attn_rows_kernel<D, NRB, EXACT, false>), grid, dim3(RW_NT), 0, st, a, ap);
 }
 
 template <int D, bool EXACT>
-hipError_t launch_rows_d(const RowsArgs& args, int nrb, hipStream_t st)
+hipError_t launch_rows_d(const RowsArgs& args, int nrb, const AppendJob& ap, hipStream_t st)
 {
     RowsArgs a = args;
     a.inv_g = (uint32_t)((1ull << 32) / (unsigned)a.G + 1);
-    if (nrb == 1) launch_rows_cfg<D, 1, EXACT>(a, st);
-    else if (EXACT || nrb == 2) launch_rows_cfg<D, 2, EXACT>(a, st);
-    else if constexpr (D == 128) launch_rows64(a, st);
+    if (nrb == 1) launch_rows_cfg<D, 1, EXACT>(a, ap, st);
+    else if (EXACT || nrb == 2) launch_rows_cfg<D, 2, EXACT>(a, ap, st);
+    else if constexpr (D == 128) launch_rows64(a, ap, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.nsplit == 1 || a.arrived) return e;
     launch_merge_rows<uint16_t, D, false>(a, st);
@@ -328,8 +336,8 @@ hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void*
     if ((long)g.Hq * T * a.nsplit > sc.cap_rows) return hipErrorInvalidValue;
     const int M = T * g.G, nrb = M <= 16 ? 1 : 2;
     a.arrived = M <= 16 && M * a.nsplit <= RW_TICKET_PARTS ? sc.arrived : nullptr;
-    if (g.d == 128) return launch_rows_d<128, true>(a, nrb, st);
-    if (g.d == 64) return launch_rows_d<64, true>(a, nrb, st);
+    if (g.d == 128) return launch_rows_d<128, true>(a, nrb, AppendJob{}, st);
+    if (g.d == 64) return launch_rows_d<64, true>(a, nrb, AppendJob{}, st);
     return hipErrorInvalidValue;
 }
 
@@ -367,7 +375,8 @@ float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, RowsPlan& 
 }
 
 hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                             void* out, float* lse, const RowsScratch& sc, const RowsPlan& plan, hipStream_t st)
+                             void* out, float* lse, const RowsScratch& sc, const RowsPlan& plan, const AppendJob& ap,
+                             hipStream_t st)
 {
     RowsArgs a{};
     a.q = (const uint16_t*)q; a.K = (uint16_t*)c.K; a.V = (uint16_t*)c.V;
@@ -379,8 +388,8 @@ hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySou
     a.c = (float)(g.scale * (double)LOG2E);
     if (a.nsplit > 1 && (long)g.Hq * L * a.nsplit > sc.cap_rows) return hipErrorInvalidValue;
     a.arrived = plan.nrb == 1 && L * g.G <= 16 && L * g.G * a.nsplit <= RW_TICKET_PARTS ? sc.arrived : nullptr;
-    if (g.d == 128) return launch_rows_d<128, false>(a, plan.nrb, st);
-    if (g.d == 64) return launch_rows_d<64, false>(a, plan.nrb, st);
+    if (g.d == 128) return launch_rows_d<128, false>(a, plan.nrb, ap, st);
+    if (g.d == 64) return launch_rows_d<64, false>(a, plan.nrb, ap, st);
     return hipErrorInvalidValue;
 }
 

@@ -7,6 +7,7 @@
 // LDS, which all wavefronts share, beside the K fragments.  K and V have one buffer each per wavefront: a run's K
 // buffer is refilled as soon as S has its fragments, its V buffer as soon as O has.  A pass of 256 keys takes 1.9 us (LDS:
 // 384 KB, 1.5 us; products 1.0), two workgroups of 32 rows 2.7.
+#include "append_body.h"
 #include "attn_rows.h"
 
 namespace infmllm {
@@ -23,9 +24,10 @@ struct Rows64Cfg {
     static_assert(ROWS * MC * 4 <= STAGE, "the merge reuses the buffers of the tiles");
 };
 
-template <int D>
+// APPEND: an instance of its own, the job's arguments would cost the other one registers it does not have
+template <int D, bool APPEND>
 __global__ void __launch_bounds__(RW_NT)
-attn_rows64_kernel(RowsArgs a)
+attn_rows64_kernel(RowsArgs a, AppendJob ap)
 {
     using C = Rows64Cfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[RW_NW * C::STAGE];
@@ -188,6 +190,7 @@ attn_rows64_kernel(RowsArgs a)
         products(I1{});
     }
 
+    if constexpr (APPEND) append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     // ---- merge the wavefronts (see attn_rows_kernel), half of the columns at a time
 #pragma unroll
     for (int x = 0; x < C::NX; ++x) {
@@ -219,10 +222,11 @@ attn_rows64_kernel(RowsArgs a)
 
 }  // namespace
 
-void launch_rows64(const RowsArgs& a, hipStream_t st)
+void launch_rows64(const RowsArgs& a, const AppendJob& ap, hipStream_t st)
 {
     const dim3 grid((unsigned)a.nsplit, (unsigned)a.Hkv, (unsigned)((a.L * a.G + Rows64Cfg<128>::ROWS - 1) / Rows64Cfg<128>::ROWS));
-    hipLaunchKernelGGL(attn_rows64_kernel<128>, grid, dim3(RW_NT), 0, st, a);
+    if (ap.k) hipLaunchKernelGGL((attn_rows64_kernel<128, true>), grid, dim3(RW_NT), 0, st, a, ap);
+    else hipLaunchKernelGGL((attn_rows64_kernel<128, false>), grid, dim3(RW_NT), 0, st, a, ap);
 }
 
 }  // namespace infmllm

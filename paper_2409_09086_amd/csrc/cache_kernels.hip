@@ -1,9 +1,12 @@
-// Cache maintenance kernels for gfx950: append (Sec. 3.2, first paragraph), the warm-up index
+// Cache maintenance kernels for gfx950: append (Sec. 3.2, first paragraph) with the warm-up index
 // list, the placement that completes an eviction (Alg. 1 l.8: only the retained rows that are not
 // already inside physical rows 0..B-1 are moved, into the rows the eviction frees) and the export of
 // the cache in stream order.  All are pure data movement and HBM-bound: every thread moves 16-byte
 // vectors, a row of head_dim elements is covered by consecutive lanes so that each wavefront touches
 // whole rows.
+#include <algorithm>
+
+#include "append_body.h"
 #include "launch.h"
 
 namespace infmllm {
@@ -12,30 +15,10 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// chunk k/v [L][Hkv][d]  ->  cache rows [h][t+i][d]
 __global__ void __launch_bounds__(256)
-append_kernel(const u32x4* __restrict__ k, const u32x4* __restrict__ v, u32x4* __restrict__ K,
-              u32x4* __restrict__ V, int32_t* __restrict__ pos, float* __restrict__ score,
-              int32_t* __restrict__ rank, int32_t* __restrict__ row, int t, int L, int Hkv, int cap, int vec_per_row,
-              int pos0)
+append_kernel(AppendJob job)
 {
-    const long total = (long)L * Hkv * vec_per_row;
-    for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (long)gridDim.x * blockDim.x) {
-        const int x = (int)(idx % vec_per_row);
-        const long ih = idx / vec_per_row;
-        const int h = (int)(ih % Hkv);
-        const int i = (int)(ih / Hkv);
-        const long dst = ((long)h * cap + t + i) * vec_per_row + x;
-        K[dst] = k[idx];
-        V[dst] = v[idx];
-        if (x == 0) {
-            pos[(long)h * cap + t + i] = pos0 + i;
-            score[(long)h * cap + t + i] = __builtin_inff();
-            rank[(long)h * cap + t + i] = t + i;          // the cached rows fill physical rows 0..t-1, so the
-            row[(long)h * cap + t + i] = t + i;           // next stream-order index and the next free row agree
-        }
-    }
+    append_share(job, blockIdx.x, gridDim.x, threadIdx.x, 256);
 }
 
 __global__ void __launch_bounds__(256)
@@ -43,17 +26,6 @@ zero_kernel(u32x4* __restrict__ p, size_t nvec)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += (size_t)gridDim.x * blockDim.x)
         p[i] = u32x4{0u, 0u, 0u, 0u};
-}
-
-__global__ void __launch_bounds__(256)
-iota_kernel(int32_t* __restrict__ I, int32_t* __restrict__ count, int n, int Hkv, int B)
-{
-    const int total = n * Hkv;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += gridDim.x * blockDim.x) {
-        const int h = idx / n, j = idx - h * n;
-        if (I) I[(long)h * B + j] = j;
-    }
-    if (count && blockIdx.x == 0 && threadIdx.x == 0) *count = n;
 }
 
 __global__ void __launch_bounds__(256)
@@ -186,15 +158,19 @@ export_scalars_kernel(const int32_t* __restrict__ pos, const float* __restrict__
 
 }  // namespace
 
-hipError_t launch_append(const Geometry& g, const CacheView& c, const void* k, const void* v, int t,
-                         int L, int64_t T, hipStream_t st)
+AppendJob append_job(const Geometry& g, const CacheView& c, const void* k, const void* v, int t, int L, int64_t T,
+                     int32_t* list, int32_t* count)
 {
-    const int vpr = g.d * g.elt / 16;
-    const long total = (long)L * g.Hkv * vpr;
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(append_kernel, dim3(blocks), dim3(256), 0, st, (const u32x4*)k, (const u32x4*)v,
-                       (u32x4*)c.K, (u32x4*)c.V, c.pos, c.score, c.rank, c.row, t, L, g.Hkv, g.cap, vpr, (int)T);
+    int shift = 0;
+    while ((16 << shift) < g.d * g.elt) ++shift;              // a row is 128, 256 or 512 bytes
+    return AppendJob{k, v, c, list, count, t, L, (int)T, g.Hkv, g.cap, g.B, t + L, shift};
+}
+
+hipError_t launch_append(const AppendJob& job, hipStream_t st)
+{
+    const size_t total = std::max((size_t)job.L * job.Hkv << job.vec_shift, job.list ? (size_t)job.n * job.Hkv : (size_t)0);
+    const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 4096);
+    hipLaunchKernelGGL(append_kernel, dim3(blocks), dim3(256), 0, st, job);
     return hipGetLastError();
 }
 
@@ -206,15 +182,6 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t st)
     size_t blocks = (nvec + 255) / 256;
     if (blocks > 8192) blocks = 8192;
     hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (u32x4*)p, nvec);
-    return hipGetLastError();
-}
-
-hipError_t launch_iota(const Geometry& g, int n, int32_t* user_I, int32_t* user_count, hipStream_t st)
-{
-    if (!user_I && !user_count) return hipSuccess;
-    int blocks = (n * g.Hkv + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(iota_kernel, dim3(blocks), dim3(256), 0, st, user_I, user_count, n, g.Hkv, g.B);
     return hipGetLastError();
 }
 

@@ -59,9 +59,20 @@ struct MoveList {
     int max;
 };
 
-// a1: physical rows t..t+L-1 <- chunk; pos <- T..T+L-1; score <- +inf; rank and row <- identity there.
-hipError_t launch_append(const Geometry& g, const CacheView& c, const void* k, const void* v,
-                         int t, int L, int64_t T, hipStream_t st);
+// a1 and the list of a step that evicts nothing: physical rows t..t+L-1 <- chunk; pos <- pos0..pos0+L-1; score <- +inf;
+// rank and row <- identity there; list[h][j] = j for j < n (list and count may be null).  The attention kernels that
+// read the chunk in place take the job along (append_share in append_body.h), else launch_append does it.
+// k == nullptr: nothing to do.
+struct AppendJob {
+    const void *k, *v;  // chunk tensors [L][Hkv][d]
+    CacheView c;
+    int32_t* list;      // [Hkv][B]
+    int32_t* count;
+    int t, L, pos0, Hkv, cap, B, n, vec_shift;      // 2^vec_shift 16-byte vectors per row
+};
+AppendJob append_job(const Geometry& g, const CacheView& c, const void* k, const void* v, int t, int L, int64_t T,
+                     int32_t* list, int32_t* count);
+hipError_t launch_append(const AppendJob& job, hipStream_t st);
 
 // a2 (plain fp32 arithmetic on bf16 streams, the debug override): out and per-row log-sum-exp (natural).
 hipError_t launch_attn_simple(const Geometry& g, const CacheView& c, const void* q, int t, int L,
@@ -101,13 +112,14 @@ struct RowsScratch {
     long cap_rows;      // most (query row, piece) pairs of a launch
 };
 
-// a2 on bf16 MFMA (bf16 streams only): out and the row log-sum-exp (base 2).
+// a2 on bf16 MFMA (bf16 streams only): out and the row log-sum-exp (base 2).  With a job (ap.k set) the chunk also
+// enters the cache, beside the attention.
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                            void* out, float* lse, const RowsScratch& sc, hipStream_t st);
+                            void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st);
 
 // a2 and a3+a4 of fp32 streams, on the fp32 matrix cores; lse is the natural log-sum-exp.
 hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                           void* out, float* lse, const RowsScratch& sc, hipStream_t st);
+                           void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st);
 hipError_t launch_score_f32(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, const float* lse,
                             const FwdScratch& sc, int t, int L, float* Wb, hipStream_t st);
 
@@ -128,7 +140,8 @@ hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void*
 struct RowsPlan { int nrb, keys; };
 float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, RowsPlan& plan);
 hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                             void* out, float* lse, const RowsScratch& sc, const RowsPlan& plan, hipStream_t st);
+                             void* out, float* lse, const RowsScratch& sc, const RowsPlan& plan, const AppendJob& ap,
+                             hipStream_t st);
 
 // a3+a4 on bf16 MFMA (bf16 streams only).
 hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q,
@@ -185,9 +198,6 @@ hipError_t launch_rope(const Geometry& g, const void* K, void* Krot, const int32
 // Clears `bytes` bytes (a multiple of 16) at p (16-byte aligned) with a fill kernel, which, unlike a
 // memset node, may be recorded into a HIP graph.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
-
-// warm-up: I[h][j] = j for j < n.
-hipError_t launch_iota(const Geometry& g, int n, int32_t* user_I, int32_t* user_count, hipStream_t st);
 
 // Decoding step in plain fp32 arithmetic (fp32 streams, bf16 ones with the plain-arithmetic override): appends the
 // token's k, v as cache row t and attends all t + 1 keys with q (one

@@ -58,3 +58,39 @@ def test_tokens_do_not_depend_on_how_many_share_a_call(heads, kv, d, budget, rop
         assert (err <= 2.0 ** -8 * np.abs(ref) + 2e-5).all(), err.max()
     for x, y in zip(a.export(), b.export()):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("heads,kv,d,dtype,budget,chunks,report", [
+    (8, 2, 128, "bf16", 700, [300, 1, 17, 333, 49], True),          # attn_rows with 16 and 32 rows, cut and uncut
+    (16, 2, 128, "bf16", 1700, [333, 500, 867], True),              # 64 rows per workgroup
+    (32, 8, 128, "bf16", 2400, [1100, 1300], True),                 # attn_fwd: more keys than the first wave of shares copies
+    (32, 32, 128, "bf16", 3100, [2048, 1024], False),               # attn_fwd64: appended by a launch of its own; no lists wanted
+    (16, 4, 64, "bf16", 2100, [1024, 1030], True),
+    (6, 3, 64, "fp32", 300, [5, 128, 130], True),
+    (2, 1, 128, "fp32", 600, [333, 267], False),
+])
+def test_chunks_that_fit_enter_the_cache_as_given(heads, kv, d, dtype, budget, chunks, report):
+    """Steps that evict nothing: the cache is the concatenation of the chunks, bit for bit, with its positions and tables
+    (the export goes through them), and the list counts up.  A chunk whose output overwrites its own values included."""
+    dt = {"bf16": torch.bfloat16, "fp32": torch.float32}[dtype]
+    s = B.Stream(budget, budget // 4, heads, kv, d, dtype=dt, max_chunk=max(chunks))
+    twin = B.Stream(budget, budget // 4, heads, kv, d, dtype=dt, max_chunk=max(chunks))
+    Ks, Vs, n = [], [], 0
+    for step, L in enumerate(chunks):
+        print("fits", (heads, kv, d, dtype, budget), "step", step, "L", L, flush=True)
+        q, k, v = (x.cuda() for x in random_chunk(3400 + step, L, heads, kv, d, dtype))
+        out, ret, cnt = s.step(q, k, v, report=report)
+        Ks.append(k.transpose(0, 1)); Vs.append(v.transpose(0, 1)); n += L
+        K, V, pos, score = s.export()
+        assert torch.equal(K, torch.cat(Ks, 1)) and torch.equal(V, torch.cat(Vs, 1))
+        want = torch.arange(n, dtype=torch.int32, device="cuda").expand(kv, n)
+        assert torch.equal(pos, want) and torch.isinf(score).all()
+        if report:
+            assert int(cnt.item()) == n and torch.equal(ret[:, :n], want)
+        if heads == kv:                                       # out and v have the same shape
+            over = v.clone()
+            twin.step(q, k, over, out=over)
+            assert torch.equal(over, out)
+    if heads == kv:
+        for x, y in zip(s.export(), twin.export()):
+            assert torch.equal(x, y)
