@@ -676,6 +676,122 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// score_once: the same scores where a workgroup has at most four 32-row blocks to go through.  score_kernel's loop and its
+// two buffers (87 KB of LDS, one workgroup per CU) are for many rows; with few of them a launch is one trip to memory for
+// keys, queries and log-sum-exps, 5 us per workgroup, and several rounds of workgroups pay it one after the other.  Here a
+// workgroup is that trip and nothing else: 256 columns, one buffer (35 KB), at most 128 registers, so that two share a CU
+// and one's keys come in beside the other's products; the stream-order indices that the last lines need are requested
+// with the keys.  Slices of more than four blocks' worth of rows are added as in score_kernel.
+// ---------------------------------------------------------------------------------------------
+constexpr int ONCE_BLOCKS = 4;
+template <int D>
+__global__ void __launch_bounds__(512, 4)
+score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ kc, int tc,
+                  const float* __restrict__ lse2, const float* __restrict__ carry, const int32_t* __restrict__ rank,
+                  float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd, int ncol,
+                  int nxb, float c, float dstep /* b / c, Alg. 1 l.2 */, int nslice, float* __restrict__ spart)
+{
+    constexpr int QP = D * 2 + 16, CPR = D / 8, NS = D / 16;  // pitch, 16-byte pieces of a staged row; MFMAs per block
+    constexpr int NLD = ONCE_BLOCKS * 32 * CPR / 512;         // pieces per thread
+    __shared__ __attribute__((aligned(16))) char qs[ONCE_BLOCKS * 32 * QP];
+    __shared__ __attribute__((aligned(16))) float ls[ONCE_BLOCKS * 32];
+    __shared__ int s_ticket;
+
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int h, bx, rs;                                            // all workgroups of a kv-head on one XCD (see score_kernel)
+    {
+        const int bid = blockIdx.x, per_head = nxb * nslice, li = (Hkv & 7) == 0 ? bid >> 3 : bid;
+        h = (Hkv & 7) == 0 ? (bid & 7) + 8 * (li / per_head) : li / per_head;
+        const int rem = li % per_head;
+        bx = rem % nxb;
+        rs = rem / nxb;
+    }
+    // blocks of 32 scored rows, head after head of the group; this slice's
+    const int nblk = (lq + 31) / 32, total = G * nblk;
+    const int b0 = (int)((long)rs * total / nslice), nb = (int)((long)(rs + 1) * total / nslice) - b0;
+    u32x4 st[NLD];
+#pragma unroll
+    for (int u = 0; u < NLD; ++u) {
+        const int x = tid + u * 512, slot = x / (32 * CPR), rr = (x / CPR) & 31;   // slot: uniform over a wavefront
+        st[u] = u32x4{0u, 0u, 0u, 0u};
+        if (slot < nb) {
+            const int b = b0 + slot, i = L - lq + 32 * (b % nblk) + rr;
+            if (i < L) st[u] = *(const u32x4*)(q + ((size_t)i * Hq + h * G + b / nblk) * D + (x % CPR) * 8);
+        }
+    }
+    float row_lse = __builtin_inff();                         // no row: weight 0
+    if (tid < 32 * nb) {
+        const int b = b0 + (tid >> 5), i = L - lq + 32 * (b % nblk) + (tid & 31);
+        if (i < L) row_lse = lse2[(size_t)(h * G + b / nblk) * max_chunk + i];
+    }
+    // key fragments and stream-order index of this lane's column (see score_kernel); past the last column all zeros
+    const int col = bx * 256 + wave * 32 + l32;
+    const int cc = col < ncol ? col : 0;
+    bf16x8 kf[NS];
+    {
+        const uint16_t* kp = (cc < tc ? K + ((size_t)h * cap + cc) * D : kc + ((size_t)(cc - tc) * Hkv + h) * D) + 8 * hh;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            u32x4 v = *(const u32x4*)(kp + 16 * s);
+            if (col >= ncol) v = u32x4{0u, 0u, 0u, 0u};
+            kf[s] = as_bf16x8(v);
+        }
+    }
+    const int j = col < tc ? (col < ncol ? rank[(size_t)h * cap + col] : cnd) : col;
+#pragma unroll
+    for (int u = 0; u < NLD; ++u) {
+        const int x = tid + u * 512;
+        if (x / (32 * CPR) < nb) *(u32x4*)(qs + (x / CPR) * QP + (x % CPR) * 16) = st[u];
+    }
+    if (tid < ONCE_BLOCKS * 32) ls[tid] = row_lse;
+    __syncthreads();
+    f32x16 part = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < nb; ++k) {
+        const char* qp = qs + (32 * k + l32) * QP + 16 * hh;
+        f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*(const u32x4*)(qp + 32 * s)), kf[s], acc, 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {                         // lane (column, half hh) holds rows 8a + 4hh + e in register 4a + e
+            const f32x4 lv = *(const f32x4*)(ls + 32 * k + 8 * a + 4 * hh);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[4 * a + e] += fast_exp2(__builtin_fmaf(acc[4 * a + e], c, -lv[e]));
+        }
+    }
+    float s0 = 0.f;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) s0 += (part[4 * a] + part[4 * a + 1]) + (part[4 * a + 2] + part[4 * a + 3]);
+    float sum = s0 + xhalf(s0);
+    float* my_part = nullptr;
+    if (nslice > 1) {                                         // the hand-off of score_kernel
+        my_part = spart + ((size_t)(h * nslice + rs) * nxb + bx) * 256 + wave * 32 + l32;
+        if (hh == 0) __hip_atomic_store(my_part, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int* arrived = (int*)(spart + (size_t)SCORE_SPLIT_WGS * 256) + h * nxb + bx;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) s_ticket = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_ticket != nslice - 1) return;
+        if (tid == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    }
+    if (hh != 0 || j >= cnd) return;
+    if (nslice > 1) {
+        sum = 0.f;
+        for (int sp = 0; sp < nslice; ++sp)                   // in the order of the slices, whoever does the adding
+            sum += __hip_atomic_load(my_part + (ptrdiff_t)(sp - rs) * nxb * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const float S = lq > 0 ? sum * (1.0f / (float)(G * lq)) : 0.f;
+    float w = S - (float)(cnd - 1 - j) * dstep;               // Alg. 1 l.1, l.3-4
+    if (carry) {                                              // cumulative policy (see score_kernel)
+        const float a = col < tc ? carry[(size_t)h * cap + col] : 0.f;
+        w = S + (a < __builtin_inff() ? a : 0.f);
+    }
+    Wb[(size_t)h * cap + j] = w;
+}
+
 }  // namespace
 
 template <int D, int RB, int KW, int KVB>
@@ -743,6 +859,24 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
     if (cnd <= 0) return hipSuccess;
     const int ncol = ks.rows > cnd ? ks.rows : cnd;          // every cached row, and the chunk rows below cnd
     const float cc = (float)(g.scale * (double)LOG2E);
+    const float dstep = (float)(g.bias / (double)cnd);
+    const float* carry = g.policy == POLICY_CUMULATIVE ? c.score : nullptr;
+    // Few scored rows, or few columns whose rows then are shared out: score_once, as long as the slices of a launch fit
+    // into one round of two workgroups per CU.
+    const int blocks = g.G * ((lq + 31) / 32), nslice = blocks > ONCE_BLOCKS ? (blocks + ONCE_BLOCKS - 1) / ONCE_BLOCKS : 1;
+    const long once_wgs = (long)((ncol + 255) / 256) * g.Hkv * nslice;
+    if (nslice == 1 || (sc.score_part && once_wgs <= SCORE_SPLIT_WGS)) {
+        const int nxb = (ncol + 255) / 256;
+#define INFMLLM_ONCE(DD)                                                                                                   \
+    hipLaunchKernelGGL(score_once_kernel<DD>, dim3((unsigned)once_wgs), dim3(512), 0, st, (const uint16_t*)q,                  \
+                       (const uint16_t*)c.K, (const uint16_t*)ks.k, ks.rows, lse, carry, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, \
+                       g.cap, g.max_chunk, cnd, ncol, nxb, cc, dstep, nslice, sc.score_part)
+        if (g.d == 128) INFMLLM_ONCE(128);
+        else if (g.d == 64) INFMLLM_ONCE(64);
+        else return hipErrorInvalidValue;
+#undef INFMLLM_ONCE
+        return hipGetLastError();
+    }
     // 512 columns per workgroup (256 at head_dim 64, where the wider variant runs out of registers).  Where
     // that leaves CUs without one, the scored rows of a column block are shared out over up to four workgroups
     // (whose sums the last to finish adds up); where there are too few rows for that, a workgroup takes 256 columns.
@@ -764,9 +898,8 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
 #define INFMLLM_SCORE(DD, CB)                                                                              \
     hipLaunchKernelGGL((score_kernel<DD, CB>), grid, block, 0, st, (const uint16_t*)q, (const uint16_t*)c.K, \
                        (const uint16_t*)ks.k, ks.rows, lse,                                                  \
-                       g.policy == POLICY_CUMULATIVE ? c.score : nullptr, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, g.cap, \
-                       g.max_chunk,                                                                          \
-                       cnd, ncol, nxb, cc, (float)(g.bias / (double)cnd), rsplit, sc.score_part)
+                       carry, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, g.cap, g.max_chunk,                        \
+                       cnd, ncol, nxb, cc, dstep, rsplit, sc.score_part)
     if (g.d == 128 && wide) INFMLLM_SCORE(128, 2);
     else if (g.d == 128) INFMLLM_SCORE(128, 1);
     else if (g.d == 64) INFMLLM_SCORE(64, 1);

@@ -60,6 +60,32 @@ def test_tokens_do_not_depend_on_how_many_share_a_call(heads, kv, d, budget, rop
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("heads,kv,d,budget,recent,chunks", [
+    (4, 4, 128, 512, 128, [512, 1, 31, 32, 33, 128]),     # one slice of one to four blocks, ragged last block
+    (4, 4, 128, 511, 160, [511, 129, 160, 300]),          # slices of 3 and 2 blocks; 160 rows scored of 300
+    (8, 2, 128, 300, 64, [257, 43, 1, 5, 33, 64]),        # grouped heads: slices that cross from head to head
+    (6, 2, 64, 255, 0, [255, 16, 256]),                   # no scored row at all: selection by age
+    (16, 1, 64, 700, 512, [512, 188, 512, 100]),          # 256 blocks: 64 slices of a column block; columns past a tile's end
+])
+def test_scores_of_few_rows_match_oracle(heads, kv, d, budget, recent, chunks):
+    """score_once: W' against the oracle's, without bias.  p = exp2(s c - lse) with s, lse of size up to 8 in fp32 is off by
+    8 * 2^-23 * ln 2 < 1e-6 relative and the sums of positive terms by as much again: well inside 2e-5."""
+    gpu = B.Stream(budget, recent, heads, kv, d, dtype=torch.bfloat16, bias=0.0, max_chunk=max(chunks))
+    orc = OracleStream(budget, recent, heads, kv, d, bias=0.0)
+    for step, L in enumerate(chunks):
+        print("scores", (heads, kv, d, budget, recent), "step", step, "L", L, flush=True)
+        q, k, v = random_chunk(3300 + step, L, heads, kv, d, "bf16")
+        _, ret, cnt = gpu.step(q.cuda(), k.cuda(), v.cuda())
+        orc.attend(*(x.double().numpy() for x in (q, k, v)))
+        sc = orc.scores()
+        got = gpu.last_scores()
+        assert (got is None) == (sc is None)
+        if sc is not None:
+            assert np.allclose(got.double().cpu().numpy(), sc[1], rtol=2e-5, atol=1e-12), np.abs(got.double().cpu().numpy() - sc[1]).max()
+        orc.select()
+        orc.commit(ret.cpu().numpy()[:, : int(cnt.item())])
+
+
 @pytest.mark.parametrize("heads,kv,d,dtype,budget,chunks,report", [
     (8, 2, 128, "bf16", 700, [300, 1, 17, 333, 49], True),          # attn_rows with 16 and 32 rows, cut and uncut
     (16, 2, 128, "bf16", 1700, [333, 500, 867], True),              # 64 rows per workgroup
