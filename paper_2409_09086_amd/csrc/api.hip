@@ -76,7 +76,6 @@ struct infmllm_stream {
     int pend_n = 0, pend_L = 0;
     float* lse;          // [Hq][max_chunk]
     float* Wb;           // [Hkv][cap]
-    int32_t* I;          // [Hkv][B]
     FwdScratch fwd;      // scratch of the row-split scoring launch
     float* dec_part;     // partials of the decoding step (plain-arithmetic kernels)
     RowsScratch rows{nullptr, nullptr, nullptr, 0};   // partials of attention launches with a cut key range (bf16 on the matrix cores)
@@ -105,7 +104,7 @@ struct infmllm_stream {
     bool f32() const { return dtype == INFMLLM_FP32; }
 
     struct Layout {
-        size_t K, V, pos, score, rank, row, lse, Wb, I, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, dec_part, rows_o,
+        size_t K, V, pos, score, rank, row, lse, Wb, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, dec_part, rows_o,
             rows_ml, rows_arrived, K_rot, kc_rot, q_rot, rope_tab, total;
         long rows_cap;
     };
@@ -123,7 +122,6 @@ struct infmllm_stream {
         L.row = off; off += ps;
         L.lse = off; off += up((size_t)g.Hq * g.max_chunk * 4);
         L.Wb = off; off += ps;
-        L.I = off; off += up((size_t)g.Hkv * g.B * 4);
         const size_t ml = up((size_t)g.Hkv * (g.max_chunk + g.max_decode) * 4);
         L.mv_src = off; off += ml;
         L.mv_dst = off; off += ml;
@@ -185,7 +183,7 @@ int infmllm_stream_create(int budget, int recent, int heads, int kv_heads, int h
     s->g.policy = POLICY_INFMLLM;
     s->g.attn_tile = 0;
     s->dtype = dtype; s->impl = 0; s->attached = false; s->st = nullptr; s->len = 0;
-    s->streamed = 0; s->last_cnd = 0; s->lse = nullptr; s->Wb = nullptr; s->I = nullptr;
+    s->streamed = 0; s->last_cnd = 0; s->lse = nullptr; s->Wb = nullptr;
     *out = s;
     return INFMLLM_OK;
 }
@@ -287,7 +285,6 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     s->mv.max = s->g.max_chunk + s->g.max_decode;
     s->lse = (float*)(base + L.lse);
     s->Wb = (float*)(base + L.Wb);
-    s->I = (int32_t*)(base + L.I);
     s->fwd.score_part = (float*)(base + L.score_part);
     s->dec_part = (float*)(base + L.dec_part);
     s->rows.o = (float*)(base + L.rows_o);
@@ -482,7 +479,7 @@ int infmllm_step(infmllm_stream_t* s, const void* q, const void* k, const void* 
     const int n = s->len + L;
     hipError_t e;
     s->mark(INFMLLM_K_SELECT, 0);
-    if ((e = launch_select(g, s->Wb, n, ks.rows, s->I, retained, n_retained, s->cache, s->mv, s->st)) != hipSuccess)
+    if ((e = launch_select(g, s->Wb, n, ks.rows, retained, n_retained, s->cache, s->mv, s->st)) != hipSuccess)
         return fail_hip(e, "step: select");
     s->mark(INFMLLM_K_SELECT, 1);
     s->mark(INFMLLM_K_COMPACT, 0);
@@ -535,7 +532,7 @@ int infmllm_evict_batched(infmllm_stream_t* const* streams, int count, int32_t* 
         for (int j = 0; j < eb.count; ++j) {
             infmllm_stream* s = streams[base + j];
             EvictJob& job = eb.job[j];
-            job.Wb = s->Wb; job.I = s->I;
+            job.Wb = s->Wb;
             job.user_I = retained ? retained[base + j] : nullptr;
             job.user_count = n_retained ? n_retained[base + j] : nullptr;
             job.c = s->cache; job.mv = s->mv;

@@ -147,13 +147,13 @@ hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySou
 hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q,
                              const float* lse, const FwdScratch& sc, int t, int L, float* Wb, hipStream_t st);
 
-// a5+a6: I[h] = sort_asc(top-r of W'[h][0..cnd)) ++ [cnd, n), in stream-order indices.  I has row
-// stride B.  user_I (row stride B) and user_count may be null.  The same workgroup then plans the
+// a5+a6: user_I[h] = sort_asc(top-r of W'[h][0..cnd)) ++ [cnd, n), in stream-order indices, row stride B.  user_I
+// and user_count may be null.  The same workgroup then plans the
 // placement (Alg. 1 l.8 without moving the rows that stay): a retained token whose physical row is
 // below B keeps it and gets its new rank, row and score entries here; the others go into the move
 // list, paired in order with the physical rows the eviction frees.  tc = rows in the cache (stream-order
 // indices from tc on are chunk rows read in place).
-hipError_t launch_select(const Geometry& g, const float* Wb, int n, int tc, int32_t* I, int32_t* user_I,
+hipError_t launch_select(const Geometry& g, const float* Wb, int n, int tc, int32_t* user_I,
                          int32_t* user_count, const CacheView& c, const MoveList& mv, hipStream_t st);
 
 // a7: copies the K and V rows of the move list to their new physical rows and writes their pos, rank,
@@ -165,7 +165,6 @@ hipError_t launch_place(const Geometry& g, const CacheView& c, const KeySource& 
 // Alg. 1 Input note).  All streams of a batch have the same geometry.
 struct EvictJob {
     const float* Wb;          // [Hkv][cap] biased scores of this stream
-    int32_t* I;               // [Hkv][B] index list (stream scratch)
     int32_t* user_I;          // [Hkv][B] or null
     int32_t* user_count;      // one int or null
     CacheView c;

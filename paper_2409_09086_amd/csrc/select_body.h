@@ -14,6 +14,11 @@ __device__ __forceinline__ uint32_t order_key(float f)
 }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+// lanes of a ballot below this one
+__device__ __forceinline__ uint32_t lanes_below(uint64_t b)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+}
 
 // Workgroup barrier for data handed over through LDS only.  `__syncthreads` also waits for every global store
 // and load of the wavefront to complete (about a microsecond for a store on its way to memory), which the
@@ -35,6 +40,38 @@ __device__ __forceinline__ void wave_histogram(uint32_t* hist, uint32_t digit, b
         if (lane_id() == leader) atomicAdd(&hist[dl], (uint32_t)__popcll(same));
         todo &= ~same;
     }
+}
+
+// Histogram of 256 bins in LDS.  An atomic on one address is as many operations as it has lanes, and the leading digit of
+// scores tends to be the same for most keys of a head (8K cache: 10 us of counting in such a head, 4 in others): every
+// eighth lane has counters of its own (4 us and 2.6).  The copies of a bin lie in different banks, and a lane that reads four neighbouring
+// bins of a copy reads 16 bytes.  (Counting the lanes that share the first one's digit as one took 1.1 us longer
+// where digits differ.)
+constexpr int HIST_COPIES = 8, HIST_PITCH = 256 + 8, HIST_WORDS = HIST_COPIES * HIST_PITCH;
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void count_digit(uint32_t* hist, uint32_t digit)
+{
+    atomicAdd(&hist[(lane_id() & (HIST_COPIES - 1)) * HIST_PITCH + digit], 1u);
+}
+__device__ __forceinline__ u32x4_t four_bins(const uint32_t* hist, int bin)      // counts of bins bin .. bin + 3
+{
+    u32x4_t v = *(const u32x4_t*)&hist[bin];
+#pragma unroll
+    for (int c = 1; c < HIST_COPIES; ++c) v += *(const u32x4_t*)&hist[c * HIST_PITCH + bin];
+    return v;
+}
+__device__ __forceinline__ void clear_hist(uint32_t* hist, int thread)           // by HIST_WORDS / 4 threads
+{
+    if (thread >= 0 && thread < HIST_WORDS / 4) *(u32x4_t*)&hist[4 * thread] = u32x4_t{0u, 0u, 0u, 0u};
+}
+
+// p[i] for i < 2^30, addressed as a uniform base and a 32-bit offset: one instruction where a signed or 64-bit index
+// costs four
+template <typename T>
+__device__ __forceinline__ T& at32(T* p, uint32_t i)
+{
+    static_assert(sizeof(T) == 4, "");
+    return *(T*)((char*)p + (uint32_t)(i * 4u));
 }
 
 // Inclusive prefix sum over the 64 lanes of a wavefront whose lanes are all active, through the
@@ -81,7 +118,7 @@ __device__ __forceinline__ uint32_t wave_extreme_to_last_lane(uint32_t x)
     return x;
 }
 
-// What the selection leaves in LDS for the placement plan: for every segment of 64 candidates (stream-order
+// What the selection of candidates left in memory leaves in LDS for the placement plan: for every segment of 64 candidates (stream-order
 // indices 64 s .. 64 s + 63) which of them are retained, and how many retained candidates precede the
 // segment.  The new stream-order index of a retained candidate j is base[j / 64] plus the retained ones below
 // it in its segment; a token of the recent window (j >= c) is retained with index r + (j - c).
@@ -112,21 +149,39 @@ struct PlanTables {
 // free row, both in ascending order, which makes the layout a function of the retained set alone.  The K/V
 // copies and the movers' table entries are left to the placement launch.
 // What the plan reads from memory does not depend on the selection: the stream-order index of every physical
-// row and the score W' of that index.  The first PLAN_PRE items of every thread are therefore requested before
+// row.  The first PLAN_PRE items of every thread are therefore requested before
 // the selection starts and have long arrived when the plan wants them; a plan with more items (more than
-// PLAN_PRE * 1024 rows) loads the rest pass by pass.
+// PLAN_PRE * 1024 rows) loads the rest pass by pass.  Candidates that
+// were in registers leave their fate, new index and score by token, in LDS: one 8-byte read per item.  (The plan is bound by
+// its vector instructions, one workgroup's on one CU: 1.5 us per 4096 items, 1.9 with the new index from a bit map and
+// a prefix count and the score gathered from memory.  Selection and plan, from the first workgroup's start to the last one's end:
+// 10.7 -> 9.6 us at 8 heads, 4096 + 1024 rows; 22.6 -> 14.4 at 32 heads, 8192 + 2048 rows; 11.8 -> 9.5 at 4096 + 37 rows with a
+// steep ramp.  Putting `row` together in LDS, so that its stores are coalesced, gained nothing.)
 constexpr int PLAN_PRE = 12;
 struct PlanPre {
     int jj[PLAN_PRE];
-    float w[PLAN_PRE];
+    float w[PLAN_PRE];         // KPT = 0 only
+};
+// What the selection leaves for the plan.  KPT = candidates per thread that it holds in registers (0: in memory).
+struct Candidate {
+    int x;                     // new stream-order index, -1: evicted
+    float w;                   // W'
+};
+template <int KPT, int TPB>
+struct PlanLds {
+    Candidate cand[KPT * TPB];
+};
+template <int TPB>
+struct PlanLds<0, TPB> {
+    KeptMap km;
 };
 // item q of the plan: a physical row below max(tc, B), then the chunk rows read in place; its token, or -1
 __device__ __forceinline__ int plan_item_token(const int32_t* __restrict__ rank, int q, int tc, int P1, int nitems)
 {
-    return q < tc ? rank[q] : (q >= P1 && q < nitems ? tc + (q - P1) : -1);
+    return q < tc ? at32(rank, q) : (q >= P1 && q < nitems ? tc + (q - P1) : -1);
 }
-// The two halves of the prefetch: the tokens of the items (table reads), and, once those have arrived, their scores.
-// The selection requests its candidates between the two, so that it does not wait for the second trip to memory.
+// The prefetch: the tokens of the items (table reads), and, with the candidates in memory, once those have arrived,
+// their scores.
 template <int TPB>
 __device__ __forceinline__ void plan_prefetch_tokens(PlanPre& pre, const int32_t* __restrict__ rank, int n, int tc, int B)
 {
@@ -138,27 +193,34 @@ template <int TPB>
 __device__ __forceinline__ void plan_prefetch_scores(PlanPre& pre, const float* __restrict__ W, int cnd)
 {
 #pragma unroll
-    for (int g = 0; g < PLAN_PRE; ++g) pre.w[g] = (pre.jj[g] >= 0 && pre.jj[g] < cnd) ? W[pre.jj[g]] : __builtin_inff();
+    for (int g = 0; g < PLAN_PRE; ++g) pre.w[g] = (uint32_t)pre.jj[g] < (uint32_t)cnd ? at32(W, pre.jj[g]) : __builtin_inff();
 }
 
-template <int TPB>
-__device__ __forceinline__ void plan_moves(const KeptMap& km, const float* __restrict__ W, int n, int tc, int cnd,
+template <int KPT, int TPB>
+__device__ __forceinline__ void plan_moves(const PlanLds<KPT, TPB>& pl, const float* __restrict__ W, int n, int tc, int cnd,
                                            int B, int r, const PlanTables& pt, const PlanPre& pre)
 {
     constexpr int NW = TPB / 64, CH = 64 / NW;                 // CH passes of TPB items share one table of 64 counts
     __shared__ uint32_t cnt_free[64], cnt_mov[64];
     __shared__ uint32_t tot_free, tot_mov;
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-    const uint64_t below = (l == 0) ? 0ull : (~0ull >> (64 - l));
     const int P1 = tc > B ? tc : B;                           // physical rows looked at
     const int nitems = P1 + (n - tc);                         // ... then the chunk rows read in place
-    // new index of token j, or -1 if it is evicted
-    auto new_index = [&](int j) -> int {
-        if (j >= cnd) return r + (j - cnd);
-        const uint64_t bits = km.bits[j >> 6];
-        if (!((bits >> (j & 63)) & 1ull)) return -1;
-        return (int)km.base[j >> 6] + __popcll(bits & ((1ull << (j & 63)) - 1ull));
+    // new index of token j, or -1 if it is evicted (or there is none, j < 0), and its score entry: W' (pre_w if the
+    // candidates are in memory), +inf inside the recent window
+    auto fate = [&](int j, float pre_w) -> Candidate {
+        const bool ranked = (uint32_t)j < (uint32_t)cnd;
+        if constexpr (KPT > 0) {
+            const Candidate c = pl.cand[ranked ? j : 0];
+            return Candidate{ranked ? c.x : (j < 0 ? -1 : j + (r - cnd)), ranked ? c.w : __builtin_inff()};
+        } else {
+            if (!ranked) return Candidate{j < 0 ? -1 : j + (r - cnd), __builtin_inff()};
+            const uint64_t bits = pl.km.bits[j >> 6];
+            const bool kept = (bits >> (j & 63)) & 1ull;
+            return Candidate{kept ? (int)(pl.km.base[j >> 6] + (uint32_t)__popcll(bits & ((1ull << (j & 63)) - 1ull))) : -1, pre_w};
+        }
     };
+    const int stay_end = tc < B ? tc : B;                     // rows below it keep the tokens that are retained
     uint32_t fbase = 0, mbase = 0;                            // free rows / movers listed so far (uniform)
     lds_barrier();                                          // the kept map is complete
     static_assert(PLAN_PRE % CH == 0, "prefetched items are consumed in whole passes");
@@ -168,21 +230,22 @@ __device__ __forceinline__ void plan_moves(const KeptMap& km, const float* __res
         float sc[CH];
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            xs[u] = jj[u] >= 0 ? new_index(jj[u]) : -1;
-            sc[u] = (xs[u] >= 0 && xs[u] < r) ? wv[u] : __builtin_inff();
+            const Candidate f = fate(jj[u], wv[u]);
+            xs[u] = f.x;
+            sc[u] = f.w;
         }
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
             const int q = q0 + u * TPB + tid;
             const bool kept = xs[u] >= 0;
-            const bool stays = kept && q < tc && q < B;
+            const bool stays = kept && q < stay_end;
             const bool moves = kept && !stays;
             const bool is_free = !kept && q < B;
             src[u] = q < P1 ? q : jj[u];                      // a cache row below tc, or tc + chunk row
             if (stays) {
-                pt.rank[q] = xs[u];
-                pt.row[xs[u]] = q;
-                pt.score[q] = sc[u];
+                at32(pt.rank, q) = xs[u];
+                at32(pt.row, xs[u]) = q;
+                at32(pt.score, q) = sc[u];
             }
             bfree[u] = __ballot(is_free);
             bmov[u] = __ballot(moves);
@@ -205,12 +268,12 @@ __device__ __forceinline__ void plan_moves(const KeptMap& km, const float* __res
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
             const int q = q0 + u * TPB + tid;
-            if ((bfree[u] >> l) & 1ull) pt.mv_dst[fbase + cnt_free[u * NW + w] + (uint32_t)__popcll(bfree[u] & below)] = q;
+            if ((bfree[u] >> l) & 1ull) at32(pt.mv_dst, fbase + cnt_free[u * NW + w] + lanes_below(bfree[u])) = q;
             if ((bmov[u] >> l) & 1ull) {
-                const uint32_t k = mbase + cnt_mov[u * NW + w] + (uint32_t)__popcll(bmov[u] & below);
-                pt.mv_src[k] = src[u];
-                pt.mv_x[k] = xs[u];
-                pt.mv_score[k] = sc[u];
+                const uint32_t k = mbase + cnt_mov[u * NW + w] + lanes_below(bmov[u]);
+                at32(pt.mv_src, k) = src[u];
+                at32(pt.mv_x, k) = xs[u];
+                at32(pt.mv_score, k) = sc[u];
             }
         }
         fbase += tot_free;
@@ -223,7 +286,7 @@ __device__ __forceinline__ void plan_moves(const KeptMap& km, const float* __res
             int jj[CH];
             float wv[CH];
 #pragma unroll
-            for (int u = 0; u < CH; ++u) { jj[u] = pre.jj[p * CH + u]; wv[u] = pre.w[p * CH + u]; }
+            for (int u = 0; u < CH; ++u) { jj[u] = pre.jj[p * CH + u]; wv[u] = KPT == 0 ? pre.w[p * CH + u] : 0.f; }
             pass(p * CH * TPB, jj, wv);
         }
     }
@@ -233,7 +296,8 @@ __device__ __forceinline__ void plan_moves(const KeptMap& km, const float* __res
 #pragma unroll
         for (int u = 0; u < CH; ++u) jj[u] = plan_item_token(pt.rank, q0 + u * TPB + tid, tc, P1, nitems);
 #pragma unroll
-        for (int u = 0; u < CH; ++u) wv[u] = (jj[u] >= 0 && jj[u] < cnd) ? W[jj[u]] : __builtin_inff();
+        for (int u = 0; u < CH; ++u)
+            wv[u] = KPT == 0 && (uint32_t)jj[u] < (uint32_t)cnd ? at32(W, jj[u]) : 0.f;
         pass(q0, jj, wv);
     }
     if (tid == 0) *pt.mv_count = (int32_t)mbase;               // = fbase: B tokens are retained, B rows lie below B
@@ -247,32 +311,28 @@ __device__ __forceinline__ void plan_moves(const KeptMap& km, const float* __res
 // bin search and a pass costs two barriers.  The digits stop as soon as the bin that holds the
 // r-th largest key is wanted whole (as a rule after the second: few of a few thousand candidates
 // share 16 bits), and the ordered write needs two more barriers.
-template <int KPT, int TPB, typename AfterLoads>
-__device__ __forceinline__ void select_reg_body(const float* __restrict__ Wb, int32_t* __restrict__ I,
-                                                int32_t* __restrict__ userI, int32_t* __restrict__ user_count,
-                                                int h, int cnd, int r, int R, int B, int cap, KeptMap& km,
-                                                AfterLoads&& after_loads)
+template <int KPT, int TPB>
+__device__ __forceinline__ void select_reg_body(const float* __restrict__ Wb, int32_t* __restrict__ userI, int32_t* __restrict__ user_count,
+                                                int h, int cnd, int r, int R, int B, int cap, PlanLds<KPT, TPB>& pl)
 {
     constexpr int NW = TPB / 64;
-    static_assert(TPB >= 512, "one wavefront searches the bins while four others clear the next histogram");
-    __shared__ uint32_t hist[2][256];
+    static_assert(TPB >= 640 && HIST_WORDS / 4 <= 576, "one wavefront searches the bins while nine others clear the next histogram");
+    __shared__ __attribute__((aligned(16))) uint32_t hist[2][HIST_WORDS];
     __shared__ uint32_t s_min, s_max, s_prefix, s_remaining, s_ties, s_done;
     __shared__ uint32_t tab_eq[KPT * NW], tab_gt[KPT * NW];
 
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const float* W = Wb + (size_t)h * cap;
-    int32_t* Ih = I + (size_t)h * B;
     int32_t* Uh = userI ? userI + (size_t)h * B : nullptr;
 
     if (r > 0) {
         if (tid == 0) { s_min = 0xffffffffu; s_max = 0u; s_remaining = (uint32_t)r; s_ties = (uint32_t)cnd; s_done = 0; }
-        if (tid < 256) hist[0][tid] = 0;
+        clear_hist(hist[0], tid);
         uint32_t key[KPT];
         float wj[KPT];
         uint32_t lo_key = 0xffffffffu, hi_key = 0u;
 #pragma unroll
-        for (int k = 0; k < KPT; ++k) wj[k] = W[k * TPB + tid < cnd ? k * TPB + tid : 0];   // cnd >= 1 here
-        after_loads();                                        // further loads of the caller, behind the candidates
+        for (int k = 0; k < KPT; ++k) wj[k] = at32(W, k * TPB + tid < cnd ? k * TPB + tid : 0);   // cnd >= 1 here
 #pragma unroll
         for (int k = 0; k < KPT; ++k) {
             const int j = k * TPB + tid;
@@ -298,11 +358,12 @@ __device__ __forceinline__ void select_reg_body(const float* __restrict__ Wb, in
             const uint32_t himask = hi >= 32 ? 0u : (0xffffffffu << hi), dmask = (1u << (hi - lo)) - 1u;
 #pragma unroll
             for (int k = 0; k < KPT; ++k)
-                if ((k * TPB + tid < cnd) && ((key[k] & himask) == T)) atomicAdd(&hp[(key[k] >> lo) & dmask], 1u);
+                if ((k * TPB + tid < cnd) && ((key[k] & himask) == T)) count_digit(hp, (key[k] >> lo) & dmask);
             lds_barrier();
             if (tid < 64) {
                 // wavefront 0 walks the bins from the top; lane l owns bins 255-4l .. 252-4l
-                uint32_t c0 = hp[255 - 4 * l], c1 = hp[254 - 4 * l], c2 = hp[253 - 4 * l], c3 = hp[252 - 4 * l];
+                const u32x4_t four = four_bins(hp, 252 - 4 * l);
+                const uint32_t c0 = four[3], c1 = four[2], c2 = four[1], c3 = four[0];
                 const uint32_t mine = c0 + c1 + c2 + c3, incl = wave_inclusive_sum(mine);
                 const uint32_t before = incl - mine, need = s_remaining;
                 if (before < need && need <= incl) {          // the r-th largest falls in my bins
@@ -319,15 +380,14 @@ __device__ __forceinline__ void select_reg_body(const float* __restrict__ Wb, in
                     // decide nothing (T = that lowest key, no tie dropped)
                     if (need - acc == cnt) s_done = 1;
                 }
-            } else if (tid >= 256 && tid < 512) {
-                hist[(pass + 1) & 1][tid - 256] = 0;
+            } else if (tid >= TPB - 576) {
+                clear_hist(hist[(pass + 1) & 1], tid - (TPB - 576));
             }
             lds_barrier();
             T = s_prefix;
             hi = s_done ? 0 : lo;
         }
         const uint32_t skip_eq = s_ties - s_remaining;        // oldest ties that are dropped
-        const uint64_t below = (l == 0) ? 0ull : (~0ull >> (64 - l));
 
         // kept = {key > T} U {ties of rank >= skip_eq in index order}; a segment is the 64 keys of
         // slot k in wavefront w, and segments follow index order
@@ -349,30 +409,23 @@ __device__ __forceinline__ void select_reg_body(const float* __restrict__ Wb, in
 #pragma unroll
         for (int k = 0; k < KPT; ++k) {
             const uint32_t eq_before = tab_eq[k * NW + w];
-            const uint32_t eq_rank = eq_before + (uint32_t)__popcll(beq[k] & below);
+            const uint32_t eq_rank = eq_before + lanes_below(beq[k]);
             const bool keep_eq = ((beq[k] >> l) & 1ull) && eq_rank >= skip_eq;
+            const int j = k * TPB + tid;
             const uint64_t bke = __ballot(keep_eq);
             // kept before this segment: every greater key, and the ties past the dropped ones
             const uint32_t seg_base = tab_gt[k * NW + w] + (eq_before > skip_eq ? eq_before - skip_eq : 0u);
-            if (l == 0) {                                     // for the placement plan
-                km.bits[k * NW + w] = bgt[k] | bke;
-                km.base[k * NW + w] = seg_base;
-            }
-            if (keep_eq || ((bgt[k] >> l) & 1ull)) {
-                const uint32_t dst = seg_base + (uint32_t)__popcll((bgt[k] | bke) & below);
-                const int j = k * TPB + tid;
-                Ih[dst] = j;
-                if (Uh) Uh[dst] = j;
-            }
+            const bool keep = keep_eq || ((bgt[k] >> l) & 1ull);
+            const uint32_t dst = seg_base + lanes_below(bgt[k] | bke);
+            pl.cand[j] = Candidate{keep ? (int)dst : -1, wj[k]};      // for the placement plan
+            if (keep && Uh) at32(Uh, dst) = j;
         }
     }
     else {
-        after_loads();
-        for (int sgm = tid; sgm < (cnd + 63) / 64; sgm += TPB) { km.bits[sgm] = 0ull; km.base[sgm] = 0u; }   // nothing ranked
+        for (int j = tid; j < cnd; j += TPB) pl.cand[j] = Candidate{-1, 0.f};     // nothing ranked
     }
-    for (int x = tid; x < R; x += TPB) {                      // recent window: [c, n)
-        Ih[r + x] = cnd + x;
-        if (Uh) Uh[r + x] = cnd + x;
+    for (int x = Uh ? tid : R; x < R; x += TPB) {             // recent window: [c, n)
+        at32(Uh, r + x) = cnd + x;
     }
     if (user_count && h == 0 && tid == 0) *user_count = B;
 }

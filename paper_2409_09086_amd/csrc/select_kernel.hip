@@ -20,8 +20,7 @@ constexpr int TPB = 1024;
 constexpr int NW = TPB / 64;
 
 // Selection of kv-head h by one workgroup, candidates re-read from memory in every pass.
-__device__ __forceinline__ void select_mem_body(const float* __restrict__ Wb, int32_t* __restrict__ I,
-                                                int32_t* __restrict__ userI, int32_t* __restrict__ user_count,
+__device__ __forceinline__ void select_mem_body(const float* __restrict__ Wb, int32_t* __restrict__ userI, int32_t* __restrict__ user_count,
                                                 int h, int cnd, int r, int R, int B, int cap, KeptMap& km)
 {
     __shared__ uint32_t hist[256];
@@ -30,7 +29,6 @@ __device__ __forceinline__ void select_mem_body(const float* __restrict__ Wb, in
     __shared__ uint32_t run_eq, run_keep;
 
     const float* W = Wb + (size_t)h * cap;
-    int32_t* Ih = I + (size_t)h * B;
     int32_t* Uh = userI ? userI + (size_t)h * B : nullptr;
 
     if (r > 0) {
@@ -100,10 +98,7 @@ __device__ __forceinline__ void select_mem_body(const float* __restrict__ Wb, in
                 km.base[j0 / 64 + w] = seg_base;
             }
             const uint32_t dst = seg_base + (uint32_t)__popcll(bk & below);
-            if (keep) {
-                Ih[dst] = j;
-                if (Uh) Uh[dst] = j;
-            }
+            if (keep && Uh) Uh[dst] = j;
             __syncthreads();
             if (threadIdx.x == 0) {
                 uint32_t te = 0, tk = 0;
@@ -118,44 +113,40 @@ __device__ __forceinline__ void select_mem_body(const float* __restrict__ Wb, in
         for (int sgm = threadIdx.x; sgm < (cnd + 63) / 64; sgm += TPB) { km.bits[sgm] = 0ull; km.base[sgm] = 0u; }
     }
     // ---- recent window: [c, n) -------------------------------------------------------------
-    for (int x = threadIdx.x; x < R; x += TPB) {
-        Ih[r + x] = cnd + x;
-        if (Uh) Uh[r + x] = cnd + x;
-    }
+    if (Uh)
+        for (int x = threadIdx.x; x < R; x += TPB) Uh[r + x] = cnd + x;
     if (user_count && h == 0 && threadIdx.x == 0) *user_count = B;
 }
 
 
-// KPT = 0: candidates stay in memory.
-// after_loads is called once, when the selection has requested its candidates and not yet used them.
-template <int KPT, typename AfterLoads>
-__device__ __forceinline__ void select_body(const float* Wb, int32_t* I, int32_t* userI, int32_t* user_count, int h,
-                                            int cnd, int r, int R, int B, int cap, KeptMap& km, AfterLoads&& after_loads)
-{
-    if constexpr (KPT == 0) {
-        after_loads();
-        select_mem_body(Wb, I, userI, user_count, h, cnd, r, R, B, cap, km);
-    } else {
-        select_reg_body<KPT, TPB>(Wb, I, userI, user_count, h, cnd, r, R, B, cap, km, after_loads);
-    }
-}
-
-// One workgroup per kv-head: selection, then the placement plan.
+// One head: selection, then the placement plan.  KPT = 0: candidates stay in memory.
 template <int KPT>
-__global__ void __launch_bounds__(TPB)
-select_kernel(const float* __restrict__ Wb, int32_t* __restrict__ I, int32_t* __restrict__ userI,
-              int32_t* __restrict__ user_count, int cnd, int r, int R, int B, int cap, int tc, CacheView c, MoveList mv)
+__device__ __forceinline__ void select_head(const float* Wb, int32_t* userI, int32_t* user_count, int h, int n, int r, int R,
+                                            int B, int cap, int tc, const CacheView& c, const MoveList& mv)
 {
-    __shared__ KeptMap km;
-    const int h = blockIdx.x;
+    __shared__ PlanLds<KPT, TPB> pl;
+    const int cnd = n - R;
     const size_t hb = (size_t)h * cap, mb = (size_t)h * mv.max;
     PlanPre pre;
-    plan_prefetch_tokens<TPB>(pre, c.rank + hb, cnd + R, tc, B);
-    select_body<KPT>(Wb, I, userI, user_count, h, cnd, r, R, B, cap, km,
-                     [&]() __attribute__((always_inline)) { plan_prefetch_scores<TPB>(pre, Wb + hb, cnd); });
+    plan_prefetch_tokens<TPB>(pre, c.rank + hb, n, tc, B);
+    if constexpr (KPT == 0) {
+        plan_prefetch_scores<TPB>(pre, Wb + hb, cnd);
+        select_mem_body(Wb, userI, user_count, h, cnd, r, R, B, cap, pl.km);
+    } else {
+        select_reg_body<KPT, TPB>(Wb, userI, user_count, h, cnd, r, R, B, cap, pl);
+    }
     const PlanTables pt{c.rank + hb, c.row + hb, c.score + hb, mv.src + mb, mv.dst + mb, mv.x + mb, mv.score + mb,
                         mv.count + h};
-    plan_moves<TPB>(km, Wb + hb, cnd + R, tc, cnd, B, r, pt, pre);
+    plan_moves<KPT, TPB>(pl, Wb + hb, n, tc, cnd, B, r, pt, pre);
+}
+
+// One workgroup per kv-head.
+template <int KPT>
+__global__ void __launch_bounds__(TPB)
+select_kernel(const float* __restrict__ Wb, int32_t* __restrict__ userI, int32_t* __restrict__ user_count, int cnd, int r,
+              int R, int B, int cap, int tc, CacheView c, MoveList mv)
+{
+    select_head<KPT>(Wb, userI, user_count, blockIdx.x, cnd + R, r, R, B, cap, tc, c, mv);
 }
 
 // Several streams of one geometry (the layers of a model, Alg. 1 Input note): stream j owns
@@ -164,30 +155,20 @@ template <int KPT>
 __global__ void __launch_bounds__(TPB)
 select_batch_kernel(EvictBatch eb, int r, int R, int B, int cap, int Hkv)
 {
-    const int j = blockIdx.x / Hkv, h = blockIdx.x % Hkv;
-    const EvictJob& job = eb.job[j];
-    __shared__ KeptMap km;
-    const int cnd = job.n - R;
-    const size_t hb = (size_t)h * cap, mb = (size_t)h * job.mv.max;
-    PlanPre pre;
-    plan_prefetch_tokens<TPB>(pre, job.c.rank + hb, job.n, job.tc, B);
-    select_body<KPT>(job.Wb, job.I, job.user_I, job.user_count, h, cnd, r, R, B, cap, km,
-                     [&]() __attribute__((always_inline)) { plan_prefetch_scores<TPB>(pre, job.Wb + hb, cnd); });
-    const PlanTables pt{job.c.rank + hb, job.c.row + hb, job.c.score + hb, job.mv.src + mb, job.mv.dst + mb,
-                        job.mv.x + mb, job.mv.score + mb, job.mv.count + h};
-    plan_moves<TPB>(km, job.Wb + hb, job.n, job.tc, cnd, B, r, pt, pre);
+    const EvictJob& job = eb.job[blockIdx.x / Hkv];
+    select_head<KPT>(job.Wb, job.user_I, job.user_count, blockIdx.x % Hkv, job.n, r, R, B, cap, job.tc, job.c, job.mv);
 }
 
 }  // namespace
 
-hipError_t launch_select(const Geometry& g, const float* Wb, int n, int tc, int32_t* I, int32_t* user_I,
+hipError_t launch_select(const Geometry& g, const float* Wb, int n, int tc, int32_t* user_I,
                          int32_t* user_count, const CacheView& c, const MoveList& mv, hipStream_t st)
 {
     const int cnd = n - g.R, r = g.B - g.R;
     if (cnd > PLAN_MAX_C) return hipErrorInvalidValue;
     const dim3 grid(g.Hkv);
 #define INFMLLM_SELECT(KPT)                                                                                \
-    hipLaunchKernelGGL(select_kernel<KPT>, grid, dim3(TPB), 0, st, Wb, I, user_I, user_count, cnd, r, g.R, g.B, g.cap, \
+    hipLaunchKernelGGL(select_kernel<KPT>, grid, dim3(TPB), 0, st, Wb, user_I, user_count, cnd, r, g.R, g.B, g.cap, \
                        tc, c, mv)
     if (cnd <= 2 * TPB) INFMLLM_SELECT(2);
     else if (cnd <= 4 * TPB) INFMLLM_SELECT(4);

@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (2, 1, 64, 5000, 500, [2500, 2500, 2, 40]),           # more than sixteen pieces' worth of keys
     (16, 16, 64, 600, 150, [300, 300, 128, 31]),          # many heads: few pieces or one
     (1, 1, 128, 31, 8, [31, 7, 20]),                      # fewer keys than a run
+    (4, 2, 64, 96, 96, [96, 33, 96]),                     # the whole budget is recent window: nothing is ranked
     (16, 2, 128, 2600, 300, [1300, 1300, 270, 301]),      # 64 rows per workgroup, three pieces, ragged rows and keys
 ])
 def test_short_chunks_match_oracle(heads, kv, d, budget, recent, chunks):
