@@ -140,7 +140,8 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* dev_workspace, size_t bytes
  * its HIP stream would race with the next holder, so the caller orders the two, e.g. by using one HIP
  * stream).  The array keeps its last contents between holders; everything a stream relies on is cleared
  * at attach.  Errors: EINVAL (null stream, rotary position table requested: its table is uploaded from a
- * host buffer), ENOMEM (infmllm_stream_workspace_bytes(s) exceeds INFMLLM_STATIC_WORKSPACE_BYTES),
+ * host buffer), ENOMEM (the stream does not fit into INFMLLM_STATIC_WORKSPACE_BYTES; scratch that only makes
+ * launches faster is left out before that happens, so infmllm_stream_workspace_bytes(s) may be up to 9 MB larger),
  * ESTATE (already attached, array in use), EHIP.
  */
 #define INFMLLM_STATIC_WORKSPACE_BYTES (64u << 20)

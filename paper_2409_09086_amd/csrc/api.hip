@@ -56,6 +56,7 @@ struct infmllm_stream {
     int dtype;
     int impl;            // 0 = matrix cores where the dtype allows, 1 = plain arithmetic
     bool attached;
+    bool lean = false;   // workspace without the scratch that launches can do without (see layout)
     int static_dev = -1; // device whose library-owned workspace this stream holds (-1: caller's workspace)
     hipStream_t st;
     CacheView cache;
@@ -128,16 +129,17 @@ struct infmllm_stream {
         L.mv_x = off; off += ml;
         L.mv_score = off; off += ml;
         L.mv_count = off; off += up((size_t)g.Hkv * 4);
-        // row-split scoring: partial column sums and arrival counters
-        L.score_part = off; off += up(mfma() || f32() ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
+        // row-split scoring: partial column sums and arrival counters.  fp32 streams score without it, and every chunk
+        // attention runs without partials, only slower: a lean workspace leaves both out.
+        L.score_part = off; off += up(mfma() || (f32() && !lean) ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
         L.dec_part = off; off += up(g.max_decode > 0 && !mfma() ? (size_t)g.Hq * DECODE_MAX_SPLIT * (g.d + 2) * 4 + (size_t)g.Hkv * 4 : 0);
         // (query row, piece) pairs of a launch with a cut key range: at most ROWS_MAX_PARTS, at least one token's
         L.rows_cap = 0;
         if (mfma()) {
             const long most = (long)g.Hq * std::max(g.max_chunk, g.max_decode) * ((g.cap + 127) / 128);
             const int ksd = rows_decode_keys_per_piece(g);
-            L.rows_cap = std::max(std::min(most, ROWS_MAX_PARTS), (long)g.Hq * ((g.B + g.max_decode + ksd - 1) / ksd));
-        } else if (f32()) {
+            L.rows_cap = std::max(lean ? 0L : std::min(most, ROWS_MAX_PARTS), (long)g.Hq * ((g.B + g.max_decode + ksd - 1) / ksd));
+        } else if (f32() && !lean) {
             L.rows_cap = std::min((long)g.Hq * g.max_chunk * ((g.cap + 127) / 128), ROWS_MAX_PARTS);
         }
         L.rows_o = off; off += up((size_t)L.rows_cap * g.d * 4);
@@ -285,7 +287,7 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     s->mv.max = s->g.max_chunk + s->g.max_decode;
     s->lse = (float*)(base + L.lse);
     s->Wb = (float*)(base + L.Wb);
-    s->fwd.score_part = (float*)(base + L.score_part);
+    s->fwd.score_part = L.dec_part > L.score_part ? (float*)(base + L.score_part) : nullptr;
     s->dec_part = (float*)(base + L.dec_part);
     s->rows.o = (float*)(base + L.rows_o);
     s->rows.ml = (float2*)(base + L.rows_ml);
@@ -329,10 +331,16 @@ int infmllm_stream_attach_static(infmllm_stream_t* s, void* hip_stream)
     if (s->rope_base > 0.0)
         return fail(INFMLLM_EINVAL, "attach_static: streams with the rotary position table are not supported "
                                     "(the table is uploaded from a host buffer)");
+    // where the whole workspace is too large for the array, one without the dispensable scratch may fit
+    s->lean = s->layout().total > (size_t)INFMLLM_STATIC_WORKSPACE_BYTES;
     const size_t need = s->layout().total;
-    if (need > (size_t)INFMLLM_STATIC_WORKSPACE_BYTES)
+    if (need > (size_t)INFMLLM_STATIC_WORKSPACE_BYTES) {
+        s->lean = false;
         return fail(INFMLLM_ENOMEM, "attach_static: the stream needs %zu bytes of workspace, the library's array holds %zu",
                     need, (size_t)INFMLLM_STATIC_WORKSPACE_BYTES);
+    }
+    const bool lean = s->lean;
+    s->lean = false;                                           // every failure below leaves the stream as it was
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail_hip(e, "attach_static: hipGetDevice");
@@ -352,11 +360,13 @@ int infmllm_stream_attach_static(infmllm_stream_t* s, void* hip_stream)
         ptr = g_static_ptr[dev];
     }
     s->static_dev = dev;
+    s->lean = lean;
     const int rc = infmllm_stream_attach(s, ptr, (size_t)INFMLLM_STATIC_WORKSPACE_BYTES, hip_stream);
     if (rc != INFMLLM_OK) {
         std::lock_guard<std::mutex> lk(g_static_mu);
         g_static_owner[dev] = nullptr;
         s->static_dev = -1;
+        s->lean = false;
     }
     return rc;
 }

@@ -43,7 +43,7 @@ attn_f32_kernel(RowsArgsT<float> a, AppendJob ap)
     __shared__ __attribute__((aligned(1024))) char smem[RW_NW * STAGE];
     __shared__ float s_m[RW_NW][16], s_l[RW_NW][16];
 
-    const int sp = blockIdx.x, h = blockIdx.y, rg = blockIdx.z;    // piece, kv-head, row group
+    const int sp = blockIdx.x, h = blockIdx.y, rg = a.rg0 + blockIdx.z;    // piece, kv-head, row group
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.L * a.G, row0 = 16 * rg, t = a.t;
@@ -64,7 +64,7 @@ attn_f32_kernel(RowsArgsT<float> a, AppendJob ap)
         for (int j = 0; j < NJ; ++j) qf[j] = *(const f32x4*)(qp + 16 * j);
     }
     if constexpr (APPEND)
-        append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
+        append_share(ap, sp + gridDim.x * (h + gridDim.y * blockIdx.z), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     f32x4 o[NJ];                                               // block b: lane (row c16, group g4) holds columns VW (4 g4 + i) + b
 #pragma unroll
     for (int b = 0; b < NJ; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -263,7 +263,7 @@ hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySourc
     a.q = (const float*)q; a.K = (float*)c.K; a.V = (float*)c.V; a.kc = (const float*)ks.k; a.vc = (const float*)ks.v;
     a.out = (float*)out; a.lse = lse; a.part_o = sc.o; a.part_ml = sc.ml;
     a.t = t; a.L = L; a.tc = ks.rows; a.Hq = g.Hq; a.Hkv = g.Hkv; a.G = g.G; a.cap = g.cap; a.max_chunk = g.max_chunk;
-    a.inv_g = (uint32_t)((1ull << 32) / (unsigned)g.G + 1);
+    a.inv_g = rows_inv_g(L, g.G);
     a.c = (float)g.scale;
     // Pieces: as many as keep the chip's 256 CUs busy, of at least three passes (below that the merging launch costs more
     // than the passes it takes away).
@@ -272,18 +272,19 @@ hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySourc
     const int pieces = (int)std::max<long>(1, std::min<long>(most, RW_CLASSES));
     a.ks = ((n + pieces - 1) / pieces + F32_RUN - 1) / F32_RUN * F32_RUN;
     a.nsplit = (n + a.ks - 1) / a.ks;
-    const dim3 grid((unsigned)a.nsplit, (unsigned)g.Hkv, (unsigned)((L * g.G + 15) / 16)), block(RW_NT);
-    if (g.d == 128) {
-        if (ap.k) hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, block, 0, st, a, ap);
-        else hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, block, 0, st, a, ap);
-        if (a.nsplit > 1) launch_merge_rows<float, 128, true>(a, st);
-    } else if (g.d == 64) {
-        if (ap.k) hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, block, 0, st, a, ap);
+    if (g.d != 64 && g.d != 128) return hipErrorInvalidValue;
+    // one launch, but for the 65535 row groups that a grid dimension takes
+    const int groups = (L * g.G + 15) / 16;
+    for (a.rg0 = 0; a.rg0 < groups; a.rg0 += 65535) {
+        const dim3 grid((unsigned)a.nsplit, (unsigned)g.Hkv, (unsigned)std::min(groups - a.rg0, 65535)), block(RW_NT);
+        const bool append = ap.k && a.rg0 == 0;
+        if (g.d == 128 && append) hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, block, 0, st, a, ap);
+        else if (g.d == 128) hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, block, 0, st, a, ap);
+        else if (append) hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, block, 0, st, a, ap);
         else hipLaunchKernelGGL((attn_f32_kernel<64, false>), grid, block, 0, st, a, ap);
-        if (a.nsplit > 1) launch_merge_rows<float, 64, true>(a, st);
-    } else {
-        return hipErrorInvalidValue;
     }
+    if (a.nsplit > 1 && g.d == 128) launch_merge_rows<float, 128, true>(a, st);
+    else if (a.nsplit > 1) launch_merge_rows<float, 64, true>(a, st);
     return hipGetLastError();
 }
 
@@ -295,7 +296,7 @@ hipError_t launch_score_f32(const Geometry& g, const CacheView& c, const KeySour
     const int ncol = ks.rows > cnd ? ks.rows : cnd;            // every cached row, and the chunk rows below cnd
     const int nxb = (ncol + 127) / 128, blocks = g.G * ((lq + 15) / 16);
     int rsplit = std::min(256 / (nxb * g.Hkv), blocks / 2);    // slices of at least two blocks, one workgroup per CU
-    if (rsplit < 1 || nxb * g.Hkv * rsplit > SCORE_SPLIT_WGS) rsplit = 1;
+    if (rsplit < 1 || !sc.score_part || nxb * g.Hkv * rsplit > SCORE_SPLIT_WGS) rsplit = 1;
     const dim3 grid((unsigned)nxb, (unsigned)g.Hkv, (unsigned)rsplit), block(RW_NT);
 #define INFMLLM_SCORE(DD)                                                                                                 \
     hipLaunchKernelGGL(score_f32_kernel<DD>, grid, block, 0, st, (const float*)q, (const float*)c.K, (const float*)ks.k,      \

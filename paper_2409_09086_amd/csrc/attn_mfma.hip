@@ -812,7 +812,7 @@ hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySour
                             void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st)
 {
     if (g.d != 64 && g.d != 128) return hipErrorInvalidValue;
-    if (g.attn_tile == 0) {
+    if (g.attn_tile == 0 && (long)L * g.G <= (1 << 20) && (long)L * g.G * g.G < (1l << 32)) {   // what its grid and rows_token take
         // Few query rows: attn_rows, which cuts the key range over the workgroups.  Examples, measured, attn_rows against
         // the kernels below: 32 x 128 heads, 4096 keys: 24 / 49 us with 37 rows, 22 / 50 with 64; 16 heads on 4 of 128,
         // 5000 keys, 320 rows: 37 / 61; 8 x 64 heads, 4000 keys, 320 rows: 19 / 72.  The time of the kernels below, fitted

@@ -24,12 +24,14 @@ struct RowsArgsT {
     int32_t* row;
     int pos0;
     int t, L, tc, Hq, Hkv, G, cap, max_chunk, ks, nsplit;
-    uint32_t inv_g;            // floor(2^32 / G) + 1
+    int rg0;                   // first row group of the launch (attn_f32)
+    uint32_t inv_g;            // see rows_token
     float c;                   // scale * log2(e); fp32: scale
 };
 typedef RowsArgsT<uint16_t> RowsArgs;
 
 void launch_rows64(const RowsArgs& a, const AppendJob& ap, hipStream_t st);
+inline uint32_t rows_inv_g(int L, int G) { return (uint64_t)L * G * G < (1ull << 32) ? (uint32_t)((1ull << 32) / (unsigned)G + 1) : 0u; }
 
 namespace {
 
@@ -239,10 +241,16 @@ __device__ __forceinline__ void store_out4(float* p, f32x4 v) { *(f32x4*)p = v; 
 
 
 
-// token of a row (row = token * G + head in group): row / G; inv_g = floor(2^32 / G) + 1 is exact for the at most 2^20
-// rows of a kv-head
+// token of a row (row = token * G + head in group): row / G.  rho * inv_g / 2^32 exceeds rho / G by less than rho / 2^32, so it is
+// exact while rho * G < 2^32.  Launches of fp32 streams may have more rows than that (inv_g = 0); those of bf16 streams have
+// at most 2^20, and the division would cost attn_rows64 registers that it does not have.
 template <typename T>
-__device__ __forceinline__ int rows_token(const RowsArgsT<T>& a, int rho) { return a.G == 1 ? rho : (int)__umulhi((uint32_t)rho, a.inv_g); }
+__device__ __forceinline__ int rows_token(const RowsArgsT<T>& a, int rho) 
+{
+    if (a.G == 1) return rho;
+    if (sizeof(T) == 4 && a.inv_g == 0) return rho / a.G;
+    return (int)__umulhi((uint32_t)rho, a.inv_g);
+}
 
 // Tiles in LDS: rows are not padded; the 16-byte pieces of a row are permuted at load time instead (by choosing which
 // piece of its row a lane fetches), so that sixteen rows of K (or Q) at one piece, and the sixteen rows of a transpose
@@ -278,8 +286,8 @@ struct RunLoader {
         // (past the last key the rows of a warm-up step's cache are read as they are: finite, and masked)
         const bool in_cache = k0 + KEYS <= (tc == n ? cap : tc), in_chunk = k0 >= tc && k0 + KEYS <= n;
         if (in_cache || in_chunk) {                // rows a fixed stride apart
-            const int stride = in_cache ? ROWB : crs * (int)sizeof(T), at = (in_cache ? k0 : k0 - tc) * stride;
-            const int bytes = (in_cache ? cap : L) * stride - at;
+            const int stride = in_cache ? ROWB : crs * (int)sizeof(T), bytes = KEYS * stride;
+            const size_t at = (size_t)(in_cache ? k0 : k0 - tc) * stride;
             const T *k_cache = Kh, *k_chunk = kch, *v_cache = Vh, *v_chunk = vch;
             const char* kp = (const char*)(in_cache ? k_cache : k_chunk) + at;
             const char* vp = (const char*)(in_cache ? v_cache : v_chunk) + at;

@@ -76,8 +76,6 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
         for (int s = 0; s < C::NS; ++s) qf[x][s] = as_bf16x8(*(const u32x4*)(qp + 32 * s));
     }
 
-    if constexpr (APPEND)
-        append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     f32x4 o[NRB][C::NC];
     float m_ref[NRB], m_use[NRB], lsum[NRB];
 #pragma unroll
@@ -191,6 +189,8 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
         }
     }
 
+    if constexpr (APPEND)
+        append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     // ---- decoding: tokens sp, sp + nsplit, .. become cache rows (read from the chunk tensors by everyone)
     if (a.pos && rg == 0 && sp < a.L) {
         constexpr int VPR = D / 8;
@@ -297,7 +297,7 @@ template <int D, bool EXACT>
 hipError_t launch_rows_d(const RowsArgs& args, int nrb, const AppendJob& ap, hipStream_t st)
 {
     RowsArgs a = args;
-    a.inv_g = (uint32_t)((1ull << 32) / (unsigned)a.G + 1);
+    a.inv_g = rows_inv_g(a.L, a.G);
     if (nrb == 1) launch_rows_cfg<D, 1, EXACT>(a, ap, st);
     else if (EXACT || nrb == 2) launch_rows_cfg<D, 2, EXACT>(a, ap, st);
     else if constexpr (D == 128) launch_rows64(a, ap, st);

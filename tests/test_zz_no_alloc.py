@@ -63,3 +63,28 @@ def test_static_workspace_is_exclusive_and_bounded():
     with pytest.raises(B.InfMLLMError) as e:
         B.Stream(64, 16, 2, 2, 64, dtype=torch.bfloat16, max_chunk=32, rope_base=10000.0, static_workspace=True)
     assert e.value.code == B.EINVAL
+
+
+@pytest.mark.parametrize("dtype,heads,kv,budget,decode", [(torch.bfloat16, 8, 8, 14600, 2), (torch.float32, 4, 4, 14000, 0)])
+def test_static_workspace_leaves_dispensable_scratch_out(dtype, heads, kv, budget, decode):
+    """Streams whose whole workspace exceeds the array, but not without the partials of cut key ranges (8.5 MB): accepted,
+    and within the oracle's bars."""
+    recent, d, lens = budget // 4, 128, [300, 33]
+    mk = lambda static: B.Stream(budget, recent, heads, kv, d, dtype=dtype, bias=1e-3, max_chunk=max(lens), max_decode=decode,
+                                 static_workspace=static)
+    assert mk(False).workspace.numel() > 64 << 20
+    a = mk(True)
+    ls = LockStep(a, OracleStream(budget, recent, heads, kv, d, bias=1e-3))
+    g = torch.Generator().manual_seed(23)
+    K, V = (torch.randn((kv, budget, d), generator=g).to(dtype) for _ in range(2))
+    pos = torch.arange(budget, dtype=torch.int32).repeat(kv, 1).contiguous()
+    a.load(K.cuda(), V.cuda(), pos.cuda(), budget)
+    ls.oracle.load(K.double().numpy(), V.double().numpy(), pos.numpy(), budget)
+    name = "bf16" if dtype == torch.bfloat16 else "fp32"
+    for step, L in enumerate(lens):
+        print("lean workspace", name, "step", step, "L", L, flush=True)
+        ls.step(*random_chunk(2300 + step, L, heads, kv, d, name), check_state=True)
+    for i in range(decode):
+        ls.decode(*random_chunk(2350 + i, 1, heads, kv, d, name))
+    torch.cuda.synchronize()
+    a.close()
