@@ -488,14 +488,15 @@ int infmllm_step(infmllm_stream_t* s, const void* q, const void* k, const void* 
     const Geometry& g = s->g;
     const int n = s->len + L;
     hipError_t e;
+    // rows that can need a new home: the chunk rows read in place and the cached rows at or above the budget
+    const int nmax = (n - ks.rows) + (ks.rows > g.B ? ks.rows - g.B : 0);
+    const bool placed = place_in_select(g, nmax);
     s->mark(INFMLLM_K_SELECT, 0);
-    if ((e = launch_select(g, s->Wb, n, ks.rows, retained, n_retained, s->cache, s->mv, s->st)) != hipSuccess)
+    if ((e = launch_select(g, s->Wb, n, ks.rows, retained, n_retained, s->cache, s->mv, ks, s->streamed, placed, s->st)) != hipSuccess)
         return fail_hip(e, "step: select");
     s->mark(INFMLLM_K_SELECT, 1);
     s->mark(INFMLLM_K_COMPACT, 0);
-    // rows that can need a new home: the chunk rows read in place and the cached rows at or above the budget
-    const int nmax = (n - ks.rows) + (ks.rows > g.B ? ks.rows - g.B : 0);
-    if ((e = launch_place(g, s->cache, ks, s->streamed, s->mv, nmax, s->st)) != hipSuccess)
+    if (!placed && (e = launch_place(g, s->cache, ks, s->streamed, s->mv, nmax, s->st)) != hipSuccess)
         return fail_hip(e, "step: placement");
     s->mark(INFMLLM_K_COMPACT, 1);
     step_done(s, n, L);
@@ -552,11 +553,12 @@ int infmllm_evict_batched(infmllm_stream_t* const* streams, int count, int32_t* 
             nmax = m > nmax ? m : nmax;
         }
         hipError_t e;
+        const bool placed = place_in_select(lead->g, nmax);
         lead->mark(INFMLLM_K_SELECT, 0);
-        if ((e = launch_select_batch(lead->g, eb, lead->st)) != hipSuccess) return fail_hip(e, "evict_batched: select");
+        if ((e = launch_select_batch(lead->g, eb, placed, lead->st)) != hipSuccess) return fail_hip(e, "evict_batched: select");
         lead->mark(INFMLLM_K_SELECT, 1);
         lead->mark(INFMLLM_K_COMPACT, 0);
-        if ((e = launch_place_batch(lead->g, eb, nmax, lead->st)) != hipSuccess) return fail_hip(e, "evict_batched: placement");
+        if (!placed && (e = launch_place_batch(lead->g, eb, nmax, lead->st)) != hipSuccess) return fail_hip(e, "evict_batched: placement");
         lead->mark(INFMLLM_K_COMPACT, 1);
         for (int j = 0; j < eb.count; ++j) step_done(streams[base + j], streams[base + j]->pend_n, streams[base + j]->pend_L);
     }

@@ -152,9 +152,13 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
 // placement (Alg. 1 l.8 without moving the rows that stay): a retained token whose physical row is
 // below B keeps it and gets its new rank, row and score entries here; the others go into the move
 // list, paired in order with the physical rows the eviction frees.  tc = rows in the cache (stream-order
-// indices from tc on are chunk rows read in place).
+// indices from tc on are chunk rows read in place).  With `place` it moves them as well (ks, T as in launch_place).
 hipError_t launch_select(const Geometry& g, const float* Wb, int n, int tc, int32_t* user_I,
-                         int32_t* user_count, const CacheView& c, const MoveList& mv, hipStream_t st);
+                         int32_t* user_count, const CacheView& c, const MoveList& mv, const KeySource& ks, int64_t T, bool place,
+                         hipStream_t st);
+// Whether the selection also places (a7) when at most nmax rows of a head have to move; launch_place is not called then.
+constexpr int PLACE_HERE_ROWS = 512;
+bool place_in_select(const Geometry& g, int nmax);
 
 // a7: copies the K and V rows of the move list to their new physical rows and writes their pos, rank,
 // row and score entries.  nmax = most entries a head's list can hold in this step.
@@ -178,7 +182,7 @@ struct EvictBatch {
     int count, pad_;
     EvictJob job[EVICT_MAX_JOBS];
 };
-hipError_t launch_select_batch(const Geometry& g, const EvictBatch& eb, hipStream_t st);
+hipError_t launch_select_batch(const Geometry& g, const EvictBatch& eb, bool place, hipStream_t st);
 hipError_t launch_place_batch(const Geometry& g, const EvictBatch& eb, int nmax, hipStream_t st);
 
 // Comparison policies that rank by age: W'[h][j] = sign * j for j < cnd (sign +1 keeps the newest,

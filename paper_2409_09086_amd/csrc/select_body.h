@@ -196,10 +196,59 @@ __device__ __forceinline__ void plan_prefetch_scores(PlanPre& pre, const float* 
     for (int g = 0; g < PLAN_PRE; ++g) pre.w[g] = (uint32_t)pre.jj[g] < (uint32_t)cnd ? at32(W, pre.jj[g]) : __builtin_inff();
 }
 
+// The placement of a short move list by the workgroup that made it (Alg. 1 l.8), instead of a launch of its own: see
+// place_in_select.
+struct PlaceHere {
+    bool on;
+    int vec_shift, Hkv, h, cap, pos0;              // 2^vec_shift 16-byte vectors per row
+    const u32x4_t *kc, *vc;                        // chunk tensors
+    u32x4_t *K, *V;                                // the cache (all heads)
+    int32_t* pos;                                  // of this head
+};
+struct Mover {
+    int src, dst, x;
+    float score;
+};
+template <int TPB>
+__device__ __forceinline__ void place_movers(const Mover* mv, int count, int tc, const PlanTables& pt, const PlaceHere& ph)
+{
+    const size_t hb = (size_t)ph.h * ph.cap;
+    const int total = count << ph.vec_shift, xmask = (1 << ph.vec_shift) - 1;
+    constexpr int U = 2;                           // vectors in flight per thread and tensor
+    for (int i0 = threadIdx.x; i0 < total; i0 += U * TPB) {
+        u32x4_t kk[U], vv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * TPB, total - 1), src = mv[i >> ph.vec_shift].src;
+            const bool cached = src < tc;
+            const size_t row = cached ? hb + src : (size_t)(src - tc) * ph.Hkv + ph.h;
+            const size_t at = (row << ph.vec_shift) + (i & xmask);
+            kk[u] = __builtin_nontemporal_load((cached ? (const u32x4_t*)ph.K : ph.kc) + at);
+            vv[u] = __builtin_nontemporal_load((cached ? (const u32x4_t*)ph.V : ph.vc) + at);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * TPB;
+            if (i >= total) break;
+            const Mover m = mv[i >> ph.vec_shift];
+            const size_t at = ((hb + m.dst) << ph.vec_shift) + (i & xmask);
+            ph.K[at] = kk[u];
+            ph.V[at] = vv[u];
+            if ((i & xmask) == 0) {
+                ph.pos[m.dst] = m.src < tc ? ph.pos[m.src] : ph.pos0 + (m.src - tc);
+                pt.rank[m.dst] = m.x;
+                pt.row[m.x] = m.dst;
+                pt.score[m.dst] = m.score;
+            }
+        }
+    }
+}
+
 template <int KPT, int TPB>
 __device__ __forceinline__ void plan_moves(const PlanLds<KPT, TPB>& pl, const float* __restrict__ W, int n, int tc, int cnd,
-                                           int B, int r, const PlanTables& pt, const PlanPre& pre)
+                                           int B, int r, const PlanTables& pt, const PlanPre& pre, const PlaceHere& ph)
 {
+    __shared__ Mover movers[PLACE_HERE_ROWS];
     constexpr int NW = TPB / 64, CH = 64 / NW;                 // CH passes of TPB items share one table of 64 counts
     __shared__ uint32_t cnt_free[64], cnt_mov[64];
     __shared__ uint32_t tot_free, tot_mov;
@@ -268,12 +317,22 @@ __device__ __forceinline__ void plan_moves(const PlanLds<KPT, TPB>& pl, const fl
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
             const int q = q0 + u * TPB + tid;
-            if ((bfree[u] >> l) & 1ull) at32(pt.mv_dst, fbase + cnt_free[u * NW + w] + lanes_below(bfree[u])) = q;
+            if ((bfree[u] >> l) & 1ull) {
+                const uint32_t k = fbase + cnt_free[u * NW + w] + lanes_below(bfree[u]);
+                if (ph.on) movers[k].dst = q;
+                else at32(pt.mv_dst, k) = q;
+            }
             if ((bmov[u] >> l) & 1ull) {
                 const uint32_t k = mbase + cnt_mov[u * NW + w] + lanes_below(bmov[u]);
-                at32(pt.mv_src, k) = src[u];
-                at32(pt.mv_x, k) = xs[u];
-                at32(pt.mv_score, k) = sc[u];
+                if (ph.on) {
+                    movers[k].src = src[u];
+                    movers[k].x = xs[u];
+                    movers[k].score = sc[u];
+                } else {
+                    at32(pt.mv_src, k) = src[u];
+                    at32(pt.mv_x, k) = xs[u];
+                    at32(pt.mv_score, k) = sc[u];
+                }
             }
         }
         fbase += tot_free;
@@ -300,7 +359,8 @@ __device__ __forceinline__ void plan_moves(const PlanLds<KPT, TPB>& pl, const fl
             wv[u] = KPT == 0 && (uint32_t)jj[u] < (uint32_t)cnd ? at32(W, jj[u]) : 0.f;
         pass(q0, jj, wv);
     }
-    if (tid == 0) *pt.mv_count = (int32_t)mbase;               // = fbase: B tokens are retained, B rows lie below B
+    if (ph.on) place_movers<TPB>(movers, (int)mbase, tc, pt, ph);   // the last pass ended with a barrier
+    else if (tid == 0) *pt.mv_count = (int32_t)mbase;               // = fbase: B tokens are retained, B rows lie below B
 }
 
 // Same selection with the candidates of a head held in registers (KPT keys per thread, key

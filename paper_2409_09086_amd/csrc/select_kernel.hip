@@ -122,7 +122,7 @@ __device__ __forceinline__ void select_mem_body(const float* __restrict__ Wb, in
 // One head: selection, then the placement plan.  KPT = 0: candidates stay in memory.
 template <int KPT>
 __device__ __forceinline__ void select_head(const float* Wb, int32_t* userI, int32_t* user_count, int h, int n, int r, int R,
-                                            int B, int cap, int tc, const CacheView& c, const MoveList& mv)
+                                            int B, int cap, int tc, const CacheView& c, const MoveList& mv, PlaceHere ph)
 {
     __shared__ PlanLds<KPT, TPB> pl;
     const int cnd = n - R;
@@ -137,39 +137,64 @@ __device__ __forceinline__ void select_head(const float* Wb, int32_t* userI, int
     }
     const PlanTables pt{c.rank + hb, c.row + hb, c.score + hb, mv.src + mb, mv.dst + mb, mv.x + mb, mv.score + mb,
                         mv.count + h};
-    plan_moves<KPT, TPB>(pl, Wb + hb, n, tc, cnd, B, r, pt, pre);
+    plan_moves<KPT, TPB>(pl, Wb + hb, n, tc, cnd, B, r, pt, pre, ph);
 }
 
 // One workgroup per kv-head.
 template <int KPT>
 __global__ void __launch_bounds__(TPB)
 select_kernel(const float* __restrict__ Wb, int32_t* __restrict__ userI, int32_t* __restrict__ user_count, int cnd, int r,
-              int R, int B, int cap, int tc, CacheView c, MoveList mv)
+              int R, int B, int cap, int tc, CacheView c, MoveList mv, int here, const void* kc, const void* vc, int pos0,
+              int Hkv, int vec_shift)
 {
-    select_head<KPT>(Wb, userI, user_count, blockIdx.x, cnd + R, r, R, B, cap, tc, c, mv);
+    const int h = blockIdx.x;
+    const PlaceHere ph{here != 0, vec_shift, Hkv, h, cap, pos0, (const u32x4_t*)kc, (const u32x4_t*)vc, (u32x4_t*)c.K, (u32x4_t*)c.V,
+                       c.pos + (size_t)h * cap};
+    select_head<KPT>(Wb, userI, user_count, h, cnd + R, r, R, B, cap, tc, c, mv, ph);
 }
 
 // Several streams of one geometry (the layers of a model, Alg. 1 Input note): stream j owns
 // workgroups [j * Hkv, (j + 1) * Hkv).
 template <int KPT>
 __global__ void __launch_bounds__(TPB)
-select_batch_kernel(EvictBatch eb, int r, int R, int B, int cap, int Hkv)
+select_batch_kernel(EvictBatch eb, int r, int R, int B, int cap, int Hkv, int here, int vec_shift)
 {
     const EvictJob& job = eb.job[blockIdx.x / Hkv];
-    select_head<KPT>(job.Wb, job.user_I, job.user_count, blockIdx.x % Hkv, job.n, r, R, B, cap, job.tc, job.c, job.mv);
+    const int h = blockIdx.x % Hkv;
+    const PlaceHere ph{here != 0, vec_shift, Hkv, h, cap, job.pos0, (const u32x4_t*)job.kc, (const u32x4_t*)job.vc, (u32x4_t*)job.c.K,
+                       (u32x4_t*)job.c.V, job.c.pos + (size_t)h * cap};
+    select_head<KPT>(job.Wb, job.user_I, job.user_count, h, job.n, r, R, B, cap, job.tc, job.c, job.mv, ph);
 }
 
 }  // namespace
 
+static int vec_shift(const Geometry& g)
+{
+    int s = 0;
+    while ((16 << s) < g.d * g.elt) ++s;                      // a row is 128, 256 or 512 bytes
+    return s;
+}
+
+bool place_in_select(const Geometry& g, int nmax)
+{
+    // The placement's launch is 4 to 5 us of launch, list and drain before its bytes count; one workgroup per head moves 128 KB of
+    // K and V (4096 vectors each) in that time.  Whole steps, us, with the launch / without: 32 x 128 heads, 4096 rows,
+    // chunk of 37 41.9 / 38.3, of 64 42.4 / 39.7, of 128 48.5 / 46.0, of 256 (4096 vectors) 60.7 / 60.0; 8 kv-heads, 256: 62.9 / 60.8;
+    // head_dim 64, 4 kv-heads, chunk of 197: 27.2 / 24.1; fp32, 8 x 128: chunk of 128 (4096) 37.8 / 37.7, of 256 (8192) 45.4 / 47.9; eight
+    // layers of 32 x 128 in a batch, chunk of 256: 306.5 / 303.7.
+    return nmax <= PLACE_HERE_ROWS && (nmax << vec_shift(g)) <= 4096;
+}
+
 hipError_t launch_select(const Geometry& g, const float* Wb, int n, int tc, int32_t* user_I,
-                         int32_t* user_count, const CacheView& c, const MoveList& mv, hipStream_t st)
+                         int32_t* user_count, const CacheView& c, const MoveList& mv, const KeySource& ks, int64_t T, bool place,
+                         hipStream_t st)
 {
     const int cnd = n - g.R, r = g.B - g.R;
     if (cnd > PLAN_MAX_C) return hipErrorInvalidValue;
     const dim3 grid(g.Hkv);
 #define INFMLLM_SELECT(KPT)                                                                                \
     hipLaunchKernelGGL(select_kernel<KPT>, grid, dim3(TPB), 0, st, Wb, user_I, user_count, cnd, r, g.R, g.B, g.cap, \
-                       tc, c, mv)
+                       tc, c, mv, place ? 1 : 0, ks.k, ks.v, (int)T, g.Hkv, vec_shift(g))
     if (cnd <= 2 * TPB) INFMLLM_SELECT(2);
     else if (cnd <= 4 * TPB) INFMLLM_SELECT(4);
     else if (cnd <= 8 * TPB) INFMLLM_SELECT(8);
@@ -179,7 +204,7 @@ hipError_t launch_select(const Geometry& g, const float* Wb, int n, int tc, int3
     return hipGetLastError();
 }
 
-hipError_t launch_select_batch(const Geometry& g, const EvictBatch& eb, hipStream_t st)
+hipError_t launch_select_batch(const Geometry& g, const EvictBatch& eb, bool place, hipStream_t st)
 {
     if (eb.count < 1 || eb.count > EVICT_MAX_JOBS) return hipErrorInvalidValue;
     const int r = g.B - g.R;
@@ -188,7 +213,7 @@ hipError_t launch_select_batch(const Geometry& g, const EvictBatch& eb, hipStrea
     if (cnd > PLAN_MAX_C) return hipErrorInvalidValue;
     const dim3 grid(g.Hkv * eb.count);
 #define INFMLLM_SELECT(KPT) \
-    hipLaunchKernelGGL(select_batch_kernel<KPT>, grid, dim3(TPB), 0, st, eb, r, g.R, g.B, g.cap, g.Hkv)
+    hipLaunchKernelGGL(select_batch_kernel<KPT>, grid, dim3(TPB), 0, st, eb, r, g.R, g.B, g.cap, g.Hkv, place ? 1 : 0, vec_shift(g))
     if (cnd <= 2 * TPB) INFMLLM_SELECT(2);
     else if (cnd <= 4 * TPB) INFMLLM_SELECT(4);
     else if (cnd <= 8 * TPB) INFMLLM_SELECT(8);

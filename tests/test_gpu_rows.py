@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (16, 16, 64, 600, 150, [300, 300, 128, 31]),          # many heads: few pieces or one
     (1, 1, 128, 31, 8, [31, 7, 20]),                      # fewer keys than a run
     (4, 2, 64, 96, 96, [96, 33, 96]),                     # the whole budget is recent window: nothing is ranked
+    (2, 2, 64, 900, 100, [900, 511, 512, 513]),           # as many moved rows as the selection places itself, and one more
+    (2, 1, 128, 600, 50, [600, 255, 256, 257]),
     (16, 2, 128, 2600, 300, [1300, 1300, 270, 301]),      # 64 rows per workgroup, three pieces, ragged rows and keys
 ])
 def test_short_chunks_match_oracle(heads, kv, d, budget, recent, chunks):
