@@ -136,9 +136,12 @@ def retention_leg(cfg, binding, dev, impl):
 
 
 def attn_kernel_name(cfg, L, mfma):
-    """Which attention kernel the library's launch picks for this shape (the rule of launch_attn_mfma)."""
+    """Which attention kernel the library's launch picks for a workload's shape (the rule of launch_attn_mfma; the cost
+    model of rows_chunk_plan prefers attn_rows and attn_rows64 where 64-row workgroups are one round of the CUs)."""
     if not mfma:
-        return "attn_simple"
+        return "attn_f32" if cfg.dtype == "fp32" else "attn_simple"
+    if cfg.kv_heads * -(-L * cfg.heads // cfg.kv_heads // 64) <= 256:
+        return "attn_rows64" if cfg.head_dim == 128 else "attn_rows"
     wgs64 = (cfg.heads * (-(-L // 64)) + 3) // 4
     rounds = -(-wgs64 // 256)
     fills = wgs64 * 5 >= rounds * 256 * 4
@@ -352,8 +355,9 @@ def measure(cfg, args, binding, dev, steps, nchunks, full):
     attn = kernels["attn"]
     mfma = cfg.dtype == "bf16" and args.impl != 1
     peak = PEAK_BF16_TFLOPS if mfma else PEAK_FP32_TFLOPS
-    ctr = read_counters("attn_fwd_%s_pmc.txt" % cfg.name)
-    roofline = {"kernel": attn_kernel_name(cfg, L, mfma), "bound": "mfma" if mfma else "alu",
+    kernel = attn_kernel_name(cfg, L, mfma)
+    ctr = read_counters("%s_%s_pmc.txt" % (kernel if kernel.startswith("attn_rows") else "attn_fwd", cfg.name))
+    roofline = {"kernel": kernel, "bound": "mfma" if mfma else "alu",
                 "achieved": attn["tflops"], "peak": peak, "unit": "TFLOP/s", "frac": round(attn["tflops"] / peak, 4),
                 "traffic": ctr["traffic"], "mfma_busy_counter": ctr["mfma_busy"], "counters_from": ctr["source"],
                 "algorithmic_flops_per_launch": work["attn"]["flops"], "avg_us": attn["us"]}
