@@ -28,6 +28,7 @@
  *   - A stream is not thread-safe; different streams may be used from different threads.
  *   - Tensors are dense, row-major, token-major: q and out are [chunk_len, heads, head_dim],
  *     k and v are [chunk_len, kv_heads, head_dim], in the stream's dtype.
+ *   - The out of a chunk step may overlap its k and v (their values before the call are used).
  */
 #ifndef INFMLLM_H
 #define INFMLLM_H

@@ -36,6 +36,11 @@ int fail_hip(hipError_t e, const char* what)
     return fail(INFMLLM_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 constexpr size_t ALIGN = 256;
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -397,16 +402,16 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
     const bool mfma = s->mfma(), f32 = s->f32();
     hipError_t e;
 
-    // On the matrix cores attention and scoring read the chunk's rows in place.  An evicting step never appends: the
+    // On the matrix cores attention and scoring read the chunk's rows in place.  An evicting step then never appends: the
     // placement writes the survivors into the rows the eviction frees; in one that evicts nothing the attention launch
-    // writes the chunk into the cache as well.  The position encoding turns rows of the cache, so with it (and where out
-    // overwrites the chunk's tensors) a step that evicts nothing appends first.
+    // writes the chunk into the cache as well.  Where out overwrites the chunk's tensors a step appends first and reads the
+    // chunk from the cache: workgroups still read keys and values when others have stored their output, and the placement
+    // reads them after the attention.  So does a step that evicts nothing with the position encoding, which turns rows of
+    // the cache.
     const bool warm = n <= g.B;
     const size_t kv_bytes = (size_t)L * g.Hkv * g.d * g.elt, out_bytes = (size_t)L * g.Hq * g.d * g.elt;
-    auto overwritten = [&](const void* x) {
-        return (uintptr_t)out < (uintptr_t)x + kv_bytes && (uintptr_t)x < (uintptr_t)out + out_bytes;
-    };
-    const bool in_place = (mfma || f32) && !(warm && (s->rope_base > 0.0 || overwritten(k) || overwritten(v)));
+    const bool in_place = (mfma || f32) && !(warm && s->rope_base > 0.0) && !overlap(out, out_bytes, k, kv_bytes) &&
+                          !overlap(out, out_bytes, v, kv_bytes);
     const KeySource ks = in_place ? KeySource{t, k, v} : KeySource{n, nullptr, nullptr};
     AppendJob job{};
     if (warm || !in_place)

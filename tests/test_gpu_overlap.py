@@ -1,0 +1,54 @@
+"""Calls whose output overwrites their own inputs: the values before the call count."""
+import pytest
+import torch
+
+from paper_2409_09086_amd import binding as B
+from paper_2409_09086_amd.workloads import random_chunk
+
+pytestmark = pytest.mark.gpu
+DT = {"fp32": torch.float32, "bf16": torch.bfloat16}
+
+
+def same(a, b):
+    for x, y in zip(a.export(), b.export()):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("over", ["k", "v"])
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("dtype,impl,heads,kv,d,budget,chunks,rope", [
+    ("fp32", 0, 4, 4, 64, 200, [120, 80, 130, 33, 7], None),
+    ("fp32", 0, 2, 2, 128, 640, [340, 300, 300, 256], None),           # moves more rows than the selection places itself
+    ("fp32", 0, 2, 2, 64, 200, [200, 70, 33], 10000.0),
+    ("bf16", 0, 4, 4, 128, 300, [300, 129, 40, 1], None),
+    ("bf16", 0, 4, 4, 64, 300, [300, 129, 40], 10000.0),
+    ("bf16", 1, 4, 4, 128, 200, [200, 100, 33], None),
+    ("bf16", 0, 8, 2, 128, 300, [300, 130, 40], None),            # grouped heads: out is larger than k and covers it
+])
+def test_evicting_steps_whose_output_overwrites_the_chunk(dtype, impl, heads, kv, d, budget, chunks, rope, batched, over):
+    """Against a twin with an output of its own.  The twin reads the chunk in place, this stream from the cache, the same
+    keys in the same order: outputs, lists and cache agree bit for bit."""
+    a, b = (B.Stream(budget, budget // 4, heads, kv, d, dtype=DT[dtype], bias=1e-3, max_chunk=max(chunks), impl=impl,
+                     rope_base=rope) for _ in range(2))
+    for step, L in enumerate(chunks):
+        print("overlap", (dtype, impl, heads, kv, d, budget, rope, batched, over), "step", step, "L", L, flush=True)
+        q, k, v = (x.cuda() for x in random_chunk(4100 + step, L, heads, kv, d, dtype))
+        n = k.numel()
+        buf = torch.empty(q.numel() + 64, dtype=q.dtype, device="cuda")
+        out = buf[: q.numel()].view(q.shape)                      # the chunk's tensor lies at the start of the output
+        mine = buf[:n].view(k.shape)
+        mine.copy_(k if over == "k" else v)
+        args = (q, mine, v) if over == "k" else (q, k, mine)
+        if batched:
+            r = a.step_attend(*args, out=out)
+            w = b.step_attend(q, k, v)
+            if a.pending:
+                B.evict_batched([a])
+                B.evict_batched([b])
+        else:
+            r = a.step(*args, out=out)
+            w = b.step(q, k, v)
+        cnt = int(w[2].item())
+        assert int(r[2].item()) == cnt
+        assert torch.equal(r[0], w[0]) and torch.equal(r[1][:, :cnt], w[1][:, :cnt])
+        same(a, b)
