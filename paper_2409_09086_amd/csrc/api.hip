@@ -676,8 +676,12 @@ int infmllm_decode_n(infmllm_stream_t* s, const void* q, const void* k, const vo
     if (s->streamed + n_tokens > (int64_t)INT32_MAX)
         return fail(INFMLLM_ECAPACITY, "decode: stream positions would exceed 2^31-1");
     const size_t qrow = (size_t)s->g.Hq * s->g.d * s->g.elt, krow = (size_t)s->g.Hkv * s->g.d * s->g.elt;
+    // Tokens that share a launch read each other's keys and values while finished rows are stored: where the output
+    // overwrites the inputs they are decoded one after the other.  (out == q is safe: whoever stores a row has read it.)
+    const size_t qb = n_tokens * qrow, kb = n_tokens * krow;
+    const bool alone = overlap(out, qb, k, kb) || overlap(out, qb, v, kb) || (out != q && overlap(out, qb, q, qb));
     for (int i = 0; i < n_tokens;) {
-        const int T = decode_tokens_per_launch(s, n_tokens - i);
+        const int T = alone ? 1 : decode_tokens_per_launch(s, n_tokens - i);
         const int rc = decode_some(s, (const char*)q + i * qrow, (const char*)k + i * krow, (const char*)v + i * krow,
                                    (char*)out + i * qrow, T);
         if (rc != INFMLLM_OK) return rc;

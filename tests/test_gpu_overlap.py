@@ -9,10 +9,6 @@ pytestmark = pytest.mark.gpu
 DT = {"fp32": torch.float32, "bf16": torch.bfloat16}
 
 
-def same(a, b):
-    for x, y in zip(a.export(), b.export()):
-        assert torch.equal(x, y)
-
 
 @pytest.mark.parametrize("over", ["k", "v"])
 @pytest.mark.parametrize("batched", [False, True])
@@ -51,4 +47,32 @@ def test_evicting_steps_whose_output_overwrites_the_chunk(dtype, impl, heads, kv
         cnt = int(w[2].item())
         assert int(r[2].item()) == cnt
         assert torch.equal(r[0], w[0]) and torch.equal(r[1][:, :cnt], w[1][:, :cnt])
-        same(a, b)
+        for x, y in zip(a.export(), b.export()):
+            assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("over", ["q", "k", "v"])
+@pytest.mark.parametrize("dtype,heads,kv,d,held,n,rope", [
+    ("bf16", 4, 4, 128, 30, 60, None),        # one piece, two row groups
+    ("bf16", 2, 2, 64, 100, 64, None),
+    ("bf16", 4, 4, 128, 900, 40, None),       # several pieces, a merging launch
+    ("bf16", 8, 2, 128, 100, 40, None),
+    ("bf16", 4, 4, 64, 100, 40, 10000.0),
+    ("fp32", 2, 2, 64, 100, 5, None),
+])
+def test_tokens_whose_output_overwrites_their_inputs(dtype, heads, kv, d, held, n, rope, over):
+    """decode_n against a twin with an output of its own: outputs and cache bit for bit."""
+    if over != "q" and heads != kv:
+        pytest.skip("only tensors of one shape may coincide")
+    a, b = (B.Stream(1000, 100, heads, kv, d, dtype=DT[dtype], max_chunk=max(held, 64), max_decode=64, rope_base=rope) for _ in range(2))
+    for s in (a, b):
+        s.step(*(x.cuda() for x in random_chunk(4200, held, heads, kv, d, dtype)))
+    for call in range(2):
+        print("overlap", (dtype, heads, kv, d, held, n, rope, over), "call", call, flush=True)
+        q, k, v = (x.cuda() for x in random_chunk(4201 + call, n, heads, kv, d, dtype))
+        want = b.decode_n(q, k, v)
+        args = {"q": q.clone(), "k": k.clone(), "v": v.clone()}
+        out = a.decode_n(args["q"], args["k"], args["v"], out=args[over])
+        assert torch.equal(out, want)
+        for x, y in zip(a.export(), b.export()):
+            assert torch.equal(x, y)
