@@ -66,9 +66,7 @@ attn_f32_kernel(RowsArgsT<float> a, AppendJob ap)
     if constexpr (APPEND)
         append_share(ap, sp + gridDim.x * (h + gridDim.y * blockIdx.z), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     f32x4 o[NJ];                                               // block b: lane (row c16, group g4) holds columns VW (4 g4 + i) + b
-#pragma unroll
-    for (int b = 0; b < NJ; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_ref = -__builtin_inff(), m_use = 0.f, lsum = 0.f;
+    float m_ref, m_use, lsum;
 
     const uint32_t base = (uint32_t)(uintptr_t)(lds_void*)mine;
     uint32_t kaddr[NJ], vaddr[VP];                             // K: row c16, piece 4j + g4; V: row 4 g4 (+ i), pieces VP c16 + x
@@ -77,63 +75,97 @@ attn_f32_kernel(RowsArgsT<float> a, AppendJob ap)
 #pragma unroll
     for (int x = 0; x < VP; ++x) vaddr[x] = base + RUN + 4 * g4 * ROWB + Runs::Swz::v(0, VP * c16 + x) * 16;
 
-    for (int p = 0; p < np; ++p) {
-        const int k0 = k_first + p * F32_PASS;
-        wait_loads<0>();
-        f32x4 kf[NJ], vf[4][VP];
+    // A hidden key's weight is 0, but 0 times a value that is not finite is NaN, in every row of the group.  A wavefront
+    // that finds its accumulators not finite goes through its keys again (CAREFUL), the rows that see the same number of a run's
+    // keys at a time, hidden values replaced by 0.
+    auto sweep = [&](auto careful) __attribute__((always_inline)) {
+        constexpr bool CAREFUL = decltype(careful)::value;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) kf[j] = rw_read_f32x4<0>(kaddr[j]);
-        static_for<0, 4>([&](auto I) {
-            constexpr int i = decltype(I)::value;
+        for (int b = 0; b < NJ; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m_ref = -__builtin_inff(); m_use = 0.f; lsum = 0.f;
+        for (int p = 0; p < np; ++p) {
+            const int k0 = k_first + p * F32_PASS;
+            wait_loads<0>();
+            f32x4 kf[NJ], vf[4][VP];
 #pragma unroll
-            for (int x = 0; x < VP; ++x) vf[i][x] = rw_read_f32x4<i * ROWB>(vaddr[x]);
-        });
-        // reads return in order: K has arrived when only the V reads are outstanding
-        asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]) : "n"(4 * VP));
-        if constexpr (NJ == 8) asm volatile("" : "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7]));
-        // ---- S^T = K.Q^T, in two chains
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < NJ; ++j) kf[j] = rw_read_f32x4<0>(kaddr[j]);
+            static_for<0, 4>([&](auto I) {
+                constexpr int i = decltype(I)::value;
 #pragma unroll
-        for (int j = 0; j < NJ; j += 2)
+                for (int x = 0; x < VP; ++x) vf[i][x] = rw_read_f32x4<i * ROWB>(vaddr[x]);
+            });
+            // reads return in order: K has arrived when only the V reads are outstanding
+            asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]) : "n"(4 * VP));
+            if constexpr (NJ == 8) asm volatile("" : "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7]));
+            // ---- S^T = K.Q^T, in two chains
+            f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                s0 = mfma16_f32(kf[j][e], qf[j][e], s0);
-                s1 = mfma16_f32(kf[j + 1][e], qf[j + 1][e], s1);
+            for (int j = 0; j < NJ; j += 2)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s0 = mfma16_f32(kf[j][e], qf[j][e], s0);
+                    s1 = mfma16_f32(kf[j + 1][e], qf[j + 1][e], s1);
+                }
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vf[0][0]), "+v"(vf[1][0]), "+v"(vf[2][0]), "+v"(vf[3][0]));
+            if constexpr (VP == 2) asm volatile("" : "+v"(vf[0][VP - 1]), "+v"(vf[1][VP - 1]), "+v"(vf[2][VP - 1]), "+v"(vf[3][VP - 1]));
+            if (p + 1 < np) runs.template load<true, true>(k0 + F32_PASS, mine);   // this stage has been read
+            // ---- mask, softmax
+            float s[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = (s0[i] + s1[i]) * a.c;
+            if (k0 + F32_RUN - 1 > first_lim) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (k0 + 4 * g4 + i > lim) s[i] = -__builtin_inff();
             }
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vf[0][0]), "+v"(vf[1][0]), "+v"(vf[2][0]), "+v"(vf[3][0]));
-        if constexpr (VP == 2) asm volatile("" : "+v"(vf[0][VP - 1]), "+v"(vf[1][VP - 1]), "+v"(vf[2][VP - 1]), "+v"(vf[3][VP - 1]));
-        if (p + 1 < np) runs.template load<true, true>(k0 + F32_PASS, mine);   // this stage has been read
-        // ---- mask, softmax
-        float s[4];
+            const float mx = groups_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+            if (__any(mx > m_ref + F32_TAU)) {
+                const float m_new = fmaxf(m_ref, mx);
+                const float mu = (m_new == -__builtin_inff()) ? 0.f : m_new;
+                const float alpha = expf(m_ref - mu);              // m_ref = -inf gives 0
+                m_ref = m_new;
+                m_use = mu;
+                lsum *= alpha;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[i] = (s0[i] + s1[i]) * a.c;
-        if (k0 + F32_RUN - 1 > first_lim) {
+                for (int b = 0; b < NJ; ++b) o[b] *= alpha;
+            }
+            float w[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (k0 + 4 * g4 + i > lim) s[i] = -__builtin_inff();
+            for (int i = 0; i < 4; ++i) {
+                w[i] = expf(s[i] - m_use);
+                lsum += w[i];
+            }
+            // ---- O^T += V^T.P^T
+            if constexpr (CAREFUL) {
+                const int last = max(min(lim - k0, F32_RUN - 1), -1);      // last key of the run that the row sees, -1: none
+#pragma nounroll
+                for (int end = 0; end < F32_RUN; ++end) {
+                    if (!__any(last == end)) continue;
+#pragma unroll
+                    for (int b = 0; b < NJ; ++b) {
+                        f32x4 sum = o[b];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sum = mfma16_f32(4 * g4 + i > end ? 0.f : vf[i][b / 4][b % 4], w[i], sum);
+                        if (last == end) o[b] = sum;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int b = 0; b < NJ; ++b) o[b] = mfma16_f32(vf[i][b / 4][b % 4], w[i], o[b]);
+            }
         }
-        const float mx = groups_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
-        if (__any(mx > m_ref + F32_TAU)) {
-            const float m_new = fmaxf(m_ref, mx);
-            const float mu = (m_new == -__builtin_inff()) ? 0.f : m_new;
-            const float alpha = expf(m_ref - mu);              // m_ref = -inf gives 0
-            m_ref = m_new;
-            m_use = mu;
-            lsum *= alpha;
+    };
+    sweep(std::false_type{});
+    float z = 0.f;
 #pragma unroll
-            for (int b = 0; b < NJ; ++b) o[b] *= alpha;
-        }
-        float w[4];
+    for (int b = 0; b < NJ; ++b)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            w[i] = expf(s[i] - m_use);
-            lsum += w[i];
-        }
-        // ---- O^T += V^T.P^T
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int b = 0; b < NJ; ++b) o[b] = mfma16_f32(vf[i][b / 4][b % 4], w[i], o[b]);
+        for (int i = 0; i < 4; ++i) z = __builtin_fmaf(o[b][i], 0.f, z);
+    if (__builtin_expect(__any(z != 0.f), 0)) {
+        runs.template load<true, true>(k_first, mine);         // np > 0
+        sweep(std::true_type{});
     }
 
     // ---- merge the wavefronts (see attn_rows_kernel)

@@ -353,8 +353,11 @@ merge_rows_kernel(const float* __restrict__ part_o, const float2* __restrict__ p
     for (int c = 0; c < N; ++c) {                              // all requested before any is used
         const int s = min(c, nsplit - 1);
         const float2 ml = pml[s];
-        ps[c] = PieceSumT<NAT>{c < nsplit ? ml.x : -__builtin_inff(), ml.y, *(const f32x4*)(po + (size_t)s * D)};
+        ps[c] = PieceSumT<NAT>{ml.x, ml.y, *(const f32x4*)(po + (size_t)s * D)};
     }
+#pragma unroll
+    for (int c = 0; c < N; ++c)                                // no such piece (0 times an infinite output would not be 0)
+        if (c >= nsplit) ps[c] = PieceSumT<NAT>{-__builtin_inff(), 0.f, f32x4{0.f, 0.f, 0.f, 0.f}};
     if (N == RW_CLASSES)
         for (int s0 = RW_CLASSES; s0 < nsplit; s0 += RW_CLASSES)
 #pragma unroll

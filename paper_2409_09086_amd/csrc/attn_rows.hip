@@ -62,29 +62,30 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
     // wavefront 0, which has a run more than the others if any has, has a second stage for its odd runs
     const int nst = wave == 0 ? 2 : 1;
     const uint32_t stage1 = wave == 0 ? RW_NW * C::STAGE : 0;
-    if (np > 0) load_run(k_first, mine);
-    if (nst == 2 && np > 1) load_run(k_first + RW_PASS, mine + stage1);
+    auto load_first = [&]() {
+        if (np > 0) load_run(k_first, mine);
+        if (nst == 2 && np > 1) load_run(k_first + RW_PASS, mine + stage1);
+    };
+    load_first();
     // query fragments: B operand of S^T = K.Q^T, lane (row c16, group g4) holds Q[row][32s + 8 g4 .. +8)
     bf16x8 qf[NRB][C::NS];
     int lim[NRB];
+    auto query_row = [&](int x, int& tok) -> const uint16_t* {
+        const int rho = min(row0 + 16 * x + c16, M - 1);
+        tok = token(rho);
+        return a.q + ((size_t)tok * a.Hq + h * a.G + (rho - tok * a.G)) * D + 8 * g4;
+    };
 #pragma unroll
     for (int x = 0; x < NRB; ++x) {
-        const int rho = min(row0 + 16 * x + c16, M - 1), tok = token(rho);
+        int tok;
+        const uint16_t* qp = query_row(x, tok);
         lim[x] = t + tok;
-        const uint16_t* qp = a.q + ((size_t)tok * a.Hq + h * a.G + (rho - tok * a.G)) * D + 8 * g4;
 #pragma unroll
         for (int s = 0; s < C::NS; ++s) qf[x][s] = as_bf16x8(*(const u32x4*)(qp + 32 * s));
     }
 
     f32x4 o[NRB][C::NC];
     float m_ref[NRB], m_use[NRB], lsum[NRB];
-#pragma unroll
-    for (int x = 0; x < NRB; ++x) {
-#pragma unroll
-        for (int b = 0; b < C::NC; ++b) o[x][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        m_ref[x] = -__builtin_inff(); m_use[x] = 0.f; lsum[x] = 0.f;
-    }
-
     // K fragments: lane (row c16, group g4) reads piece 4s + g4.  V: a 16-lane group reads keys 4 g4 .. +3 (then
     // 16 + 4 g4 .. +3) of sixteen columns; lane l of the group supplies the address of key l / 4, columns 4 (l % 4).
     uint32_t kaddr[C::NS], vaddr[C::NC];
@@ -98,94 +99,160 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
             vaddr[b] = base + C::RUN + vkey * C::ROWB + (((2 * b + (q4 >> 1)) ^ swz_v<D>(vkey)) * 16) + 8 * (q4 & 1);
     }
 
-    for (int p = 0; p < np; ++p) {
-        const int k0 = k_first + p * RW_PASS;
-        const uint32_t stage = (p & 1) ? stage1 : 0;
-        if (nst == 2 && p + 1 < np) wait_loads<2 * C::NL>();   // this run has landed, the next one may be on its way
-        else wait_loads<0>();
-        // fragments: K, then V [column block] (keys 4 g4.. and 16 + 4 g4..), whose way through the LDS the products of
-        // S hide
-        bf16x8 kf[2][C::NS];
-        bf16x4 vlo[C::NC], vhi[C::NC];
-#pragma unroll
-        for (int s = 0; s < C::NS; ++s) {
-            kf[0][s] = rw_read_b128<0>(kaddr[s] + stage);
-            kf[1][s] = rw_read_b128<16 * C::ROWB>(kaddr[s] + stage);
-        }
-#pragma unroll
-        for (int b = 0; b < C::NC; ++b) {
-            vlo[b] = rw_read_tr16<0>(vaddr[b] + stage);
-            vhi[b] = rw_read_tr16<16 * C::ROWB>(vaddr[b] + stage);
-        }
-        // reads return in order: K has arrived when at most the V reads are outstanding (the counter ends at 15)
-        asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(kf[0][0]), "+v"(kf[1][0]), "+v"(kf[0][1]), "+v"(kf[1][1])
-                     : "n"(2 * C::NC < 15 ? 2 * C::NC : 15));
-        if constexpr (C::NS == 4) asm volatile("" : "+v"(kf[0][2]), "+v"(kf[1][2]), "+v"(kf[0][3]), "+v"(kf[1][3]));
-        // ---- S^T = K.Q^T
-        f32x4 S[NRB][2];
-#pragma unroll
-        for (int s = 0; s < C::NS; ++s)
-#pragma unroll
-            for (int x = 0; x < NRB; ++x)
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-                    S[x][kb] = mfma16(kf[kb][s], qf[x][s], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : S[x][kb]);
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vlo[0]), "+v"(vhi[0]), "+v"(vlo[1]), "+v"(vhi[1]), "+v"(vlo[2]), "+v"(vhi[2]),
-                     "+v"(vlo[3]), "+v"(vhi[3]));
-        if constexpr (C::NC == 8)
-            asm volatile("" : "+v"(vlo[4]), "+v"(vhi[4]), "+v"(vlo[5]), "+v"(vhi[5]), "+v"(vlo[6]), "+v"(vhi[6]), "+v"(vlo[7]), "+v"(vhi[7]));
-        // this stage has been read: its next run goes there
-        if (p + nst < np) load_run(k0 + nst * RW_PASS, mine + stage);
-        // ---- mask, softmax
-        bf16x8 pf[NRB][EXACT ? 3 : 1];
-        const bool masked = k0 + RW_RUN - 1 > first_lim;
+    // A hidden key's weight is 0, but 0 times a value that is not finite is NaN, in every row of the group; and such a value
+    // times a weight's three terms is not its product with the weight.  Both show in the accumulators.  A wavefront of a
+    // decoding launch that finds them not finite goes through its keys again (CAREFUL): the rows that see the same number
+    // of a run's keys at a time, hidden values replaced by 0, values that are not finite taken by a weight's first term alone.  What
+    // is finite comes out with the same bits, so that a token's output does not depend on the tokens decoded with it.
+    auto sweep = [&](auto careful) __attribute__((always_inline)) {
+        constexpr bool CAREFUL = decltype(careful)::value;
 #pragma unroll
         for (int x = 0; x < NRB; ++x) {
-            if (masked) {
+#pragma unroll
+            for (int b = 0; b < C::NC; ++b) o[x][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            m_ref[x] = -__builtin_inff(); m_use[x] = 0.f; lsum[x] = 0.f;
+        }
+        for (int p = 0; p < np; ++p) {
+            const int k0 = k_first + p * RW_PASS;
+            const uint32_t stage = (p & 1) ? stage1 : 0;
+            if (nst == 2 && p + 1 < np) wait_loads<2 * C::NL>();   // this run has landed, the next one may be on its way
+            else wait_loads<0>();
+            // fragments: K, then V [column block] (keys 4 g4.. and 16 + 4 g4..), whose way through the LDS the products of
+            // S hide
+            bf16x8 kf[2][C::NS];
+            bf16x4 vlo[C::NC], vhi[C::NC];
+#pragma unroll
+            for (int s = 0; s < C::NS; ++s) {
+                kf[0][s] = rw_read_b128<0>(kaddr[s] + stage);
+                kf[1][s] = rw_read_b128<16 * C::ROWB>(kaddr[s] + stage);
+            }
+#pragma unroll
+            for (int b = 0; b < C::NC; ++b) {
+                vlo[b] = rw_read_tr16<0>(vaddr[b] + stage);
+                vhi[b] = rw_read_tr16<16 * C::ROWB>(vaddr[b] + stage);
+            }
+            // reads return in order: K has arrived when at most the V reads are outstanding (the counter ends at 15)
+            asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(kf[0][0]), "+v"(kf[1][0]), "+v"(kf[0][1]), "+v"(kf[1][1])
+                         : "n"(2 * C::NC < 15 ? 2 * C::NC : 15));
+            if constexpr (C::NS == 4) asm volatile("" : "+v"(kf[0][2]), "+v"(kf[1][2]), "+v"(kf[0][3]), "+v"(kf[1][3]));
+            // ---- S^T = K.Q^T
+            f32x4 S[NRB][2];
+            if constexpr (CAREFUL) {                           // the registers are wanted below
+#pragma unroll
+                for (int x = 0; x < NRB; ++x) {
+                    int tok;
+                    const uint16_t* qp = query_row(x, tok);
+#pragma unroll
+                    for (int s = 0; s < C::NS; ++s) qf[x][s] = as_bf16x8(*(const u32x4*)(qp + 32 * s));
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < C::NS; ++s)
+#pragma unroll
+                for (int x = 0; x < NRB; ++x)
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+                        S[x][kb] = mfma16(kf[kb][s], qf[x][s], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : S[x][kb]);
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vlo[0]), "+v"(vhi[0]), "+v"(vlo[1]), "+v"(vhi[1]), "+v"(vlo[2]), "+v"(vhi[2]),
+                         "+v"(vlo[3]), "+v"(vhi[3]));
+            if constexpr (C::NC == 8)
+                asm volatile("" : "+v"(vlo[4]), "+v"(vhi[4]), "+v"(vlo[5]), "+v"(vhi[5]), "+v"(vlo[6]), "+v"(vhi[6]), "+v"(vlo[7]), "+v"(vhi[7]));
+            // this stage has been read: its next run goes there
+            if (p + nst < np) load_run(k0 + nst * RW_PASS, mine + stage);
+            // ---- mask, softmax
+            bf16x8 pf[NRB][EXACT ? 3 : 1];
+            const bool masked = k0 + RW_RUN - 1 > first_lim;
+#pragma unroll
+            for (int x = 0; x < NRB; ++x) {
+                if (masked) {
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (k0 + 16 * kb + 4 * g4 + i > lim[x]) S[x][kb][i] = -__builtin_inff();
+                }
+                float mx = fmaxf(fmaxf(fmaxf(S[x][0][0], S[x][0][1]), fmaxf(S[x][0][2], S[x][0][3])),
+                                 fmaxf(fmaxf(S[x][1][0], S[x][1][1]), fmaxf(S[x][1][2], S[x][1][3])));
+                mx = groups_max(mx) * a.c;
+                const bool moves = mx > m_ref[x] + RESCALE_TAU;    // each row for itself
+                if (__any(moves)) {
+                    const float m_new = moves ? mx : m_ref[x];
+                    const float mu = (m_new == -__builtin_inff()) ? 0.f : m_new;
+                    const float alpha = moves ? fast_exp2(m_ref[x] - mu) : 1.f;   // m_ref = -inf gives 0
+                    m_ref[x] = m_new;
+                    m_use[x] = mu;
+                    lsum[x] *= alpha;
+#pragma unroll
+                    for (int b = 0; b < C::NC; ++b) o[x][b] *= alpha;
+                }
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (k0 + 16 * kb + 4 * g4 + i > lim[x]) S[x][kb][i] = -__builtin_inff();
+                    for (int i = 0; i < 4; ++i) {
+                        const float p = fast_exp2(__builtin_fmaf(S[x][kb][i], a.c, -m_use[x]));
+                        lsum[x] += p;
+                        const __bf16 hi = (__bf16)p;
+                        pf[x][0][4 * kb + i] = hi;
+                        if constexpr (EXACT) {
+                            const float r1 = p - (float)hi;
+                            const __bf16 mid = (__bf16)r1;
+                            pf[x][1][4 * kb + i] = mid;
+                            pf[x][2][4 * kb + i] = (__bf16)(r1 - (float)mid);
+                        }
+                    }
             }
-            float mx = fmaxf(fmaxf(fmaxf(S[x][0][0], S[x][0][1]), fmaxf(S[x][0][2], S[x][0][3])),
-                             fmaxf(fmaxf(S[x][1][0], S[x][1][1]), fmaxf(S[x][1][2], S[x][1][3])));
-            mx = groups_max(mx) * a.c;
-            const bool moves = mx > m_ref[x] + RESCALE_TAU;    // each row for itself
-            if (__any(moves)) {
-                const float m_new = moves ? mx : m_ref[x];
-                const float mu = (m_new == -__builtin_inff()) ? 0.f : m_new;
-                const float alpha = moves ? fast_exp2(m_ref[x] - mu) : 1.f;   // m_ref = -inf gives 0
-                m_ref[x] = m_new;
-                m_use[x] = mu;
-                lsum[x] *= alpha;
+            // ---- O^T += V^T.P^T
+            if constexpr (CAREFUL) {
 #pragma unroll
-                for (int b = 0; b < C::NC; ++b) o[x][b] *= alpha;
-            }
+                for (int x = 0; x < NRB; ++x) {
+                    const int last = max(min(lim[x] - k0, RW_RUN - 1), -1);    // last key of the run that the row sees, -1: none
+#pragma nounroll
+                    for (int end = 0; end < RW_RUN; ++end) {
+                        if (!__any(last == end)) continue;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                        for (int b = 0; b < C::NC; ++b) {
+                            asm volatile("" : "+v"(vlo[b]), "+v"(vhi[b]));     // not unpacked for all blocks ahead of the loop
+                            const bf16x8 v = __builtin_shufflevector(vlo[b], vhi[b], 0, 1, 2, 3, 4, 5, 6, 7);
+                            u32x4 vis = __builtin_bit_cast(u32x4, v), fin;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float p = fast_exp2(__builtin_fmaf(S[x][kb][i], a.c, -m_use[x]));
-                    lsum[x] += p;
-                    const __bf16 hi = (__bf16)p;
-                    pf[x][0][4 * kb + i] = hi;
-                    if constexpr (EXACT) {
-                        const float r1 = p - (float)hi;
-                        const __bf16 mid = (__bf16)r1;
-                        pf[x][1][4 * kb + i] = mid;
-                        pf[x][2][4 * kb + i] = (__bf16)(r1 - (float)mid);
+                            for (int e = 0; e < 4; ++e) {      // elements 2e and 2e + 1: two consecutive keys
+                                const int key = 4 * g4 + (e < 2 ? 2 * e : 2 * e + 12);
+                                vis[e] &= key + 1 <= end ? ~0u : (key <= end ? 0xffffu : 0u);
+                                const uint32_t inf = 0x7f80u;
+                                fin[e] = vis[e] & (((vis[e] & inf) == inf ? 0u : 0xffffu) | (((vis[e] >> 16) & inf) == inf ? 0u : 0xffff0000u));
+                            }
+                            f32x4 sum = mfma16(as_bf16x8(vis), pf[x][0], o[x][b]);
+#pragma unroll
+                            for (int term = 1; term < (EXACT ? 3 : 1); ++term) sum = mfma16(as_bf16x8(fin), pf[x][term], sum);
+                            if (last == end) o[x][b] = sum;
+                            __builtin_amdgcn_sched_barrier(0); // one block at a time: fewer registers
+                        }
                     }
                 }
+            } else {
+#pragma unroll
+                for (int b = 0; b < C::NC; ++b) {
+                    const bf16x8 vf = __builtin_shufflevector(vlo[b], vhi[b], 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+                    for (int term = 0; term < (EXACT ? 3 : 1); ++term)
+#pragma unroll
+                        for (int x = 0; x < NRB; ++x) o[x][b] = mfma16(vf, pf[x][term], o[x][b]);
+                }
+            }
         }
-        // ---- O^T += V^T.P^T
+    };
+    sweep(std::false_type{});
+    if constexpr (EXACT) {
+        float z = 0.f;
 #pragma unroll
-        for (int b = 0; b < C::NC; ++b) {
-            const bf16x8 vf = __builtin_shufflevector(vlo[b], vhi[b], 0, 1, 2, 3, 4, 5, 6, 7);
+        for (int x = 0; x < NRB; ++x)
 #pragma unroll
-            for (int term = 0; term < (EXACT ? 3 : 1); ++term)
+            for (int b = 0; b < C::NC; ++b)
 #pragma unroll
-                for (int x = 0; x < NRB; ++x) o[x][b] = mfma16(vf, pf[x][term], o[x][b]);
+                for (int i = 0; i < 4; ++i) z = __builtin_fmaf(o[x][b][i], 0.f, z);
+        if (__builtin_expect(__any(z != 0.f), 0)) {
+            load_first();
+            sweep(std::true_type{});
         }
     }
 
