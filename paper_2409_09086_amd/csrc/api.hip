@@ -4,6 +4,7 @@
 #include "../../include/infmllm.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -84,6 +85,7 @@ struct infmllm_stream {
     float* Wb;           // [Hkv][cap]
     FwdScratch fwd;      // scratch of the row-split scoring launch
     float* dec_part;     // partials of the decoding step (plain-arithmetic kernels)
+    int dec_pieces = 1, dec_keys = 0;   // see Layout
     RowsScratch rows{nullptr, nullptr, nullptr, 0};   // partials of attention launches with a cut key range (bf16 on the matrix cores)
     // optional per-kernel timing: one event pair per kernel per step, up to prof_cap steps
     std::vector<hipEvent_t> prof_ev;   // [prof_cap][INFMLLM_K_COUNT][2]
@@ -110,9 +112,11 @@ struct infmllm_stream {
     bool f32() const { return dtype == INFMLLM_FP32; }
 
     struct Layout {
-        size_t K, V, pos, score, rank, row, lse, Wb, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, dec_part, rows_o,
-            rows_ml, rows_arrived, K_rot, kc_rot, q_rot, rope_tab, total;
+        size_t K, V, pos, score, rank, row, lse, Wb, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, rows_arrived, K_rot,
+            kc_rot, q_rot, rope_tab, rows_o, rows_ml, dec_part, total;
         long rows_cap;
+        int dec_pieces;      // most pieces a decoding launch may cut the keys into
+        int dec_keys;        // keys of a piece (on the matrix cores)
     };
     Layout layout() const
     {
@@ -134,27 +138,32 @@ struct infmllm_stream {
         L.mv_x = off; off += ml;
         L.mv_score = off; off += ml;
         L.mv_count = off; off += up((size_t)g.Hkv * 4);
-        // row-split scoring: partial column sums and arrival counters.  fp32 streams score without it, and every chunk
-        // attention runs without partials, only slower: a lean workspace leaves both out.
+        // row-split scoring: partial column sums and arrival counters (fp32 streams score without as well, only slower)
         L.score_part = off; off += up(mfma() || (f32() && !lean) ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
-        L.dec_part = off; off += up(g.max_decode > 0 && !mfma() ? (size_t)g.Hq * DECODE_MAX_SPLIT * (g.d + 2) * 4 + (size_t)g.Hkv * 4 : 0);
-        // (query row, piece) pairs of a launch with a cut key range: at most ROWS_MAX_PARTS, at least one token's
-        L.rows_cap = 0;
-        if (mfma()) {
-            const long most = (long)g.Hq * std::max(g.max_chunk, g.max_decode) * ((g.cap + 127) / 128);
-            const int ksd = rows_decode_keys_per_piece(g);
-            L.rows_cap = std::max(lean ? 0L : std::min(most, ROWS_MAX_PARTS), (long)g.Hq * ((g.B + g.max_decode + ksd - 1) / ksd));
-        } else if (f32() && !lean) {
-            L.rows_cap = std::min((long)g.Hq * g.max_chunk * ((g.cap + 127) / 128), ROWS_MAX_PARTS);
-        }
-        L.rows_o = off; off += up((size_t)L.rows_cap * g.d * 4);
-        L.rows_ml = off; off += up((size_t)L.rows_cap * 8);
         L.rows_arrived = off; off += up(mfma() ? (size_t)g.Hkv * 4 : 0);
         const bool rope = rope_base > 0.0;
         L.K_rot = off; off += rope ? kv : 0;
         L.kc_rot = off; off += up(rope ? (size_t)g.max_chunk * g.Hkv * g.d * g.elt : 0);
         L.q_rot = off; off += up(rope ? (size_t)g.max_chunk * g.Hq * g.d * g.elt : 0);
         L.rope_tab = off; off += up(rope ? (size_t)g.cap * (g.d / 2) * 2 * sizeof(double) : 0);
+        // Partials of launches whose key range is cut.  Nothing needs them, launches with uncut ranges are only slower: a
+        // lean workspace has none for chunks.
+        const size_t part = (size_t)g.Hq * (g.d + 2) * 4;      // of a piece, every head's
+        L.rows_cap = 0;
+        L.dec_pieces = 1;
+        if (mfma()) {
+            L.dec_pieces = rows_decode_pieces(g, L.dec_keys = rows_decode_keys_per_piece(g, INT_MAX));
+            if (L.dec_pieces > 1) L.rows_cap = (long)g.Hq * L.dec_pieces;
+        } else {
+            L.dec_pieces = lean && g.max_decode == 0 ? 1 : decode_pieces(g);
+        }
+        // (query row, piece) pairs of a chunk's launch: at most ROWS_MAX_PARTS
+        if (!lean && (mfma() || f32()))
+            L.rows_cap = std::max(L.rows_cap, std::min((long)g.Hq * std::max(g.max_chunk, mfma() ? g.max_decode : 0) * ((g.cap + 127) / 128),
+                                                       ROWS_MAX_PARTS));
+        L.rows_o = off; off += up((size_t)L.rows_cap * g.d * 4);
+        L.rows_ml = off; off += up((size_t)L.rows_cap * 8);
+        L.dec_part = off; off += up(!mfma() && L.dec_pieces > 1 ? part * L.dec_pieces + (size_t)g.Hkv * 4 : 0);
         L.total = off;
         return L;
     }
@@ -292,12 +301,14 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     s->mv.max = s->g.max_chunk + s->g.max_decode;
     s->lse = (float*)(base + L.lse);
     s->Wb = (float*)(base + L.Wb);
-    s->fwd.score_part = L.dec_part > L.score_part ? (float*)(base + L.score_part) : nullptr;
+    s->fwd.score_part = L.rows_arrived > L.score_part ? (float*)(base + L.score_part) : nullptr;
     s->dec_part = (float*)(base + L.dec_part);
     s->rows.o = (float*)(base + L.rows_o);
     s->rows.ml = (float2*)(base + L.rows_ml);
     s->rows.arrived = (int*)(base + L.rows_arrived);
     s->rows.cap_rows = L.rows_cap;
+    s->dec_pieces = L.dec_pieces;
+    s->dec_keys = L.dec_keys;
     s->K_rot = base + L.K_rot;
     s->kc_rot = base + L.kc_rot;
     s->q_rot = base + L.q_rot;
@@ -642,8 +653,8 @@ static int decode_some(infmllm_stream* s, const void* q, const void* k, const vo
         k = s->kc_rot;
         s->rot_rows = t + T;
     }
-    e = s->mfma() ? launch_rows_decode(s->g, att, q, k, v, t, T, s->streamed, out, s->rows, s->st)
-                  : launch_decode(s->g, att, q, k, v, t, s->streamed, out, s->dec_part, DECODE_MAX_SPLIT, s->st);
+    e = s->mfma() ? launch_rows_decode(s->g, att, q, k, v, t, T, s->streamed, s->dec_keys, out, s->rows, s->st)
+                  : launch_decode(s->g, att, q, k, v, t, s->streamed, out, s->dec_part, s->dec_pieces, s->st);
     if (e != hipSuccess) return fail_hip(e, "decode");
     s->mark(INFMLLM_K_DECODE, 1);
     s->len += T;
@@ -658,8 +669,11 @@ static int decode_tokens_per_launch(const infmllm_stream* s, int left)
     if (!s->mfma()) return 1;
     int T = left < DECODE_MAX_TOKENS ? left : DECODE_MAX_TOKENS;
     if (s->rope_base > 0.0 && T > s->g.max_chunk) T = s->g.max_chunk;      // what the turned copies hold
-    const int ks = rows_decode_keys_per_piece(s->g);
-    while (T > 1 && (long)s->g.Hq * T * ((s->len + T + ks - 1) / ks) > s->rows.cap_rows) --T;
+    auto fits = [&]() {
+        const long pieces = ((long)s->len + T + s->dec_keys - 1) / s->dec_keys;
+        return (pieces == 1 || s->g.Hq * T * pieces <= s->rows.cap_rows) && (long)T * s->g.G * s->g.G < (1l << 32);   // rows_token
+    };
+    while (T > 1 && !fits()) --T;
     return T;
 }
 

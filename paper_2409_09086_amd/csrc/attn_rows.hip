@@ -376,20 +376,20 @@ hipError_t launch_rows_d(const RowsArgs& args, int nrb, const AppendJob& ap, hip
 
 }  // namespace
 
-int rows_decode_keys_per_piece(const Geometry& g)
+int rows_decode_keys_per_piece(const Geometry& g, int most)
 {
     // A function of the stream's geometry alone (see EXACT above): a whole number of runs, about 192 workgroups with
     // the cache at its fullest, a merge of at most sixteen pieces, and at least one run per wavefront.  Measured at 32 x 128
     // heads and 2048 + 48 rows: 13.2 us per token with 256 keys per piece, 11.8 with 288 (256 workgroups), 10.9 with 352
     // (192), 10.6 with 384, 11.6 with 576 (128); 4096 rows: 20.7 with 288, 17.1 with 544, 16.4 with 704 (192), 17.0 with
     // 1408; 8 kv-heads and 4096 rows: 12.3 with 256, 12.0 with 288, 13.3 with 704.
-    const int pieces = std::max(1, std::min(192 / g.Hkv, RW_CLASSES));
+    const int pieces = std::max(1, std::min({192 / g.Hkv, RW_CLASSES, most}));
     const int ks = ((g.B + g.max_decode + pieces - 1) / pieces + RW_RUN - 1) / RW_RUN * RW_RUN;
     return ks < 256 ? 256 : ks;
 }
 
 hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void* q, const void* k, const void* v, int t,
-                              int T, int64_t pos, void* out, const RowsScratch& sc, hipStream_t st)
+                              int T, int64_t pos, int keys, void* out, const RowsScratch& sc, hipStream_t st)
 {
     RowsArgs a{};
     a.q = (const uint16_t*)q; a.K = (uint16_t*)c.K; a.V = (uint16_t*)c.V;
@@ -397,10 +397,10 @@ hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void*
     a.part_o = sc.o; a.part_ml = sc.ml;
     a.pos = c.pos; a.score = c.score; a.rank = c.rank; a.row = c.row; a.pos0 = (int)pos;
     a.t = t; a.L = T; a.tc = t; a.Hq = g.Hq; a.Hkv = g.Hkv; a.G = g.G; a.cap = g.cap; a.max_chunk = g.max_chunk;
-    a.ks = rows_decode_keys_per_piece(g);
+    a.ks = keys;
     a.nsplit = (t + T + a.ks - 1) / a.ks;
     a.c = (float)(g.scale * (double)LOG2E);
-    if ((long)g.Hq * T * a.nsplit > sc.cap_rows) return hipErrorInvalidValue;
+    if (a.nsplit > 1 && (long)g.Hq * T * a.nsplit > sc.cap_rows) return hipErrorInvalidValue;
     const int M = T * g.G, nrb = M <= 16 ? 1 : 2;
     a.arrived = M <= 16 && M * a.nsplit <= RW_TICKET_PARTS ? sc.arrived : nullptr;
     if (g.d == 128) return launch_rows_d<128, true>(a, nrb, AppendJob{}, st);

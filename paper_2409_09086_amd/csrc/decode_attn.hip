@@ -11,6 +11,8 @@
 // so the step is one launch; the partials travel through agent-scope stores and loads, which go
 // through to memory, so no cache has to be flushed.  The token's own k, v are read from the
 // caller's tensors and written to cache row t by the workgroup that owns the last piece.
+#include <algorithm>
+
 #include "launch.h"
 
 namespace infmllm {
@@ -90,6 +92,18 @@ decode_partial_kernel(const T* __restrict__ q, const T* __restrict__ knew, const
     const T* Kh = K + (size_t)h * cap * D;
     const T* Vh = V + (size_t)h * cap * D;
 
+    auto append = [&]() {                              // the token's own row becomes cache row t
+        if (tid < LPR) {
+            *(raw*)(K + ((size_t)h * cap + t) * D + tid * VEC) = *(const raw*)(knew + (size_t)h * D + tid * VEC);
+            *(raw*)(V + ((size_t)h * cap + t) * D + tid * VEC) = *(const raw*)(vnew + (size_t)h * D + tid * VEC);
+        }
+        if (tid == 0) {
+            pos[(size_t)h * cap + t] = pos_new;
+            score[(size_t)h * cap + t] = __builtin_inff();
+            rank[(size_t)h * cap + t] = t;                     // the newest token, in the first free physical row
+            row[(size_t)h * cap + t] = t;
+        }
+    };
     for (int g0 = 0; g0 < G; g0 += NG) {               // G is a multiple of NG
         float qv[NG][VEC];
 #pragma unroll
@@ -141,6 +155,7 @@ decode_partial_kernel(const T* __restrict__ q, const T* __restrict__ knew, const
                 }
             }
         }
+        if (nsplit == 1 && g0 == 0) append();              // before the output, which may be stored over knew or vnew
         // merge the row slots of the workgroup
         __syncthreads();
 #pragma unroll
@@ -161,6 +176,10 @@ decode_partial_kernel(const T* __restrict__ q, const T* __restrict__ knew, const
                 lt += w * s_l[s][gg];
                 ot += w * s_o[s][gg][x];
             }
+            if (nsplit == 1) {                              // nothing to merge
+                out[(size_t)(h * G + g0 + gg) * D + x] = VT::from_float(ot / lt);
+                continue;
+            }
             // The partials are read by whichever workgroup of this kv-head finishes last, possibly on another
             // XCD with its own L2: they are written with agent-scope stores, which go through to memory.
             float* pp = part + ((size_t)(h * G + g0 + gg) * nsplit + sp) * (D + 2);
@@ -171,19 +190,8 @@ decode_partial_kernel(const T* __restrict__ q, const T* __restrict__ knew, const
             }
         }
     }
-    // the token's own row becomes cache row t
-    if (sp == nsplit - 1) {
-        if (tid < LPR) {
-            *(raw*)(K + ((size_t)h * cap + t) * D + tid * VEC) = *(const raw*)(knew + (size_t)h * D + tid * VEC);
-            *(raw*)(V + ((size_t)h * cap + t) * D + tid * VEC) = *(const raw*)(vnew + (size_t)h * D + tid * VEC);
-        }
-        if (tid == 0) {
-            pos[(size_t)h * cap + t] = pos_new;
-            score[(size_t)h * cap + t] = __builtin_inff();
-            rank[(size_t)h * cap + t] = t;                     // the newest token, in the first free physical row
-            row[(size_t)h * cap + t] = t;
-        }
-    }
+    if (nsplit == 1) return;
+    if (sp == nsplit - 1) append();
     // The workgroup of this kv-head that arrives last merges the splits: every workgroup waits until its own
     // partials have been written through, then takes a ticket.  No workgroup waits for another one.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -229,14 +237,15 @@ decode_partial_kernel(const T* __restrict__ q, const T* __restrict__ knew, const
 
 }  // namespace
 
+// One workgroup per CU (more only add partials to merge) of at least 256 keys each: two passes of its row slots.
+static int pieces_of(const Geometry& g, int n) { return std::min({256 / g.Hkv, n / 256, DECODE_MAX_SPLIT}); }
+
+int decode_pieces(const Geometry& g) { return std::max(1, pieces_of(g, g.B + g.max_decode)); }
+
 hipError_t launch_decode(const Geometry& g, const CacheView& c, const void* q, const void* k, const void* v, int t,
                          int64_t T, void* out, float* part, int max_split, hipStream_t st)
 {
-    const int n = t + 1;
-    int nsplit = 256 / g.Hkv;                           // one workgroup per CU (more only add partials to merge) ...
-    if (nsplit > n / 256) nsplit = n / 256;             // ... of at least 256 keys each: two passes of its row slots
-    if (nsplit > max_split) nsplit = max_split;
-    if (nsplit < 1) nsplit = 1;
+    const int nsplit = std::max(1, std::min(pieces_of(g, t + 1), max_split));
     const float cc = (float)(g.scale * 1.4426950408889634);
     int* arrived = (int*)(part + (size_t)g.Hq * max_split * (g.d + 2));   // one ticket counter per kv-head, zero between launches
     const dim3 grid(nsplit, g.Hkv);

@@ -131,10 +131,13 @@ hipError_t launch_attn_mfma64(const Geometry& g, const CacheView& c, const KeySo
 constexpr long ROWS_MAX_PARTS = 16384;
 constexpr int DECODE_MAX_TOKENS = 64;    // most tokens a launch decodes
 // Decoding on bf16 MFMA: T tokens in one launch (and a merging one where there are many rows); the tokens' keys and
-// values become cache rows t .. t+T-1 (stream positions pos ..).  Needs Hq * T * pieces <= sc.cap_rows.
-int rows_decode_keys_per_piece(const Geometry& g);
+// values become cache rows t .. t+T-1 (stream positions pos ..).  Needs Hq * T * pieces <= sc.cap_rows unless there is one piece.
+// `keys` per piece, a constant of the stream; rows_decode_keys_per_piece proposes one that makes at most `most` pieces of the
+// fullest cache.
+int rows_decode_keys_per_piece(const Geometry& g, int most);
+inline int rows_decode_pieces(const Geometry& g, int keys) { return (g.B + g.max_decode + keys - 1) / keys; }
 hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void* q, const void* k, const void* v, int t,
-                              int T, int64_t pos, void* out, const RowsScratch& sc, hipStream_t st);
+                              int T, int64_t pos, int keys, void* out, const RowsScratch& sc, hipStream_t st);
 // Chunk attention (a2) with few query rows, the key range cut into pieces of plan.keys keys, workgroups of 16 * plan.nrb
 // query rows.  rows_chunk_plan fills the plan in and returns the time it should take, in us.
 struct RowsPlan { int nrb, keys; };
@@ -204,9 +207,11 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 
 // Decoding step in plain fp32 arithmetic (fp32 streams, bf16 ones with the plain-arithmetic override): appends the
 // token's k, v as cache row t and attends all t + 1 keys with q (one
-// row per query head).  part is scratch of [Hq][max_split][d + 2] floats followed by Hkv ints that are zero
-// between launches (ticket counters; the last workgroup of a kv-head to finish merges its splits).
+// row per query head).  The keys are cut into at most max_split pieces (decode_pieces: what the fullest cache is worth).  With
+// max_split > 1 part is scratch of [Hq][max_split][d + 2] floats followed by Hkv ints that are zero
+// between launches (ticket counters; the last workgroup of a kv-head to finish merges its splits), else it is not used.
 constexpr int DECODE_MAX_SPLIT = 64;
+int decode_pieces(const Geometry& g);
 hipError_t launch_decode(const Geometry& g, const CacheView& c, const void* q, const void* k, const void* v, int t,
                          int64_t T, void* out, float* part, int max_split, hipStream_t st);
 
