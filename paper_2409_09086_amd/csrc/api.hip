@@ -147,15 +147,23 @@ struct infmllm_stream {
         L.q_rot = off; off += up(rope ? (size_t)g.max_chunk * g.Hq * g.d * g.elt : 0);
         L.rope_tab = off; off += up(rope ? (size_t)g.cap * (g.d / 2) * 2 * sizeof(double) : 0);
         // Partials of launches whose key range is cut.  Nothing needs them, launches with uncut ranges are only slower: a
-        // lean workspace has none for chunks.
+        // lean workspace has none for chunks, and for decoding as many pieces as the rest of the library's array takes.
+        const size_t room = !lean ? SIZE_MAX : off < INFMLLM_STATIC_WORKSPACE_BYTES ? INFMLLM_STATIC_WORKSPACE_BYTES - off : 0;
         const size_t part = (size_t)g.Hq * (g.d + 2) * 4;      // of a piece, every head's
+        auto fits = [&](int pieces) {
+            const size_t most = room < 3 * ALIGN + (size_t)g.Hkv * 4 ? 0 : (room - 3 * ALIGN - (size_t)g.Hkv * 4) / part;
+            return most < (size_t)pieces ? (int)most : pieces;
+        };
         L.rows_cap = 0;
         L.dec_pieces = 1;
         if (mfma()) {
             L.dec_pieces = rows_decode_pieces(g, L.dec_keys = rows_decode_keys_per_piece(g, INT_MAX));
+            const int can = fits(L.dec_pieces);
+            if (can < L.dec_pieces) L.dec_pieces = rows_decode_pieces(g, L.dec_keys = rows_decode_keys_per_piece(g, std::max(can, 1)));
             if (L.dec_pieces > 1) L.rows_cap = (long)g.Hq * L.dec_pieces;
         } else {
-            L.dec_pieces = lean && g.max_decode == 0 ? 1 : decode_pieces(g);
+            // one more than one only with the tickets behind the partials
+            L.dec_pieces = std::max(1, fits(decode_pieces(g)));
         }
         // (query row, piece) pairs of a chunk's launch: at most ROWS_MAX_PARTS
         if (!lean && (mfma() || f32()))

@@ -142,3 +142,26 @@ def test_step_argument_checks_after_attach():
     assert L.infmllm_stream_import(h, None, None, None, 17, 17) == B.EINVAL
     assert L.infmllm_stream_len(h) == 0
     L.infmllm_stream_destroy(h)
+
+
+@pytest.mark.parametrize("heads,kv,d,dtype", [(32, 8, 128, B.BF16), (64, 1, 128, B.BF16), (512, 1, 128, B.BF16),
+                                              (32, 32, 64, B.BF16), (4, 4, 128, B.FP32), (8, 1, 64, B.FP32)])
+def test_static_workspace_takes_every_stream_whose_cache_and_tables_fit(heads, kv, d, dtype):
+    """Scratch that launches can do without is not a reason to refuse a stream: accepted as far as the device call, which
+    fails here if there is no GPU."""
+    up = lambda x: (x + 255) // 256 * 256
+    elt = 4 if dtype == B.FP32 else 2
+
+    def need(b):                               # see largest_static_budget in test_gpu_decode_scratch.py
+        rows = b + 16
+        return (2 * up((kv * rows + 256) * d * elt) + 5 * up(kv * rows * 4) + up(heads * 16 * 4) + 4 * up(kv * 16 * 4) +
+                up(kv * 4) + up(kv * b * 4) + (up(512 * 257 * 4) if elt == 2 else 0))
+    budget = max(b for b in range(1, 131072 - 16) if need(b) <= 64 << 20)
+    if elt == 4:
+        budget = min(budget, 38400 - 16)       # what fp32 streams are limited to
+    L = B.lib()
+    rc, h = make(budget, 0, heads, kv, d, dtype)
+    assert rc == B.OK and L.infmllm_stream_set_param(h, B.PARAM_MAX_CHUNK, 16.0) == B.OK
+    rc = L.infmllm_stream_attach_static(h, None)
+    assert rc in (B.OK, B.EHIP), B.last_error()
+    L.infmllm_stream_destroy(h)

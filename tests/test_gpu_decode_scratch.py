@@ -45,3 +45,43 @@ def test_decoding_below_the_budget_without_max_decode(dtype, impl, heads, kv, d,
     assert (tail == 0xA5).all()
 
 
+
+
+def largest_static_budget(heads, kv, d, elt, max_chunk):
+    """Largest budget whose cache, tables, move lists, scores, one index list and (bf16) row-split scoring sums, max_decode =
+    0, fit the library's array."""
+    up = lambda x: (x + 255) // 256 * 256
+
+    def need(b):
+        rows = b + max_chunk
+        return (2 * up((kv * rows + 256) * d * elt) + 5 * up(kv * rows * 4) + up(heads * max_chunk * 4) + 4 * up(kv * max_chunk * 4) +
+                up(kv * 4) + up(kv * b * 4) + (up(512 * 257 * 4) if elt == 2 else 0))
+    return max(b for b in range(1, 131072 - max_chunk) if need(b) <= 64 << 20)
+
+
+@pytest.mark.parametrize("dtype,heads,kv,d", [
+    ("fp32", 4, 4, 128),                      # partials for three pieces fit
+    ("bf16", 64, 1, 128),                     # for fourteen of sixteen
+    ("bf16", 512, 1, 128),                    # for none: one piece
+    ("bf16", 32, 8, 128),
+])
+def test_streams_that_fill_the_static_workspace_decode(dtype, heads, kv, d):
+    """Such a stream is accepted, and its tokens are those of a twin with a workspace of its own, whose keys are cut
+    otherwise, to the rounding of an output (2^-8, both sides) and of sums of weights that add up to 1 (2e-5)."""
+    budget = largest_static_budget(heads, kv, d, 4 if dtype == "fp32" else 2, 16)
+    a, b = (B.Stream(budget, budget // 4, heads, kv, d, dtype=DT[dtype], max_chunk=16, static_workspace=x) for x in (True, False))
+    g = torch.Generator(device="cuda").manual_seed(31)
+    K, V = (torch.randn((kv, budget - 10, d), generator=g, device="cuda").to(a.dtype) for _ in range(2))
+    pos = torch.arange(budget - 10, dtype=torch.int32, device="cuda").repeat(kv, 1).contiguous()
+    for s in (a, b):
+        s.load(K, V, pos, budget - 10)
+    print("full static workspace", (dtype, heads, kv, d, budget), flush=True)
+    for call, n in enumerate((1, 9)):
+        x = [y.cuda() for y in random_chunk(4430 + call, n, heads, kv, d, dtype)]
+        assert torch.allclose(a.decode_n(*x).double(), b.decode_n(*x).double(), rtol=2.0 ** -7 if dtype == "bf16" else 0, atol=2e-5)
+    for x, y in zip(a.export(), b.export()):
+        assert torch.equal(x, y)
+    x = [y.cuda() for y in random_chunk(4440, 16, heads, kv, d, dtype)]
+    assert torch.allclose(a.step(*x)[0].double(), b.step(*x)[0].double(), rtol=2.0 ** -6 if dtype == "bf16" else 0, atol=2e-4)
+    torch.cuda.synchronize()
+    a.close()
