@@ -88,11 +88,11 @@ attn_f32_kernel(RowsArgsT<float> a, AppendJob ap)
             wait_loads<0>();
             f32x4 kf[NJ], vf[4][VP];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) kf[j] = rw_read_f32x4<0>(kaddr[j]);
+            for (int j = 0; j < NJ; ++j) kf[j] = rw_read_f32x4<0, CAREFUL>(kaddr[j]);
             static_for<0, 4>([&](auto I) {
                 constexpr int i = decltype(I)::value;
 #pragma unroll
-                for (int x = 0; x < VP; ++x) vf[i][x] = rw_read_f32x4<i * ROWB>(vaddr[x]);
+                for (int x = 0; x < VP; ++x) vf[i][x] = rw_read_f32x4<i * ROWB, CAREFUL>(vaddr[x]);
             });
             // reads return in order: K has arrived when only the V reads are outstanding
             asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]) : "n"(4 * VP));

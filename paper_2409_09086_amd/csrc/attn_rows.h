@@ -113,28 +113,28 @@ __device__ __forceinline__ float lanes_max(float x)
 
 // LDS reads as statements of their own: the compiler, which cannot tell one buffer from the other, would wait for
 // every direct load in flight before each read it knows of.  They are waited for by hand, and the registers are
-// first touched after that wait.
-template <int OFF>
+// first touched after that wait, which only holds where the compiler has no reason to move or spill them in between; WAITED:
+// elsewhere, the wait is part of the read.
+template <int OFF, bool WAITED = false>
 __device__ __forceinline__ bf16x4 rw_read_tr16(uint32_t addr)
 {
     bf16x4 v;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+    if constexpr (WAITED) asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr), "n"(OFF));
+    else asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
     return v;
 }
-template <int OFF>
-__device__ __forceinline__ bf16x8 rw_read_b128(uint32_t addr)
+template <typename V, int OFF, bool WAITED>
+__device__ __forceinline__ V rw_read16(uint32_t addr)
 {
-    bf16x8 v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+    V v;
+    if constexpr (WAITED) asm volatile("ds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr), "n"(OFF));
+    else asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
     return v;
 }
-template <int OFF>
-__device__ __forceinline__ f32x4 rw_read_f32x4(uint32_t addr)
-{
-    f32x4 v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
+template <int OFF, bool WAITED = false>
+__device__ __forceinline__ bf16x8 rw_read_b128(uint32_t addr) { return rw_read16<bf16x8, OFF, WAITED>(addr); }
+template <int OFF, bool WAITED = false>
+__device__ __forceinline__ f32x4 rw_read_f32x4(uint32_t addr) { return rw_read16<f32x4, OFF, WAITED>(addr); }
 template <int N>
 __device__ __forceinline__ void wait_loads()       // all but the N newest
 {

@@ -33,7 +33,7 @@ namespace infmllm {
 namespace {
 
 template <int D, int NRB, bool EXACT, bool APPEND>
-__global__ void __launch_bounds__(RW_NT)
+__global__ void __launch_bounds__(RW_NT, D == 64 ? 4 : 2)       // head_dim 64: two workgroups per CU (CAREFUL spills then)
 attn_rows_kernel(RowsArgs a, AppendJob ap)
 {
     using C = RowsCfg<D, NRB>;
@@ -123,13 +123,13 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
             bf16x4 vlo[C::NC], vhi[C::NC];
 #pragma unroll
             for (int s = 0; s < C::NS; ++s) {
-                kf[0][s] = rw_read_b128<0>(kaddr[s] + stage);
-                kf[1][s] = rw_read_b128<16 * C::ROWB>(kaddr[s] + stage);
+                kf[0][s] = rw_read_b128<0, CAREFUL>(kaddr[s] + stage);
+                kf[1][s] = rw_read_b128<16 * C::ROWB, CAREFUL>(kaddr[s] + stage);
             }
 #pragma unroll
             for (int b = 0; b < C::NC; ++b) {
-                vlo[b] = rw_read_tr16<0>(vaddr[b] + stage);
-                vhi[b] = rw_read_tr16<16 * C::ROWB>(vaddr[b] + stage);
+                vlo[b] = rw_read_tr16<0, CAREFUL>(vaddr[b] + stage);
+                vhi[b] = rw_read_tr16<16 * C::ROWB, CAREFUL>(vaddr[b] + stage);
             }
             // reads return in order: K has arrived when at most the V reads are outstanding (the counter ends at 15)
             asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(kf[0][0]), "+v"(kf[1][0]), "+v"(kf[0][1]), "+v"(kf[1][1])
@@ -200,18 +200,13 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
                             pf[x][2][4 * kb + i] = (__bf16)(r1 - (float)mid);
                         }
                     }
-            }
-            // ---- O^T += V^T.P^T
-            if constexpr (CAREFUL) {
-#pragma unroll
-                for (int x = 0; x < NRB; ++x) {
+                if constexpr (CAREFUL) {                       // ---- O^T += V^T.P^T, see above
                     const int last = max(min(lim[x] - k0, RW_RUN - 1), -1);    // last key of the run that the row sees, -1: none
 #pragma nounroll
                     for (int end = 0; end < RW_RUN; ++end) {
                         if (!__any(last == end)) continue;
 #pragma unroll
                         for (int b = 0; b < C::NC; ++b) {
-                            asm volatile("" : "+v"(vlo[b]), "+v"(vhi[b]));     // not unpacked for all blocks ahead of the loop
                             const bf16x8 v = __builtin_shufflevector(vlo[b], vhi[b], 0, 1, 2, 3, 4, 5, 6, 7);
                             u32x4 vis = __builtin_bit_cast(u32x4, v), fin;
 #pragma unroll
@@ -225,11 +220,12 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
 #pragma unroll
                             for (int term = 1; term < (EXACT ? 3 : 1); ++term) sum = mfma16(as_bf16x8(fin), pf[x][term], sum);
                             if (last == end) o[x][b] = sum;
-                            __builtin_amdgcn_sched_barrier(0); // one block at a time: fewer registers
                         }
                     }
                 }
-            } else {
+            }
+            // ---- O^T += V^T.P^T
+            if constexpr (!CAREFUL) {
 #pragma unroll
                 for (int b = 0; b < C::NC; ++b) {
                     const bf16x8 vf = __builtin_shufflevector(vlo[b], vhi[b], 0, 1, 2, 3, 4, 5, 6, 7);
