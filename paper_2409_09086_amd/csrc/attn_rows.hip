@@ -375,12 +375,19 @@ hipError_t launch_rows_d(const RowsArgs& args, int nrb, const AppendJob& ap, hip
 int rows_decode_keys_per_piece(const Geometry& g, int most)
 {
     // A function of the stream's geometry alone (see EXACT above): a whole number of runs, about 192 workgroups with
-    // the cache at its fullest, a merge of at most sixteen pieces, and at least one run per wavefront.  Measured at 32 x 128
+    // the cache at its fullest, as a rule a merge of at most sixteen pieces, and at least one run per wavefront.  Measured at 32 x 128
     // heads and 2048 + 48 rows: 13.2 us per token with 256 keys per piece, 11.8 with 288 (256 workgroups), 10.9 with 352
     // (192), 10.6 with 384, 11.6 with 576 (128); 4096 rows: 20.7 with 288, 17.1 with 544, 16.4 with 704 (192), 17.0 with
     // 1408; 8 kv-heads and 4096 rows: 12.3 with 256, 12.0 with 288, 13.3 with 704.
-    const int pieces = std::max(1, std::min({192 / g.Hkv, RW_CLASSES, most}));
-    const int ks = ((g.B + g.max_decode + pieces - 1) / pieces + RW_RUN - 1) / RW_RUN * RW_RUN;
+    // Few kv-heads leave CUs without a piece, which long caches show.  Where a token's rows fill a row group four times over at
+    // most, they are cut into up to 64 pieces of 768 keys or more, as long as two row groups of each fit on the chip.  One token
+    // (16 together), us, with sixteen pieces / 32 / 64: 1 kv-head, 1 x 128 heads, 32768 rows 14.9 (27) / 10.7 (21) / 8.7 (28),
+    // 130000 rows 45 (57) / 27 (36) / 18 (35); 4 heads on 1, 130000 rows 47 (68) / 29 (47) / 21 (44); 16 on 4, 32768 rows
+    // 19.2 (28) / 17.1 (28) / 48 pieces 18.0 (46).  Not with more heads to a kv-head: 8 on 1, 32768 rows 18.9 (27) / 16.0 (27),
+    // but 32 on 4, 16384 rows 15.3 (22) and with 21 pieces 15.2 (34).
+    const int rows = g.B + g.max_decode, longs = g.G <= 4 ? std::min({rows / 768, 128 / g.Hkv, 4 * RW_CLASSES}) : 1;
+    const int pieces = std::max(1, std::min(std::max(std::min(192 / g.Hkv, RW_CLASSES), longs), most));
+    const int ks = ((rows + pieces - 1) / pieces + RW_RUN - 1) / RW_RUN * RW_RUN;
     return ks < 256 ? 256 : ks;
 }
 

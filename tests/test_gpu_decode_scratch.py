@@ -85,3 +85,22 @@ def test_streams_that_fill_the_static_workspace_decode(dtype, heads, kv, d):
     assert torch.allclose(a.step(*x)[0].double(), b.step(*x)[0].double(), rtol=2.0 ** -6 if dtype == "bf16" else 0, atol=2e-4)
     torch.cuda.synchronize()
     a.close()
+
+
+@pytest.mark.parametrize("heads,kv,d,budget", [(1, 1, 128, 50000), (4, 1, 64, 20000), (2, 2, 64, 25000), (4, 4, 128, 20000)])
+def test_long_caches_of_few_heads_are_cut_into_more_than_sixteen_pieces(heads, kv, d, budget):
+    """Tokens one by one (a ticketed merge) and together (a merging launch): the same bits, and the oracle's values to a
+    rounding of the output and 2e-5 for the sums (see test_tokens_do_not_depend_on_how_many_share_a_call)."""
+    a, b = (B.Stream(budget, budget // 4, heads, kv, d, dtype=torch.bfloat16, max_chunk=16, max_decode=24) for _ in range(2))
+    ls = LockStep(a, OracleStream(budget, budget // 4, heads, kv, d))
+    load_both(ls, budget, 37)
+    b.load(*a.export()[:3], budget)
+    for call, n in enumerate((1, 6, 17)):
+        print("long cache", (heads, kv, d, budget), "tokens", n, flush=True)
+        x = random_chunk(4450 + call, n, heads, kv, d, "bf16")
+        out = a.decode_n(*(y.cuda() for y in x))
+        one = torch.cat([b.decode(*(y[i:i + 1].contiguous().cuda() for y in x)) for i in range(n)])
+        assert torch.equal(out.view(torch.int16), one.view(torch.int16))
+        ref = np.concatenate([ls.oracle.decode(*(y[i:i + 1].double().numpy() for y in x)) for i in range(n)])
+        err = np.abs(out.double().cpu().numpy() - ref)
+        assert (err <= 2.0 ** -8 * np.abs(ref) + 2e-5).all(), err.max()
