@@ -24,7 +24,10 @@ struct Rows64Cfg {
     static_assert(ROWS * MC * 4 <= STAGE, "the merge reuses the buffers of the tiles");
 };
 
-// APPEND: an instance of its own, the job's arguments would cost the other one registers it does not have
+// The attention has no register left for a share of the append: the first half of the row groups of a launch
+// with APPEND are workgroups that append and nothing else, which costs less than a launch of its own (us, 32 x 128 heads, 400 rows on 3500 keys / 32 on 8,
+// 300 on 2000: shares after the loop, with a spilled register whose reload drained the loads in flight in every pass, 47.2 /
+// 31.9; a launch of its own 48.2 / 34.0; workgroups of its own 45.7 / 30.0).
 template <int D, bool APPEND>
 __global__ void __launch_bounds__(RW_NT)
 attn_rows64_kernel(RowsArgs a, AppendJob ap)
@@ -34,7 +37,13 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
     __shared__ __attribute__((aligned(1024))) char qmem[C::ROWS * C::ROWB];
     __shared__ float s_m[RW_NW][C::ROWS], s_l[RW_NW][C::ROWS];
 
-    const int sp = blockIdx.x, h = blockIdx.y, rg = blockIdx.z;    // piece, kv-head, row group (see attn_rows_kernel)
+    const int sp = blockIdx.x, h = blockIdx.y;                 // piece, kv-head
+    if constexpr (APPEND)
+        if (blockIdx.z < gridDim.z / 2) {
+            append_share(ap, sp + gridDim.x * (h + gridDim.y * blockIdx.z), gridDim.x * gridDim.y * (gridDim.z / 2), threadIdx.x, RW_NT);
+            return;
+        }
+    const int rg = APPEND ? blockIdx.z - gridDim.z / 2 : blockIdx.z;               // row group (see attn_rows_kernel)
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.L * a.G, row0 = rg * C::ROWS, t = a.t;
@@ -190,7 +199,6 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
         products(I1{});
     }
 
-    if constexpr (APPEND) append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
     // ---- merge the wavefronts (see attn_rows_kernel), half of the columns at a time
 #pragma unroll
     for (int x = 0; x < C::NX; ++x) {
@@ -224,8 +232,9 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
 
 void launch_rows64(const RowsArgs& a, const AppendJob& ap, hipStream_t st)
 {
-    const dim3 grid((unsigned)a.nsplit, (unsigned)a.Hkv, (unsigned)((a.L * a.G + Rows64Cfg<128>::ROWS - 1) / Rows64Cfg<128>::ROWS));
-    if (ap.k) hipLaunchKernelGGL((attn_rows64_kernel<128, true>), grid, dim3(RW_NT), 0, st, a, ap);
+    const unsigned groups = (unsigned)((a.L * a.G + Rows64Cfg<128>::ROWS - 1) / Rows64Cfg<128>::ROWS);
+    const dim3 grid((unsigned)a.nsplit, (unsigned)a.Hkv, groups), with_append((unsigned)a.nsplit, (unsigned)a.Hkv, 2 * groups);
+    if (ap.k) hipLaunchKernelGGL((attn_rows64_kernel<128, true>), with_append, dim3(RW_NT), 0, st, a, ap);
     else hipLaunchKernelGGL((attn_rows64_kernel<128, false>), grid, dim3(RW_NT), 0, st, a, ap);
 }
 
