@@ -42,6 +42,9 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb)
     return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
 }
 
+// What the kernels that load directly into LDS, sixteen bytes a lane, take.
+bool aligned16(const void* p) { return (uintptr_t)p % 16 == 0; }
+
 constexpr size_t ALIGN = 256;
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -426,10 +429,10 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
     // writes the chunk into the cache as well.  Where out overwrites the chunk's tensors a step appends first and reads the
     // chunk from the cache: workgroups still read keys and values when others have stored their output, and the placement
     // reads them after the attention.  So does a step that evicts nothing with the position encoding, which turns rows of
-    // the cache.
+    // the cache, and one whose tensors are not aligned for direct loads.
     const bool warm = n <= g.B;
     const size_t kv_bytes = (size_t)L * g.Hkv * g.d * g.elt, out_bytes = (size_t)L * g.Hq * g.d * g.elt;
-    const bool in_place = (mfma || f32) && !(warm && s->rope_base > 0.0) && !overlap(out, out_bytes, k, kv_bytes) &&
+    const bool in_place = (mfma || f32) && aligned16(k) && aligned16(v) && !(warm && s->rope_base > 0.0) && !overlap(out, out_bytes, k, kv_bytes) &&
                           !overlap(out, out_bytes, v, kv_bytes);
     const KeySource ks = in_place ? KeySource{t, k, v} : KeySource{n, nullptr, nullptr};
     AppendJob job{};
@@ -649,18 +652,21 @@ static int decode_some(infmllm_stream* s, const void* q, const void* k, const vo
     const int t = s->len;
     hipError_t e;
     CacheView att = s->cache;
-    if (s->rope_base > 0.0) {
+    const bool rope = s->rope_base > 0.0, in_place = !s->mfma() || (aligned16(k) && aligned16(v));
+    if (rope || !in_place)
+        if ((e = launch_append(append_job(s->g, s->cache, k, v, t, T, s->streamed, nullptr, nullptr), s->st)) != hipSuccess) return fail_hip(e, "decode: append");
+    if (rope) {
         // the tokens' rows enter the cache as given; the decoding kernels see the turned copies (and put the
         // turned keys at rows t.. of K_rot themselves)
-        if ((e = launch_append(append_job(s->g, s->cache, k, v, t, T, s->streamed, nullptr, nullptr), s->st)) != hipSuccess) return fail_hip(e, "decode: append");
-        e = launch_rope(s->g, s->cache.K, s->K_rot, s->cache.rank, s->rot_rows < t ? s->rot_rows : t, t, k, s->kc_rot, q,
-                        s->q_rot, t, T, s->rope_tab, s->st);
+        e = launch_rope(s->g, s->cache.K, s->K_rot, s->cache.rank, s->rot_rows < t ? s->rot_rows : t, in_place ? t : t + T,
+                        in_place ? k : nullptr, s->kc_rot, q, s->q_rot, t, T, s->rope_tab, s->st);
         if (e != hipSuccess) return fail_hip(e, "decode: position encoding");
         att.K = s->K_rot;
         q = s->q_rot;
         k = s->kc_rot;
         s->rot_rows = t + T;
     }
+    if (!in_place) k = v = nullptr;                            // they are in the cache
     e = s->mfma() ? launch_rows_decode(s->g, att, q, k, v, t, T, s->streamed, s->dec_keys, out, s->rows, s->st)
                   : launch_decode(s->g, att, q, k, v, t, s->streamed, out, s->dec_part, s->dec_pieces, s->st);
     if (e != hipSuccess) return fail_hip(e, "decode");

@@ -825,7 +825,8 @@ hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySour
                             : wgs2 >= 140 ? rounds * (10.f + 0.0148f * (float)n)
                                           : rounds * (9.f + 0.0096f * (float)n) * (1.f + 0.15f * fill);
         RowsPlan plan{};
-        if (rows_chunk_plan(g, n, L, sc.cap_rows, plan) < other) return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, plan, ap, st);
+        const int max_nrb = (uintptr_t)q % 16 == 0 ? 4 : 2;      // with 64 rows the queries are loaded directly into LDS
+        if (rows_chunk_plan(g, n, L, sc.cap_rows, max_nrb, plan) < other) return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, plan, ap, st);
     }
     if (g.d == 64) return launch_fwd_cfg<64, 4, 1, 2>(g, c, ks, q, t, L, out, lse, ap, st);
     // 128 query rows x 64 keys per wavefront-tile is the efficient shape; when that grid would cover

@@ -398,8 +398,8 @@ hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void*
     a.q = (const uint16_t*)q; a.K = (uint16_t*)c.K; a.V = (uint16_t*)c.V;
     a.kc = (const uint16_t*)k; a.vc = (const uint16_t*)v; a.out = (uint16_t*)out; a.lse = nullptr;
     a.part_o = sc.o; a.part_ml = sc.ml;
-    a.pos = c.pos; a.score = c.score; a.rank = c.rank; a.row = c.row; a.pos0 = (int)pos;
-    a.t = t; a.L = T; a.tc = t; a.Hq = g.Hq; a.Hkv = g.Hkv; a.G = g.G; a.cap = g.cap; a.max_chunk = g.max_chunk;
+    a.pos = k ? c.pos : nullptr; a.score = c.score; a.rank = c.rank; a.row = c.row; a.pos0 = (int)pos;
+    a.t = t; a.L = T; a.tc = k ? t : t + T; a.Hq = g.Hq; a.Hkv = g.Hkv; a.G = g.G; a.cap = g.cap; a.max_chunk = g.max_chunk;
     a.ks = keys;
     a.nsplit = (t + T + a.ks - 1) / a.ks;
     a.c = (float)(g.scale * (double)LOG2E);
@@ -419,7 +419,7 @@ hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void*
 // 34.1 / 34.0; 512 workgroups, 4512 keys 63.7 / 63.3; four pieces, 256 workgroups, 8064 keys 25.2 / 25.0; 64 rows,
 // 256 workgroups, 4608 keys 51.7 / 49.3, 2560 keys 36.6 / 34.3; at head_dim 64 rows of 64 gain nothing over 32: 24.9 and
 // 24.8 us for 32 heads, 512 rows, 2560 keys.)
-float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, RowsPlan& plan)
+float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, int max_nrb, RowsPlan& plan)
 {
     struct Cost { float fixed, more_rounds, pass; };
     static constexpr Cost COST[2][3] = {{{6.5f, 1.f, 0.66f}, {8.7f, 1.f, 0.85f}, {}},                      // head_dim 64: 16, 32 rows
@@ -428,6 +428,7 @@ float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, RowsPlan& 
     float best = 1e30f;
     for (int i = 0; i < (g.d == 128 ? 3 : 2); ++i) {
         const int nrb = 1 << i;
+        if (nrb > max_nrb) break;
         const Cost& c = COST[g.d == 128][i];
         const long units = (long)g.Hkv * ((L * g.G + 16 * nrb - 1) / (16 * nrb));       // workgroups per piece
         const long most = std::min<long>(std::min<long>(256 / units, (n + 255) / 256), cap_rows / ((long)g.Hq * L));

@@ -132,6 +132,7 @@ constexpr long ROWS_MAX_PARTS = 16384;
 constexpr int DECODE_MAX_TOKENS = 64;    // most tokens a launch decodes
 // Decoding on bf16 MFMA: T tokens in one launch (and a merging one where there are many rows); the tokens' keys and
 // values become cache rows t .. t+T-1 (stream positions pos ..).  Needs Hq * T * pieces <= sc.cap_rows unless there is one piece.
+// k, v null: the tokens are in the cache already.
 // `keys` per piece, a constant of the stream; rows_decode_keys_per_piece proposes one that makes at most `most` pieces of the
 // fullest cache.
 int rows_decode_keys_per_piece(const Geometry& g, int most);
@@ -139,9 +140,9 @@ inline int rows_decode_pieces(const Geometry& g, int keys) { return (g.B + g.max
 hipError_t launch_rows_decode(const Geometry& g, const CacheView& c, const void* q, const void* k, const void* v, int t,
                               int T, int64_t pos, int keys, void* out, const RowsScratch& sc, hipStream_t st);
 // Chunk attention (a2) with few query rows, the key range cut into pieces of plan.keys keys, workgroups of 16 * plan.nrb
-// query rows.  rows_chunk_plan fills the plan in and returns the time it should take, in us.
+// query rows, nrb <= max_nrb.  rows_chunk_plan fills the plan in and returns the time it should take, in us.
 struct RowsPlan { int nrb, keys; };
-float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, RowsPlan& plan);
+float rows_chunk_plan(const Geometry& g, int n, int L, long cap_rows, int max_nrb, RowsPlan& plan);
 hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
                              void* out, float* lse, const RowsScratch& sc, const RowsPlan& plan, const AppendJob& ap,
                              hipStream_t st);
