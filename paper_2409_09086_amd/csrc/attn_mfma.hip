@@ -863,10 +863,16 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
     const float dstep = (float)(g.bias / (double)cnd);
     const float* carry = g.policy == POLICY_CUMULATIVE ? c.score : nullptr;
     // Few scored rows, or few columns whose rows then are shared out: score_once, as long as the slices of a launch fit
-    // into one round of two workgroups per CU.
+    // into one round of two workgroups per CU (which is also what the scratch holds), and those of five to eight blocks (at
+    // head_dim 128 twelve), where score_kernel needs no slices or few, into one per CU.  Time of score_once over that of score_kernel,
+    // 400 shapes of 1 to 32 kv-heads, groups of 1 to 32, 700 to 16384 columns, head_dim 128 / 64: one slice, up to 2048 workgroups
+    // 0.58 to 1.07 / 0.40 to 0.99; two slices, up to 256 workgroups 0.88 to 1.04 / 0.89 to 1.03, 257 to 512 workgroups 1.06 to
+    // 1.23 / 1.00 to 1.16; three, up to 256 at most 0.91, 257 to 512 0.97 to 1.08 / 0.90 to 1.00; more, up to 512 0.44 to 0.85 /
+    // 0.79 to 1.13.  In us at 8 x 128 heads, 8192 columns, 256 rows 15.5 / 12.9, 16 heads on 4, 4096 columns, 256 rows 17.2 / 20.4.
     const int blocks = g.G * ((lq + 31) / 32), nslice = blocks > ONCE_BLOCKS ? (blocks + ONCE_BLOCKS - 1) / ONCE_BLOCKS : 1;
     const long once_wgs = (long)((ncol + 255) / 256) * g.Hkv * nslice;
-    if (nslice == 1 || (sc.score_part && once_wgs <= SCORE_SPLIT_WGS)) {
+    const int most_wgs = nslice == 2 || (nslice == 3 && g.d == 128) ? 256 : SCORE_SPLIT_WGS;
+    if (nslice == 1 || (sc.score_part && once_wgs <= most_wgs)) {
         const int nxb = (ncol + 255) / 256;
 #define INFMLLM_ONCE(DD)                                                                                                   \
     hipLaunchKernelGGL(score_once_kernel<DD>, dim3((unsigned)once_wgs), dim3(512), 0, st, (const uint16_t*)q,                  \
