@@ -297,10 +297,13 @@ hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySourc
     a.t = t; a.L = L; a.tc = ks.rows; a.Hq = g.Hq; a.Hkv = g.Hkv; a.G = g.G; a.cap = g.cap; a.max_chunk = g.max_chunk;
     a.inv_g = rows_inv_g(L, g.G);
     a.c = (float)g.scale;
-    // Pieces: as many as keep the chip's 256 CUs busy, of at least three passes (below that the merging launch costs more
-    // than the passes it takes away).
+    // Pieces: as many as keep the chip's 256 CUs busy, of at least two passes.  Attention of evicting steps, us, with pieces of at
+    // least one pass / two / three / four: 8 x 128 heads, 256 rows on 1280 keys 26.2 / 25.4 / 25.1 / 24.9, 64 on 664 15.5 /
+    // 18.9 / 21.7 / 22.0, 16 on 3016 16.6 / 18.6 / 20.5 / 24.5; 8 on 2, 64 on 1564 17.6 / 18.2 / 19.4 / 21.6; 4 x 64 heads, 64 on
+    // 1064 12.3 / 12.7 / 15.5 / 15.4, but 64 on 320 11.2 / 10.4 / 10.2 / 10.4: there the merging launch costs more than the
+    // passes it takes away.
     const int n = t + L, units = g.Hkv * ((L * g.G + 15) / 16);
-    const long most = std::min<long>(std::min(256 / units, n / (3 * F32_PASS)), sc.cap_rows / ((long)g.Hq * L));
+    const long most = std::min<long>(std::min(256 / units, n / (2 * F32_PASS)), sc.cap_rows / ((long)g.Hq * L));
     const int pieces = (int)std::max<long>(1, std::min<long>(most, RW_CLASSES));
     a.ks = ((n + pieces - 1) / pieces + F32_RUN - 1) / F32_RUN * F32_RUN;
     a.nsplit = (n + a.ks - 1) / a.ks;
