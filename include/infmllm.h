@@ -291,6 +291,15 @@ enum {
 };
 
 /*
+ * Debug/test: the kernel that an infmllm_step of `tokens` tokens on `cached` cached rows launches for its attention
+ * (which = INFMLLM_K_ATTN), scoring (INFMLLM_K_SCORE) and placement (INFMLLM_K_COMPACT), or an infmllm_decode_n for
+ * its tokens (INFMLLM_K_DECODE); "" if it launches none (a step that evicts nothing; a placement that the selection
+ * takes along).  Host-only, and the stream need not be attached.  The names are the library's own and may change; they hold
+ * for tensors aligned to 16 bytes that do not overlap.  Null for arguments no such call can have.
+ */
+const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cached, int tokens);
+
+/*
  * Measurement: brackets every kernel of the next max_steps steps with HIP events on the
  * attached stream (max_steps = 0 switches this off and releases the events).  The events cost
  * a few microseconds per step, so whole-step throughput is measured with profiling off.

@@ -24,7 +24,7 @@ EXPORTS = [
     "infmllm_stream_last_scores", "infmllm_last_error", "infmllm_stream_destroy",
     "infmllm_stream_profile", "infmllm_stream_profile_read", "infmllm_decode", "infmllm_decode_n", "infmllm_stream_max_len",
     "infmllm_step_attend", "infmllm_stream_pending", "infmllm_evict_batched", "infmllm_stream_profile_select",
-    "infmllm_stream_attach_static",
+    "infmllm_stream_attach_static", "infmllm_stream_kernel",
 ]
 STATIC_WORKSPACE_BYTES = 64 << 20
 KERNELS = ["append", "attn", "score", "select", "compact", "decode", "rope", "evict"]
@@ -69,6 +69,8 @@ def lib():
         L.infmllm_stream_profile.argtypes = [P, I]
         L.infmllm_stream_profile_select.argtypes = [P, ctypes.c_uint]
         L.infmllm_stream_profile_read.argtypes = [P, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(I)]
+        L.infmllm_stream_kernel.argtypes = [P, I, I, I]
+        L.infmllm_stream_kernel.restype = ctypes.c_char_p
         L.infmllm_last_error.restype = ctypes.c_char_p
         L.infmllm_stream_destroy.argtypes = [P]
         L.infmllm_stream_destroy.restype = None
@@ -266,6 +268,11 @@ class Stream:
         cnt = (ctypes.c_int * len(KERNELS))()
         _check(lib().infmllm_stream_profile_read(self._h, ms, cnt))
         return {k: (float(ms[i]), int(cnt[i])) for i, k in enumerate(KERNELS)}
+
+    def kernel(self, name, cached, tokens):
+        """infmllm_stream_kernel for an interval of KERNELS: the kernel a call of `tokens` tokens launches for it, "" if none."""
+        k = lib().infmllm_stream_kernel(self._h, KERNELS.index(name), int(cached), int(tokens))
+        return None if k is None else k.decode()
 
     def last_scores(self):
         """Biased scores W' [kv_heads, c] of the most recent evicting step, or None."""

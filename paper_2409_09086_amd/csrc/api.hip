@@ -787,6 +787,31 @@ int infmllm_stream_import(infmllm_stream_t* s, const void* K, const void* V, con
     return INFMLLM_OK;
 }
 
+const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cached, int tokens)
+{
+    if (!s || cached < 0 || cached > s->g.B + s->g.max_decode || tokens < 1) return nullptr;
+    const Geometry& g = s->g;
+    const int n = cached + tokens;
+    const bool evicts = n > g.B, ranks_by_age = g.policy == POLICY_WINDOW || g.policy == POLICY_INITIAL_RECENT;
+    switch (which) {
+        case INFMLLM_K_ATTN:
+            if (tokens > g.max_chunk) return nullptr;
+            return s->mfma() ? attn_mfma_kernel(g, n, tokens, s->attached ? s->rows.cap_rows : s->layout().rows_cap) : s->f32() ? "attn_f32" : "attn_simple";
+        case INFMLLM_K_SCORE:
+            if (tokens > g.max_chunk) return nullptr;
+            if (!evicts || n <= g.R) return "";
+            if (ranks_by_age) return "rank_score";
+            return s->mfma() ? score_mfma_kernel(g, std::max(cached, n - g.R), std::min(g.R, tokens)) : s->f32() ? "score_f32" : "score_simple";
+        case INFMLLM_K_COMPACT: {
+            if (tokens > g.max_chunk) return nullptr;
+            const int in_cache = s->mfma() || s->f32() ? cached : n;
+            return evicts && !place_in_select(g, (n - in_cache) + std::max(in_cache - g.B, 0)) ? "place" : "";
+        }
+        case INFMLLM_K_DECODE: return s->mfma() ? "attn_rows" : "decode";
+        default: return nullptr;
+    }
+}
+
 int infmllm_stream_last_scores(infmllm_stream_t* s, float* w, int* n_candidates)
 {
     if (!s || !n_candidates) return fail(INFMLLM_EINVAL, "last_scores: null argument");

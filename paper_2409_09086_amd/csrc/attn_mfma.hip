@@ -808,27 +808,35 @@ hipError_t launch_fwd_cfg(const Geometry& g, const CacheView& c, const KeySource
     return hipGetLastError();
 }
 
-hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                            void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st)
+namespace {
+
+// tile: 0 = attn_rows or attn_rows64 with `rows`, 1..5 as INFMLLM_PARAM_ATTN_TILE, 6 = attn_fwd at head_dim 64
+struct AttnPlan {
+    int tile;
+    RowsPlan rows;
+};
+AttnPlan attn_plan(const Geometry& g, int n, int L, long cap_rows, bool q_aligned)
 {
-    if (g.d != 64 && g.d != 128) return hipErrorInvalidValue;
+    AttnPlan p{};
     if (g.attn_tile == 0 && (long)L * g.G <= (1 << 20) && (long)L * g.G * g.G < (1l << 32)) {   // what its grid and rows_token take
         // Few query rows: attn_rows, which cuts the key range over the workgroups.  Examples, measured, attn_rows against
         // the kernels below: 32 x 128 heads, 4096 keys: 24 / 49 us with 37 rows, 22 / 50 with 64; 16 heads on 4 of 128,
         // 5000 keys, 320 rows: 37 / 61; 8 x 64 heads, 4000 keys, 320 rows: 19 / 72.  The time of the kernels below, fitted
         // to measurements like that of rows_chunk_plan: per round of workgroups over the 256 CUs, and the more the
         // fuller the chip; at head_dim 64 several workgroups share a CU.
-        const int n = t + L, wgs = g.d == 128 ? g.Hq * ((L + 63) / 64) : g.Hq * ((L + 127) / 128);
+        const int wgs = g.d == 128 ? g.Hq * ((L + 63) / 64) : g.Hq * ((L + 127) / 128);
         const int wgs2 = g.Hq * ((L + 31) / 32) / 4;             // of 128 rows, head_dim 128 (see below)
         const float rounds = (float)(((g.d == 128 && wgs2 >= 140 ? wgs2 : wgs) + 255) / 256), fill = wgs < 256 ? (float)wgs / 256.f : 1.f;
         const float other = g.d == 64 ? (7.f + 0.0136f * (float)n) * (1.f + 0.35f * (rounds - 1.f))
                             : wgs2 >= 140 ? rounds * (10.f + 0.0148f * (float)n)
                                           : rounds * (9.f + 0.0096f * (float)n) * (1.f + 0.15f * fill);
-        RowsPlan plan{};
-        const int max_nrb = (uintptr_t)q % 16 == 0 ? 4 : 2;      // with 64 rows the queries are loaded directly into LDS
-        if (rows_chunk_plan(g, n, L, sc.cap_rows, max_nrb, plan) < other) return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, plan, ap, st);
+        // with 64 rows the queries are loaded directly into LDS
+        if (rows_chunk_plan(g, n, L, cap_rows, q_aligned ? 4 : 2, p.rows) < other) return p;
     }
-    if (g.d == 64) return launch_fwd_cfg<64, 4, 1, 2>(g, c, ks, q, t, L, out, lse, ap, st);
+    if (g.d == 64) {
+        p.tile = 6;
+        return p;
+    }
     // 128 query rows x 64 keys per wavefront-tile is the efficient shape; when that grid would cover
     // only about half of the chip (128 workgroups at 32 heads x 512 rows), 64-row workgroups with four
     // key ways inside the workgroup are faster.  g.attn_tile > 0 (a test hook) forces one shape.
@@ -839,8 +847,25 @@ hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySour
     const int wgs64 = (g.Hq * ((L + 63) / 64) + 3) / 4;
     const int rounds64 = (wgs64 + 255) / 256;
     const bool fills = wgs64 * 5 >= rounds64 * 256 * 4;
-    const int v = g.attn_tile > 0 ? g.attn_tile : (fills && t + L >= 1024 ? 5 : (wgs128 >= 140 ? 1 : 2));
-    switch (v) {
+    p.tile = g.attn_tile > 0 ? g.attn_tile : (fills && n >= 1024 ? 5 : (wgs128 >= 140 ? 1 : 2));
+    return p;
+}
+
+}  // namespace
+
+const char* attn_mfma_kernel(const Geometry& g, int n, int L, long cap_rows)
+{
+    const AttnPlan p = attn_plan(g, n, L, cap_rows, true);
+    return p.tile == 0 ? (p.rows.nrb == 4 ? "attn_rows64" : "attn_rows") : p.tile == 5 ? "attn_fwd64" : "attn_fwd";
+}
+
+hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
+                            void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st)
+{
+    if (g.d != 64 && g.d != 128) return hipErrorInvalidValue;
+    const AttnPlan p = attn_plan(g, t + L, L, sc.cap_rows, (uintptr_t)q % 16 == 0);
+    switch (p.tile) {
+        case 0: return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, p.rows, ap, st);
         case 5: {
             // no share of the job here: the kernel has its SIMDs to itself and no register to spare
             const hipError_t e = ap.k ? launch_append(ap, st) : hipSuccess;
@@ -849,19 +874,19 @@ hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySour
         case 1: return launch_fwd_cfg<128, 4, 2, 2>(g, c, ks, q, t, L, out, lse, ap, st);
         case 2: return launch_fwd_cfg<128, 2, 4, 1>(g, c, ks, q, t, L, out, lse, ap, st);
         case 3: return launch_fwd_cfg<128, 4, 2, 1>(g, c, ks, q, t, L, out, lse, ap, st);
-        default: return launch_fwd_cfg<128, 4, 1, 2>(g, c, ks, q, t, L, out, lse, ap, st);
+        case 4: return launch_fwd_cfg<128, 4, 1, 2>(g, c, ks, q, t, L, out, lse, ap, st);
+        default: return launch_fwd_cfg<64, 4, 1, 2>(g, c, ks, q, t, L, out, lse, ap, st);
     }
 }
 
-hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q,
-                             const float* lse, const FwdScratch& sc, int t, int L, float* Wb, hipStream_t st)
+namespace {
+
+struct ScorePlan {
+    bool once, wide;           // score_once; score_kernel with 512 columns per workgroup (head_dim 128)
+    int nxb, split;            // column blocks, slices of the scored rows
+};
+ScorePlan score_plan(const Geometry& g, int ncol, int lq, bool has_part)
 {
-    const int n = t + L, cnd = n - g.R, lq = g.R < L ? g.R : L;
-    if (cnd <= 0) return hipSuccess;
-    const int ncol = ks.rows > cnd ? ks.rows : cnd;          // every cached row, and the chunk rows below cnd
-    const float cc = (float)(g.scale * (double)LOG2E);
-    const float dstep = (float)(g.bias / (double)cnd);
-    const float* carry = g.policy == POLICY_CUMULATIVE ? c.score : nullptr;
     // Few scored rows, or few columns whose rows then are shared out: score_once, as long as the slices of a launch fit
     // into one round of two workgroups per CU (which is also what the scratch holds), and those of five to eight blocks (at
     // head_dim 128 twelve), where score_kernel needs no slices or few, into one per CU.  Time of score_once over that of score_kernel,
@@ -872,18 +897,7 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
     const int blocks = g.G * ((lq + 31) / 32), nslice = blocks > ONCE_BLOCKS ? (blocks + ONCE_BLOCKS - 1) / ONCE_BLOCKS : 1;
     const long once_wgs = (long)((ncol + 255) / 256) * g.Hkv * nslice;
     const int most_wgs = nslice == 2 || (nslice == 3 && g.d == 128) ? 256 : SCORE_SPLIT_WGS;
-    if (nslice == 1 || (sc.score_part && once_wgs <= most_wgs)) {
-        const int nxb = (ncol + 255) / 256;
-#define INFMLLM_ONCE(DD)                                                                                                   \
-    hipLaunchKernelGGL(score_once_kernel<DD>, dim3((unsigned)once_wgs), dim3(512), 0, st, (const uint16_t*)q,                  \
-                       (const uint16_t*)c.K, (const uint16_t*)ks.k, ks.rows, lse, carry, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, \
-                       g.cap, g.max_chunk, cnd, ncol, nxb, cc, dstep, nslice, sc.score_part)
-        if (g.d == 128) INFMLLM_ONCE(128);
-        else if (g.d == 64) INFMLLM_ONCE(64);
-        else return hipErrorInvalidValue;
-#undef INFMLLM_ONCE
-        return hipGetLastError();
-    }
+    if (nslice == 1 || (has_part && once_wgs <= most_wgs)) return ScorePlan{true, false, (ncol + 255) / 256, nslice};
     // 512 columns per workgroup (256 at head_dim 64, where the wider variant runs out of registers).  Where
     // that leaves CUs without one, the scored rows of a column block are shared out over up to four workgroups
     // (whose sums the last to finish adds up); where there are too few rows for that, a workgroup takes 256 columns.
@@ -897,17 +911,48 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
         rsplit = (int)(256 / wgsw);
         if (rsplit > 4) rsplit = 4;
         if (rsplit > niter / 2) rsplit = niter / 2;
-        if (rsplit < 1 || !sc.score_part || wgsw * rsplit * (wcols / 256) > SCORE_SPLIT_WGS) rsplit = 1;
+        if (rsplit < 1 || !has_part || wgsw * rsplit * (wcols / 256) > SCORE_SPLIT_WGS) rsplit = 1;
     }
     const bool wide = wgsw >= 200 || rsplit > 1;
-    const int nxb = wide ? nxw : (ncol + 255) / 256;
-    const dim3 grid(nxb * g.Hkv * rsplit), block(512);
+    return ScorePlan{false, wide, wide ? nxw : (ncol + 255) / 256, rsplit};
+}
+
+}  // namespace
+
+const char* score_mfma_kernel(const Geometry& g, int ncol, int lq)
+{
+    const ScorePlan p = score_plan(g, ncol, lq, true);
+    return p.once ? (p.split > 1 ? "score_once, sliced" : "score_once") : p.split > 1 ? "score_kernel, sliced" : "score_kernel";
+}
+
+hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q,
+                             const float* lse, const FwdScratch& sc, int t, int L, float* Wb, hipStream_t st)
+{
+    const int n = t + L, cnd = n - g.R, lq = g.R < L ? g.R : L;
+    if (cnd <= 0) return hipSuccess;
+    const int ncol = ks.rows > cnd ? ks.rows : cnd;          // every cached row, and the chunk rows below cnd
+    const float cc = (float)(g.scale * (double)LOG2E);
+    const float dstep = (float)(g.bias / (double)cnd);
+    const float* carry = g.policy == POLICY_CUMULATIVE ? c.score : nullptr;
+    const ScorePlan p = score_plan(g, ncol, lq, sc.score_part != nullptr);
+    if (p.once) {
+#define INFMLLM_ONCE(DD)                                                                                                   \
+    hipLaunchKernelGGL(score_once_kernel<DD>, dim3((unsigned)(p.nxb * g.Hkv * p.split)), dim3(512), 0, st, (const uint16_t*)q,                  \
+                       (const uint16_t*)c.K, (const uint16_t*)ks.k, ks.rows, lse, carry, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, \
+                       g.cap, g.max_chunk, cnd, ncol, p.nxb, cc, dstep, p.split, sc.score_part)
+        if (g.d == 128) INFMLLM_ONCE(128);
+        else if (g.d == 64) INFMLLM_ONCE(64);
+        else return hipErrorInvalidValue;
+#undef INFMLLM_ONCE
+        return hipGetLastError();
+    }
+    const dim3 grid(p.nxb * g.Hkv * p.split), block(512);
 #define INFMLLM_SCORE(DD, CB)                                                                              \
     hipLaunchKernelGGL((score_kernel<DD, CB>), grid, block, 0, st, (const uint16_t*)q, (const uint16_t*)c.K, \
                        (const uint16_t*)ks.k, ks.rows, lse,                                                  \
                        carry, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, g.cap, g.max_chunk,                        \
-                       cnd, ncol, nxb, cc, dstep, rsplit, sc.score_part)
-    if (g.d == 128 && wide) INFMLLM_SCORE(128, 2);
+                       cnd, ncol, p.nxb, cc, dstep, p.split, sc.score_part)
+    if (g.d == 128 && p.wide) INFMLLM_SCORE(128, 2);
     else if (g.d == 128) INFMLLM_SCORE(128, 1);
     else if (g.d == 64) INFMLLM_SCORE(64, 1);
     else return hipErrorInvalidValue;

@@ -117,6 +117,9 @@ struct RowsScratch {
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
                             void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st);
 
+// Which kernel that is for a chunk of L rows that makes n keys (tensors aligned to 16 bytes).
+const char* attn_mfma_kernel(const Geometry& g, int n, int L, long cap_rows);
+
 // a2 and a3+a4 of fp32 streams, on the fp32 matrix cores; lse is the natural log-sum-exp.
 hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
                            void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st);
@@ -150,6 +153,9 @@ hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySou
 // a3+a4 on bf16 MFMA (bf16 streams only).
 hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q,
                              const float* lse, const FwdScratch& sc, int t, int L, float* Wb, hipStream_t st);
+
+// Which kernel that is for ncol columns (cached rows, or candidates if they are more) and lq scored rows per head.
+const char* score_mfma_kernel(const Geometry& g, int ncol, int lq);
 
 // a5+a6: user_I[h] = sort_asc(top-r of W'[h][0..cnd)) ++ [cnd, n), in stream-order indices, row stride B.  user_I
 // and user_count may be null.  The same workgroup then plans the

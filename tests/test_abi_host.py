@@ -165,3 +165,35 @@ def test_static_workspace_takes_every_stream_whose_cache_and_tables_fit(heads, k
     rc = L.infmllm_stream_attach_static(h, None)
     assert rc in (B.OK, B.EHIP), B.last_error()
     L.infmllm_stream_destroy(h)
+
+
+def test_kernel_names_on_the_host():
+    """infmllm_stream_kernel: what the launches' rules choose, without a device."""
+    L = B.lib()
+    kernel = lambda h, name, cached, n: L.infmllm_stream_kernel(h, B.KERNELS.index(name), cached, n)
+
+    def stream(chunk, *args, **params):
+        rc, h = make(*args)
+        assert rc == B.OK and L.infmllm_stream_set_param(h, B.PARAM_MAX_CHUNK, float(chunk)) == B.OK
+        for k, v in params.items():
+            assert L.infmllm_stream_set_param(h, getattr(B, "PARAM_" + k), v) == B.OK
+        return h
+    for chunk, args, want in [(512, (2048, 512, 32, 32, 128, B.BF16), (b"attn_rows64", b"score_kernel", b"place")),
+                              (1024, (4096, 1024, 32, 8, 128, B.BF16), (b"attn_fwd", b"score_kernel, sliced", b"place")),
+                              (2048, (8192, 2048, 32, 32, 128, B.BF16), (b"attn_fwd64", b"score_kernel", b"place")),
+                              (37, (4096, 1152, 32, 32, 128, B.BF16), (b"attn_rows", b"score_once", b"")),
+                              (64, (256, 64, 4, 4, 64, B.FP32), (b"attn_f32", b"score_f32", b""))]:
+        h = stream(chunk, *args)
+        assert tuple(kernel(h, n, args[0], chunk) for n in ("attn", "score", "compact")) == want
+        assert kernel(h, "score", 0, 1) == b"" and kernel(h, "compact", 0, 1) == b""        # nothing is evicted
+        assert kernel(h, "attn", args[0], chunk + 1) is None and kernel(h, "attn", args[0] + 1, 1) is None
+        assert kernel(h, "attn", 0, 0) is None and kernel(h, "rope", 0, 1) is None
+        L.infmllm_stream_destroy(h)
+    h = stream(37, 4096, 1152, 32, 32, 128, B.BF16, IMPL=1.0)
+    assert kernel(h, "attn", 4096, 37) == b"attn_simple" and kernel(h, "score", 4096, 37) == b"score_simple"
+    assert kernel(h, "decode", 10, 1) == b"decode"
+    L.infmllm_stream_destroy(h)
+    h = stream(37, 4096, 1152, 32, 32, 128, B.BF16, POLICY=1.0)
+    assert kernel(h, "score", 4096, 37) == b"rank_score"
+    L.infmllm_stream_destroy(h)
+    assert kernel(None, "attn", 0, 1) is None

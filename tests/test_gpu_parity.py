@@ -50,9 +50,9 @@ def test_cfg1_tiny_fp32_stream(bias):
     (4, 2, 128, 96, 32, [150, 40, 150, 1, 97]),                     # chunks longer than the budget: the first step evicts
     (2, 2, 64, 24, 8, [40, 3, 17, 24, 5]),                          # budget below one 32-row tile
     (2, 1, 128, 40, 40, [64, 9]),                                   # r = 0 and chunk > budget
-    (8, 2, 128, 256, 128, [128, 128, 128, 128]),                    # scored rows shared out over 2 workgroups
-    (4, 1, 128, 384, 192, [192, 192, 192, 101, 192]),               # ... over 3
-    (16, 2, 64, 320, 160, [160, 160, 160, 45, 160]),                # ... over 4, uneven shares, ragged last block
+    (8, 2, 128, 256, 128, [128, 128, 128, 128]),                    # scored rows of a group in 4 slices
+    (4, 1, 128, 384, 192, [192, 192, 192, 101, 192]),               # ... in 6
+    (16, 2, 64, 320, 160, [160, 160, 160, 45, 160]),                # ... in 10 and 4, uneven shares, ragged last block
     (32, 32, 128, 640, 128, [576, 608, 576, 530]),                  # full head count, chunks of 9 and 10 row tiles
 ])
 def test_small_bf16_streams(impl, heads, kv, d, budget, recent, chunks):
@@ -259,12 +259,13 @@ def test_sixteen_candidates_per_thread():
 def test_more_scored_rows_than_the_scoring_kernel_keeps_in_lds(d):
     """G * l_q = 8 * 1024 scored rows per kv-head: beyond 4096 the scoring kernel reads each staged row's
     log-sum-exp from memory instead of from its LDS copy."""
-    heads, kv, budget, recent, L = 8, 1, 2048, 1024, 1024
+    heads, kv, budget, recent, L = 8, 1, 4096, 1024, 1024
     ls = pair(budget, recent, heads, kv, d, "bf16", 1e-3, max_chunk=L)
-    for step in range(4):                                          # two warm-up steps, two evicting ones
+    assert ls.gpu.kernel("score", budget, L) == "score_kernel, sliced"
+    for step in range(6):                                          # four warm-up steps, two evicting ones
         print("direct lse d", d, "step", step, flush=True)
         q, k, v = random_chunk(1300 + step, L, heads, kv, d, "bf16")
-        ls.step(q, k, v, check_state=(step == 3))
+        ls.step(q, k, v, check_state=(step == 5))
     print("max err %.3g swaps %d" % (ls.max_err, ls.swaps))
 
 
@@ -302,7 +303,7 @@ def test_scores_reported_match_oracle_scores():
 def test_scores_do_not_depend_on_workgroup_order():
     """Where the scored rows of a column block are shared out over several workgroups, whichever finishes last
     adds the slices up; the slices are added in slice order, so W' is the same bits on every run."""
-    heads, kv, d, budget, recent, L = 16, 2, 64, 320, 160, 160          # four slices per column block
+    heads, kv, d, budget, recent, L = 16, 2, 64, 320, 160, 160          # ten slices per column block
     chunks = [random_chunk(900 + step, L, heads, kv, d, "bf16") for step in range(4)]
     seen = None
     for rep in range(6):
