@@ -282,11 +282,11 @@ enum {
     INFMLLM_K_ATTN = 1,
     INFMLLM_K_SCORE = 2,
     INFMLLM_K_SELECT = 3,
-    INFMLLM_K_COMPACT = 4,
+    INFMLLM_K_COMPACT = 4, /* the placement; no interval in steps whose selection places the rows itself */
     INFMLLM_K_DECODE = 5,
     INFMLLM_K_ROPE = 6,
-    INFMLLM_K_EVICT = 7,  /* not a kernel: from the start of the selection launch to the end of the gather launch of
-                             a step (Alg. 1 l.5-8 as a whole, one event pair instead of two) */
+    INFMLLM_K_EVICT = 7,  /* not a kernel: from the start of the selection launch to the end of the last launch of the
+                             eviction of a step (Alg. 1 l.5-8 as a whole, one event pair instead of two) */
     INFMLLM_K_COUNT = 8
 };
 
@@ -311,7 +311,7 @@ int infmllm_stream_profile(infmllm_stream_t* s, int max_steps);
  * Chooses which of the INFMLLM_K_* intervals get events in the steps recorded from now on: bit k of
  * `kernels` switches interval k on (default: all).  Every event pair delays the stream a little, so a
  * caller who wants the undisturbed duration of one interval records only that one; INFMLLM_K_EVICT
- * alone records two events per step, before the selection launch and after the gather launch.
+ * alone records two events per step, before the selection launch and after the eviction's last launch.
  * Errors: EINVAL (null stream, empty mask or bits beyond INFMLLM_K_COUNT).
  */
 int infmllm_stream_profile_select(infmllm_stream_t* s, unsigned kernels);

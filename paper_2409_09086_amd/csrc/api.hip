@@ -96,11 +96,11 @@ struct infmllm_stream {
     int prof_cap = 0, prof_steps = 0;
 
     unsigned prof_mask = ~0u;          // kernels whose events are recorded (bit INFMLLM_K_*)
-    void mark(int kernel, int edge)
+    // ends: the eviction's last launch (INFMLLM_K_EVICT runs from the start of the selection to there)
+    void mark(int kernel, int edge, bool ends = false)
     {
         if (prof_steps >= prof_cap) return;
-        const bool bracket = ((prof_mask >> INFMLLM_K_EVICT) & 1u) &&
-                             ((kernel == INFMLLM_K_SELECT && edge == 0) || (kernel == INFMLLM_K_COMPACT && edge == 1));
+        const bool bracket = ((prof_mask >> INFMLLM_K_EVICT) & 1u) && ((kernel == INFMLLM_K_SELECT && edge == 0) || ends);
         if (!((prof_mask >> kernel) & 1u) && !bracket) return;
         const size_t slot = (size_t)prof_steps * INFMLLM_K_COUNT + kernel;
         if (hipEventRecord(prof_ev[slot * 2 + edge], st) == hipSuccess) prof_used[slot] |= (char)(1 << edge);
@@ -521,11 +521,12 @@ int infmllm_step(infmllm_stream_t* s, const void* q, const void* k, const void* 
     s->mark(INFMLLM_K_SELECT, 0);
     if ((e = launch_select(g, s->Wb, n, ks.rows, retained, n_retained, s->cache, s->mv, ks, s->streamed, placed, s->st)) != hipSuccess)
         return fail_hip(e, "step: select");
-    s->mark(INFMLLM_K_SELECT, 1);
-    s->mark(INFMLLM_K_COMPACT, 0);
-    if (!placed && (e = launch_place(g, s->cache, ks, s->streamed, s->mv, nmax, s->st)) != hipSuccess)
-        return fail_hip(e, "step: placement");
-    s->mark(INFMLLM_K_COMPACT, 1);
+    s->mark(INFMLLM_K_SELECT, 1, placed);
+    if (!placed) {
+        s->mark(INFMLLM_K_COMPACT, 0);
+        if ((e = launch_place(g, s->cache, ks, s->streamed, s->mv, nmax, s->st)) != hipSuccess) return fail_hip(e, "step: placement");
+        s->mark(INFMLLM_K_COMPACT, 1, true);
+    }
     step_done(s, n, L);
     return INFMLLM_OK;
 }
@@ -583,10 +584,12 @@ int infmllm_evict_batched(infmllm_stream_t* const* streams, int count, int32_t* 
         const bool placed = place_in_select(lead->g, nmax);
         lead->mark(INFMLLM_K_SELECT, 0);
         if ((e = launch_select_batch(lead->g, eb, placed, lead->st)) != hipSuccess) return fail_hip(e, "evict_batched: select");
-        lead->mark(INFMLLM_K_SELECT, 1);
-        lead->mark(INFMLLM_K_COMPACT, 0);
-        if (!placed && (e = launch_place_batch(lead->g, eb, nmax, lead->st)) != hipSuccess) return fail_hip(e, "evict_batched: placement");
-        lead->mark(INFMLLM_K_COMPACT, 1);
+        lead->mark(INFMLLM_K_SELECT, 1, placed);
+        if (!placed) {
+            lead->mark(INFMLLM_K_COMPACT, 0);
+            if ((e = launch_place_batch(lead->g, eb, nmax, lead->st)) != hipSuccess) return fail_hip(e, "evict_batched: placement");
+            lead->mark(INFMLLM_K_COMPACT, 1, true);
+        }
         for (int j = 0; j < eb.count; ++j) step_done(streams[base + j], streams[base + j]->pend_n, streams[base + j]->pend_L);
     }
     return INFMLLM_OK;
@@ -629,7 +632,8 @@ int infmllm_stream_profile_read(infmllm_stream_t* s, float* ms, int* launches)
             const size_t slot = (size_t)step * INFMLLM_K_COUNT + k;
             const bool whole_eviction = (k == INFMLLM_K_EVICT);
             const size_t first = whole_eviction ? (size_t)step * INFMLLM_K_COUNT + INFMLLM_K_SELECT : slot;
-            const size_t last = whole_eviction ? (size_t)step * INFMLLM_K_COUNT + INFMLLM_K_COMPACT : slot;
+            size_t last = whole_eviction ? (size_t)step * INFMLLM_K_COUNT + INFMLLM_K_COMPACT : slot;
+            if (whole_eviction && !(s->prof_used[last] & 2)) last = first;       // the selection placed
             if (!(s->prof_used[first] & 1) || !(s->prof_used[last] & 2)) continue;
             if (!((s->prof_mask >> k) & 1u)) continue;
             hipError_t e = hipEventSynchronize(s->prof_ev[last * 2 + 1]);

@@ -86,3 +86,25 @@ def test_calls_of_more_tokens_than_share_a_launch(heads, kv, d, budget, n, launc
     assert torch.equal(out.view(torch.int16), one.view(torch.int16))
     for x, y in zip(a.export(), b.export()):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("L,placed", [(64, True), (300, False)])
+def test_profile_has_a_placement_interval_only_where_there_is_a_launch(L, placed):
+    heads, kv, d, budget = 4, 4, 128, 600
+    s = B.Stream(budget, 100, heads, kv, d, dtype=torch.bfloat16, max_chunk=300)
+    assert (s.kernel("compact", budget, L) == "") == placed
+    chunks = [[x.cuda() for x in random_chunk(4900 + i, n, heads, kv, d, "bf16")] for i, n in enumerate((300, 300, L))]
+    for c in chunks:
+        s.step(*c)
+    for names in (B.KERNELS, ["evict"], ["select", "evict"], ["compact", "evict"]):
+        s.profile_select(names)
+        s.profile(8)
+        for _ in range(3):
+            s.step(*chunks[2])
+        s.step_attend(*chunks[2])
+        B.evict_batched([s])
+        p = s.profile_read()
+        want = {"select": 4, "compact": 0 if placed else 4, "evict": 4}
+        assert all(p[k][1] == (want[k] if k in names else 0) for k in want), (names, p)
+        if len(names) > 2:
+            assert p["evict"][0] >= p["select"][0] + p["compact"][0] - 1e-3
