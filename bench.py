@@ -24,12 +24,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
-PEAK_FP32_TFLOPS = 157.3       # MI355X fp32 vector
+PEAK_FP32_TFLOPS = 157.3       # MI355X fp32, vector and matrix
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 
 
-def algorithmic_work(cfg, L, t):
-    """Per-launch algorithmic flops/bytes of each kernel in steady state (cache full)."""
+def algorithmic_work(cfg, L, t, placed):
+    """Per-launch algorithmic flops/bytes of each kernel in steady state (cache full).  placed: the selection's launch
+    moves the rows as well, there is none for the placement."""
     n, B, R = t + L, cfg.budget, cfg.recent
     d, Hq, Hkv = cfg.head_dim, cfg.heads, cfg.kv_heads
     elt = 2 if cfg.dtype == "bf16" else 4
@@ -40,18 +41,22 @@ def algorithmic_work(cfg, L, t):
     # rows 0..B-1, i.e. the chunk's survivors.  With L <= R (all five workloads) every chunk row is inside the
     # recent window, so that is exactly L rows per kv-head; the r + R - L retained cached rows stay in place.
     moved = min(L, R)
-    return {
+    work = {
         "attn": {"flops": 4.0 * d * pairs * Hq, "bytes": elt * d * (2 * n * Hkv + 2 * L * Hq)},
         "score": {"flops": 2.0 * d * lq * c * Hq, "bytes": elt * d * (c * Hkv + lq * Hq) + 4 * c * Hkv},
         "append": {"bytes": 2 * (2 * L * Hkv * d * elt) + 8 * L * Hkv},
-        # selection launch: W' read, the index list written twice (stream scratch and the caller's), and the
-        # placement plan: old row table read, rank / new row table / score written for the rows that stay
-        "select": {"bytes": (4 * c + 8 * B + 16 * (B - moved) + 12 * moved) * Hkv},
+        # selection launch: W' read, the index list written, and the placement plan: stream-order index of every
+        # row read, rank / row table / score written for the rows that stay, the move list
+        "select": {"bytes": (4 * c + 8 * B + 12 * (B - moved) + 16 * moved) * Hkv},
         # placement launch: the moved rows' K and V read and written, their table entries
         "compact": {"bytes": (row + 12 + 12) * moved * Hkv, "rows_moved": moved * Hkv},
         # position-encoding pre-pass: every cached key, the chunk's keys and the queries read and written once
         "rope": {"bytes": 2 * elt * d * (n * Hkv + L * Hq)},
     }
+    if placed:                                               # no move list in memory, the moved rows instead
+        del work["compact"]
+        work["select"]["bytes"] = (4 * c + 8 * B + 12 * (B - moved) + (row + 12) * moved) * Hkv
+    return work
 
 
 def read_counters(name):
@@ -135,19 +140,6 @@ def retention_leg(cfg, binding, dev, impl):
             "all_kept_frac": round(float(kept[:, old].mean()), 4)}
 
 
-def attn_kernel_name(cfg, L, mfma):
-    """Which attention kernel the library's launch picks for a workload's shape (the rule of launch_attn_mfma; the cost
-    model of rows_chunk_plan prefers attn_rows and attn_rows64 where 64-row workgroups are one round of the CUs)."""
-    if not mfma:
-        return "attn_f32" if cfg.dtype == "fp32" else "attn_simple"
-    if cfg.kv_heads * -(-L * cfg.heads // cfg.kv_heads // 64) <= 256:
-        return "attn_rows64" if cfg.head_dim == 128 else "attn_rows"
-    wgs64 = (cfg.heads * (-(-L // 64)) + 3) // 4
-    rounds = -(-wgs64 // 256)
-    fills = wgs64 * 5 >= rounds * 256 * 4
-    return "attn_fwd64" if cfg.head_dim == 128 and fills and cfg.budget + L >= 1024 else "attn_fwd"
-
-
 def decode_leg(cfg, binding, chunks, dev, impl, ntok=64):
     """Secondary figure: decoding steps (one token, no eviction) on the same layer with the cache full."""
     import torch
@@ -160,7 +152,8 @@ def decode_leg(cfg, binding, chunks, dev, impl, ntok=64):
     toks = [(q[i:i + 1].contiguous(), k[i:i + 1].contiguous(), v[i:i + 1].contiguous())
             for q, k, v in chunks[:2] for i in range(ntok // 2)]
     out = torch.empty_like(toks[0][0])
-    # the ntok tokens as one infmllm_decode_n call (known tokens: on bf16 matrix cores up to 64 share a sweep of the cache)
+    # the ntok tokens as one infmllm_decode_n call (known tokens: on bf16 matrix cores up to 64 share a launch,
+    # which sweeps the cache once; fewer where the partials of that many do not fit the workspace's scratch)
     qn, kn, vn = [torch.cat([t[j] for t in toks]).contiguous() for j in range(3)]
     outn = torch.empty_like(qn)
     s.decode_n(qn[:8], kn[:8], vn[:8], out=outn[:8])         # untimed: the kernel's first launches
@@ -180,15 +173,22 @@ def decode_leg(cfg, binding, chunks, dev, impl, ntok=64):
         s2.decode(q, k, v, out=out)
     torch.cuda.synchronize()
     ms, cnt = s2.profile_read()["decode"]
-    s2.profile(0)
     us = 1e3 * ms / cnt
+    # ... and the call once more, for the launches it took: each sweeps the cache once
+    for i in range(2):
+        q, k, v = chunks[i % len(chunks)]
+        s2.step(q, k, v, report=False)
+    s2.profile(ntok)
+    s2.decode_n(qn, kn, vn, out=outn)
+    torch.cuda.synchronize()
+    sweeps = s2.profile_read()["decode"][1]
+    s2.profile(0)
     elt = 2 if cfg.dtype == "bf16" else 4
     n_avg = cfg.budget + (ntok + 1) / 2.0
     nbytes = 2 * n_avg * cfg.kv_heads * cfg.head_dim * elt          # every K and V row once
     gbs = nbytes / (us * 1e-6) / 1e9
-    sweeps = -(-ntok // 64) if cfg.dtype == "bf16" and not impl else ntok
     return {"tokens_per_s": round(ntok / elapsed, 1), "us_per_token": round(1e6 * elapsed / ntok, 3),
-            "kernels_us": round(us, 3), "launches": cnt, "call": "infmllm_decode_n, %d tokens per call" % ntok,
+            "kernels_us": round(us, 3), "launches": cnt, "launches_of_the_call": sweeps, "call": "infmllm_decode_n, %d tokens per call" % ntok,
             "hbm_frac_of_the_call": round(sweeps * nbytes / elapsed / 1e9 / PEAK_HBM_GBS, 4),
             "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                          "frac": round(gbs / PEAK_HBM_GBS, 4), "algorithmic_bytes_per_token": nbytes}}
@@ -337,7 +337,7 @@ def measure(cfg, args, binding, dev, steps, nchunks, full):
         latency = {"p50": round(lat[len(lat) // 2], 2), "p99": round(lat[min(len(lat) - 1, int(0.99 * len(lat)))], 2),
                    "max": round(lat[-1], 2), "steps": lat_steps}
 
-    work = algorithmic_work(cfg, L, cfg.budget)
+    work = algorithmic_work(cfg, L, cfg.budget, s.kernel("compact", cfg.budget, L) == "")
     kernels = {}
     for name, (ms, cnt) in prof.items():
         if not cnt:
@@ -355,15 +355,14 @@ def measure(cfg, args, binding, dev, steps, nchunks, full):
     attn = kernels["attn"]
     mfma = cfg.dtype == "bf16" and args.impl != 1
     peak = PEAK_BF16_TFLOPS if mfma else PEAK_FP32_TFLOPS
-    kernel = attn_kernel_name(cfg, L, mfma)
-    ctr = read_counters("%s_%s_pmc.txt" % (kernel if kernel.startswith("attn_rows") else "attn_fwd", cfg.name))
-    roofline = {"kernel": kernel, "bound": "mfma" if mfma else "alu",
+    ctr = read_counters("attn_%s_pmc.txt" % cfg.name)
+    roofline = {"kernel": s.kernel("attn", cfg.budget, L), "bound": "mfma" if mfma or cfg.dtype == "fp32" else "alu",
                 "achieved": attn["tflops"], "peak": peak, "unit": "TFLOP/s", "frac": round(attn["tflops"] / peak, 4),
                 "traffic": ctr["traffic"], "mfma_busy_counter": ctr["mfma_busy"], "counters_from": ctr["source"],
                 "algorithmic_flops_per_launch": work["attn"]["flops"], "avg_us": attn["us"]}
-    # selection + placement as one bracket (start of the selection launch to end of the last eviction launch)
+    # selection + placement as one bracket (start of the selection launch to end of the eviction's last launch)
     evict_us = kernels.get("evict", {}).get("us", 0.0)
-    evict_bytes = work["select"]["bytes"] + work["compact"]["bytes"]
+    evict_bytes = work["select"]["bytes"] + work.get("compact", {"bytes": 0})["bytes"]
     evict = {"bound": "hbm", "achieved": round(evict_bytes / (evict_us * 1e-6) / 1e9, 1) if evict_us else None,
              "peak": PEAK_HBM_GBS, "unit": "GB/s",
              "frac": round(evict_bytes / (evict_us * 1e-6) / 1e9 / PEAK_HBM_GBS, 4) if evict_us else None,
@@ -375,7 +374,7 @@ def measure(cfg, args, binding, dev, steps, nchunks, full):
                    % (cfg.name, cfg.heads, cfg.kv_heads, cfg.head_dim, cfg.budget, cfg.recent, L, cfg.budget + L),
                    "bias": cfg.bias, "seed": cfg.seed, "chunks_in_hbm": nchunks, "policy": args.policy,
                    "rope_base": args.rope, "spinup_ms": args.spinup_ms, "spinup_steps": spin_steps,
-                   "kernels": "mfma" if mfma else "plain"},
+                   "kernels": "mfma" if mfma or cfg.dtype == "fp32" else "plain"},
         "roofline": roofline, "evict_roofline": evict, "kernels": kernels,
     }
     if latency:
