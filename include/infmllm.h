@@ -78,11 +78,13 @@ enum {
                                     (pairs (x[i], x[i + head_dim/2]), angle p * base^(-2i/head_dim)), so
                                     relative distances never exceed the cache size.  Costs one extra pass over
                                     the cached keys per step and workspace for the turned copies     */
-    INFMLLM_PARAM_IMPL = 3,      /* debug/test: 0 (default) = bf16 streams run attention and
-                                    scoring on the matrix cores; 1 = every dtype runs the
-                                    plain fp32-arithmetic kernels (fp32 streams always do)   */
-    INFMLLM_PARAM_ATTN_TILE = 7  /* debug/test, head_dim 128 on the matrix cores: 0 (default) = the
-                                    attention launch picks its workgroup shape from the chunk length;
+    INFMLLM_PARAM_IMPL = 3,      /* debug/test: 0 (default) = attention and scoring run on the matrix cores
+                                    (bf16 products with fp32 sums; fp32 products for fp32 streams);
+                                    1 = bf16 streams run plain fp32-arithmetic kernels, fp32 streams as with 0.
+                                    Decoding: bf16 on the matrix cores with 0, else plain fp32 arithmetic */
+    INFMLLM_PARAM_ATTN_TILE = 7  /* debug/test, bf16 on the matrix cores: 0 (default) = the attention launch picks
+                                    its kernel and workgroup shape from the chunk and cache lengths.  head_dim 64:
+                                    any other value = 128 query rows per workgroup, keys uncut.  head_dim 128:
                                     1 = 128 query rows x 2 key ways x 64 keys, 2 = 64 rows x 4 ways x 32,
                                     3 = 128 rows x 2 ways x 32, 4 = 128 rows x 1 way x 64, 5 = 256 rows with
                                     64 rows per wavefront.  Results are the same up to rounding order  */
@@ -125,7 +127,8 @@ size_t infmllm_stream_workspace_bytes(const infmllm_stream_t* s);
  * an eviction leaves the retained rows where they are and only moves the chunk's survivors into the rows
  * it frees) and per-step temporaries; attach enqueues a clear of the whole workspace on that stream.
  * The cache starts empty.  Errors: EINVAL (null/misaligned workspace; budget + max_decode + max_chunk - recent
- * above 131072, the most candidates a step can rank), ENOMEM (too small), ESTATE (already attached), EHIP.
+ * above 131072, the most candidates a step can rank, or budget + max_decode + max_chunk above 38400 for fp32 streams and
+ * with INFMLLM_PARAM_IMPL = 1), ENOMEM (too small), ESTATE (already attached), EHIP.
  */
 int infmllm_stream_attach(infmllm_stream_t* s, void* dev_workspace, size_t bytes, void* hip_stream);
 
@@ -220,8 +223,8 @@ int infmllm_stream_pending(const infmllm_stream_t* s);
 
 /*
  * Selection, recent-window move and gather (Alg. 1 l.5-8) of `count` streams with a pending
- * eviction, as one selection launch and one gather launch per 16 streams, enqueued on their
- * common HIP stream.  The result for every stream is the one infmllm_step would have produced.
+ * eviction, as one selection launch per 16 streams and one placement launch (none where the rows to move are few:
+ * the selection moves them), enqueued on their common HIP stream.  The result for every stream is the one infmllm_step would have produced.
  *   streams     host array of `count` distinct streams that have the same budget, recent, heads,
  *               kv_heads, head_dim, dtype, max_chunk and max_decode and are attached to the same
  *               HIP stream (their chunk lengths and cached lengths may differ)

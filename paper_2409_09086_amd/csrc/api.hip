@@ -287,8 +287,8 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     if (bytes < L.total)
         return fail(INFMLLM_ENOMEM, "attach: workspace has %zu bytes, %zu needed", bytes, L.total);
     if ((size_t)s->g.cap * 4 > 150 * 1024 && (s->dtype == INFMLLM_FP32 || s->impl == 1))
-        return fail(INFMLLM_EINVAL, "attach: budget + max_chunk = %d rows is beyond what the plain-arithmetic "
-                                    "attention kernel keeps in LDS (38400)", s->g.cap);
+        return fail(INFMLLM_EINVAL, "attach: budget + max_decode + max_chunk = %d rows is beyond the 38400 of fp32 streams and of "
+                                    "the plain-arithmetic override, whose attention kernel keeps a row's logits in LDS", s->g.cap);
     if (s->g.cap - s->g.R > 131072)
         return fail(INFMLLM_EINVAL, "attach: budget + max_decode + max_chunk - recent = %d exceeds the 131072 candidates "
                                     "a step can rank", s->g.cap - s->g.R);

@@ -7,7 +7,9 @@
 //              products: step e of piece j contracts head dimensions {16j + 4g + e} of lane group g, on both operands.
 //              The weights of a run are the B operand of O^T += V^T.P^T as they stand (step i contracts keys 4g + i), and
 //              a lane's 32 bytes of a V row are its operands of D/16 column blocks (block b is columns D/16 * c + b).
-//              Bound: the matrix cores, 2048 cycles per run and wavefront at head_dim 128.
+//              The matrix cores take 2048 cycles per run and wavefront at head_dim 128: busy 45 % of the SIMD-cycles of
+//              a launch of 256 rows on 1280 keys, 8 x 128 heads (21 us, prologue, passes that only some wavefronts have and the
+//              merge of the wavefronts included), 32 % where the cache is filling.
 //   score_f32  column-stationary, as score_kernel (attn_mfma.hip): a wavefront keeps sixteen key columns as B operands,
 //              the scored query rows go through LDS sixteen at a time, and S = Q.K^T leaves a column to a lane, so that a
 //              column's weights are added without leaving it.  Where the columns do not fill the chip, the scored

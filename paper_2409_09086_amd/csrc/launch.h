@@ -26,7 +26,7 @@ struct Geometry {
     double scale; // softmax scale (kernels take it, times log2(e) where they work in base 2, rounded once to float)
     double bias;  // b of Alg. 1 (the ramp step b / c is formed in double and rounded once to float)
     int policy;   // score ranked by the selection: 0 Alg. 1, 1 window, 2 initial + recent, 3 cumulative
-    int attn_tile;// test hook: 0 = the matrix-core attention picks its tile shape, 1..4 = forces one
+    int attn_tile;// test hook: 0 = the matrix-core attention picks its tile shape, 1..5 = forces one
 };
 enum { POLICY_INFMLLM = 0, POLICY_WINDOW = 1, POLICY_INITIAL_RECENT = 2, POLICY_CUMULATIVE = 3 };
 
