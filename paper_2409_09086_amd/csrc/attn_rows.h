@@ -273,18 +273,17 @@ struct RunLoader {
     static constexpr int ROWB = D * (int)sizeof(T), RUN = KEYS * ROWB, NL = RUN / 1024, RPL = 1024 / ROWB;
     typedef Tile<T, D> Swz;
     const T *Kh, *Vh, *kch, *vch;
-    int tc, n, cap, L, crs;                        // crs: row stride of the chunk tensors
+    int tc, n, crs;                                // crs: row stride of the chunk tensors
     int lrow, lpos;                                // this lane's row and slot of a load
     __device__ __forceinline__ RunLoader(const RowsArgsT<T>& a, int h, int lane)
         : Kh(a.K + (size_t)h * a.cap * D), Vh(a.V + (size_t)h * a.cap * D), kch(a.kc + (size_t)h * D), vch(a.vc + (size_t)h * D),
-          tc(a.tc), n(a.t + a.L), cap(a.cap), L(a.L), crs(a.Hkv * D), lrow(lane / (ROWB / 16)), lpos(lane % (ROWB / 16))
+          tc(a.tc), n(a.t + a.L), crs(a.Hkv * D), lrow(lane / (ROWB / 16)), lpos(lane % (ROWB / 16))
     {
     }
     template <bool K, bool V>
     __device__ __forceinline__ void load(int k0, char* dst) const
     {
-        // (past the last key the rows of a warm-up step's cache are read as they are: finite, and masked)
-        const bool in_cache = k0 + KEYS <= (tc == n ? cap : tc), in_chunk = k0 >= tc && k0 + KEYS <= n;
+        const bool in_cache = k0 + KEYS <= tc, in_chunk = k0 >= tc && k0 + KEYS <= n;
         if (in_cache || in_chunk) {                // rows a fixed stride apart
             const int stride = in_cache ? ROWB : crs * (int)sizeof(T), bytes = KEYS * stride;
             const size_t at = (size_t)(in_cache ? k0 : k0 - tc) * stride;
@@ -301,7 +300,7 @@ struct RunLoader {
                 for (int u = 0; u < NL; ++u)
                     buffer_to_lds(vp, bytes, dst + RUN + u * 1024, lrow * stride + (Swz::v(u * RPL + lrow, lpos) * 16), u * RPL * stride);
             }
-        } else {                                   // where the cache or the chunk ends: row by row
+        } else {                                   // where the cache or the chunk ends: row by row, past it the last row again
 #pragma nounroll
             for (int u = 0; u < NL; ++u) {
                 const int r = u * RPL + lrow, key = min(k0 + r, n - 1);

@@ -53,13 +53,16 @@ def test_fp32_rows_that_do_not_see_a_value_are_as_without_it(heads, kv, d, chunk
         t += L
 
 
-def test_fp32_rows_past_the_cache_are_not_multiplied():
-    """With the position encoding a step that fits reads the cache past its last row."""
-    q, k, v = (x.cuda() for x in random_chunk(4310, 40, 2, 2, 64, "fp32"))
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_rows_past_the_cache_are_not_multiplied(dtype):
+    """With the position encoding a step that fits reads the chunk from the cache, whose next rows are left from before."""
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    q, k, v = (x.cuda() for x in random_chunk(4310, 40, 2, 2, 64, dtype))
     w = spoil(v, range(22, 40))
     outs = []
     for old in (v, w):
-        s = B.Stream(100, 20, 2, 2, 64, dtype=torch.float32, max_chunk=40, rope_base=10000.0)
+        s = B.Stream(100, 20, 2, 2, 64, dtype=dt, max_chunk=40, rope_base=10000.0)
+        assert dtype == "fp32" or s.kernel("attn", 20, 2) == "attn_rows"
         s.step(q, k, old)
         K, V, pos = (x.transpose(0, 1)[:, :20].contiguous() for x in (k, v, torch.arange(40, dtype=torch.int32, device="cuda")[:, None].repeat(1, 2)))
         s.load(K, V, pos, 20)
