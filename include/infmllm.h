@@ -145,7 +145,7 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* dev_workspace, size_t bytes
  * stream).  The array keeps its last contents between holders; everything a stream relies on is cleared
  * at attach.  Errors: EINVAL (null stream, rotary position table requested: its table is uploaded from a
  * host buffer), ENOMEM (the stream does not fit into INFMLLM_STATIC_WORKSPACE_BYTES; scratch that only makes
- * launches faster is left out before that happens, so infmllm_stream_workspace_bytes(s) may be up to 9 MB larger),
+ * launches faster is left out before that happens, so infmllm_stream_workspace_bytes(s) may be larger),
  * ESTATE (already attached, array in use), EHIP.
  */
 #define INFMLLM_STATIC_WORKSPACE_BYTES (64u << 20)

@@ -165,7 +165,6 @@ struct infmllm_stream {
             if (can < L.dec_pieces) L.dec_pieces = rows_decode_pieces(g, L.dec_keys = rows_decode_keys_per_piece(g, std::max(can, 1)));
             if (L.dec_pieces > 1) L.rows_cap = (long)g.Hq * L.dec_pieces;
         } else {
-            // one more than one only with the tickets behind the partials
             L.dec_pieces = std::max(1, fits(decode_pieces(g)));
         }
         // (query row, piece) pairs of a chunk's launch: at most ROWS_MAX_PARTS
@@ -432,8 +431,8 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
     // the cache, and one whose tensors are not aligned for direct loads.
     const bool warm = n <= g.B;
     const size_t kv_bytes = (size_t)L * g.Hkv * g.d * g.elt, out_bytes = (size_t)L * g.Hq * g.d * g.elt;
-    const bool in_place = (mfma || f32) && aligned16(k) && aligned16(v) && !(warm && s->rope_base > 0.0) && !overlap(out, out_bytes, k, kv_bytes) &&
-                          !overlap(out, out_bytes, v, kv_bytes);
+    const bool in_place = (mfma || f32) && aligned16(k) && aligned16(v) && !(warm && s->rope_base > 0.0) &&
+                          !overlap(out, out_bytes, k, kv_bytes) && !overlap(out, out_bytes, v, kv_bytes);
     const KeySource ks = in_place ? KeySource{t, k, v} : KeySource{n, nullptr, nullptr};
     AppendJob job{};
     if (warm || !in_place)
