@@ -27,6 +27,27 @@ struct Rows64Cfg {
     static_assert(ROWS * MC * 4 <= STAGE, "the merge reuses the buffers of the tiles");
 };
 
+// Eight columns of a merged row (see leave_row).
+template <int D>
+__device__ __forceinline__ void leave_row8(const RowsArgs& a, int h, int sp, int rho, int d, float2 ml, f32x4 lo, f32x4 hi)
+{
+    if (a.nsplit == 1) {
+        const int tok = rows_token(a, rho), gq = h * a.G + rho - tok * a.G;
+        const float inv = 1.0f / ml.y;
+        bf16x8 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { w[e] = (__bf16)(lo[e] * inv); w[4 + e] = (__bf16)(hi[e] * inv); }
+        *(bf16x8*)(a.out + ((size_t)tok * a.Hq + gq) * D + d) = w;
+        if (a.lse && d == 0) a.lse[(size_t)gq * a.max_chunk + tok] = ml.x + __builtin_log2f(ml.y);
+        return;
+    }
+    const size_t at = ((size_t)h * a.L * a.G + rho) * a.nsplit + sp;
+    float* po = a.part_o + at * D + d;
+    *(f32x4*)po = lo;
+    *(f32x4*)(po + 4) = hi;
+    if (d == 0) a.part_ml[at] = ml;
+}
+
 // The attention has no register left for a share of the append: the first half of the row groups of a launch
 // with APPEND are workgroups that append and nothing else, which costs less than a launch of its own (us, 32 x 128 heads, 400 rows on 3500 keys / 32 on 8,
 // 300 on 2000: shares after the loop, with a spilled register whose reload drained the loads in flight in every pass, 47.2 /
@@ -38,7 +59,8 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
     using C = Rows64Cfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[RW_NW * C::STAGE];
     __shared__ __attribute__((aligned(1024))) char qmem[C::ROWS * C::ROWB];
-    __shared__ float s_m[RW_NW][C::ROWS], s_l[RW_NW][C::ROWS];
+    __shared__ __attribute__((aligned(16))) float s_m[C::ROWS][RW_NW], s_l[C::ROWS][RW_NW];
+    __shared__ float2 s_tot[C::ROWS];                          // reference and sum of the merged rows
 
     const int sp = blockIdx.x, h = blockIdx.y;                 // piece, kv-head
     if constexpr (APPEND)
@@ -54,7 +76,7 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
     const int n_end = t + rows_token(a, min(row0 + C::ROWS, M) - 1) + 1;
     const int k_end = min((sp + 1) * a.ks, n_end);
 
-    const RunLoader<uint16_t, D, RW_RUN> runs(a, h, lane);
+    RunLoader<uint16_t, D, RW_RUN> runs(a, h, lane);
     char* const mine = smem + wave * C::STAGE;
     // queries: row r of the group in LDS row r, swizzled like K
 #pragma unroll
@@ -83,7 +105,7 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
     }
     // Fragment addresses: K and Q as in attn_rows (lane (row c16, group g4), piece 4s + g4), V by the transpose read.  The
     // step or column block only flips address bits that are clear in the rest, so one address each is kept, in a form
-    // that the compiler does not see through (it would keep all sixteen, and run out of registers).
+    // that the compiler does not see through (it would keep all sixteen, and run out of registers); so is the lane's slot of a load.
     uint32_t k0addr, q0addr, v0addr;
     {
         const uint32_t base = (uint32_t)(uintptr_t)(lds_void*)mine, qbase = (uint32_t)(uintptr_t)(lds_void*)qmem;
@@ -98,7 +120,11 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
     for (int p = 0; p < np; ++p) {
         const int k0 = k_first + p * RW_PASS;
         const bool more = p + 1 < np;
-        asm volatile("" : "+v"(k0addr), "+v"(q0addr), "+v"(v0addr));
+        // The SIMD prefers the older of its two wavefronts, which then leaves the other one 4 us of a launch of 33 to itself (7 of
+        // 50): they take turns of four passes (one pass 32.8, two 32.5, four 32.3 us against 33.5; 50.1, 49.1, 48.7 against 50.5).
+        if (((p >> 2) ^ (wave >> 2)) & 1) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+        asm volatile("" : "+v"(k0addr), "+v"(q0addr), "+v"(v0addr), "+v"(runs.lpos));
         wait_loads<C::NL>();                                   // this run's K has landed, its V may be on its way
         // ---- S^T = K.Q^T, the fragments of a step requested a step ahead
         bf16x8 kf[2][2], qf[2][C::NX];
@@ -202,16 +228,42 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
         products(I1{});
     }
 
-    // ---- merge the wavefronts (see attn_rows_kernel), half of the columns at a time
+    // ---- merge the wavefronts, half of the columns at a time: the tree of add_tree, whose products every wavefront takes
+    // in its registers, so that the thread that adds eight columns of a row only adds.  Bound by 512 KB through the LDS,
+    // 2 us; with a weight for each share of every four columns and two rounds of items per half a whole step took 58.6 us
+    // instead of 58.1 (32 x 128 heads, 512 rows on 2560 keys), 95.1 instead of 94.4 (32 on 8, 512 rows on 4608 keys).
+    int me = 64 * wave + 16 * g4 + c16;                        // tid, which needs no register in the loop
+    asm volatile("" : "+v"(me));                               // nothing of this is made ready before the loop
 #pragma unroll
     for (int x = 0; x < C::NX; ++x) {
         const float l = groups_sum(lsum[x]);
-        if (g4 == 0) { s_m[wave][16 * x + c16] = m_ref[x]; s_l[wave][16 * x + c16] = l; }
+        if (g4 == 0) { s_m[16 * x + c16][wave] = m_ref[x]; s_l[16 * x + c16][wave] = l; }
+    }
+    __syncthreads();
+    auto row_max = [&](int r) -> float {
+        const f32x4 a4 = *(const f32x4*)s_m[r], b4 = *(const f32x4*)(s_m[r] + 4);
+        return fmaxf(fmaxf(fmaxf(a4[0], a4[1]), fmaxf(a4[2], a4[3])), fmaxf(fmaxf(b4[0], b4[1]), fmaxf(b4[2], b4[3])));
+    };
+    auto finite = [](float m) -> float { return m == -__builtin_inff() ? 0.f : m; };
+#pragma unroll
+    for (int x = 0; x < C::NX; ++x) {
+        const float w = fast_exp2(m_ref[x] - finite(row_max(16 * x + c16)));
+#pragma unroll
+        for (int b = 0; b < C::NC; ++b) o[x][b] *= w;
+    }
+    if (me < C::ROWS) {
+#pragma clang fp contract(off)
+        const float m = row_max(me), mz = finite(m);
+        float wl[RW_NW];
+#pragma unroll
+        for (int w = 0; w < RW_NW; ++w) wl[w] = fast_exp2(s_m[me][w] - mz) * s_l[me][w];
+        s_tot[me] = float2{m, ((wl[0] + wl[1]) + (wl[2] + wl[3])) + ((wl[4] + wl[5]) + (wl[6] + wl[7]))};
     }
     auto merged = [&](int w, int r, int p) -> char* {
         return smem + w * C::STAGE + r * (C::MC * 4) + ((p ^ ((r ^ w) & 7)) * 16);
     };
-    const int rows = min(C::ROWS, M - row0);
+    static_assert(C::ROWS * C::MC == 8 * RW_NT, "eight columns of a row per thread");
+    const int r = me / (C::MC / 8), rho = row0 + r;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
         if (hf > 0) __syncthreads();
@@ -221,12 +273,17 @@ attn_rows64_kernel(RowsArgs a, AppendJob ap)
 #pragma unroll
             for (int b = 0; b < CBH; ++b) *(f32x4*)merged(wave, 16 * x + c16, 4 * b + g4) = o[x][hf * CBH + b];
         __syncthreads();
-        for (int i = tid; i < rows * (C::MC / 4); i += RW_NT) {
-            const int r = i / (C::MC / 4), d4 = i % (C::MC / 4);
-            PieceSum ps[RW_NW];
+        if (rho < M) {
+            const int p0 = 2 * (me % (C::MC / 8)), d = hf * C::MC + 4 * p0;
+            f32x4 sum[2];
 #pragma unroll
-            for (int w = 0; w < RW_NW; ++w) ps[w] = PieceSum{s_m[w][r], s_l[w][r], *(const f32x4*)merged(w, r, d4)};
-            leave_row<D>(a, h, sp, row0 + r, hf * C::MC + 4 * d4, add_tree(ps));
+            for (int u = 0; u < 2; ++u) {
+                f32x4 s[RW_NW];
+#pragma unroll
+                for (int w = 0; w < RW_NW; ++w) s[w] = *(const f32x4*)merged(w, r, p0 + u);
+                sum[u] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+            }
+            leave_row8<D>(a, h, sp, rho, d, s_tot[r], sum[0], sum[1]);
         }
     }
 }
