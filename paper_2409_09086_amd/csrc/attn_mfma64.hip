@@ -69,6 +69,13 @@ __device__ __forceinline__ bf16x4 lds_read_tr16_b64(uint32_t addr)
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
     return v;
 }
+template <int OFF>                                           // into accumulation registers
+__device__ __forceinline__ bf16x8 lds_read_b128_acc(uint32_t addr)
+{
+    bf16x8 v;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=a"(v) : "v"(addr), "n"(OFF));
+    return v;
+}
 // waits for every LDS read issued so far; the registers are named so that their consumers stay behind the wait
 __device__ __forceinline__ void lds_wait(bf16x8 (&f)[8])
 {
@@ -149,35 +156,16 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     const int rowsB_end = min(L, 32 * (2 * npair - pair0));  // end of the workgroup's last block B (its first wavefront's)
     const int n_end = t + rowsB_end;                         // keys any row of the workgroup can see
     const int Hkv = Hq / G, n = t + L;
-    int my_row[2], my_lim[2];
+    int my_lim[2];                                           // last visible key of my row, per block
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        my_row[x] = 32 * (x == 0 ? blkA : blkB) + l32;
-        my_lim[x] = t + min(my_row[x], L - 1);               // last visible key of my row
-    }
+    for (int x = 0; x < 2; ++x) my_lim[x] = t + min(32 * (x == 0 ? blkA : blkB) + l32, L - 1);
     const uint16_t* Kh = K + (size_t)h * cap * D;
     const uint16_t* Vh = V + (size_t)h * cap * D;
     const uint16_t* kch = kc + (size_t)h * D;                // chunk rows of this kv-head: row stride Hkv * D
     const uint16_t* vch = vc + (size_t)h * D;
 
-    // query fragments: B operand of S^T = K.Q^T, lane (row l32, half hh) holds Q[row][16s + 8hh .. +8)
-    bf16x8 qf[2][D / 16];
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        const bool ok = my_row[x] < L;
-        const uint16_t* qp = q + ((size_t)(ok ? my_row[x] : 0) * Hq + g) * D + 8 * hh;
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) {
-            u32x4 v = *(const u32x4*)(qp + 16 * s);
-            if (!ok) v = u32x4{0u, 0u, 0u, 0u};
-            qf[x][s] = as_bf16x8(v);
-            // the fragments live in accumulation registers, which the MFMA reads directly: as ordinary vector
-            // registers they would be parked there anyway and copied back before every use
-            asm volatile("" : "+a"(qf[x][s]));
-        }
-    }
-
     f32x16 o[2][D / 32];                                     // O^T accumulators of the two blocks
+    bf16x8 qf[2][D / 16];                                    // query fragments, per block
     f32x16 S[2];                                             // logits of the sub-block in its softmax stage, per block
     u32x4 pf[2][2];                                          // weights of one sub-block, bf16 pairs: [block][16-key step]
     bf16x8 kf[D / 16];                                       // K fragments of one sub-block: [head-dim step]
@@ -527,10 +515,37 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         pf[1][1][3] = pack_bf16_after_nop(tw[1][14], tw[1][15]);
     };
 
-    // ---- prologue: tiles 0, 1 and 2 requested, 0 and 1 awaited, S(0) formed ------------------------------
+    // ---- prologue: queries and tiles 0, 1 and 2 requested, 0 and 1 awaited, S(0) formed -------------------
+    // The wavefront's 64 query rows go through the tile buffers 2 and 3 (16 KB each wavefront, four whole rows per load,
+    // pieces permuted like K's): read from memory as fragments, 32 bytes of 32 rows each, and one after the other ahead of
+    // the tiles, they made the first product start 4.6 us into the kernel; so 2.8.  Rows past the last are the last row
+    // again; nobody stores them.
+    char* const qlds = smem + (wave < 2 ? KREG : VREG) + 2 * TBYTES + (wave & 1) * TBYTES;
+    static_assert(2 * 32 * ROWB == TBYTES, "a wavefront's queries fill one tile buffer");
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int r = 4 * u + (lane >> 4);                   // row of the wavefront: block A's, then block B's
+        const int row = min(32 * (u < 8 ? blkA : blkB) + (r & 31), L - 1);
+        const uint16_t* src = q + ((size_t)row * Hq + g) * D + ((lane & 15) ^ (r & 15)) * 8;
+        __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)(qlds + u * 1024), 16, 0, 0);
+    }
     issue_tile(0, 0);
     issue_tile(min(1, ntiles - 1), 1);
-    issue_tile(min(2, ntiles - 1), 2);
+    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");        // the queries have landed
+    {
+        const uint32_t base = (uint32_t)(uintptr_t)(lds_void*)qlds + (kaddr[0] - (uint32_t)(uintptr_t)(lds_void*)smem - KREG);
+        const uint32_t piece0 = (uint32_t)((hh ^ (l32 & 15)) * 16);
+        static_for<0, 8>([&](auto I) {
+            constexpr int s = decltype(I)::value;
+            const uint32_t addr = base - piece0 + (piece0 ^ (32 * s));
+            qf[0][s] = lds_read_b128_acc<0>(addr);
+            qf[1][s] = lds_read_b128_acc<32 * ROWB>(addr);
+        });
+    }
+    // the fragments live in accumulation registers, which the MFMA reads directly
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+a"(qf[0][0]), "+a"(qf[0][1]), "+a"(qf[0][2]), "+a"(qf[0][3]), "+a"(qf[0][4]), "+a"(qf[0][5]), "+a"(qf[0][6]), "+a"(qf[0][7]));
+    asm volatile("" : "+a"(qf[1][0]), "+a"(qf[1][1]), "+a"(qf[1][2]), "+a"(qf[1][3]), "+a"(qf[1][4]), "+a"(qf[1][5]), "+a"(qf[1][6]), "+a"(qf[1][7]));
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -539,8 +554,9 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int p = 0; p < 8; ++p) vf[i][p] = (__bf16)0.f;
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");         // all but the newest tile's eight loads have landed
-    __builtin_amdgcn_s_barrier();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wavefront's loads of tiles 0 and 1 have landed
+    __builtin_amdgcn_s_barrier();                            // everyone's have, and everyone has its queries
+    issue_tile(min(2, ntiles - 1), 2);
     read_k(Flag<false>{});
     lds_wait(kf);
 #pragma unroll
@@ -600,12 +616,18 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
                 o[x][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * tt + b], as_bf16x8(pf[x][tt]), o[x][b], 0, 0, 0);
 
     // ---- normalise and store: lane (row l32, half hh) holds O[row][32b + 8(i/4) + 4hh + i%4] in o[x][b][i] ----
+    // Through LDS, so that a store takes four whole rows: eight bytes of 32 rows each, straight from the registers, took
+    // 3.4 us, so 2.1 (both together: 275 -> 272 us a launch of 2048 rows on 8192 + 2048 keys of 32 heads).  The tiles' buffers are free (the loads still in flight go to the scratch area); a wavefront has
+    // 16 KB of them to itself.  Piece p (eight columns) of row r lies in slot p ^ (r & 15).
+    char* const olds = smem + wave * (64 * ROWB);
+    int el = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));   // the lane
+    asm volatile("" : "+v"(el));                             // the compiler would keep what the prologue made of it through the loop
+    const int e32 = el & 31, eh = el >> 5;
+    float ltot[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-        if (my_row[x] >= L) continue;
-        const float ltot = lsum[x] + xhalf(lsum[x]);
-        const float inv = 1.0f / ltot;
-        uint16_t* op = out + ((size_t)my_row[x] * Hq + g) * D;
+        ltot[x] = lsum[x] + xhalf(lsum[x]);
+        const float inv = 1.0f / ltot[x];
 #pragma unroll
         for (int b = 0; b < D / 32; ++b)
 #pragma unroll
@@ -613,9 +635,17 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
                 bf16x4 w;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[x][b][4 * q4 + e] * inv);
-                *(bf16x4*)(op + 32 * b + 8 * q4 + 4 * hh) = w;
+                *(bf16x4*)(olds + (32 * x + e32) * ROWB + (((4 * b + q4) ^ (e32 & 15)) * 16) + 8 * eh) = w;
             }
-        if (hh == 0) lse2[(size_t)g * max_chunk + my_row[x]] = m_ref[x] + __builtin_log2f(ltot);
+        const int row = 32 * (x == 0 ? blkA : blkB) + e32;
+        if (eh == 0 && row < L) lse2[(size_t)g * max_chunk + row] = m_ref[x] + __builtin_log2f(ltot[x]);
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int r = 4 * u + (el >> 4);
+        const int row = 32 * (u < 8 ? blkA : blkB) + (r & 31);
+        const u32x4 v = *(const u32x4*)(olds + r * ROWB + (((el & 15) ^ (r & 15)) * 16));
+        if (row < L) *(u32x4*)(out + ((size_t)row * Hq + g) * D + (el & 15) * 8) = v;
     }
 }
 
