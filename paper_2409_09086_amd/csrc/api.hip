@@ -804,7 +804,7 @@ const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cach
             if (tokens > g.max_chunk) return nullptr;
             if (!evicts || n <= g.R) return "";
             if (ranks_by_age) return "rank_score";
-            return s->mfma() ? score_mfma_kernel(g, std::max(cached, n - g.R), std::min(g.R, tokens)) : s->f32() ? "score_f32" : "score_simple";
+            return s->mfma() ? score_mfma_kernel(g, n - g.R, std::min(g.R, tokens)) : s->f32() ? "score_f32" : "score_simple";
         case INFMLLM_K_COMPACT: {
             if (tokens > g.max_chunk) return nullptr;
             const int in_cache = s->mfma() || s->f32() ? cached : n;

@@ -372,12 +372,51 @@ attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, 
     fwd_finish<D, RB, KW>(smem, C::NBUF == 1, o, m_ref, lsum, rb, kw, lane, hh, my_row, g, L, Hq, max_chunk, out, lse2);
 }
 
+// Key columns of the scoring kernels, 32 at a time: from memory to LDS as whole rows (1 KB a load, pieces permuted so that 16
+// rows of a fragment read hit different banks), from there into the layout of the MFMA's B operand, lane (column l32, half hh)
+// holding K[col][16s + 8hh .. +8).  Read in that layout from memory, 32 bytes of 32 rows at a time, the 128 KB of a workgroup
+// came in at 17 bytes a cycle, 3.8 us; so they have landed 0.3 to 1.5 us after they were asked for.
+template <int D>
+struct ScoreCols {
+    static constexpr int ROWB = D * 2, BLOCK = 32 * ROWB, NL = BLOCK / 1024, RPL = 1024 / ROWB, PPR = ROWB / 16;
+    static __device__ __forceinline__ int swz(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+    // K row of a lane's column col0 + lane: cached rows in the order of the cache or, with rows (stream-order index -> cache
+    // row), of the stream.  The lookup is a trip to memory of its own: first thing in a kernel.
+    static __device__ __forceinline__ int lookup(const int32_t* rows, int h, int cap, int col0, int ncol, int lane)
+    {
+        const int col = min(col0 + lane, ncol - 1);           // past the last column: the last one again
+        return rows ? rows[(size_t)h * cap + col] : col;
+    }
+    template <int NB>
+    static __device__ __forceinline__ void request(char* dst, const uint16_t* K, const uint16_t* kc, int row, int tc,
+                                                   int h, int Hkv, int cap, int col0, int lane)
+    {
+        const uint16_t* const Kh = K + (size_t)h * cap * D;
+        const int slot = lane % PPR, sub = lane / PPR;
+#pragma unroll
+        for (int u = 0; u < NB * NL; ++u) {
+            const int k = __shfl(row, u * RPL + sub), piece = slot ^ swz((u * RPL + sub) & 31);
+            const uint16_t* src = Kh + (uint32_t)(k * D + piece * 8);
+            if (__any(k >= tc))                               // the chunk's own rows, where any of them is a candidate
+                if (k >= tc) src = kc + ((size_t)(k - tc) * Hkv + h) * D + piece * 8;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                             (__attribute__((address_space(3))) void*)(dst + u * 1024), 16, 0, 0);
+        }
+    }
+    static __device__ __forceinline__ bf16x8 fragment(const char* block, int l32, int hh, int s)
+    {
+        return as_bf16x8(*(const u32x4*)(block + l32 * ROWB + (((2 * s + hh) ^ swz(l32)) * 16)));
+    }
+};
+
 // ---------------------------------------------------------------------------------------------
 // score: W'[h][j] = (1/(G lq)) sum_{g in group h} sum_{i = L-lq}^{L-1} exp2(c q_i.k_j - lse2_i)
 //                   - (cnd-1-j) b / cnd
-// A column is a physical cache row (col < tc; its stream-order index j is rank[col]) or a chunk row
-// (col >= tc, j = col).  Columns 0 .. ncol-1 are swept, ncol = max(tc, cnd): any cached row may be a
-// candidate; W' is written at index j, for the columns with j < cnd.
+// Where every cached row is a candidate (cnd >= tc) a column is a cache row (col < tc; its stream-order index j is rank[col])
+// or a chunk row (col >= tc, j = col).  Otherwise the columns are the candidates in stream order (j = col, in cache row
+// rows[j]): sweeping all cached rows for them is up to a quarter more work where the recent window is longer than the chunk
+// (launch, us: 32 x 128 heads, 576 rows, 3520 candidates among 4096 rows 29.4 -> 27.2; 32 heads on 8, 512 rows, 3584 of 4096
+// 29.2 -> 27.1; 32 heads, 37 rows, 2981 of 4096 12.4 -> 11.3).  Columns 0 .. ncol-1 are swept, ncol = cnd in both cases.
 // Workgroup = 8 wavefronts = 8 column groups of 32*CB key columns each, held in registers as MFMA
 // operands; every wavefront takes all four 32-row query blocks of an iteration, which are staged once
 // per workgroup (double-buffered in LDS) and so serve 256*CB columns.  Every scored row sees every
@@ -387,7 +426,7 @@ template <int D, int CB>
 __global__ void __launch_bounds__(512)
 score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ kc, int tc,
              const float* __restrict__ lse2, const float* __restrict__ carry, const int32_t* __restrict__ rank,
-             float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd, int ncol,
+             const int32_t* __restrict__ rows, float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd, int ncol,
              int nxb, float c, float dstep /* b / c, Alg. 1 l.2 */, int rsplit, float* __restrict__ spart)
 {
     constexpr int QP = D * 2 + 16;                            // pitch of a staged query row
@@ -397,8 +436,11 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
     constexpr int QBYTES = TROWS * QP;
     constexpr int BUF = QBYTES + TROWS * 4;                   // rows + their log-sum-exp
     constexpr int LSE_ROWS = 4096;                            // scored rows whose log-sum-exp is kept in LDS
-    __shared__ __attribute__((aligned(16))) char smem[2 * BUF];
-    __shared__ float s_lse[LSE_ROWS];
+    using Cols = ScoreCols<D>;
+    constexpr int KBYTES = 8 * CB * Cols::BLOCK;              // the key columns on their way to the registers, before anything else
+    constexpr int LDS = 2 * BUF + LSE_ROWS * 4;
+    __shared__ __attribute__((aligned(1024))) char smem[LDS > KBYTES ? LDS : KBYTES];
+    float* const s_lse = (float*)(smem + 2 * BUF);
     __shared__ int s_ticket;
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
@@ -423,6 +465,8 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
         rs = rem / nxb;
     }
     const int col0 = bx * (256 * CB) + cg * (32 * CB);
+    char* const mine = smem + cg * (CB * Cols::BLOCK);
+    const int krow = Cols::lookup(rows, h, cap, col0, ncol, CB == 2 ? lane : l32);
 
     f32x16 part[CB];
 #pragma unroll
@@ -437,15 +481,19 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
     const int niter = (int)((long)(rs + 1) * niter_all / rsplit) - it_first;
     // Row log-sum-exp of every scored row of the group, once per workgroup: row (gg, i) -> s_lse[gg*lq + i].
     auto row_lse = [&](int g, int i) -> float { return lse2[(size_t)g * max_chunk + i]; };
-    const bool lse_in_lds = G * lq <= LSE_ROWS;
+    const bool lse_in_lds = lq > 0 && G * lq <= LSE_ROWS;
     // every load is issued before the first value is stored, together with those of the first query blocks
     // and of the key tile below: the prologue then waits for memory once, not once per group of 512 rows
     float lse_in[LSE_ROWS / 512];
     if (lse_in_lds) {
+        int gg = tid / lq, i = tid - gg * lq;                 // row tid + 512 u; two divisions, not sixteen
+        const int dg = 512 / lq, di = 512 - dg * lq;
 #pragma unroll
         for (int u = 0; u < LSE_ROWS / 512; ++u) {
-            const int x = tid + u * 512;
-            lse_in[u] = x < G * lq ? row_lse(h * G + x / lq, L - lq + x % lq) : 0.f;
+            lse_in[u] = gg < G ? row_lse(h * G + gg, L - lq + i) : 0.f;
+            i += di;
+            gg += dg + (i >= lq);
+            i -= i >= lq ? lq : 0;
         }
     }
 
@@ -509,23 +557,14 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
         if (tid < TROWS) *(float*)(base + QBYTES + tid * 4) = (stl_idx >= 0) ? s_lse[stl_idx] : stl;
     };
     if (niter > 0) fetch(true);
-    // Key fragments: B operand of S = Q.K^T, lane (column l32, half hh) holds K[col][16s + 8hh .. +8), loaded in
-    // that layout straight from memory (a wavefront's load touches 32 rows, 32 bytes of each; the four loads
-    // that share a row's 128-byte line follow one another).  A column past the last one is all zeros.
+    Cols::template request<CB>(mine, K, kc, krow, tc, h, Hkv, cap, col0, lane);
     bf16x8 kf[CB][D / 16];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the wavefront's columns have landed
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-        const int col = col0 + 32 * cb + l32;
-        const bool ok = col < ncol;
-        const int cc = ok ? col : 0;
-        const uint16_t* kp = (cc < tc ? K + ((size_t)h * cap + cc) * D : kc + ((size_t)(cc - tc) * Hkv + h) * D) + 8 * hh;
+    for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int s = 0; s < D / 16; ++s) {
-            u32x4 v = *(const u32x4*)(kp + 16 * s);
-            if (!ok) v = u32x4{0u, 0u, 0u, 0u};
-            kf[cb][s] = as_bf16x8(v);
-        }
-    }
+        for (int s = 0; s < D / 16; ++s) kf[cb][s] = Cols::fragment(mine + cb * Cols::BLOCK, l32, hh, s);
+    __syncthreads();                                          // everyone's are in registers
     if (lse_in_lds) {
 #pragma unroll
         for (int u = 0; u < LSE_ROWS / 512; ++u) {
@@ -601,22 +640,26 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
             unit(base, I0{}, I1{}, accB, accA);
             unit(base, I1{}, I0{}, accA, accB);
             unit(base, I1{}, I1{}, accB, accA);
-            unit(base, I2{}, I0{}, accA, accB);
-            unit(base, I2{}, I1{}, accB, accA);
-            unit(base, I3{}, I0{}, accA, accB);
-            unit(base, I3{}, I1{}, accB, accA);
+            if (4 * (it_first + it) + 2 < total) {            // the last iteration may have no more than two blocks
+                unit(base, I2{}, I0{}, accA, accB);
+                unit(base, I2{}, I1{}, accB, accA);
+                unit(base, I3{}, I0{}, accA, accB);
+                unit(base, I3{}, I1{}, accB, accA);
+            }
         } else {
             unit(base, I0{}, I0{}, accA, accB);
             unit(base, I1{}, I0{}, accB, accA);
-            unit(base, I2{}, I0{}, accA, accB);
-            unit(base, I3{}, I0{}, accB, accA);
+            if (4 * (it_first + it) + 2 < total) {
+                unit(base, I2{}, I0{}, accA, accB);
+                unit(base, I3{}, I0{}, accB, accA);
+            }
         }
         // the other buffer was last read one iteration ago, before the barrier that ended it
         if (it + 1 < niter) stash((it + 1) & 1);
         if (it + 2 < niter) fetch();
         __syncthreads();
     }
-    if (niter > 0) {                                          // the last unit: block 3, column block CB - 1
+    if (niter > 0) {                                          // the last unit: block 3 or 1, column block CB - 1
 #pragma unroll
         for (int i = 0; i < 16; ++i) part[CB - 1][i] += fast_exp2(__builtin_fmaf(accB[i], c, -ls[i / 4][i % 4]));
     }
@@ -653,7 +696,7 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int col = col0 + 32 * cb + l32;
-            const int j = col < tc ? (col < ncol ? rank[(size_t)h * cap + col] : cnd) : col;   // stream-order index
+            const int j = col < tc && !rows ? (col < ncol ? rank[(size_t)h * cap + col] : cnd) : col;   // stream-order index
             if (j < cnd) {
                 float tot = sum[cb];
                 if (rsplit > 1) {
@@ -667,7 +710,7 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
                 if (carry) {
                     // cumulative policy: this step's S on top of what the row has gathered, no bias; the
                     // chunk's own rows (read in place, col >= tc) and rows never ranked (+inf) carry nothing
-                    const float a = col < tc ? carry[(size_t)h * cap + col] : 0.f;
+                    const float a = col < tc ? carry[(size_t)h * cap + (rows ? rows[(size_t)h * cap + col] : col)] : 0.f;
                     w = tot * norm + (a < __builtin_inff() ? a : 0.f);
                 }
                 Wb[(size_t)h * cap + j] = w;
@@ -689,12 +732,14 @@ template <int D>
 __global__ void __launch_bounds__(512, 4)
 score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ kc, int tc,
                   const float* __restrict__ lse2, const float* __restrict__ carry, const int32_t* __restrict__ rank,
-                  float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd, int ncol,
+                  const int32_t* __restrict__ rows, float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd, int ncol,
                   int nxb, float c, float dstep /* b / c, Alg. 1 l.2 */, int nslice, float* __restrict__ spart)
 {
     constexpr int QP = D * 2 + 16, CPR = D / 8, NS = D / 16;  // pitch, 16-byte pieces of a staged row; MFMAs per block
     constexpr int NLD = ONCE_BLOCKS * 32 * CPR / 512;         // pieces per thread
-    __shared__ __attribute__((aligned(16))) char qs[ONCE_BLOCKS * 32 * QP];
+    using Cols = ScoreCols<D>;
+    constexpr int QBYTES = ONCE_BLOCKS * 32 * QP;
+    __shared__ __attribute__((aligned(1024))) char qs[QBYTES > 8 * Cols::BLOCK ? QBYTES : 8 * Cols::BLOCK];   // key columns, then queries
     __shared__ __attribute__((aligned(16))) float ls[ONCE_BLOCKS * 32];
     __shared__ int s_ticket;
 
@@ -708,6 +753,9 @@ score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         bx = rem % nxb;
         rs = rem / nxb;
     }
+    const int col = bx * 256 + wave * 32 + l32;               // this lane's
+    char* const mine = qs + wave * Cols::BLOCK;
+    const int krow = Cols::lookup(rows, h, cap, bx * 256 + wave * 32, ncol, l32);
     // blocks of 32 scored rows, head after head of the group; this slice's
     const int nblk = (lq + 31) / 32, total = G * nblk;
     const int b0 = (int)((long)rs * total / nslice), nb = (int)((long)(rs + 1) * total / nslice) - b0;
@@ -726,20 +774,13 @@ score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         const int b = b0 + (tid >> 5), i = L - lq + 32 * (b % nblk) + (tid & 31);
         if (i < L) row_lse = lse2[(size_t)(h * G + b / nblk) * max_chunk + i];
     }
-    // key fragments and stream-order index of this lane's column (see score_kernel); past the last column all zeros
-    const int col = bx * 256 + wave * 32 + l32;
-    const int cc = col < ncol ? col : 0;
+    const int j = col < tc && !rows ? (col < ncol ? rank[(size_t)h * cap + col] : cnd) : col;   // stream-order index
+    Cols::template request<1>(mine, K, kc, krow, tc, h, Hkv, cap, bx * 256 + wave * 32, lane);
     bf16x8 kf[NS];
-    {
-        const uint16_t* kp = (cc < tc ? K + ((size_t)h * cap + cc) * D : kc + ((size_t)(cc - tc) * Hkv + h) * D) + 8 * hh;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            u32x4 v = *(const u32x4*)(kp + 16 * s);
-            if (col >= ncol) v = u32x4{0u, 0u, 0u, 0u};
-            kf[s] = as_bf16x8(v);
-        }
-    }
-    const int j = col < tc ? (col < ncol ? rank[(size_t)h * cap + col] : cnd) : col;
+    for (int s = 0; s < NS; ++s) kf[s] = Cols::fragment(mine, l32, hh, s);
+    __syncthreads();                                          // the columns are in registers, the queries may take their place
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
         const int x = tid + u * 512;
@@ -786,7 +827,7 @@ score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     const float S = lq > 0 ? sum * (1.0f / (float)(G * lq)) : 0.f;
     float w = S - (float)(cnd - 1 - j) * dstep;               // Alg. 1 l.1, l.3-4
     if (carry) {                                              // cumulative policy (see score_kernel)
-        const float a = col < tc ? carry[(size_t)h * cap + col] : 0.f;
+        const float a = col < tc ? carry[(size_t)h * cap + (rows ? rows[(size_t)h * cap + col] : col)] : 0.f;
         w = S + (a < __builtin_inff() ? a : 0.f);
     }
     Wb[(size_t)h * cap + j] = w;
@@ -930,7 +971,8 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
 {
     const int n = t + L, cnd = n - g.R, lq = g.R < L ? g.R : L;
     if (cnd <= 0) return hipSuccess;
-    const int ncol = ks.rows > cnd ? ks.rows : cnd;          // every cached row, and the chunk rows below cnd
+    const int32_t* rows = cnd < ks.rows ? c.row : nullptr;   // some cached rows are no candidates: by stream order
+    const int ncol = cnd;
     const float cc = (float)(g.scale * (double)LOG2E);
     const float dstep = (float)(g.bias / (double)cnd);
     const float* carry = g.policy == POLICY_CUMULATIVE ? c.score : nullptr;
@@ -938,7 +980,7 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
     if (p.once) {
 #define INFMLLM_ONCE(DD)                                                                                                   \
     hipLaunchKernelGGL(score_once_kernel<DD>, dim3((unsigned)(p.nxb * g.Hkv * p.split)), dim3(512), 0, st, (const uint16_t*)q,                  \
-                       (const uint16_t*)c.K, (const uint16_t*)ks.k, ks.rows, lse, carry, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, \
+                       (const uint16_t*)c.K, (const uint16_t*)ks.k, ks.rows, lse, carry, c.rank, rows, Wb, L, lq, g.Hq, g.Hkv, g.G, \
                        g.cap, g.max_chunk, cnd, ncol, p.nxb, cc, dstep, p.split, sc.score_part)
         if (g.d == 128) INFMLLM_ONCE(128);
         else if (g.d == 64) INFMLLM_ONCE(64);
@@ -950,7 +992,7 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
 #define INFMLLM_SCORE(DD, CB)                                                                              \
     hipLaunchKernelGGL((score_kernel<DD, CB>), grid, block, 0, st, (const uint16_t*)q, (const uint16_t*)c.K, \
                        (const uint16_t*)ks.k, ks.rows, lse,                                                  \
-                       carry, c.rank, Wb, L, lq, g.Hq, g.Hkv, g.G, g.cap, g.max_chunk,                        \
+                       carry, c.rank, rows, Wb, L, lq, g.Hq, g.Hkv, g.G, g.cap, g.max_chunk,                        \
                        cnd, ncol, p.nxb, cc, dstep, p.split, sc.score_part)
     if (g.d == 128 && p.wide) INFMLLM_SCORE(128, 2);
     else if (g.d == 128) INFMLLM_SCORE(128, 1);

@@ -154,7 +154,7 @@ hipError_t launch_rows_chunk(const Geometry& g, const CacheView& c, const KeySou
 hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q,
                              const float* lse, const FwdScratch& sc, int t, int L, float* Wb, hipStream_t st);
 
-// Which kernel that is for ncol columns (cached rows, or candidates if they are more) and lq scored rows per head.
+// Which kernel that is for ncol columns (candidates) and lq scored rows per head.
 const char* score_mfma_kernel(const Geometry& g, int ncol, int lq);
 
 // a5+a6: user_I[h] = sort_asc(top-r of W'[h][0..cnd)) ++ [cnd, n), in stream-order indices, row stride B.  user_I
