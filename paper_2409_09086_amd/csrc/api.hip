@@ -65,7 +65,7 @@ struct infmllm_stream {
     int dtype;
     int impl;            // 0 = matrix cores where the dtype allows, 1 = plain arithmetic
     bool attached;
-    bool lean = false;   // workspace without the scratch that launches can do without (see layout)
+    int lean = 0;        // workspace without the scratch that launches can do without: 1 without that of cut ranges of attn_fwd64, 2 without any
     int static_dev = -1; // device whose library-owned workspace this stream holds (-1: caller's workspace)
     hipStream_t st;
     CacheView cache;
@@ -89,6 +89,7 @@ struct infmllm_stream {
     FwdScratch fwd;      // scratch of the row-split scoring launch
     float* dec_part;     // partials of the decoding step (plain-arithmetic kernels)
     int dec_pieces = 1, dec_keys = 0;   // see Layout
+    CutScratch cut{nullptr, nullptr, 0};                // the same of attn_fwd64
     RowsScratch rows{nullptr, nullptr, nullptr, 0};   // partials of attention launches with a cut key range (bf16 on the matrix cores)
     // optional per-kernel timing: one event pair per kernel per step, up to prof_cap steps
     std::vector<hipEvent_t> prof_ev;   // [prof_cap][INFMLLM_K_COUNT][2]
@@ -116,8 +117,9 @@ struct infmllm_stream {
 
     struct Layout {
         size_t K, V, pos, score, rank, row, lse, Wb, mv_src, mv_dst, mv_x, mv_score, mv_count, score_part, rows_arrived, K_rot,
-            kc_rot, q_rot, rope_tab, rows_o, rows_ml, dec_part, total;
+            kc_rot, q_rot, rope_tab, rows_o, rows_ml, dec_part, cut_part, cut_arrived, total;
         long rows_cap;
+        int cut_units;       // workgroups of attn_fwd64 whose key ranges may be cut
         int dec_pieces;      // most pieces a decoding launch may cut the keys into
         int dec_keys;        // keys of a piece (on the matrix cores)
     };
@@ -142,7 +144,7 @@ struct infmllm_stream {
         L.mv_score = off; off += ml;
         L.mv_count = off; off += up((size_t)g.Hkv * 4);
         // row-split scoring: partial column sums and arrival counters (fp32 streams score without as well, only slower)
-        L.score_part = off; off += up(mfma() || (f32() && !lean) ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
+        L.score_part = off; off += up(mfma() || (f32() && lean < 2) ? (size_t)SCORE_SPLIT_WGS * (256 + 1) * 4 : 0);
         L.rows_arrived = off; off += up(mfma() ? (size_t)g.Hkv * 4 : 0);
         const bool rope = rope_base > 0.0;
         L.K_rot = off; off += rope ? kv : 0;
@@ -151,7 +153,7 @@ struct infmllm_stream {
         L.rope_tab = off; off += up(rope ? (size_t)g.cap * (g.d / 2) * 2 * sizeof(double) : 0);
         // Partials of launches whose key range is cut.  Nothing needs them, launches with uncut ranges are only slower: a
         // lean workspace has none for chunks, and for decoding as many pieces as the rest of the library's array takes.
-        const size_t room = !lean ? SIZE_MAX : off < INFMLLM_STATIC_WORKSPACE_BYTES ? INFMLLM_STATIC_WORKSPACE_BYTES - off : 0;
+        const size_t room = lean < 2 ? SIZE_MAX : off < INFMLLM_STATIC_WORKSPACE_BYTES ? INFMLLM_STATIC_WORKSPACE_BYTES - off : 0;
         const size_t part = (size_t)g.Hq * (g.d + 2) * 4;      // of a piece, every head's
         auto fits = [&](int pieces) {
             const size_t most = room < 3 * ALIGN + (size_t)g.Hkv * 4 ? 0 : (room - 3 * ALIGN - (size_t)g.Hkv * 4) / part;
@@ -168,12 +170,15 @@ struct infmllm_stream {
             L.dec_pieces = std::max(1, fits(decode_pieces(g)));
         }
         // (query row, piece) pairs of a chunk's launch: at most ROWS_MAX_PARTS
-        if (!lean && (mfma() || f32()))
+        if (lean < 2 && (mfma() || f32()))
             L.rows_cap = std::max(L.rows_cap, std::min((long)g.Hq * std::max(g.max_chunk, mfma() ? g.max_decode : 0) * ((g.cap + 127) / 128),
                                                        ROWS_MAX_PARTS));
         L.rows_o = off; off += up((size_t)L.rows_cap * g.d * 4);
         L.rows_ml = off; off += up((size_t)L.rows_cap * 8);
         L.dec_part = off; off += up(!mfma() && L.dec_pieces > 1 ? part * L.dec_pieces + (size_t)g.Hkv * 4 : 0);
+        L.cut_units = mfma() && !lean ? attn_cut_units(g) : 0;
+        L.cut_part = off; off += up((size_t)L.cut_units * 2 * attn_mfma64_piece_bytes());
+        L.cut_arrived = off; off += up((size_t)L.cut_units * 4);
         L.total = off;
         return L;
     }
@@ -317,6 +322,7 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     s->rows.ml = (float2*)(base + L.rows_ml);
     s->rows.arrived = (int*)(base + L.rows_arrived);
     s->rows.cap_rows = L.rows_cap;
+    s->cut = CutScratch{(float*)(base + L.cut_part), (int*)(base + L.cut_arrived), L.cut_units};
     s->dec_pieces = L.dec_pieces;
     s->dec_keys = L.dec_keys;
     s->K_rot = base + L.K_rot;
@@ -358,15 +364,15 @@ int infmllm_stream_attach_static(infmllm_stream_t* s, void* hip_stream)
         return fail(INFMLLM_EINVAL, "attach_static: streams with the rotary position table are not supported "
                                     "(the table is uploaded from a host buffer)");
     // where the whole workspace is too large for the array, one without the dispensable scratch may fit
-    s->lean = s->layout().total > (size_t)INFMLLM_STATIC_WORKSPACE_BYTES;
+    while (s->lean < 2 && s->layout().total > (size_t)INFMLLM_STATIC_WORKSPACE_BYTES) ++s->lean;
     const size_t need = s->layout().total;
     if (need > (size_t)INFMLLM_STATIC_WORKSPACE_BYTES) {
-        s->lean = false;
+        s->lean = 0;
         return fail(INFMLLM_ENOMEM, "attach_static: the stream needs %zu bytes of workspace, the library's array holds %zu",
                     need, (size_t)INFMLLM_STATIC_WORKSPACE_BYTES);
     }
-    const bool lean = s->lean;
-    s->lean = false;                                           // every failure below leaves the stream as it was
+    const int lean = s->lean;
+    s->lean = 0;                                               // every failure below leaves the stream as it was
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail_hip(e, "attach_static: hipGetDevice");
@@ -392,7 +398,7 @@ int infmllm_stream_attach_static(infmllm_stream_t* s, void* hip_stream)
         std::lock_guard<std::mutex> lk(g_static_mu);
         g_static_owner[dev] = nullptr;
         s->static_dev = -1;
-        s->lean = false;
+        s->lean = 0;
     }
     return rc;
 }
@@ -461,7 +467,7 @@ int step_front(infmllm_stream* s, const void* q, const void* k, const void* v, i
         s->rot_rows = in_place ? t : n;
     }
     s->mark(INFMLLM_K_ATTN, 0);
-    e = mfma  ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, job, s->st)
+    e = mfma  ? launch_attn_mfma(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, s->cut, job, s->st)
         : f32 ? launch_attn_f32(g, att, ks_att, q_att, t, L, out, s->lse, s->rows, job, s->st)
               : launch_attn_simple(g, att, q_att, t, L, out, s->lse, s->st);
     if (e != hipSuccess) return fail_hip(e, "attention");
@@ -799,7 +805,7 @@ const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cach
     switch (which) {
         case INFMLLM_K_ATTN:
             if (tokens > g.max_chunk) return nullptr;
-            return s->mfma() ? attn_mfma_kernel(g, n, tokens, s->attached ? s->rows.cap_rows : s->layout().rows_cap) : s->f32() ? "attn_f32" : "attn_simple";
+            return s->mfma() ? attn_mfma_kernel(g, n, tokens, s->attached ? s->rows.cap_rows : s->layout().rows_cap, s->attached ? s->cut.units : s->layout().cut_units) : s->f32() ? "attn_f32" : "attn_simple";
         case INFMLLM_K_SCORE:
             if (tokens > g.max_chunk) return nullptr;
             if (!evicts || n <= g.R) return "";

@@ -20,6 +20,8 @@
 //
 // fp32 is kept from the MFMA accumulators to the score: the bf16 rounding of P is applied only
 // to the copy that feeds the P.V product.
+#include <algorithm>
+
 #include "append_body.h"
 #include "launch.h"
 #include "mfma_common.h"
@@ -853,64 +855,99 @@ namespace {
 
 // tile: 0 = attn_rows or attn_rows64 with `rows`, 1..5 as INFMLLM_PARAM_ATTN_TILE, 6 = attn_fwd at head_dim 64
 struct AttnPlan {
-    int tile;
+    int tile, pieces;          // pieces: of attn_fwd64
     RowsPlan rows;
 };
-AttnPlan attn_plan(const Geometry& g, int n, int L, long cap_rows, bool q_aligned)
+// The kernel for a chunk at head_dim 128 among those that take their grid from the query rows, and the time (us, between two
+// events) it should take.  np: keys that a row in the middle of the chunk sees.  Measured at 24 to 32 heads on 8 to 32, 512 to 2700
+// rows, 512 to 8192 cached rows, at 2500 to 9000 keys within about 5 %:
+//   attn_fwd, 64-row workgroups (tile 2) while they fit into one round over the 256 CUs, else of 128 rows (tile 1), which fill
+//   the chip from about 130 workgroups on and get slower the more of it they take; a second round is never cheap.
+//   attn_fwd64 (5): as fast per CU on a full chip, twice the rows; one round of it replaces two of attn_fwd (32 heads, 1152
+//   rows, 4096 cached 112 against 142; 1600 rows 132 against 164), but a second round that is nearly empty does not pay (2304 rows: 275 / 244).
+//   attn_fwd64 with key ranges cut in two, for 65 to 128 workgroups' worth of rows: it fills the chip where attn_fwd's shorter
+//   workgroups leave part of it idle or wait for those that see most keys, and pays for the exchange, 20.5 us instead of 16
+//   before the first key (32 heads, 640 rows, 1024 cached 35.1 / 33.6, 2048 45.5 / 46.5, 8192 109.5 / 125.2; 32 heads on 8, 900
+//   rows, 1024 37.9 / 38.4, 4096 76.8 / 84.9, 8192 128.8 / 147.1).
+// A step that evicts nothing appends in a launch of its own, 5 us, beside an uncut attn_fwd64.
+float fwd_plan(const Geometry& g, int n, int L, int cut_units, AttnPlan& p)
+{
+    const float np = (float)(n - L / 2);
+    const int wgs = g.Hq * ((L + 63) / 64), wgs128 = (g.Hq * ((L + 31) / 32) + 3) / 4, units = attn_mfma64_units(g, L);
+    float best;
+    if (wgs <= 256) {
+        best = (9.f + 0.0096f * (float)n) * (1.f + 0.15f * (float)wgs / 256.f);
+        p.tile = 2;
+    } else {
+        best = wgs128 <= 256 ? 16.f + (0.0128f + 3e-5f * (float)std::max(0, wgs128 - 160)) * np
+                             : 13.f + std::max(0.0287f, 0.0192f * (float)wgs128 / 256.f) * np;
+        p.tile = 1;
+    }
+    const float whole = 20.f + (n <= g.B ? 5.f : 0.f) +
+                        (units <= 256 ? 0.0199f + 7e-5f * (float)std::max(0, units - 160) : 0.0267f * (float)((units + 255) / 256)) * np;
+    if (whole < best) { best = whole; p.tile = 5; }
+    const float cut = 20.5f + (0.0102f + 6e-5f * (float)std::max(0, units - 80)) * np;
+    if (units <= cut_units && n - L / 2 >= CUT_MIN_KEYS && cut < best) { best = cut; p.tile = 5; p.pieces = 2; }
+    return best;
+}
+
+AttnPlan attn_plan(const Geometry& g, int n, int L, long cap_rows, int cut_units, bool q_aligned)
 {
     AttnPlan p{};
-    if (g.attn_tile == 0 && (long)L * g.G <= (1 << 20) && (long)L * g.G * g.G < (1l << 32)) {   // what its grid and rows_token take
-        // Few query rows: attn_rows, which cuts the key range over the workgroups.  Examples, measured, attn_rows against
-        // the kernels below: 32 x 128 heads, 4096 keys: 24 / 49 us with 37 rows, 22 / 50 with 64; 16 heads on 4 of 128,
-        // 5000 keys, 320 rows: 37 / 61; 8 x 64 heads, 4000 keys, 320 rows: 19 / 72.  The time of the kernels below, fitted
-        // to measurements like that of rows_chunk_plan: per round of workgroups over the 256 CUs, and the more the
-        // fuller the chip; at head_dim 64 several workgroups share a CU.
-        const int wgs = g.d == 128 ? g.Hq * ((L + 63) / 64) : g.Hq * ((L + 127) / 128);
-        const int wgs2 = g.Hq * ((L + 31) / 32) / 4;             // of 128 rows, head_dim 128 (see below)
-        const float rounds = (float)(((g.d == 128 && wgs2 >= 140 ? wgs2 : wgs) + 255) / 256), fill = wgs < 256 ? (float)wgs / 256.f : 1.f;
-        const float other = g.d == 64 ? (7.f + 0.0136f * (float)n) * (1.f + 0.35f * (rounds - 1.f))
-                            : wgs2 >= 140 ? rounds * (10.f + 0.0148f * (float)n)
-                                          : rounds * (9.f + 0.0096f * (float)n) * (1.f + 0.15f * fill);
-        // with 64 rows the queries are loaded directly into LDS
-        if (rows_chunk_plan(g, n, L, cap_rows, q_aligned ? 4 : 2, p.rows) < other) return p;
-    }
-    if (g.d == 64) {
-        p.tile = 6;
+    p.pieces = 1;
+    if (g.attn_tile > 0) {                                   // a test hook: forces one shape
+        p.tile = g.d == 64 ? 6 : g.attn_tile;
+        if (p.tile == 5 && attn_mfma64_units(g, L) <= cut_units && n - L / 2 >= CUT_MIN_KEYS) p.pieces = 2;
         return p;
     }
-    // 128 query rows x 64 keys per wavefront-tile is the efficient shape; when that grid would cover
-    // only about half of the chip (128 workgroups at 32 heads x 512 rows), 64-row workgroups with four
-    // key ways inside the workgroup are faster.  g.attn_tile > 0 (a test hook) forces one shape.
-    const int wgs128 = g.Hq * ((L + 31) / 32) / 4;
-    // attn_fwd64 (attn_mfma64.hip: 64 query rows per wavefront, one wavefront per SIMD) is the faster kernel
-    // where its grid of 256-row workgroups covers the chip and the key range is long enough to fill its pipeline.
-    // Its workgroups occupy a CU each: the grid must fill at least 80 % of the rounds over the 256 CUs it takes.
-    const int wgs64 = (g.Hq * ((L + 63) / 64) + 3) / 4;
-    const int rounds64 = (wgs64 + 255) / 256;
-    const bool fills = wgs64 * 5 >= rounds64 * 256 * 4;
-    p.tile = g.attn_tile > 0 ? g.attn_tile : (fills && n >= 1024 ? 5 : (wgs128 >= 140 ? 1 : 2));
+    float other;
+    if (g.d == 64) {
+        // fitted like the times of fwd_plan; several workgroups share a CU
+        const float rounds = (float)((g.Hq * ((L + 127) / 128) + 255) / 256);
+        other = (7.f + 0.0136f * (float)n) * (1.f + 0.35f * (rounds - 1.f));
+        p.tile = 6;
+    } else {
+        other = fwd_plan(g, n, L, cut_units, p);
+    }
+    // Few query rows: attn_rows, which cuts the key range over the workgroups.  Examples, measured, attn_rows against
+    // the kernels above: 32 x 128 heads, 4096 keys: 24 / 49 us with 37 rows, 22 / 50 with 64; 16 heads on 4 of 128,
+    // 5000 keys, 320 rows: 37 / 61; 8 x 64 heads, 4000 keys, 320 rows: 19 / 72.  With 64 rows the queries are loaded
+    // directly into LDS.
+    RowsPlan rows;
+    if ((long)L * g.G <= (1 << 20) && (long)L * g.G * g.G < (1l << 32) &&                // what its grid and rows_token take
+        rows_chunk_plan(g, n, L, cap_rows, q_aligned ? 4 : 2, rows) < other) {
+        p.tile = 0;
+        p.pieces = 1;
+        p.rows = rows;
+    }
     return p;
 }
 
 }  // namespace
 
-const char* attn_mfma_kernel(const Geometry& g, int n, int L, long cap_rows)
+int attn_cut_units(const Geometry& g)
 {
-    const AttnPlan p = attn_plan(g, n, L, cap_rows, true);
-    return p.tile == 0 ? (p.rows.nrb == 4 ? "attn_rows64" : "attn_rows") : p.tile == 5 ? "attn_fwd64" : "attn_fwd";
+    const int units = g.d == 128 ? attn_mfma64_units(g, g.max_chunk) : 0;
+    return g.attn_tile == 5 || (g.attn_tile == 0 && units > 64) ? std::min(units, CUT_MAX_UNITS) : 0;
+}
+
+const char* attn_mfma_kernel(const Geometry& g, int n, int L, long cap_rows, int cut_units)
+{
+    const AttnPlan p = attn_plan(g, n, L, cap_rows, cut_units, true);
+    return p.tile == 0 ? (p.rows.nrb == 4 ? "attn_rows64" : "attn_rows") : p.tile == 5 ? (p.pieces > 1 ? "attn_fwd64, cut" : "attn_fwd64") : "attn_fwd";
 }
 
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                            void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st)
+                            void* out, float* lse, const RowsScratch& sc, const CutScratch& cut, const AppendJob& ap, hipStream_t st)
 {
     if (g.d != 64 && g.d != 128) return hipErrorInvalidValue;
-    const AttnPlan p = attn_plan(g, t + L, L, sc.cap_rows, (uintptr_t)q % 16 == 0);
+    const AttnPlan p = attn_plan(g, t + L, L, sc.cap_rows, cut.units, (uintptr_t)q % 16 == 0);
     switch (p.tile) {
         case 0: return launch_rows_chunk(g, c, ks, q, t, L, out, lse, sc, p.rows, ap, st);
         case 5: {
-            // no share of the job here: the kernel has its SIMDs to itself and no register to spare
-            const hipError_t e = ap.k ? launch_append(ap, st) : hipSuccess;
-            return e != hipSuccess ? e : launch_attn_mfma64(g, c, ks, q, t, L, out, lse, st);
+            // whole key ranges: no share of the job, every workgroup has a CU to itself until the end
+            const hipError_t e = ap.k && p.pieces == 1 ? launch_append(ap, st) : hipSuccess;
+            return e != hipSuccess ? e : launch_attn_mfma64(g, c, ks, q, t, L, out, lse, cut, p.pieces, ap, st);
         }
         case 1: return launch_fwd_cfg<128, 4, 2, 2>(g, c, ks, q, t, L, out, lse, ap, st);
         case 2: return launch_fwd_cfg<128, 2, 4, 1>(g, c, ks, q, t, L, out, lse, ap, st);

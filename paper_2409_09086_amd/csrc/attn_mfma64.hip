@@ -23,11 +23,19 @@
 // The softmax reference moves only when a row maximum outgrows it by 2^8; that rare step is taken on a side
 // path between the period's two scheduling regions.
 //
+// P = 2: 65 to 128 workgroups' worth of rows leave half of the chip idle, or, with attn_fwd's workgroups of half as many rows,
+// wait for those that see most keys.  Every key range is then cut in two pieces, which two workgroups go through; the one that
+// arrives last adds the other's (o, m, l), 132 KB, in registers, as they were left: 16-byte stores and loads of whole
+// kilobytes that bypass the L2 caches (stored four bytes a lane, and always by both pieces, the exchange took 23 us; now about 5).
+// Launch, us, before (attn_fwd) and after: 32 heads on 8, 1024 rows on 5120 keys 90.5 -> 79.9; 32 heads, 576 rows on 4672
+// 74.8 -> 69.3.
+//
 // Under the causal mask the chunk's later rows see more keys.  A wavefront's two blocks are therefore one from
 // the front and one from the back of the head's rows, which gives every wavefront the same number of (row, key)
 // pairs; when block A has seen its last key the loop continues with a 16-slot period for block B alone.
 #include <type_traits>
 
+#include "append_body.h"
 #include "launch.h"
 #include "mfma_common.h"
 
@@ -43,6 +51,7 @@ constexpr int TBYTES = TILE * ROWB;                // one tile of K or of V: 16 
 constexpr int KREG = 0, VREG = NBUF * TBYTES;      // LDS regions: the K tiles, then the V tiles
 constexpr int DUMP = 2 * NBUF * TBYTES;            // 1 KB per wavefront that loads nobody needs are sent to
 constexpr int LDS = DUMP + 4 * 1024;
+constexpr int PIECE_LEAD = 20;                     // see the kernel.  Launch, us, with 0 / 30 / 60: 32 heads on 8, 1024 rows on 5120 keys 81.6 / 80.7 / 82.7
 static_assert(LDS <= 160 * 1024, "the tiles must fit the LDS of a CU");
 static_assert(NBUF * TBYTES <= 65536, "a region must be addressable with a 16-bit instruction offset");
 static_assert(TILE <= CACHE_PAD_ROWS, "workspace padding assumes smaller tiles");
@@ -115,29 +124,32 @@ __device__ __forceinline__ uint32_t pack_bf16_after_nop(float lo, float hi)   //
 
 template <bool B> using Flag = std::integral_constant<bool, B>;
 
+template <int P>
 __global__ void __launch_bounds__(w64::NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                   const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, int tc,
                   uint16_t* __restrict__ out, float* __restrict__ lse2, int t, int L, int Hq, int G, int cap,
-                  int max_chunk, int hpw, int ntile, int ny, float c /* scale * log2(e) */)
+                  int max_chunk, int hpw, int ntile, int ny, float c /* scale * log2(e) */, float* __restrict__ part,
+                  int* __restrict__ arrived, AppendJob ap)
 {
     using namespace w64;
     __shared__ __attribute__((aligned(1024))) char smem[LDS];
 
     // Workgroup -> (row tile, head group); all row tiles of a kv-head on one XCD (ids of one residue class mod 8).
-    int bx, by;
+    int bx, by, piece;
     {
-        const int bid = blockIdx.x;
+        const int bid = blockIdx.x, per_head = ntile * P;
         int rem;
         if ((ny & 7) == 0) {
             const int xcd = bid & 7, li = bid >> 3;
-            by = xcd + 8 * (li / ntile);
-            rem = li % ntile;
+            by = xcd + 8 * (li / per_head);
+            rem = li % per_head;
         } else {
-            by = bid / ntile;
-            rem = bid % ntile;
+            by = bid / per_head;
+            rem = bid % per_head;
         }
-        bx = ntile - 1 - rem;                                // longest (most keys visible) tiles first
+        bx = ntile - 1 - rem / P;                            // longest (most keys visible) tiles first
+        piece = rem % P;
     }
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -150,15 +162,16 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     // so every wavefront gets the same number of (row, key) pairs, where two neighbouring blocks would give the last
     // wavefront a quarter more keys than the first and make the launch as long as that one.  Block A is finished
     // first; the loop then goes on with block B alone (period1).
-    const int npair = ntile * wph;                           // wavefronts per head, over all workgroups
+    const int nblk = (L + 31) / 32, npair = (nblk + 1) / 2;  // blocks of a head; its wavefronts, over all workgroups
     const int pair0 = bx * wph;                              // the workgroup's first pair
-    const int blkA = pair0 + wave / hpw, blkB = 2 * npair - 1 - blkA;
-    const int rowsB_end = min(L, 32 * (2 * npair - pair0));  // end of the workgroup's last block B (its first wavefront's)
+    const int blkA = pair0 + wave / hpw, blkB = nblk - 1 - blkA;   // a middle block is both, and stored twice alike
+    const bool active = blkA < npair;                        // else the wavefront only takes its share of the loads
+    const int rowsB_end = min(L, 32 * (nblk - pair0));       // end of the workgroup's last block B (its first wavefront's)
     const int n_end = t + rowsB_end;                         // keys any row of the workgroup can see
     const int Hkv = Hq / G, n = t + L;
     int my_lim[2];                                           // last visible key of my row, per block
 #pragma unroll
-    for (int x = 0; x < 2; ++x) my_lim[x] = t + min(32 * (x == 0 ? blkA : blkB) + l32, L - 1);
+    for (int x = 0; x < 2; ++x) my_lim[x] = t + min(max(32 * (x == 0 ? blkA : blkB), 0) + l32, L - 1);
     const uint16_t* Kh = K + (size_t)h * cap * D;
     const uint16_t* Vh = V + (size_t)h * cap * D;
     const uint16_t* kch = kc + (size_t)h * D;                // chunk rows of this kv-head: row stride Hkv * D
@@ -283,6 +296,21 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     // fixed number of rows apart as long as the tiles stay inside the cache or inside the chunk, so the
     // addresses are simply advanced after every load and set up anew only when the kind of tile changes.
     const int ntiles = (n_end + TILE - 1) / TILE;
+    // Block A's last visible key lies in sub-block mA (the workgroup's last block A decides for all its
+    // wavefronts, which keeps them in step); its weights are multiplied in period mA + 1, and the sub-block after
+    // it is all masked and leaves zeros in block A's weight registers.  From the tile after that period on the
+    // wavefront runs period1.
+    const int mA = (t + min(L, 32 * min(pair0 + wph, npair)) - 1) / 32;
+    const int j_single = min(ntiles, (mA + 3) >> 1);
+    // The piece's tiles [j0, j1): equal shares of the time, a tile of block B alone being 0.8 of a full one, but the last
+    // piece gets PIECE_LEAD tenths of a tile more: the others then have written their results when it comes to merge them.
+    int j0 = 0, j1 = ntiles;
+    if constexpr (P > 1) {
+        const int share = max(0, (10 * j_single + 8 * (ntiles - j_single) - PIECE_LEAD) / P);
+        auto tile_at = [&](int x) -> int { return x <= 10 * j_single ? x / 10 : j_single + (x - 10 * j_single) / 8; };
+        j0 = tile_at(share * piece);
+        if (piece < P - 1) j1 = tile_at(share * (piece + 1));
+    }
     const uint16_t* dma_pk = Kh;
     const uint16_t* dma_pv = Vh;
     uint32_t dma_dst = 0, dma_rstep = 0, dma_dstep = 0, dma_reg = 0;
@@ -290,7 +318,7 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     auto dma_begin = [&](int tile, int slot) {
         const int kv0 = tile * TILE;
         const bool in_cache = kv0 + TILE <= tc, in_chunk = kv0 >= tc && kv0 + TILE <= n;
-        const int kind = tile >= ntiles ? 2 : (in_cache ? 0 : (in_chunk ? 1 : 3));
+        const int kind = tile >= j1 ? 2 : (in_cache ? 0 : (in_chunk ? 1 : 3));
         if (kind != dma_kind) {                              // a handful of times per workgroup
             if (kind == 3) issue_tile(tile, slot);           // a tile that needs row-by-row addresses: all of it now
             if (kind == 0 || kind == 1) {
@@ -354,6 +382,8 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
 
     // sub-blocks from here on reach past the limit of some row of block A / of block B
     const int first_maskedA = (t + min(32 * blkA, L - 1) + 1) / 32, first_maskedB = (t + min(32 * blkB, L - 1) + 1) / 32;
+    // last sub-block that any row of the wavefront's block A / B sees
+    const int lastA = (t + min(L, 32 * blkA + 32) - 1) / 32, lastB = (t + min(L, 32 * blkB + 32) - 1) / 32;
 
     // One period: sub-block m is in its softmax stage (its logits are in S), sub-block m-1 in its O += V^T P^T
     // stage (its V fragments were requested a period ago), sub-block m+1 in its S = K Q^T stage.  SUB = m & 1.
@@ -386,7 +416,8 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         static_for<0, 16>([&](auto I) {
             constexpr int i = decltype(I)::value;
             constexpr int tt = i >> 3, b = (i >> 1) & 3, x = i & 1;
-            o[x][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * tt + b], as_bf16x8(pf[x][tt]), o[x][b], 0, 0, 0);
+            if (P == 1 || !decltype(mask)::value || SUB == 0 || x == 1 || m - 1 <= lastA)   // else hidden from all its rows
+                o[x][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * tt + b], as_bf16x8(pf[x][tt]), o[x][b], 0, 0, 0);
             if constexpr (i < 8) kf[i] = lds_read_b128<KO>(kaddr[i]);
             constexpr int xs = i >> 3, e0 = 2 * (i & 7);
             const float s0 = masked_logit(mask, xs, e0, m), s1 = masked_logit(mask, xs, e0 + 1, m);
@@ -525,12 +556,12 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int r = 4 * u + (lane >> 4);                   // row of the wavefront: block A's, then block B's
-        const int row = min(32 * (u < 8 ? blkA : blkB) + (r & 31), L - 1);
+        const int row = min(max(32 * (u < 8 ? blkA : blkB), 0) + (r & 31), L - 1);
         const uint16_t* src = q + ((size_t)row * Hq + g) * D + ((lane & 15) ^ (r & 15)) * 8;
         __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)(qlds + u * 1024), 16, 0, 0);
     }
-    issue_tile(0, 0);
-    issue_tile(min(1, ntiles - 1), 1);
+    issue_tile(j0, 0);
+    issue_tile(min(j0 + 1, ntiles - 1), 1);
     asm volatile("s_waitcnt vmcnt(16)" ::: "memory");        // the queries have landed
     {
         const uint32_t base = (uint32_t)(uintptr_t)(lds_void*)qlds + (kaddr[0] - (uint32_t)(uintptr_t)(lds_void*)smem - KREG);
@@ -556,7 +587,7 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         for (int p = 0; p < 8; ++p) vf[i][p] = (__bf16)0.f;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wavefront's loads of tiles 0 and 1 have landed
     __builtin_amdgcn_s_barrier();                            // everyone's have, and everyone has its queries
-    issue_tile(min(2, ntiles - 1), 2);
+    issue_tile(min(j0 + 2, ntiles - 1), 2);
     read_k(Flag<false>{});
     lds_wait(kf);
 #pragma unroll
@@ -570,17 +601,15 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     // In iteration j the K fragments come from tile j (second half) and tile j+1 (first half), the V fragments
     // from tile j; tile j+3 is requested into the buffer tile j-1 has left, and tile j+2 is awaited before the
     // barrier.  Past the last tile the last one is requested again, into a buffer nobody reads any more.
-    // Block A's last visible key lies in sub-block mA (the workgroup's last block A decides for all its
-    // wavefronts, which keeps them in step); its weights are multiplied in period mA + 1, and the sub-block after
-    // it is all masked and leaves zeros in block A's weight registers.  From the tile after that period on the
-    // wavefront runs period1.
-    const int mA = (t + min(L, 32 * (pair0 + wph)) - 1) / 32;
-    const int j_single = min(ntiles, (mA + 3) >> 1);
-    const int j_maskedA = min(j_single, first_maskedA >> 1);  // tiles from here on hold a masked sub-block
-    const int j_maskedB = min(ntiles, first_maskedB >> 1);
+    // In a cut range every wavefront goes by its own blocks: block A is left out once it has seen its last key, and past block
+    // B's last key only the loads go on, so that keys hidden from a block meet it no further than in attn_fwd.
+    const int j_end = !active ? j0 : P == 1 ? j1 : min(j1, (lastB >> 1) + 1);
+    const int j_both = min(j_end, P == 1 ? j_single : (lastA + 3) >> 1);
+    const int j_maskedA = min(j_both, first_maskedA >> 1);   // tiles from here on hold a masked sub-block
+    const int j_maskedB = min(j_end, first_maskedB >> 1);
     auto tile_iter = [&](int j, auto mask, auto both) {
-        const int wrap = ((j + 1) & (NBUF - 1)) == 0 ? TBYTES - NBUF * TBYTES : TBYTES;
-        dma_begin(j + 3, j + 3);
+        const int wrap = ((j - j0 + 1) & (NBUF - 1)) == 0 ? TBYTES - NBUF * TBYTES : TBYTES;
+        dma_begin(j + 3, j - j0 + 3);
         // K: tile j, sub-block 1;  V: tile j, sub-block 0
         if constexpr (decltype(both)::value) period(2 * j, Flag<false>{}, mask);
         else period1(2 * j, Flag<false>{}, mask);
@@ -594,11 +623,18 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
     };
-    int j = 0;
+    int j = j0;
     for (; j < j_maskedA; ++j) tile_iter(j, Flag<false>{}, Flag<true>{});
-    for (; j < j_single; ++j) tile_iter(j, Flag<true>{}, Flag<true>{});
+    for (; j < j_both; ++j) tile_iter(j, Flag<true>{}, Flag<true>{});
     for (; j < j_maskedB; ++j) tile_iter(j, Flag<false>{}, Flag<false>{});
-    for (; j < ntiles; ++j) tile_iter(j, Flag<true>{}, Flag<false>{});
+    for (; j < j_end; ++j) tile_iter(j, Flag<true>{}, Flag<false>{});
+    for (; j < j1; ++j) {                                    // the wavefront's share of the others' loads
+        dma_begin(j + 3, j - j0 + 3);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dma_step(i);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+    }
 #pragma unroll
     for (int x = 0; x < 2; ++x) {                            // ... and its weights are not in the row sums yet
         float tail = 0.f;
@@ -607,13 +643,16 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         lsum[x] += lsa[x] + lsb[x] + tail;
     }
     wait_v();
+    // the last sub-block still owes its O += V^T P^T
+    const bool owesA = 2 * j_end - 1 <= lastA;
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt)                           // the last sub-block still owes its O += V^T P^T
+    for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
         for (int b = 0; b < D / 32; ++b)
 #pragma unroll
             for (int x = 0; x < 2; ++x)
-                o[x][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * tt + b], as_bf16x8(pf[x][tt]), o[x][b], 0, 0, 0);
+                if (P == 1 || x == 1 || owesA)
+                    o[x][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 * tt + b], as_bf16x8(pf[x][tt]), o[x][b], 0, 0, 0);
 
     // ---- normalise and store: lane (row l32, half hh) holds O[row][32b + 8(i/4) + 4hh + i%4] in o[x][b][i] ----
     // Through LDS, so that a store takes four whole rows: eight bytes of 32 rows each, straight from the registers, took
@@ -625,8 +664,73 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     const int e32 = el & 31, eh = el >> 5;
     float ltot[2];
 #pragma unroll
+    for (int x = 0; x < 2; ++x) ltot[x] = lsum[x] + xhalf(lsum[x]);
+    // ---- pieces: (o, m, l) of a wavefront as its registers hold them, 1 KB a store, written through to memory; the hand-off
+    // is that of the scoring kernels.  The last piece looks first whether the others have arrived and then need not write its
+    // own; otherwise whoever arrives last merges.  No workgroup waits for another one.
+    if constexpr (P == 2) {
+        __shared__ int s_arrived;
+        constexpr int VECS = 2 * D / 8 + 1;                  // 16-byte vectors of a lane: o of two blocks, then (m, l) of both
+        const int unit = by * ntile + bx;
+        const int bytes = 4 * VECS * 1024;
+        auto rsrc_of = [&](int pc) { return __builtin_amdgcn_make_buffer_rsrc((char*)part + ((size_t)unit * P + pc) * bytes, 0, bytes, 0x00020000); };
+        const int voff = el * 16, soff = wave * (VECS * 1024);
+        bool all_here = false;
+        if (piece == P - 1) {
+            if (tid == 0) s_arrived = __hip_atomic_load(arrived + unit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            all_here = s_arrived == P - 1;
+        }
+        if (!all_here) {
+            const auto dst = rsrc_of(piece);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4)
+                        __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(o[x][b][4 * q4]), __float_as_uint(o[x][b][4 * q4 + 1]),
+                                                                     __float_as_uint(o[x][b][4 * q4 + 2]), __float_as_uint(o[x][b][4 * q4 + 3])},
+                                                               dst, voff, soff + (16 * x + 4 * b + q4) * 1024, 16 /* sc1 */);
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(m_ref[0]), __float_as_uint(ltot[0]), __float_as_uint(m_ref[1]), __float_as_uint(ltot[1])},
+                                                   dst, voff, soff + (VECS - 1) * 1024, 16);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid == 0) s_arrived = __hip_atomic_fetch_add(arrived + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            if (s_arrived != P - 1) {                        // one of the two: the unit's share of a chunk that enters the cache
+                if (ap.k) append_share(ap, unit, gridDim.x / P, tid, NT);
+                return;
+            }
+        }
+        if (tid == 0) __hip_atomic_store(arrived + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+        // Two products, rounded, and their sum: the same bits whichever of the two pieces does it.
+        {
+#pragma clang fp contract(off)
+            const auto src = rsrc_of(1 - piece);
+            const u32x4 ml = __builtin_amdgcn_raw_buffer_load_b128(src, voff, soff + (VECS - 1) * 1024, 16);
+            u32x4 other[2][16];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) other[x][i] = __builtin_amdgcn_raw_buffer_load_b128(src, voff, soff + (16 * x + i) * 1024, 16);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const float mo = __uint_as_float(ml[2 * x]), lo = __uint_as_float(ml[2 * x + 1]);
+                const float mt = fmaxf(m_ref[x], mo), mz = mt == -__builtin_inff() ? 0.f : mt;
+                const float w = fast_exp2(m_ref[x] - mz), wo = fast_exp2(mo - mz);   // no key seen: m = -inf, weight 0
+                m_ref[x] = mt;
+                ltot[x] = w * ltot[x] + wo * lo;
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[x][i >> 2][4 * (i & 3) + e] = w * o[x][i >> 2][4 * (i & 3) + e] + wo * __uint_as_float(other[x][i][e]);
+            }
+        }
+    }
+    if (!active) return;
+#pragma unroll
     for (int x = 0; x < 2; ++x) {
-        ltot[x] = lsum[x] + xhalf(lsum[x]);
         const float inv = 1.0f / ltot[x];
 #pragma unroll
         for (int b = 0; b < D / 32; ++b)
@@ -651,17 +755,29 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
 
 }  // namespace
 
+int attn_mfma64_units(const Geometry& g, int L)
+{
+    const int hpw = (g.G % 4 == 0) ? 4 : ((g.G % 2 == 0) ? 2 : 1);   // heads of a group that share a workgroup's K/V tiles
+    const int wph = 4 / hpw, pairs = ((L + 31) / 32 + 1) / 2;
+    return (pairs + wph - 1) / wph * g.Hkv * (g.G / hpw);
+}
+
+size_t attn_mfma64_piece_bytes() { return 4 * (2 * w64::D / 8 + 1) * 1024; }
+
 hipError_t launch_attn_mfma64(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                              void* out, float* lse, hipStream_t st)
+                              void* out, float* lse, const CutScratch& sc, int pieces, const AppendJob& ap, hipStream_t st)
 {
     if (g.d != 128) return hipErrorInvalidValue;
-    const int hpw = (g.G % 4 == 0) ? 4 : ((g.G % 2 == 0) ? 2 : 1);   // heads of a group that share a workgroup's K/V tiles
-    const int wph = 4 / hpw;
-    const int ntile = (L + 64 * wph - 1) / (64 * wph), ny = g.Hkv * (g.G / hpw);
-    hipLaunchKernelGGL(attn_fwd64_kernel, dim3(ntile * ny), dim3(w64::NT), 0, st, (const uint16_t*)q,
-                       (const uint16_t*)c.K, (const uint16_t*)c.V, (const uint16_t*)ks.k, (const uint16_t*)ks.v, ks.rows,
-                       (uint16_t*)out, lse, t, L, g.Hq, g.G, g.cap, g.max_chunk, hpw, ntile, ny,
-                       (float)(g.scale * (double)LOG2E));
+    const int hpw = (g.G % 4 == 0) ? 4 : ((g.G % 2 == 0) ? 2 : 1);
+    const int ny = g.Hkv * (g.G / hpw), units = attn_mfma64_units(g, L), ntile = units / ny;
+    if (pieces > 1 && (units > sc.units || t + L - L / 2 < CUT_MIN_KEYS)) return hipErrorInvalidValue;
+#define INFMLLM_FWD64(P)                                                                                                   \
+    hipLaunchKernelGGL(attn_fwd64_kernel<P>, dim3(units * P), dim3(w64::NT), 0, st, (const uint16_t*)q, (const uint16_t*)c.K, \
+                       (const uint16_t*)c.V, (const uint16_t*)ks.k, (const uint16_t*)ks.v, ks.rows, (uint16_t*)out, lse, t, L, \
+                       g.Hq, g.G, g.cap, g.max_chunk, hpw, ntile, ny, (float)(g.scale * (double)LOG2E), sc.part, sc.arrived, ap)
+    if (pieces == 2) INFMLLM_FWD64(2);
+    else INFMLLM_FWD64(1);
+#undef INFMLLM_FWD64
     return hipGetLastError();
 }
 

@@ -112,13 +112,23 @@ struct RowsScratch {
     long cap_rows;      // most (query row, piece) pairs of a launch
 };
 
+// The same of attn_fwd64 launches whose key ranges are cut in two.
+constexpr int CUT_MAX_UNITS = 128;   // 256 workgroups: one round
+constexpr int CUT_MIN_KEYS = 512;    // of the rows in the middle of a chunk: every piece of every unit has a tile then
+struct CutScratch {
+    float* part;
+    int* arrived;       // [units] tickets, zero between launches
+    int units;          // 0: none
+};
+
 // a2 on bf16 MFMA (bf16 streams only): out and the row log-sum-exp (base 2).  With a job (ap.k set) the chunk also
 // enters the cache, beside the attention.
 hipError_t launch_attn_mfma(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                            void* out, float* lse, const RowsScratch& sc, const AppendJob& ap, hipStream_t st);
+                            void* out, float* lse, const RowsScratch& sc, const CutScratch& cut, const AppendJob& ap, hipStream_t st);
 
 // Which kernel that is for a chunk of L rows that makes n keys (tensors aligned to 16 bytes).
-const char* attn_mfma_kernel(const Geometry& g, int n, int L, long cap_rows);
+const char* attn_mfma_kernel(const Geometry& g, int n, int L, long cap_rows, int cut_units);
+int attn_cut_units(const Geometry& g);   // most units that a chunk's launch may cut: what a workspace should hold scratch for
 
 // a2 and a3+a4 of fp32 streams, on the fp32 matrix cores; lse is the natural log-sum-exp.
 hipError_t launch_attn_f32(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
@@ -128,8 +138,12 @@ hipError_t launch_score_f32(const Geometry& g, const CacheView& c, const KeySour
 
 // The same for head_dim 128 with 64 query rows per wavefront (one wavefront per SIMD, 256-row workgroups):
 // the shape for long key ranges and grids that fill the chip; launch_attn_mfma picks it by itself.
+// With two pieces every workgroup's key range is shared by two workgroups, at most sc.units workgroups' worth of rows, and
+// the chunk enters the cache with ap.
 hipError_t launch_attn_mfma64(const Geometry& g, const CacheView& c, const KeySource& ks, const void* q, int t, int L,
-                              void* out, float* lse, hipStream_t st);
+                              void* out, float* lse, const CutScratch& sc, int pieces, const AppendJob& ap, hipStream_t st);
+int attn_mfma64_units(const Geometry& g, int L);                     // its workgroups of uncut key ranges
+size_t attn_mfma64_piece_bytes();                                    // what a piece leaves for its merge
 
 constexpr long ROWS_MAX_PARTS = 16384;
 constexpr int DECODE_MAX_TOKENS = 64;    // most tokens a launch decodes

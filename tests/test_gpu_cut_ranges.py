@@ -1,0 +1,70 @@
+"""attn_fwd64 with every key range cut in two: two workgroups share a unit of rows, whoever arrives last merges."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import OracleStream
+from paper_2409_09086_amd import binding as B
+from paper_2409_09086_amd.workloads import random_chunk
+from _parity import LockStep
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads,kv,budget,chunks,tile", [
+    # the first chunk fills most of the cache; the short one after it fits and enters the cache beside a cut launch
+    (4, 4, 768, [700, 68, 1, 33, 95, 129, 300], 5),
+    (8, 2, 700, [640, 31, 32, 64, 257, 385], 5),              # four heads share a workgroup's tiles
+    (4, 2, 600, [600, 63, 191, 320], 5),                      # two
+    (6, 2, 800, [800, 159, 500], 5),                          # three: one head per workgroup
+    (24, 24, 2400, [2300, 700], None),                        # by the launch's own rule
+])
+def test_cut_ranges_match_oracle(heads, kv, budget, chunks, tile):
+    recent, d = budget // 4, 128
+    gpu = B.Stream(budget, recent, heads, kv, d, dtype=torch.bfloat16, bias=1e-3, max_chunk=max(chunks), attn_tile=tile)
+    ls = LockStep(gpu, OracleStream(budget, recent, heads, kv, d, bias=1e-3))
+    cut = 0
+    for step, L in enumerate(chunks):
+        name = gpu.kernel("attn", len(gpu), L)
+        if tile:
+            assert name == ("attn_fwd64, cut" if len(gpu) + L - L // 2 >= 512 else "attn_fwd64")
+        cut += name == "attn_fwd64, cut"
+        print("cut ranges", (heads, kv, budget), "step", step, "L", L, name, flush=True)
+        ls.step(*random_chunk(6100 + step, L, heads, kv, d, "bf16"), check_state=True)
+    assert cut >= 1
+
+
+def one_step(heads, kv, budget, L, seed, spoil=None, cut=True):
+    """Output and scores of a step on a full cache; spoil(k, v) changes the chunk."""
+    s = B.Stream(budget, budget // 4, heads, kv, 128, dtype=torch.bfloat16, max_chunk=L, attn_tile=5 if cut else 1)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    K, V = (torch.randn((kv, budget, 128), generator=g, device="cuda").bfloat16() for _ in range(2))
+    s.load(K, V, torch.arange(budget, dtype=torch.int32, device="cuda").repeat(kv, 1).contiguous(), budget)
+    q, k, v = (x.cuda() for x in random_chunk(6200 + seed, L, heads, kv, 128, "bf16"))
+    if spoil:
+        spoil(k, v)
+    assert s.kernel("attn", budget, L) == ("attn_fwd64, cut" if cut else "attn_fwd")
+    out = s.step(q, k, v)[0]
+    return out, s.last_scores()
+
+
+@pytest.mark.parametrize("heads,kv,budget,L", [(32, 32, 1024, 576), (32, 8, 2048, 1024), (3, 3, 900, 97)])
+def test_the_same_bits_whoever_merges(heads, kv, budget, L):
+    print("merge order", (heads, kv, budget, L), flush=True)
+    want = one_step(heads, kv, budget, L, 7)
+    for _ in range(6):
+        got = one_step(heads, kv, budget, L, 7)
+        assert torch.equal(got[0].view(torch.int16), want[0].view(torch.int16)) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("heads,kv,budget,L", [(4, 4, 900, 700), (8, 2, 1000, 451), (4, 4, 641, 576)])
+@pytest.mark.parametrize("at", [0.1, 0.45, 0.8, 1.0])
+def test_hidden_values_that_are_not_finite_reach_no_more_rows_than_in_attn_fwd(heads, kv, budget, L, at):
+    row = min(L - 1, int(L * at))
+
+    def spoil(k, v):
+        v[row] = float("nan")
+
+    print("hidden nan", (heads, kv, budget, L), row, flush=True)
+    got, ref = (one_step(heads, kv, budget, L, 9, spoil, cut)[0].isnan().any(-1) for cut in (True, False))
+    assert got[row:].all() and not (got & ~ref).any(), np.argwhere((got & ~ref).cpu().numpy())[:8]
