@@ -654,14 +654,15 @@ int infmllm_stream_profile_read(infmllm_stream_t* s, float* ms, int* launches)
 }
 
 // Decoding steps of T tokens on a stream whose state has been checked: launches, then the host-side counters.  On the
-// matrix cores the T tokens share one launch (decode_tokens_per_launch says how many may), else T is 1.
-static int decode_some(infmllm_stream* s, const void* q, const void* k, const void* v, void* out, int T)
+// matrix cores the T tokens share one launch (decode_tokens_per_launch says how many may), else T is 1.  over: out overlaps an
+// input; with a single piece the launch would store it before the token enters the cache, which therefore happens first.
+static int decode_some(infmllm_stream* s, const void* q, const void* k, const void* v, void* out, int T, bool over)
 {
     s->mark(INFMLLM_K_DECODE, 0);
     const int t = s->len;
     hipError_t e;
     CacheView att = s->cache;
-    const bool rope = s->rope_base > 0.0, in_place = !s->mfma() || (aligned16(k) && aligned16(v));
+    const bool rope = s->rope_base > 0.0, in_place = !s->mfma() || (aligned16(k) && aligned16(v) && !(over && t + T <= s->dec_keys));
     if (rope || !in_place)
         if ((e = launch_append(append_job(s->g, s->cache, k, v, t, T, s->streamed, nullptr, nullptr), s->st)) != hipSuccess) return fail_hip(e, "decode: append");
     if (rope) {
@@ -720,7 +721,7 @@ int infmllm_decode_n(infmllm_stream_t* s, const void* q, const void* k, const vo
     for (int i = 0; i < n_tokens;) {
         const int T = alone ? 1 : decode_tokens_per_launch(s, n_tokens - i);
         const int rc = decode_some(s, (const char*)q + i * qrow, (const char*)k + i * krow, (const char*)v + i * krow,
-                                   (char*)out + i * qrow, T);
+                                   (char*)out + i * qrow, T, alone);
         if (rc != INFMLLM_OK) return rc;
         i += T;
     }
