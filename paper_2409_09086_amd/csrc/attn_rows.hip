@@ -42,13 +42,27 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
     __shared__ int s_ticket;
     __shared__ float2 s_part[NRB == 1 ? RW_TICKET_PARTS : 1];
 
-    // Workgroup = (piece, kv-head, row group), the piece fastest and the row group slowest: the row groups of a piece,
-    // which read the same keys, land on one XCD where the number of (piece, head) pairs is a multiple of 8.
-    const int sp = blockIdx.x, h = blockIdx.y, rg = blockIdx.z;
+    // Workgroup = (piece, kv-head, row group), the piece fastest and the row group slowest: the row groups of a piece, which
+    // read the same keys, land on one XCD where the number of (piece, head) pairs is a multiple of 8.  Groups of 32 rows may take
+    // several rounds of the chip, over more keys and values than the L2s hold (32 MB); they then get neighbouring ids of one residue
+    // class mod 8, i.e. one XCD at one time, so that a key comes into its L2 once.  us with the merge: 64 tokens over 8256 rows of 32
+    // heads, 134 MB, 384 workgroups 48.0 -> 43.5; 40 over 8232 46.1 -> 42.9; not where they fit: 64 over 2112 of 32 heads 26.6 / 26.9, 34
+    // tokens of 32 heads on 8 over 4130 30.1 / 31.4.
+    const int t = a.t;
+    int sp = blockIdx.x, h = blockIdx.y, rg = blockIdx.z;
+    if constexpr (NRB == 2) {
+        const unsigned pairs = gridDim.x * gridDim.y;
+        if (pairs * gridDim.z > (D == 64 ? 512u : 256u) && (pairs & 7) == 0 && (uint64_t)(t + a.L) * a.Hkv * (D * 4) > (48u << 20)) {
+            const unsigned id = blockIdx.x + gridDim.x * blockIdx.y + pairs * blockIdx.z, li = id >> 3;
+            const unsigned pair = li / gridDim.z * 8 + (id & 7);
+            rg = (int)(li % gridDim.z);
+            h = (int)(pair / gridDim.x);
+            sp = (int)(pair % gridDim.x);
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.L * a.G, row0 = rg * C::ROWS;
-    const int t = a.t;
     auto token = [&](int rho) -> int { return rows_token(a, rho); };
     const int first_lim = t + token(row0);                     // last key the group's first row sees
     const int n_end = t + token(min(row0 + C::ROWS, M) - 1) + 1;

@@ -108,3 +108,22 @@ def test_profile_has_a_placement_interval_only_where_there_is_a_launch(L, placed
         assert all(p[k][1] == (want[k] if k in names else 0) for k in want), (names, p)
         if len(names) > 2:
             assert p["evict"][0] >= p["select"][0] + p["compact"][0] - 1e-3
+
+
+def test_row_groups_of_a_key_beside_each_other():
+    """Launches of several rounds over more keys than the L2s hold number their workgroups in another order: tokens decoded
+    together bit for bit as one at a time."""
+    heads, kv, d, budget, n = 32, 32, 128, 3200, 64
+    a, b = (B.Stream(budget, budget // 4, heads, kv, d, dtype=torch.bfloat16, max_chunk=16, max_decode=n) for _ in range(2))
+    g = torch.Generator(device="cuda").manual_seed(53)
+    K, V = (torch.randn((kv, budget, d), generator=g, device="cuda").bfloat16() for _ in range(2))
+    pos = torch.arange(budget, dtype=torch.int32, device="cuda").repeat(kv, 1).contiguous()
+    for s in (a, b):
+        s.load(K, V, pos, budget)
+    q, k, v = (x.cuda() for x in random_chunk(4950, n, heads, kv, d, "bf16"))
+    print("row groups", flush=True)
+    out = a.decode_n(q, k, v)
+    one = torch.cat([b.decode(*(x[i:i + 1].contiguous() for x in (q, k, v))) for i in range(n)])
+    assert torch.equal(out.view(torch.int16), one.view(torch.int16))
+    for x, y in zip(a.export(), b.export()):
+        assert torch.equal(x, y)
