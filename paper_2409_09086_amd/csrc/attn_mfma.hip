@@ -468,7 +468,7 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
     }
     const int col0 = bx * (256 * CB) + cg * (32 * CB);
     char* const mine = smem + cg * (CB * Cols::BLOCK);
-    const int krow = Cols::lookup(rows, h, cap, col0, ncol, CB == 2 ? lane : l32);
+    Cols::template request<CB>(mine, K, kc, Cols::lookup(rows, h, cap, col0, ncol, CB == 2 ? lane : l32), tc, h, Hkv, cap, col0, lane);
 
     f32x16 part[CB];
 #pragma unroll
@@ -559,7 +559,6 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
         if (tid < TROWS) *(float*)(base + QBYTES + tid * 4) = (stl_idx >= 0) ? s_lse[stl_idx] : stl;
     };
     if (niter > 0) fetch(true);
-    Cols::template request<CB>(mine, K, kc, krow, tc, h, Hkv, cap, col0, lane);
     bf16x8 kf[CB][D / 16];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the wavefront's columns have landed
 #pragma unroll
@@ -990,6 +989,9 @@ ScorePlan score_plan(const Geometry& g, int ncol, int lq, bool has_part)
         if (rsplit > 4) rsplit = 4;
         if (rsplit > niter / 2) rsplit = niter / 2;
         if (rsplit < 1 || !has_part || wgsw * rsplit * (wcols / 256) > SCORE_SPLIT_WGS) rsplit = 1;
+        // two slices of few rows: their sums cost more than the narrower columns, if those fill half the chip (us, two slices / none, 32 heads on 16, 193 rows and
+        // 2760 columns 18.5 / 16.0, 300 rows 21.5 / 18.8, 420 rows 24.4 / 22.3; 20 heads, 400 rows, 2000 columns 19.4 / 16.8)
+        if (rsplit == 2 && g.d == 128 && niter < 8 && wgs256 >= 128) rsplit = 1;
     }
     const bool wide = wgsw >= 200 || rsplit > 1;
     return ScorePlan{false, wide, wide ? nxw : (ncol + 255) / 256, rsplit};
