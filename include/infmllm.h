@@ -87,7 +87,9 @@ enum {
                                     any other value = 128 query rows per workgroup, keys uncut.  head_dim 128:
                                     1 = 128 query rows x 2 key ways x 64 keys, 2 = 64 rows x 4 ways x 32,
                                     3 = 128 rows x 2 ways x 32, 4 = 128 rows x 1 way x 64, 5 = 256 rows with
-                                    64 rows per wavefront.  Results are the same up to rounding order  */
+                                    64 rows per wavefront, every key range shared by two workgroups where the middle
+                                    rows see 512 keys and the workspace has the scratch for it.  Results are the same
+                                    up to rounding order  */
 };
 
 /*
@@ -297,7 +299,8 @@ enum {
  * Debug/test: the kernel that an infmllm_step of `tokens` tokens on `cached` cached rows launches for its attention
  * (which = INFMLLM_K_ATTN), scoring (INFMLLM_K_SCORE) and placement (INFMLLM_K_COMPACT), or an infmllm_decode_n for
  * its tokens (INFMLLM_K_DECODE); "" if it launches none (a step that evicts nothing; a placement that the selection
- * takes along).  Host-only, and the stream need not be attached.  The names are the library's own and may change; they hold
+ * takes along).  Host-only, and the stream need not be attached: before that it is not known whether its workspace has the scratch
+ * for attn_fwd64's cut key ranges ("attn_fwd64, cut"), and the answer is that without it.  The names are the library's own and may change; they hold
  * for tensors aligned to 16 bytes that do not overlap.  Null for arguments no such call can have.
  */
 const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cached, int tokens);

@@ -806,7 +806,7 @@ const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cach
     switch (which) {
         case INFMLLM_K_ATTN:
             if (tokens > g.max_chunk) return nullptr;
-            return s->mfma() ? attn_mfma_kernel(g, n, tokens, s->attached ? s->rows.cap_rows : s->layout().rows_cap, s->attached ? s->cut.units : s->layout().cut_units) : s->f32() ? "attn_f32" : "attn_simple";
+            return s->mfma() ? attn_mfma_kernel(g, n, tokens, s->attached ? s->rows.cap_rows : s->layout().rows_cap, s->attached ? s->cut.units : 0) : s->f32() ? "attn_f32" : "attn_simple";
         case INFMLLM_K_SCORE:
             if (tokens > g.max_chunk) return nullptr;
             if (!evicts || n <= g.R) return "";
