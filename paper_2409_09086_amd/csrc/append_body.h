@@ -3,7 +3,8 @@
 // A launch of its own for this took 5 us and the list another 4.5 us, for 4 MB that take 1 us (1024 tokens of 8 x 128
 // heads): launch, one trip to memory, drain.  The attention kernels that read the chunk in place therefore do a share each:
 // attn_fwd and attn_f32 before their loop, where the trip overlaps with that of their first keys, attn_rows after it, because it has
-// no registers left for it earlier, attn_rows64 in workgroups of its own.  Measured, same box: small fp32 document (4 x 64 heads, four chunks of 64 that fit, four that
+// no registers left for it earlier, attn_rows64 in workgroups of its own, attn_fwd64 with cut key ranges by the one of two
+// workgroups that does not merge.  Measured, same box: small fp32 document (4 x 64 heads, four chunks of 64 that fit, four that
 // evict) 143.5 -> 121 us; fp32 document of 1280 tokens (8 x 128) 122 -> 110; bf16 document of 4500 tokens (32 heads of 128
 // on 8) 303 -> 285.
 #pragma once

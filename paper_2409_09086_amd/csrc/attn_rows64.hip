@@ -7,8 +7,8 @@
 // a wavefront's 256, eight wavefronts on a CU); the query fragments then have no place in registers and are read from
 // LDS, which all wavefronts share, beside the K fragments.  K and V have one buffer each per wavefront: a run's K
 // buffer is refilled as soon as S has its fragments, its V buffer as soon as O has.  A pass of 256 keys takes 1.9 us, two
-// workgroups of 32 rows 2.7.  No pipe is full in it: products 1.0 us (matrix pipes busy 28 % of the SIMD-cycles of a launch of
-// 33 us, 32 x 128 heads, 512 rows on 2560 keys), LDS reads 0.7 (indexed reads 21 % of its CU-cycles, no conflicts),
+// workgroups of 32 rows 2.7.  No pipe is full in it: products 1.0 us (matrix pipes busy 30 % of the SIMD-cycles of a launch of
+// 32 us, 32 x 128 heads, 512 rows on 2560 keys), LDS reads 0.7 (indexed reads 21 % of its CU-cycles, few conflicts),
 // the bytes that come in 1.1; a wavefront goes through the three one after the other, and two share a SIMD.
 #include "append_body.h"
 #include "attn_rows.h"
