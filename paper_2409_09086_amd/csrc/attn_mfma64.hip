@@ -553,12 +553,20 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     // again; nobody stores them.
     char* const qlds = smem + (wave < 2 ? KREG : VREG) + 2 * TBYTES + (wave & 1) * TBYTES;
     static_assert(2 * 32 * ROWB == TBYTES, "a wavefront's queries fill one tile buffer");
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
+    auto query_piece = [&](int u) -> const uint16_t* {       // what this lane takes of load u
         const int r = 4 * u + (lane >> 4);                   // row of the wavefront: block A's, then block B's
         const int row = min(max(32 * (u < 8 ? blkA : blkB), 0) + (r & 31), L - 1);
-        const uint16_t* src = q + ((size_t)row * Hq + g) * D + ((lane & 15) ^ (r & 15)) * 8;
-        __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)(qlds + u * 1024), 16, 0, 0);
+        return q + ((size_t)row * Hq + g) * D + ((lane & 15) ^ (r & 15)) * 8;
+    };
+    if (((uintptr_t)q & 15) == 0) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) __builtin_amdgcn_global_load_lds((global_void*)query_piece(u), (lds_void*)(qlds + u * 1024), 16, 0, 0);
+    } else {                                                 // not aligned for direct loads: by way of registers
+        u32x4 v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = *(const u32x4*)query_piece(u);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) *(u32x4*)(qlds + u * 1024 + lane * 16) = v[u];
     }
     issue_tile(j0, 0);
     issue_tile(min(j0 + 1, ntiles - 1), 1);

@@ -68,3 +68,22 @@ def test_hidden_values_that_are_not_finite_reach_no_more_rows_than_in_attn_fwd(h
     print("hidden nan", (heads, kv, budget, L), row, flush=True)
     got, ref = (one_step(heads, kv, budget, L, 9, spoil, cut)[0].isnan().any(-1) for cut in (True, False))
     assert got[row:].all() and not (got & ~ref).any(), np.argwhere((got & ~ref).cpu().numpy())[:8]
+
+
+@pytest.mark.parametrize("L,by", [(576, 1), (97, 4), (97, 8), (640, 3)])
+def test_queries_and_outputs_that_start_anywhere(L, by):
+    """The same bits as from aligned tensors, whole key ranges (the first chunk) and cut ones."""
+    heads, kv, d, budget = 4, 2, 128, 700
+    a, b = (B.Stream(budget, 200, heads, kv, d, dtype=torch.bfloat16, max_chunk=L, attn_tile=5) for _ in range(2))
+    cut = []
+    for step in range(8 if L < 100 else 3):
+        q, k, v = (x.cuda() for x in random_chunk(6300 + step, L, heads, kv, d, "bf16"))
+        print("unaligned", L, by, "step", step, flush=True)
+        cut.append(a.kernel("attn", len(a), L) == "attn_fwd64, cut")
+        buf, out = (torch.empty(q.numel() + by, dtype=torch.bfloat16, device="cuda")[by:].view(q.shape) for _ in range(2))
+        buf.copy_(q)
+        assert buf.data_ptr() % 16 == 2 * by % 16
+        assert torch.equal(a.step(buf, k, v, out=out)[0], b.step(q, k, v)[0])
+    assert not cut[0] and cut[-1]
+    for x, y in zip(a.export(), b.export()):
+        assert torch.equal(x, y)
