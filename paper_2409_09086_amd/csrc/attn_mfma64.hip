@@ -351,14 +351,20 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     };
 
     // ---- the pieces of a period ----------------------------------------------------------------------
-    auto rescale = [&](int x, float mx) {                    // rare: the reference of block x moves
-        if (__any(mx > m_ref[x] + RESCALE_TAU)) {
+    // A key that is a reference weighs exactly 1, the others' weights are rounded to bf16.  In attn_fwd a row has a reference in each
+    // of two key ways, the largest of 64 logits; with the largest of 32 in each of two pieces a cut launch's output had the larger
+    // error (against fp64, 32 heads on 8, 512 rows on 1024 keys, six inputs: 0.6 to 0.8 % above attn_fwd's; 1024 rows on 5120 keys
+    // 0.1 %).  In a cut range the references therefore move once more, by any amount, in the second sub-block: 0.2 to 0.3 %
+    // and 0.1 % below, for 0.5 to 1 us a launch.
+    auto rescale = [&](int x, float mx, float tau, bool first) {   // rare: the reference of block x moves; first: O is zero
+        if (__any(mx > m_ref[x] + tau)) {
             const float m_new = fmaxf(m_ref[x], mx);
             const float mu = (m_new == -__builtin_inff()) ? 0.f : m_new;
             const float alpha = fast_exp2(m_ref[x] - mu);    // m_ref = -inf gives 0
             m_ref[x] = m_new;
             m_use[x] = mu;
             lsum[x] *= alpha;
+            if (first) return;
 #pragma unroll
             for (int b = 0; b < D / 32; ++b)
 #pragma unroll
@@ -437,6 +443,7 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         float mmix;
         asm("v_max_f32 %0, %1, %2" : "=v"(mmix) : "v"(__uint_as_float(sw[0])), "v"(__uint_as_float(sw[1])));
         if (__any(mmix > thr_mix)) {
+            const bool first = P == 2 && SUB == 0 && m == 2 * j0, second = P == 2 && SUB == 1 && m == 2 * j0 + 1;
             // rare: O and the row sums hold all of sub-block m-1 (in the old reference) when they are rescaled
             const float mx0 = xhalf_max(mx[0]) * c, mx1 = xhalf_max(mx[1]) * c;
 #pragma unroll
@@ -444,12 +451,12 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
                 lsum[x] += lsa[x] + lsb[x];
                 lsa[x] = 0.f; lsb[x] = 0.f;
                 const float old_use = m_use[x];
-                rescale(x, x == 0 ? mx0 : mx1);
+                rescale(x, x == 0 ? mx0 : mx1, second ? 0.f : RESCALE_TAU, first);
                 const float shift = old_use - m_use[x];      // S c - m was formed with the old reference
 #pragma unroll
                 for (int e = 0; e < 16; ++e) tw[x][e] += shift;
             }
-            thr_mix = ((hh ? m_ref[1] : m_ref[0]) + RESCALE_TAU) * inv_c;
+            thr_mix = ((hh ? m_ref[1] : m_ref[0]) + (first ? 0.f : RESCALE_TAU)) * inv_c;
         }
         lds_wait(kf);
         static_for<0, 16>([&](auto I) {
@@ -518,7 +525,7 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
             lsum[1] += lsa[1] + lsb[1];
             lsa[1] = 0.f; lsb[1] = 0.f;
             const float old_use = m_use[1];
-            rescale(1, mx1);
+            rescale(1, mx1, RESCALE_TAU, false);
             const float shift = old_use - m_use[1];
 #pragma unroll
             for (int e = 0; e < 16; ++e) tw[1][e] += shift;

@@ -57,6 +57,23 @@ def test_the_same_bits_whoever_merges(heads, kv, budget, L):
         assert torch.equal(got[0].view(torch.int16), want[0].view(torch.int16)) and torch.equal(got[1], want[1])
 
 
+@pytest.mark.parametrize("heads,kv,budget,L", [(32, 8, 512, 512), (32, 16, 600, 300)])
+def test_error_is_no_larger_than_that_of_attn_fwd(heads, kv, budget, L):
+    """2-norm of the output's error against fp64, over that of attn_fwd's (128 rows, two key ways).  Both round the weights and the
+    output to bf16, so the ratio only scatters with the input, by 0.1 % over the millions of elements here; references from
+    fewer keys than attn_fwd's gave 1.005 to 1.008."""
+    for seed in (1, 2):
+        q, k, v = random_chunk(6200 + seed, L, heads, kv, 128, "bf16")
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        K, V = (torch.randn((kv, budget, 128), generator=g, device="cuda").bfloat16() for _ in range(2))
+        orc = OracleStream(budget, budget // 4, heads, kv, 128, bias=0.0)
+        orc.load(K.double().cpu().numpy(), V.double().cpu().numpy(), np.tile(np.arange(budget, dtype=np.int32), (kv, 1)), budget)
+        want = orc.attend(*(x.double().numpy() for x in (q, k, v)))
+        print("error", (heads, kv, budget, L), seed, flush=True)
+        err = [np.linalg.norm(one_step(heads, kv, budget, L, seed, cut=cut)[0].double().cpu().numpy() - want) for cut in (True, False)]
+        assert err[0] <= 1.001 * err[1], err[0] / err[1]
+
+
 @pytest.mark.parametrize("heads,kv,budget,L", [(4, 4, 900, 700), (8, 2, 1000, 451), (4, 4, 641, 576)])
 @pytest.mark.parametrize("at", [0.1, 0.45, 0.8, 1.0])
 def test_hidden_values_that_are_not_finite_reach_no_more_rows_than_in_attn_fwd(heads, kv, budget, L, at):
