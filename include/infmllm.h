@@ -299,9 +299,10 @@ enum {
  * Debug/test: the kernel that an infmllm_step of `tokens` tokens on `cached` cached rows launches for its attention
  * (which = INFMLLM_K_ATTN), scoring (INFMLLM_K_SCORE) and placement (INFMLLM_K_COMPACT), or an infmllm_decode_n for
  * its tokens (INFMLLM_K_DECODE); "" if it launches none (a step that evicts nothing; a placement that the selection
- * takes along).  Host-only, and the stream need not be attached: before that it is not known whether its workspace has the scratch
- * for attn_fwd64's cut key ranges ("attn_fwd64, cut"), and the answer is that without it.  The names are the library's own and may change; they hold
- * for tensors aligned to 16 bytes that do not overlap.  Null for arguments no such call can have.
+ * takes along).  Host-only, and the stream need not be attached; the answer before that is the one for a workspace of
+ * infmllm_stream_workspace_bytes(s) bytes (infmllm_stream_attach_static may leave scratch out, and launches then do without).  The
+ * names are the library's own and may change; they hold for tensors aligned to 16 bytes that do not overlap.  Null for arguments
+ * no such call can have.
  */
 const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cached, int tokens);
 

@@ -804,9 +804,12 @@ const char* infmllm_stream_kernel(const infmllm_stream_t* s, int which, int cach
     const int n = cached + tokens;
     const bool evicts = n > g.B, ranks_by_age = g.policy == POLICY_WINDOW || g.policy == POLICY_INITIAL_RECENT;
     switch (which) {
-        case INFMLLM_K_ATTN:
+        case INFMLLM_K_ATTN: {
             if (tokens > g.max_chunk) return nullptr;
-            return s->mfma() ? attn_mfma_kernel(g, n, tokens, s->attached ? s->rows.cap_rows : s->layout().rows_cap, s->attached ? s->cut.units : 0) : s->f32() ? "attn_f32" : "attn_simple";
+            if (!s->mfma()) return s->f32() ? "attn_f32" : "attn_simple";
+            const infmllm_stream::Layout lay = s->layout();    // what the stream holds once it is attached
+            return attn_mfma_kernel(g, n, tokens, lay.rows_cap, lay.cut_units);
+        }
         case INFMLLM_K_SCORE:
             if (tokens > g.max_chunk) return nullptr;
             if (!evicts || n <= g.R) return "";

@@ -179,7 +179,7 @@ def test_kernel_names_on_the_host():
             assert L.infmllm_stream_set_param(h, getattr(B, "PARAM_" + k), v) == B.OK
         return h
     for chunk, args, want in [(512, (2048, 512, 32, 32, 128, B.BF16), (b"attn_rows64", b"score_kernel", b"place")),
-                              (1024, (4096, 1024, 32, 8, 128, B.BF16), (b"attn_fwd", b"score_kernel, sliced", b"place")),
+                              (1024, (4096, 1024, 32, 8, 128, B.BF16), (b"attn_fwd64, cut", b"score_kernel, sliced", b"place")),
                               (2048, (8192, 2048, 32, 32, 128, B.BF16), (b"attn_fwd64", b"score_kernel", b"place")),
                               (37, (4096, 1152, 32, 32, 128, B.BF16), (b"attn_rows", b"score_once", b"")),
                               (64, (256, 64, 4, 4, 64, B.FP32), (b"attn_f32", b"score_f32", b""))]:
