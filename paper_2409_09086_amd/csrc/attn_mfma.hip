@@ -857,67 +857,73 @@ struct AttnPlan {
     int tile, pieces;          // pieces: of attn_fwd64
     RowsPlan rows;
 };
-// The kernel for a chunk at head_dim 128 among those that take their grid from the query rows, and the time (us, between two
-// events) it should take.  np: keys that a row in the middle of the chunk sees.  Measured at 24 to 32 heads on 8 to 32, 512 to 2700
-// rows, 512 to 8192 cached rows, at 2500 to 9000 keys within about 5 %:
-//   attn_fwd, 64-row workgroups (tile 2) while they fit into one round over the 256 CUs, else of 128 rows (tile 1), which fill
-//   the chip from about 130 workgroups on and get slower the more of it they take; a second round is never cheap.
-//   attn_fwd64 (5): as fast per CU on a full chip, twice the rows; one round of it replaces two of attn_fwd (32 heads, 1152
-//   rows, 4096 cached 112 against 142; 1600 rows 132 against 164), but a second round that is nearly empty does not pay (2304 rows: 275 / 244).
-//   attn_fwd64 with key ranges cut in two, for 65 to 128 workgroups' worth of rows: it fills the chip where attn_fwd's shorter
-//   workgroups leave part of it idle or wait for those that see most keys, and pays for the exchange, 20.5 us instead of 16
-//   before the first key (32 heads, 640 rows, 1024 cached 35.1 / 33.6, 2048 45.5 / 46.5, 8192 109.5 / 125.2; 32 heads on 8, 900
-//   rows, 1024 37.9 / 38.4, 4096 76.8 / 84.9, 8192 128.8 / 147.1).
-// A step that evicts nothing appends in a launch of its own, 5 us, beside an uncut attn_fwd64.
-float fwd_plan(const Geometry& g, int n, int L, int cut_units, AttnPlan& p)
+// Workgroups of attn_fwd's tile 1 (four blocks of 32 rows); with fewer than the constant they cover only about half of the chip (128 at
+// 32 heads x 512 rows), and 64-row workgroups with four key ways (tile 2) are faster.
+int fwd_wgs128(const Geometry& g, int L) { return g.Hq * ((L + 31) / 32) / 4; }
+constexpr int FWD_MIN_WGS128 = 140;
+
+// Whether attn_fwd64 with key ranges cut in two takes the place of attn_fwd's tile 1, at 70 to 128 workgroups' worth of rows: by the
+// time (us, between two events) that the two should take.  np: keys that a row in the middle of the chunk sees.  Fitted to
+// measurements at 24 to 32 heads on 8 to 32, 512 to 2700 rows, 512 to 8192 cached rows, at 2500 to 9000 keys within about 5 %;
+// over 21 other shapes that it decides for the cut, 12 to 64 heads in groups of 1 to 8, that was 1.00 to 1.19 times as fast, and in one
+// (64 heads on 8, 311 rows on 2428 keys, 44.3 / 45.4 us) 0.98.
+// attn_fwd leaves part of the chip idle or waits for the workgroups that see most keys, and gets slower the more of the chip it
+// takes; a second round is never cheap.  The cut fills the chip and pays for the exchange, 21 us instead of 16 before the first
+// key (32 heads, 640 rows, 1024 cached 35.1 / 33.6, 2048 45.5 / 46.5, 8192 109.5 / 125.2; 32 heads on 8, 900 rows, 1024 37.9 / 38.4,
+// 4096 76.8 / 84.9, 8192 128.8 / 147.1).
+bool cut_pays(const Geometry& g, int n, int L)
 {
     const float np = (float)(n - L / 2);
-    const int wgs = g.Hq * ((L + 63) / 64), wgs128 = (g.Hq * ((L + 31) / 32) + 3) / 4, units = attn_mfma64_units(g, L);
-    float best;
-    if (wgs <= 256) {
-        best = (9.f + 0.0096f * (float)n) * (1.f + 0.15f * (float)wgs / 256.f);
-        p.tile = 2;
-    } else {
-        best = wgs128 <= 256 ? 16.f + (0.0128f + 3e-5f * (float)std::max(0, wgs128 - 160)) * np
-                             : 13.f + std::max(0.0287f, 0.0192f * (float)wgs128 / 256.f) * np;
-        p.tile = 1;
-    }
-    const float whole = 20.f + (n <= g.B ? 5.f : 0.f) +
-                        (units <= 256 ? 0.0199f + 7e-5f * (float)std::max(0, units - 160) : 0.0267f * (float)((units + 255) / 256)) * np;
-    if (whole < best) { best = whole; p.tile = 5; }
-    const float cut = 20.5f + (0.0102f + 6e-5f * (float)std::max(0, units - 80)) * np;
-    if (units <= cut_units && n - L / 2 >= CUT_MIN_KEYS && cut < best) { best = cut; p.tile = 5; p.pieces = 2; }
-    return best;
+    const int wgs = fwd_wgs128(g, L), units = attn_mfma64_units(g, L);
+    const float fwd = wgs <= 256 ? 16.f + (0.0128f + 3e-5f * (float)std::max(0, wgs - 160)) * np
+                                 : 13.f + std::max(0.0287f, 0.0192f * (float)wgs / 256.f) * np;
+    return 21.2f + (0.0102f + 6e-5f * (float)std::max(0, units - 80)) * np < fwd;
 }
 
 AttnPlan attn_plan(const Geometry& g, int n, int L, long cap_rows, int cut_units, bool q_aligned)
 {
     AttnPlan p{};
     p.pieces = 1;
+    const bool can_cut = g.d == 128 && attn_mfma64_units(g, L) <= cut_units && n - L / 2 >= CUT_MIN_KEYS;
     if (g.attn_tile > 0) {                                   // a test hook: forces one shape
         p.tile = g.d == 64 ? 6 : g.attn_tile;
-        if (p.tile == 5 && attn_mfma64_units(g, L) <= cut_units && n - L / 2 >= CUT_MIN_KEYS) p.pieces = 2;
+        if (p.tile == 5 && can_cut) p.pieces = 2;
         return p;
     }
-    float other;
-    if (g.d == 64) {
-        // fitted like the times of fwd_plan; several workgroups share a CU
-        const float rounds = (float)((g.Hq * ((L + 127) / 128) + 255) / 256);
-        other = (7.f + 0.0136f * (float)n) * (1.f + 0.35f * (rounds - 1.f));
-        p.tile = 6;
-    } else {
-        other = fwd_plan(g, n, L, cut_units, p);
+    const int wgs128 = fwd_wgs128(g, L);
+    if ((long)L * g.G <= (1 << 20) && (long)L * g.G * g.G < (1l << 32)) {                // what its grid and rows_token take
+        // Few query rows: attn_rows, which cuts the key range over the workgroups.  Examples, measured, attn_rows against
+        // the kernels below: 32 x 128 heads, 4096 keys: 24 / 49 us with 37 rows, 22 / 50 with 64; 16 heads on 4 of 128,
+        // 5000 keys, 320 rows: 37 / 61; 8 x 64 heads, 4000 keys, 320 rows: 19 / 72.  The time of the kernels below, fitted
+        // to measurements like that of rows_chunk_plan: per round of workgroups over the 256 CUs, and the more the
+        // fuller the chip; at head_dim 64 several workgroups share a CU.
+        const int wgs = g.d == 128 ? g.Hq * ((L + 63) / 64) : g.Hq * ((L + 127) / 128);
+        const bool wide = g.d == 128 && wgs128 >= FWD_MIN_WGS128;
+        const float rounds = (float)(((wide ? wgs128 : wgs) + 255) / 256), fill = wgs < 256 ? (float)wgs / 256.f : 1.f;
+        const float other = g.d == 64 ? (7.f + 0.0136f * (float)n) * (1.f + 0.35f * (rounds - 1.f))
+                            : wide    ? rounds * (10.f + 0.0148f * (float)n)
+                                      : rounds * (9.f + 0.0096f * (float)n) * (1.f + 0.15f * fill);
+        // with 64 rows the queries are loaded directly into LDS
+        if (rows_chunk_plan(g, n, L, cap_rows, q_aligned ? 4 : 2, p.rows) < other) return p;
     }
-    // Few query rows: attn_rows, which cuts the key range over the workgroups.  Examples, measured, attn_rows against
-    // the kernels above: 32 x 128 heads, 4096 keys: 24 / 49 us with 37 rows, 22 / 50 with 64; 16 heads on 4 of 128,
-    // 5000 keys, 320 rows: 37 / 61; 8 x 64 heads, 4000 keys, 320 rows: 19 / 72.  With 64 rows the queries are loaded
-    // directly into LDS.
-    RowsPlan rows;
-    if ((long)L * g.G <= (1 << 20) && (long)L * g.G * g.G < (1l << 32) &&                // what its grid and rows_token take
-        rows_chunk_plan(g, n, L, cap_rows, q_aligned ? 4 : 2, rows) < other) {
-        p.tile = 0;
-        p.pieces = 1;
-        p.rows = rows;
+    if (g.d == 64) {
+        p.tile = 6;
+        return p;
+    }
+    // attn_fwd64 (attn_mfma64.hip: 64 query rows per wavefront, one wavefront per SIMD) is the faster kernel
+    // where its grid of 256-row workgroups covers the chip and the key range is long enough to fill its pipeline.
+    // Its workgroups occupy a CU each: the grid must fill at least 80 % of the rounds over the 256 CUs it takes.  With 129 to 204
+    // workgroups it would still be a fifth faster than the two rounds of attn_fwd or attn_rows (32 heads, 1152 rows, 4096 cached
+    // 112 against 142 us), but less exact: a row has one reference of weight 1 in it, in attn_fwd two or four, in attn_rows eight (error
+    // of the output against fp64 0.1 to 1.1 % larger, of the scores up to 20 %), and a value that is not finite meets more of the rows
+    // that it is hidden from.  More references, or whole-range wavefronts that go by their own rows, took 5 to 9 us of the 27.
+    const int wgs64 = (g.Hq * ((L + 63) / 64) + 3) / 4;
+    const int rounds64 = (wgs64 + 255) / 256;
+    const bool fills = wgs64 * 5 >= rounds64 * 256 * 4;
+    p.tile = fills && n >= 1024 ? 5 : wgs128 >= FWD_MIN_WGS128 ? 1 : 2;
+    if (p.tile == 1 && can_cut && cut_pays(g, n, L)) {
+        p.tile = 5;
+        p.pieces = 2;
     }
     return p;
 }
@@ -926,8 +932,8 @@ AttnPlan attn_plan(const Geometry& g, int n, int L, long cap_rows, int cut_units
 
 int attn_cut_units(const Geometry& g)
 {
-    const int units = g.d == 128 ? attn_mfma64_units(g, g.max_chunk) : 0;
-    return g.attn_tile == 5 || (g.attn_tile == 0 && units > 64) ? std::min(units, CUT_MAX_UNITS) : 0;
+    if (g.d != 128 || (g.attn_tile != 5 && (g.attn_tile != 0 || fwd_wgs128(g, g.max_chunk) < FWD_MIN_WGS128))) return 0;
+    return std::min(attn_mfma64_units(g, g.max_chunk), CUT_MAX_UNITS);
 }
 
 const char* attn_mfma_kernel(const Geometry& g, int n, int L, long cap_rows, int cut_units)

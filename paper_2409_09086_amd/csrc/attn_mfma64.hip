@@ -23,7 +23,7 @@
 // The softmax reference moves only when a row maximum outgrows it by 2^8; that rare step is taken on a side
 // path between the period's two scheduling regions.
 //
-// P = 2: 65 to 128 workgroups' worth of rows leave half of the chip idle, or, with attn_fwd's workgroups of half as many rows,
+// P = 2: 70 to 128 workgroups' worth of rows leave half of the chip idle, or, with attn_fwd's workgroups of half as many rows,
 // wait for those that see most keys.  Every key range is then cut in two pieces, which two workgroups go through; the one that
 // arrives last adds the other's (o, m, l), 132 KB, in registers, as they were left: 16-byte stores and loads of whole
 // kilobytes that bypass the L2 caches (stored four bytes a lane, and always by both pieces, the exchange took 23 us; now about 5).
@@ -162,7 +162,9 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     // so every wavefront gets the same number of (row, key) pairs, where two neighbouring blocks would give the last
     // wavefront a quarter more keys than the first and make the launch as long as that one.  Block A is finished
     // first; the loop then goes on with block B alone (period1).
-    const int nblk = (L + 31) / 32, npair = (nblk + 1) / 2;  // blocks of a head; its wavefronts, over all workgroups
+    // Blocks of a head and its wavefronts, over all workgroups.  In a cut range only wavefronts that have rows count; whole ranges
+    // have few without, whose rows past the last are not stored.
+    const int nblk = P == 1 ? 2 * ntile * wph : (L + 31) / 32, npair = (nblk + 1) / 2;
     const int pair0 = bx * wph;                              // the workgroup's first pair
     const int blkA = pair0 + wave / hpw, blkB = nblk - 1 - blkA;   // a middle block is both, and stored twice alike
     const bool active = blkA < npair;                        // else the wavefront only takes its share of the loads

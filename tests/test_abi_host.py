@@ -197,3 +197,14 @@ def test_kernel_names_on_the_host():
     assert kernel(h, "score", 4096, 37) == b"rank_score"
     L.infmllm_stream_destroy(h)
     assert kernel(None, "attn", 0, 1) is None
+    # Where attn_fwd64 does not fill the chip it takes no other kernel's place but that of attn_fwd's 128-row workgroups, with cut key
+    # ranges: rows have one softmax reference in it, eight in attn_rows.  What is cut does not depend on max_chunk.
+    for heads, kv, budget, n, want in [(32, 32, 4096, 1155, b"attn_rows"), (40, 5, 2451, 876, b"attn_rows"), (32, 16, 3164, 1077, b"attn_rows"),
+                                       (32, 8, 2309, 1108, b"attn_rows"), (16, 4, 1041, 1041, b"attn_rows"), (32, 8, 5508, 1299, b"attn_fwd"),
+                                       (32, 4, 1850, 1418, b"attn_fwd"), (32, 32, 16384, 512, b"attn_rows64"), (32, 32, 8192, 2048, b"attn_fwd64"),
+                                       (40, 20, 4028, 1549, b"attn_fwd64"), (32, 32, 4096, 576, b"attn_fwd64, cut"),
+                                       (32, 8, 4096, 1024, b"attn_fwd64, cut"), (16, 16, 2053, 1756, b"attn_fwd64, cut")]:
+        for more in (0, 1500):
+            h = stream(n + more, budget, budget // 4, heads, kv, 128, B.BF16)
+            assert kernel(h, "attn", budget, n) == want, (heads, kv, budget, n, more)
+            L.infmllm_stream_destroy(h)

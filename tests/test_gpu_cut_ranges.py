@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
     (8, 2, 700, [640, 31, 32, 64, 257, 385], 5),              # four heads share a workgroup's tiles
     (4, 2, 600, [600, 63, 191, 320], 5),                      # two
     (6, 2, 800, [800, 159, 500], 5),                          # three: one head per workgroup
-    (24, 24, 2400, [2300, 700], None),                        # by the launch's own rule
+    (24, 24, 2400, [2300, 1000], None),                       # by the launch's own rule
 ])
 def test_cut_ranges_match_oracle(heads, kv, budget, chunks, tile):
     recent, d = budget // 4, 128

@@ -108,6 +108,8 @@ def test_chunks_that_fit_enter_the_cache_as_given(heads, kv, d, dtype, budget, c
     for step, L in enumerate(chunks):
         print("fits", (heads, kv, d, dtype, budget), "step", step, "L", L, flush=True)
         q, k, v = (x.cuda() for x in random_chunk(3400 + step, L, heads, kv, d, dtype))
+        if heads == 32 and kv == 8:
+            assert s.kernel("attn", len(s), L) == "attn_fwd"
         out, ret, cnt = s.step(q, k, v, report=report)
         Ks.append(k.transpose(0, 1)); Vs.append(v.transpose(0, 1)); n += L
         K, V, pos, score = s.export()
