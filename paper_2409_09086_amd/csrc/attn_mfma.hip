@@ -418,7 +418,10 @@ struct ScoreCols {
 // or a chunk row (col >= tc, j = col).  Otherwise the columns are the candidates in stream order (j = col, in cache row
 // rows[j]): sweeping all cached rows for them is up to a quarter more work where the recent window is longer than the chunk
 // (launch, us: 32 x 128 heads, 576 rows, 3520 candidates among 4096 rows 29.4 -> 27.2; 32 heads on 8, 512 rows, 3584 of 4096
-// 29.2 -> 27.1; 32 heads, 37 rows, 2981 of 4096 12.4 -> 11.3).  Columns 0 .. ncol-1 are swept, ncol = cnd in both cases.
+// 29.2 -> 27.1; 32 heads, 37 rows, 2981 of 4096 12.4 -> 11.3).  Also where as many column blocks remain: the row table then is looked up
+// instead of the rank table, ahead of the keys but beside the queries' trip to memory (launch with warm caches / with tables, keys and queries
+// from memory: 16 x 64 heads on 4, 197 rows, 965 of 1024 by the row table 11.5 / 12.1, sweeping the cache 11.5 / 12.3; 8 x 128
+// heads, 100 rows, 1636 of 2048 9.1 / 9.9 both ways; 16 shapes, nowhere slower).  Columns 0 .. cnd-1 are swept in both cases.
 // Workgroup = 8 wavefronts = 8 column groups of 32*CB key columns each, held in registers as MFMA
 // operands; every wavefront takes all four 32-row query blocks of an iteration, which are staged once
 // per workgroup (double-buffered in LDS) and so serve 256*CB columns.  Every scored row sees every
@@ -428,7 +431,7 @@ template <int D, int CB>
 __global__ void __launch_bounds__(512)
 score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ kc, int tc,
              const float* __restrict__ lse2, const float* __restrict__ carry, const int32_t* __restrict__ rank,
-             const int32_t* __restrict__ rows, float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd, int ncol,
+             const int32_t* __restrict__ rows, float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd,
              int nxb, float c, float dstep /* b / c, Alg. 1 l.2 */, int rsplit, float* __restrict__ spart)
 {
     constexpr int QP = D * 2 + 16;                            // pitch of a staged query row
@@ -468,7 +471,7 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
     }
     const int col0 = bx * (256 * CB) + cg * (32 * CB);
     char* const mine = smem + cg * (CB * Cols::BLOCK);
-    Cols::template request<CB>(mine, K, kc, Cols::lookup(rows, h, cap, col0, ncol, CB == 2 ? lane : l32), tc, h, Hkv, cap, col0, lane);
+    Cols::template request<CB>(mine, K, kc, Cols::lookup(rows, h, cap, col0, cnd, CB == 2 ? lane : l32), tc, h, Hkv, cap, col0, lane);
 
     f32x16 part[CB];
 #pragma unroll
@@ -697,7 +700,7 @@ score_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, con
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int col = col0 + 32 * cb + l32;
-            const int j = col < tc && !rows ? (col < ncol ? rank[(size_t)h * cap + col] : cnd) : col;   // stream-order index
+            const int j = col < tc && !rows ? rank[(size_t)h * cap + col] : col;   // stream-order index
             if (j < cnd) {
                 float tot = sum[cb];
                 if (rsplit > 1) {
@@ -733,7 +736,7 @@ template <int D>
 __global__ void __launch_bounds__(512, 4)
 score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ kc, int tc,
                   const float* __restrict__ lse2, const float* __restrict__ carry, const int32_t* __restrict__ rank,
-                  const int32_t* __restrict__ rows, float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd, int ncol,
+                  const int32_t* __restrict__ rows, float* __restrict__ Wb, int L, int lq, int Hq, int Hkv, int G, int cap, int max_chunk, int cnd,
                   int nxb, float c, float dstep /* b / c, Alg. 1 l.2 */, int nslice, float* __restrict__ spart)
 {
     constexpr int QP = D * 2 + 16, CPR = D / 8, NS = D / 16;  // pitch, 16-byte pieces of a staged row; MFMAs per block
@@ -756,7 +759,7 @@ score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
     }
     const int col = bx * 256 + wave * 32 + l32;               // this lane's
     char* const mine = qs + wave * Cols::BLOCK;
-    const int krow = Cols::lookup(rows, h, cap, bx * 256 + wave * 32, ncol, l32);
+    const int krow = Cols::lookup(rows, h, cap, bx * 256 + wave * 32, cnd, l32);
     // blocks of 32 scored rows, head after head of the group; this slice's
     const int nblk = (lq + 31) / 32, total = G * nblk;
     const int b0 = (int)((long)rs * total / nslice), nb = (int)((long)(rs + 1) * total / nslice) - b0;
@@ -775,7 +778,7 @@ score_once_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         const int b = b0 + (tid >> 5), i = L - lq + 32 * (b % nblk) + (tid & 31);
         if (i < L) row_lse = lse2[(size_t)(h * G + b / nblk) * max_chunk + i];
     }
-    const int j = col < tc && !rows ? (col < ncol ? rank[(size_t)h * cap + col] : cnd) : col;   // stream-order index
+    const int j = col < tc && !rows ? rank[(size_t)h * cap + col] : col;   // stream-order index
     Cols::template request<1>(mine, K, kc, krow, tc, h, Hkv, cap, bx * 256 + wave * 32, lane);
     bf16x8 kf[NS];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1017,16 +1020,15 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
     const int n = t + L, cnd = n - g.R, lq = g.R < L ? g.R : L;
     if (cnd <= 0) return hipSuccess;
     const int32_t* rows = cnd < ks.rows ? c.row : nullptr;   // some cached rows are no candidates: by stream order
-    const int ncol = cnd;
     const float cc = (float)(g.scale * (double)LOG2E);
     const float dstep = (float)(g.bias / (double)cnd);
     const float* carry = g.policy == POLICY_CUMULATIVE ? c.score : nullptr;
-    const ScorePlan p = score_plan(g, ncol, lq, sc.score_part != nullptr);
+    const ScorePlan p = score_plan(g, cnd, lq, sc.score_part != nullptr);
     if (p.once) {
 #define INFMLLM_ONCE(DD)                                                                                                   \
     hipLaunchKernelGGL(score_once_kernel<DD>, dim3((unsigned)(p.nxb * g.Hkv * p.split)), dim3(512), 0, st, (const uint16_t*)q,                  \
                        (const uint16_t*)c.K, (const uint16_t*)ks.k, ks.rows, lse, carry, c.rank, rows, Wb, L, lq, g.Hq, g.Hkv, g.G, \
-                       g.cap, g.max_chunk, cnd, ncol, p.nxb, cc, dstep, p.split, sc.score_part)
+                       g.cap, g.max_chunk, cnd, p.nxb, cc, dstep, p.split, sc.score_part)
         if (g.d == 128) INFMLLM_ONCE(128);
         else if (g.d == 64) INFMLLM_ONCE(64);
         else return hipErrorInvalidValue;
@@ -1038,7 +1040,7 @@ hipError_t launch_score_mfma(const Geometry& g, const CacheView& c, const KeySou
     hipLaunchKernelGGL((score_kernel<DD, CB>), grid, block, 0, st, (const uint16_t*)q, (const uint16_t*)c.K, \
                        (const uint16_t*)ks.k, ks.rows, lse,                                                  \
                        carry, c.rank, rows, Wb, L, lq, g.Hq, g.Hkv, g.G, g.cap, g.max_chunk,                        \
-                       cnd, ncol, p.nxb, cc, dstep, p.split, sc.score_part)
+                       cnd, p.nxb, cc, dstep, p.split, sc.score_part)
     if (g.d == 128 && p.wide) INFMLLM_SCORE(128, 2);
     else if (g.d == 128) INFMLLM_SCORE(128, 1);
     else if (g.d == 64) INFMLLM_SCORE(64, 1);
