@@ -117,11 +117,15 @@ int infmllm_stream_create(int budget, int recent, int heads, int kv_heads, int h
  */
 int infmllm_stream_set_param(infmllm_stream_t* s, int which, double value);
 
-/* Bytes of device workspace the stream needs with its current parameters (0 if s is null). */
+/*
+ * Bytes of device workspace the stream wants with its current parameters (0 if s is null).  For bf16 streams of head_dim 128 whose
+ * largest chunk covers half of the chip (heads * max_chunk of about 18000 or more) up to 34 MB of them are scratch with which two workgroups share
+ * a key range; infmllm_stream_attach takes a workspace that is smaller by these, and launches are then slower.
+ */
 size_t infmllm_stream_workspace_bytes(const infmllm_stream_t* s);
 
 /*
- * Hands the stream its device workspace (256-byte aligned, at least
+ * Hands the stream its device workspace (256-byte aligned,
  * infmllm_stream_workspace_bytes(s) bytes, caller-owned) and the HIP stream (a
  * hipStream_t passed as void*, null for the default stream) all later work is enqueued
  * on.  The workspace holds the cache (one copy of K and V of budget + max_decode + max_chunk rows per

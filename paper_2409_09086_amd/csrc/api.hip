@@ -89,8 +89,8 @@ struct infmllm_stream {
     FwdScratch fwd;      // scratch of the row-split scoring launch
     float* dec_part;     // partials of the decoding step (plain-arithmetic kernels)
     int dec_pieces = 1, dec_keys = 0;   // see Layout
-    CutScratch cut{nullptr, nullptr, 0};                // the same of attn_fwd64
     RowsScratch rows{nullptr, nullptr, nullptr, 0};   // partials of attention launches with a cut key range (bf16 on the matrix cores)
+    CutScratch cut{nullptr, nullptr, 0};              // the same of attn_fwd64
     // optional per-kernel timing: one event pair per kernel per step, up to prof_cap steps
     std::vector<hipEvent_t> prof_ev;   // [prof_cap][INFMLLM_K_COUNT][2]
     std::vector<char> prof_used;       // [prof_cap][INFMLLM_K_COUNT]
@@ -123,7 +123,8 @@ struct infmllm_stream {
         int dec_pieces;      // most pieces a decoding launch may cut the keys into
         int dec_keys;        // keys of a piece (on the matrix cores)
     };
-    Layout layout() const
+    Layout layout() const { return layout(lean); }
+    Layout layout(int lean) const
     {
         Layout L;
         size_t off = 0;
@@ -287,7 +288,9 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     if (s->attached) return fail(INFMLLM_ESTATE, "attach: stream is already attached");
     if (!ws) return fail(INFMLLM_EINVAL, "attach: workspace is null");
     if ((uintptr_t)ws % ALIGN) return fail(INFMLLM_EINVAL, "attach: workspace must be 256-byte aligned");
-    const infmllm_stream::Layout L = s->layout();
+    int lean = s->lean;
+    infmllm_stream::Layout L = s->layout(lean);
+    if (bytes < L.total && lean == 0) L = s->layout(lean = 1);   // too small by the scratch of cut key ranges alone: without it
     if (bytes < L.total)
         return fail(INFMLLM_ENOMEM, "attach: workspace has %zu bytes, %zu needed", bytes, L.total);
     if ((size_t)s->g.cap * 4 > 150 * 1024 && (s->dtype == INFMLLM_FP32 || s->impl == 1))
@@ -352,6 +355,7 @@ int infmllm_stream_attach(infmllm_stream_t* s, void* ws, size_t bytes, void* hip
     }
     s->st = (hipStream_t)hip_stream;
     s->len = 0; s->streamed = 0; s->last_cnd = 0;
+    s->lean = lean;
     s->attached = true;
     return INFMLLM_OK;
 }

@@ -34,6 +34,31 @@ def test_cut_ranges_match_oracle(heads, kv, budget, chunks, tile):
     assert cut >= 1
 
 
+def without_scratch(monkeypatch, *args, **params):
+    """A stream whose workspace ends before the scratch of cut key ranges (streams that force attn_fwd have none)."""
+    small = B.Stream(*args, **dict(params, attn_tile=1)).workspace.numel() - 256
+    assert small < B.Stream(*args, **params).workspace.numel() - 256
+    with monkeypatch.context() as m:
+        m.setattr(B.lib(), "infmllm_stream_workspace_bytes", lambda h: small - 1)
+        with pytest.raises(B.InfMLLMError) as e:
+            B.Stream(*args, **params)
+        assert e.value.code == B.ENOMEM
+        m.setattr(B.lib(), "infmllm_stream_workspace_bytes", lambda h: small)
+        return B.Stream(*args, **params)
+
+
+def test_a_workspace_without_the_scratch_is_taken(monkeypatch):
+    """... as it was before cut key ranges: the same stream on attn_fwd, against the oracle."""
+    heads, kv, d, budget, L = 32, 8, 128, 2000, 720
+    gpu = without_scratch(monkeypatch, budget, 200, heads, kv, d, dtype=torch.bfloat16, bias=1e-3, max_chunk=L)
+    full = B.Stream(budget, 200, heads, kv, d, dtype=torch.bfloat16, bias=1e-3, max_chunk=L)
+    ls = LockStep(gpu, OracleStream(budget, 200, heads, kv, d, bias=1e-3))
+    for step in range(3):
+        assert full.kernel("attn", budget, L) == "attn_fwd64, cut" and gpu.kernel("attn", budget, L) == "attn_fwd"
+        print("no scratch", step, flush=True)
+        ls.step(*random_chunk(6400 + step, L, heads, kv, d, "bf16"), check_state=True)
+
+
 def one_step(heads, kv, budget, L, seed, spoil=None, cut=True):
     """Output and scores of a step on a full cache; spoil(k, v) changes the chunk."""
     s = B.Stream(budget, budget // 4, heads, kv, 128, dtype=torch.bfloat16, max_chunk=L, attn_tile=5 if cut else 1)
