@@ -189,7 +189,8 @@ int infmllm_step(infmllm_stream_t* s, const void* q, const void* k, const void* 
  * is evicted.  The cache may so grow to budget + max_decode rows; the next infmllm_step brings
  * it back to the budget.
  *   q      device, [1, heads, head_dim];  k, v  device, [1, kv_heads, head_dim];  read-only
- *   out    device, [1, heads, head_dim], written.  It may be q, or (heads = kv_heads) k or v
+ *   out    device, [1, heads, head_dim], written.  It may be q, or (heads = kv_heads) k or v; where it overlaps them
+ *          otherwise its contents are undefined (bf16 on the matrix cores: only where it overlaps q)
  * Errors: EINVAL (null pointer), ECAPACITY (the cache already holds budget + max_decode rows),
  * ESTATE (not attached), EHIP.
  */
@@ -201,7 +202,7 @@ int infmllm_decode(infmllm_stream_t* s, const void* q, const void* k, const void
  * token i is decoded exactly as by the i-th of n_tokens calls of infmllm_decode, so it attends the rows
  * cached before the call and tokens 0 .. i of the call.
  *   q      device, [n_tokens, heads, head_dim];  k, v  device, [n_tokens, kv_heads, head_dim];  read-only
- *   out    device, [n_tokens, heads, head_dim], written.  It may be q, or (heads = kv_heads) k or v
+ *   out    device, [n_tokens, heads, head_dim], written.  It may be q, or (heads = kv_heads) k or v (see infmllm_decode)
  * Errors: EINVAL (null pointer, n_tokens < 1), ECAPACITY (the cache would exceed budget + max_decode
  * rows: nothing is enqueued), ESTATE (not attached), EHIP.
  */

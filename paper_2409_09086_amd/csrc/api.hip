@@ -658,15 +658,17 @@ int infmllm_stream_profile_read(infmllm_stream_t* s, float* ms, int* launches)
 }
 
 // Decoding steps of T tokens on a stream whose state has been checked: launches, then the host-side counters.  On the
-// matrix cores the T tokens share one launch (decode_tokens_per_launch says how many may), else T is 1.  over: out overlaps an
-// input; with a single piece the launch would store it before the token enters the cache, which therefore happens first.
-static int decode_some(infmllm_stream* s, const void* q, const void* k, const void* v, void* out, int T, bool over)
+// matrix cores the T tokens share one launch (decode_tokens_per_launch says how many may), else T is 1.  over: 1 if out is the
+// tensor of the keys or of the values, so that a kv-head's rows of it are those that its own workgroups read (a launch of a single piece
+// would store them before the token enters the cache), 2 if it overlaps them otherwise and a kv-head's rows may be another one's
+// keys.  Where that matters the token enters the cache first and is read from there.
+static int decode_some(infmllm_stream* s, const void* q, const void* k, const void* v, void* out, int T, int over)
 {
     s->mark(INFMLLM_K_DECODE, 0);
     const int t = s->len;
     hipError_t e;
     CacheView att = s->cache;
-    const bool rope = s->rope_base > 0.0, in_place = !s->mfma() || (aligned16(k) && aligned16(v) && !(over && t + T <= s->dec_keys));
+    const bool rope = s->rope_base > 0.0, in_place = !s->mfma() || (aligned16(k) && aligned16(v) && over < (t + T <= s->dec_keys ? 1 : 2));
     if (rope || !in_place)
         if ((e = launch_append(append_job(s->g, s->cache, k, v, t, T, s->streamed, nullptr, nullptr), s->st)) != hipSuccess) return fail_hip(e, "decode: append");
     if (rope) {
@@ -721,11 +723,13 @@ int infmllm_decode_n(infmllm_stream_t* s, const void* q, const void* k, const vo
     // Tokens that share a launch read each other's keys and values while finished rows are stored: where the output
     // overwrites the inputs they are decoded one after the other.  (out == q is safe: whoever stores a row has read it.)
     const size_t qb = n_tokens * qrow, kb = n_tokens * krow;
-    const bool alone = overlap(out, qb, k, kb) || overlap(out, qb, v, kb) || (out != q && overlap(out, qb, q, qb));
+    const bool over_k = overlap(out, qb, k, kb), over_v = overlap(out, qb, v, kb);
+    const bool alone = over_k || over_v || (out != q && overlap(out, qb, q, qb));
+    const int over = !(over_k || over_v) ? 0 : qb == kb && (!over_k || out == k) && (!over_v || out == v) ? 1 : 2;
     for (int i = 0; i < n_tokens;) {
         const int T = alone ? 1 : decode_tokens_per_launch(s, n_tokens - i);
         const int rc = decode_some(s, (const char*)q + i * qrow, (const char*)k + i * krow, (const char*)v + i * krow,
-                                   (char*)out + i * qrow, T, alone);
+                                   (char*)out + i * qrow, T, over);
         if (rc != INFMLLM_OK) return rc;
         i += T;
     }

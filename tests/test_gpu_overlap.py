@@ -77,3 +77,28 @@ def test_tokens_whose_output_overwrites_their_inputs(dtype, heads, kv, d, held, 
         assert torch.equal(out, want)
         for x, y in zip(a.export(), b.export()):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("heads,kv,d,held,at_k,at_v", [
+    (8, 2, 128, 900, 2, 5),                   # several pieces: rows of out that are another kv-head's key and value
+    (32, 8, 128, 900, 20, 1),
+    (32, 32, 128, 900, 1, None),              # the keys a head further
+    (16, 16, 64, 900, None, -1),              # the values a head before
+    (8, 2, 128, 100, 2, 5),                   # one piece
+])
+def test_tokens_whose_output_overlaps_other_keys(heads, kv, d, held, at_k, at_v):
+    """Output rows of one kv-head that lie over the key or value of another: a token enters the cache, and is read from there,
+    before any row is stored.  Against a twin with an output of its own, bit for bit."""
+    a, b = (B.Stream(1000, 100, heads, kv, d, dtype=torch.bfloat16, max_chunk=held, max_decode=64) for _ in range(2))
+    for s in (a, b):
+        s.step(*(x.cuda() for x in random_chunk(4300, held, heads, kv, d, "bf16")))
+    for call in range(24):
+        print("overlap", (heads, kv, d, held, at_k, at_v), "call", call, flush=True)
+        q, k, v = (x.cuda() for x in random_chunk(4301 + call, 1, heads, kv, d, "bf16"))
+        want = b.decode(q, k, v)
+        buf = torch.empty(3 * heads * d, dtype=torch.bfloat16, device="cuda")
+        out = buf[heads * d: 2 * heads * d].view(q.shape)
+        put = lambda x, at: x if at is None else buf[(heads + at) * d:][: x.numel()].view(x.shape).copy_(x)
+        assert torch.equal(a.decode(q, put(k, at_k), put(v, at_v), out=out), want)
+        for x, y in zip(a.export(), b.export()):
+            assert torch.equal(x, y)
