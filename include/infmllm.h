@@ -82,6 +82,10 @@ enum {
                                     (bf16 products with fp32 sums; fp32 products for fp32 streams);
                                     1 = bf16 streams run plain fp32-arithmetic kernels, fp32 streams as with 0.
                                     Decoding: bf16 on the matrix cores with 0, else plain fp32 arithmetic */
+    INFMLLM_PARAM_CUT_HOLD = 8,  /* test: 0 (default) = none; else workgroups of a cut key range wait some 0.2 ms where a bit is set, so that a
+                                    test decides in which order the two pieces of a range arrive: 1 the first piece before it leaves
+                                    its results, 2 the last piece before it looks whether the other's are there, 4 the last piece
+                                    after it has looked (twice as long).  Results are the same bit for bit               */
     INFMLLM_PARAM_ATTN_TILE = 7  /* debug/test, bf16 on the matrix cores: 0 (default) = the attention launch picks
                                     its kernel and workgroup shape from the chunk and cache lengths.  head_dim 64:
                                     any other value = 128 query rows per workgroup, keys uncut.  head_dim 128:

@@ -14,7 +14,7 @@ LIB_PATH = os.path.join(_HERE, "libinfmllm.so")
 
 BF16, FP32 = 0, 1
 OK, EINVAL, ENOMEM, ECAPACITY, ESTATE, EHIP = 0, -1, -2, -3, -4, -5
-PARAM_BIAS, PARAM_SCALE, PARAM_MAX_CHUNK, PARAM_IMPL, PARAM_MAX_DECODE, PARAM_POLICY, PARAM_ROPE_BASE, PARAM_ATTN_TILE = 0, 1, 2, 3, 4, 5, 6, 7
+PARAM_BIAS, PARAM_SCALE, PARAM_MAX_CHUNK, PARAM_IMPL, PARAM_MAX_DECODE, PARAM_POLICY, PARAM_ROPE_BASE, PARAM_ATTN_TILE, PARAM_CUT_HOLD = 0, 1, 2, 3, 4, 5, 6, 7, 8
 POLICIES = {"infmllm": 0, "window": 1, "initial_recent": 2, "cumulative": 3}
 
 EXPORTS = [
@@ -104,7 +104,7 @@ class Stream:
 
     def __init__(self, budget, recent, heads, kv_heads, head_dim, dtype=torch.bfloat16, bias=None, scale=None,
                  max_chunk=None, impl=None, max_decode=None, policy=None, rope_base=None, attn_tile=None,
-                 device="cuda:0", hip_stream=None, static_workspace=False):
+                 device="cuda:0", hip_stream=None, static_workspace=False, cut_hold=None):
         L = lib()
         self.dtype = dtype
         code = {torch.bfloat16: BF16, torch.float32: FP32}.get(dtype)
@@ -117,7 +117,8 @@ class Stream:
         for which, val in ((PARAM_BIAS, bias), (PARAM_SCALE, scale), (PARAM_MAX_CHUNK, max_chunk), (PARAM_IMPL, impl),
                            (PARAM_MAX_DECODE, max_decode),
                            (PARAM_POLICY, None if policy is None else POLICIES[policy]),
-                           (PARAM_ROPE_BASE, rope_base), (PARAM_ATTN_TILE, attn_tile)):
+                           (PARAM_ROPE_BASE, rope_base), (PARAM_ATTN_TILE, attn_tile),
+                           (PARAM_CUT_HOLD, cut_hold)):
             if val is not None:
                 _check(L.infmllm_stream_set_param(self._h, which, float(val)))
         self.device = torch.device(device)

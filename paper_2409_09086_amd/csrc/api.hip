@@ -179,7 +179,7 @@ struct infmllm_stream {
         L.dec_part = off; off += up(!mfma() && L.dec_pieces > 1 ? part * L.dec_pieces + (size_t)g.Hkv * 4 : 0);
         L.cut_units = mfma() && !lean ? attn_cut_units(g) : 0;
         L.cut_part = off; off += up((size_t)L.cut_units * 2 * attn_mfma64_piece_bytes());
-        L.cut_arrived = off; off += up((size_t)L.cut_units * 4);
+        L.cut_arrived = off; off += up((size_t)L.cut_units * 8);
         L.total = off;
         return L;
     }
@@ -214,6 +214,7 @@ int infmllm_stream_create(int budget, int recent, int heads, int kv_heads, int h
     s->g.bias = 1e-4;
     s->g.policy = POLICY_INFMLLM;
     s->g.attn_tile = 0;
+    s->g.cut_hold = 0;
     s->dtype = dtype; s->impl = 0; s->attached = false; s->st = nullptr; s->len = 0;
     s->streamed = 0; s->last_cnd = 0; s->lse = nullptr; s->Wb = nullptr;
     *out = s;
@@ -274,6 +275,11 @@ int infmllm_stream_set_param(infmllm_stream_t* s, int which, double value)
             if (value < 0 || value > 5 || value != std::floor(value))
                 return fail(INFMLLM_EINVAL, "set_param: attn_tile must be 0..5");
             s->g.attn_tile = (int)value;
+            return INFMLLM_OK;
+        case INFMLLM_PARAM_CUT_HOLD:
+            if (value < 0 || value > 7 || value != std::floor(value))
+                return fail(INFMLLM_EINVAL, "set_param: cut_hold must be 0..7");
+            s->g.cut_hold = (int)value;
             return INFMLLM_OK;
         default:
             return fail(INFMLLM_EINVAL, "set_param: unknown parameter %d", which);

@@ -130,7 +130,7 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
                   const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, int tc,
                   uint16_t* __restrict__ out, float* __restrict__ lse2, int t, int L, int Hq, int G, int cap,
                   int max_chunk, int hpw, int ntile, int ny, float c /* scale * log2(e) */, float* __restrict__ part,
-                  int* __restrict__ arrived, AppendJob ap)
+                  int* __restrict__ arrived, int hold, int* __restrict__ merged_by, AppendJob ap)
 {
     using namespace w64;
     __shared__ __attribute__((aligned(1024))) char smem[LDS];
@@ -692,11 +692,18 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
         const int bytes = 4 * VECS * 1024;
         auto rsrc_of = [&](int pc) { return __builtin_amdgcn_make_buffer_rsrc((char*)part + ((size_t)unit * P + pc) * bytes, 0, bytes, 0x00020000); };
         const int voff = el * 16, soff = wave * (VECS * 1024);
+        // a test hook (see INFMLLM_PARAM_CUT_HOLD): a bounded wait, some 0.2 ms, that puts the two pieces into one order or the other
+        auto hold_back = [&](int bit, int times) {
+            if ((hold >> bit) & 1)
+                for (int i = 0; i < 50 * times; ++i) __builtin_amdgcn_s_sleep(127);
+        };
         bool all_here = false;
+        hold_back(piece, 1);
         if (piece == P - 1) {
             if (tid == 0) s_arrived = __hip_atomic_load(arrived + unit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
             all_here = s_arrived == P - 1;
+            hold_back(2, 2);
         }
         if (!all_here) {
             const auto dst = rsrc_of(piece);
@@ -720,7 +727,10 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
                 return;
             }
         }
-        if (tid == 0) __hip_atomic_store(arrived + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+        if (tid == 0) {
+            __hip_atomic_store(arrived + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+            if (hold) merged_by[unit] = 1 + piece + (all_here ? 1 : 0);
+        }
         // Two products, rounded, and their sum: the same bits whichever of the two pieces does it.
         {
 #pragma clang fp contract(off)
@@ -791,7 +801,7 @@ hipError_t launch_attn_mfma64(const Geometry& g, const CacheView& c, const KeySo
 #define INFMLLM_FWD64(P)                                                                                                   \
     hipLaunchKernelGGL(attn_fwd64_kernel<P>, dim3(units * P), dim3(w64::NT), 0, st, (const uint16_t*)q, (const uint16_t*)c.K, \
                        (const uint16_t*)c.V, (const uint16_t*)ks.k, (const uint16_t*)ks.v, ks.rows, (uint16_t*)out, lse, t, L, \
-                       g.Hq, g.G, g.cap, g.max_chunk, hpw, ntile, ny, (float)(g.scale * (double)LOG2E), sc.part, sc.arrived, ap)
+                       g.Hq, g.G, g.cap, g.max_chunk, hpw, ntile, ny, (float)(g.scale * (double)LOG2E), sc.part, sc.arrived, g.cut_hold, sc.arrived + sc.units, ap)
     if (pieces == 2) INFMLLM_FWD64(2);
     else INFMLLM_FWD64(1);
 #undef INFMLLM_FWD64

@@ -27,6 +27,7 @@ struct Geometry {
     double bias;  // b of Alg. 1 (the ramp step b / c is formed in double and rounded once to float)
     int policy;   // score ranked by the selection: 0 Alg. 1, 1 window, 2 initial + recent, 3 cumulative
     int attn_tile;// test hook: 0 = the matrix-core attention picks its tile shape, 1..5 = forces one
+    int cut_hold; // test hook: see INFMLLM_PARAM_CUT_HOLD
 };
 enum { POLICY_INFMLLM = 0, POLICY_WINDOW = 1, POLICY_INITIAL_RECENT = 2, POLICY_CUMULATIVE = 3 };
 
@@ -117,7 +118,8 @@ constexpr int CUT_MAX_UNITS = 128;   // 256 workgroups: one round
 constexpr int CUT_MIN_KEYS = 512;    // of the rows in the middle of a chunk: every piece of every unit has a tile then
 struct CutScratch {
     float* part;
-    int* arrived;       // [units] tickets, zero between launches
+    int* arrived;       // [units] tickets, zero between launches; with the test hook then [units] who merged: 1 the first piece, 2 the
+                        // last piece, 3 the last piece without having written its own results
     int units;          // 0: none
 };
 

@@ -60,6 +60,7 @@ def test_host_state_machine_without_a_device():
     assert L.infmllm_stream_set_param(h, B.PARAM_SCALE, 0.0) == B.EINVAL
     assert L.infmllm_stream_set_param(h, B.PARAM_MAX_CHUNK, 0.0) == B.EINVAL
     assert L.infmllm_stream_set_param(h, B.PARAM_IMPL, 2.0) == B.EINVAL
+    assert [L.infmllm_stream_set_param(h, B.PARAM_CUT_HOLD, v) for v in (-1.0, 8.0, 2.5, 7.0, 0.0)] == [B.EINVAL] * 3 + [B.OK] * 2
     assert L.infmllm_stream_set_param(h, 99, 1.0) == B.EINVAL
     assert L.infmllm_stream_set_param(h, B.PARAM_BIAS, 0.5) == B.OK
     # nothing below reaches a device: every call is refused on the host

@@ -59,6 +59,27 @@ def test_a_workspace_without_the_scratch_is_taken(monkeypatch):
         ls.step(*random_chunk(6400 + step, L, heads, kv, d, "bf16"), check_state=True)
 
 
+@pytest.mark.parametrize("rope", [None, 10000.0])
+@pytest.mark.parametrize("cut", [False, True])
+@pytest.mark.parametrize("heads,kv,budget,recent,chunks", [
+    (4, 4, 768, 256, [768, 512, 300, 33]),      # one head per wavefront: four pairs of row blocks per workgroup
+    (8, 2, 512, 192, [512, 448, 65]),           # groups of four heads share a workgroup's K/V tiles
+    (4, 2, 512, 128, [512, 512, 200]),          # groups of two
+    (6, 2, 800, 300, [700, 100, 159, 801]),     # groups of three: one head per workgroup
+])
+def test_whole_and_cut_ranges_match_oracle(monkeypatch, heads, kv, budget, recent, chunks, cut, rope):
+    """attn_fwd64 with whole key ranges and with cut ones: chunks of several hundred rows make every phase of its loop last
+    several tiles, ragged ones leave blocks without rows; keys from the cache and, turned with the rotary option, from the chunk."""
+    args, params = (budget, recent, heads, kv, 128), dict(dtype=torch.bfloat16, bias=1e-3, max_chunk=max(chunks), attn_tile=5, rope_base=rope)
+    gpu = B.Stream(*args, **params) if cut else without_scratch(monkeypatch, *args, **params)
+    ls = LockStep(gpu, OracleStream(budget, recent, heads, kv, 128, bias=1e-3, rope_base=rope or 0.0, rope_round="bf16" if rope else None))
+    for step, L in enumerate(chunks):
+        name = gpu.kernel("attn", len(gpu), L)
+        assert name == ("attn_fwd64, cut" if cut and len(gpu) + L - L // 2 >= 512 else "attn_fwd64")
+        print("ranges", (heads, kv, budget, recent, rope), "step", step, "L", L, name, flush=True)
+        ls.step(*random_chunk(6500 + step, L, heads, kv, 128, "bf16"), check_state=True)
+
+
 def one_step(heads, kv, budget, L, seed, spoil=None, cut=True):
     """Output and scores of a step on a full cache; spoil(k, v) changes the chunk."""
     s = B.Stream(budget, budget // 4, heads, kv, 128, dtype=torch.bfloat16, max_chunk=L, attn_tile=5 if cut else 1)
@@ -73,13 +94,39 @@ def one_step(heads, kv, budget, L, seed, spoil=None, cut=True):
     return out, s.last_scores()
 
 
-@pytest.mark.parametrize("heads,kv,budget,L", [(32, 32, 1024, 576), (32, 8, 2048, 1024), (3, 3, 900, 97)])
-def test_the_same_bits_whoever_merges(heads, kv, budget, L):
-    print("merge order", (heads, kv, budget, L), flush=True)
-    want = one_step(heads, kv, budget, L, 7)
-    for _ in range(6):
-        got = one_step(heads, kv, budget, L, 7)
-        assert torch.equal(got[0].view(torch.int16), want[0].view(torch.int16)) and torch.equal(got[1], want[1])
+def merged_by(s, units):
+    """Who merged each unit of the last cut launch (kept at the end of the workspace by streams with cut_hold)."""
+    base = (s.workspace.data_ptr() + 255) // 256 * 256 - s.workspace.data_ptr()
+    end = base + B.lib().infmllm_stream_workspace_bytes(s._h)
+    scratch = s.workspace[end - (8 * units + 255) // 256 * 256:end].view(torch.int32)
+    assert (scratch[:units] == 0).all(), "tickets are zero between launches"
+    return set(scratch[units:2 * units].tolist())
+
+
+@pytest.mark.parametrize("heads,kv,budget,L,units", [(32, 32, 1024, 576, 96), (32, 8, 2048, 1024, 128), (3, 3, 900, 97, 3)])
+def test_the_same_bits_whoever_merges(heads, kv, budget, L, units):
+    """All three ways that a cut range can end, each in turn: the first piece arrives last and merges; it arrives first and the last
+    piece sees its results at once; the last piece does not see them, leaves its own and then is the last all the same.  A chunk
+    that evicts and one that fits, which the workgroups that do not merge write into the cache."""
+    for fits in (False, True):
+        rows = budget + L if fits else budget                    # of the cache
+        g = torch.Generator(device="cuda").manual_seed(7)
+        K, V = (torch.randn((kv, budget, 128), generator=g, device="cuda").bfloat16() for _ in range(2))
+        q, k, v = (x.cuda() for x in random_chunk(6207, L, heads, kv, 128, "bf16"))
+        want = None
+        for hold, who in ((1, 1), (2, 3), (5, 2), (0, None), (0, None)):
+            s = B.Stream(rows, rows // 4, heads, kv, 128, dtype=torch.bfloat16, max_chunk=L, attn_tile=5, cut_hold=hold)
+            s.load(K, V, torch.arange(budget, dtype=torch.int32, device="cuda").repeat(kv, 1).contiguous(), budget)
+            assert s.kernel("attn", budget, L) == "attn_fwd64, cut"
+            print("merge order", (heads, kv, budget, L), "fits" if fits else "evicts", "hold", hold, flush=True)
+            out, ret, cnt = s.step(q, k, v)
+            got = [out.view(torch.int16), ret, cnt, *s.export()] + ([] if fits else [s.last_scores()])
+            if hold:
+                assert merged_by(s, units) == {who}
+            want = want or got
+            assert len(got) == len(want) and all(torch.equal(x, y) for x, y in zip(got, want))
+        if fits:
+            assert torch.equal(want[3][:, budget:], k.transpose(0, 1)) and torch.equal(want[4][:, budget:], v.transpose(0, 1))
 
 
 @pytest.mark.parametrize("heads,kv,budget,L", [(32, 8, 512, 512), (32, 16, 600, 300)])
