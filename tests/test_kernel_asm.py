@@ -55,18 +55,19 @@ def device_code(src):
     return kernels, scratch
 
 
-def registers(operands):
-    """Vector registers named in an operand list."""
+def registers(operands, kinds="v"):
+    """Vector registers (accumulation registers with kinds "a") named in an operand list."""
     out = set()
-    for m in re.finditer(r"\bv(?:\[(\d+):(\d+)\]|(\d+)\b)", operands):
-        lo = int(m.group(1) or m.group(3))
-        out.update(range(lo, int(m.group(2) or lo) + 1))
+    for m in re.finditer(r"\b([%s])(?:\[(\d+):(\d+)\]|(\d+)\b)" % kinds, operands):
+        lo = int(m.group(2) or m.group(4))
+        out.update((m.group(1), r) for r in range(lo, int(m.group(3) or lo) + 1))
     return out
 
 
-def reads_touched_too_early(body):
+def reads_touched_too_early(body, kinds="v"):
     """Vector LDS reads of asm statements that do not wait themselves: (how many there are, those whose registers an
-    instruction names, or that a branch or label follows, before a wait that covers them)."""
+    instruction names, or that a branch or label follows, before a wait that covers them).  kinds "a": reads into accumulation
+    registers only."""
     pending, found, bad, in_asm = [], 0, [], False      # pending: LDS and scalar operations in issue order, a read's registers or None
     lines = body.splitlines()
     for i, line in enumerate(lines):
@@ -88,12 +89,13 @@ def reads_touched_too_early(body):
             if any(p for p in pending):
                 bad.append((i, code))
             continue
-        names = registers(args)
+        names = registers(args, kinds)
         if any(p and p & names for p in pending):
             bad.append((i, code))
-        if op.startswith("ds_read") and in_asm:
+        target = registers(args.split(",")[0], kinds) if op.startswith("ds_read") and in_asm else None
+        if target:
             found += 1
-            pending.append(registers(args.split(",")[0]))
+            pending.append(target)
         elif op.startswith(("ds_", "s_load", "s_buffer_load", "s_memrealtime")):
             pending.append(None)
     return found, bad
@@ -116,9 +118,27 @@ def test_lds_reads_are_not_touched_before_the_wait_that_covers_them(src, name, i
         assert all(scratch[k] == 0 for k in mine), scratch
 
 
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not found")
+def test_attn_fwd64_reads_its_queries_into_the_registers_of_its_products():
+    """attn_fwd64's query fragments go from LDS into accumulation registers, waited for by hand (its other reads are checked above and by
+    the results: they stay in flight over the side path).  All of them, sixteen in each instance, none touched before the wait; and no
+    instance, the one for cut key ranges fills all 512 registers, keeps anything in scratch."""
+    kernels, scratch = device_code("attn_mfma64.hip")
+    mine = {k: v for k, v in kernels.items() if "attn_fwd64_kernel" in k}
+    assert len(mine) == 2, sorted(kernels)
+    for k, body in mine.items():
+        found, bad = reads_touched_too_early(body, "a")
+        assert found == 16 and not bad, (k, found, bad[:5])
+        assert scratch[k] == 0, scratch
+
+
 def test_the_check_finds_a_read_that_is_touched_too_early():
     read = "\t;;#ASMSTART\n\tds_read_b128 v[4:7], v1 offset:0\n\t;;#ASMEND\n"
     assert reads_touched_too_early(read + read.replace("4:7", "8:11") + "\ts_waitcnt lgkmcnt(1)\n\tv_add_f32_e32 v0, v4, v7\n") == (2, [])
     for early in ("\tv_mov_b32_e32 v0, v5\n", "\tscratch_store_dwordx4 off, v[4:7], off offset:16\n", "\ts_cbranch_scc1 .LBB0_1\n",
                   "\ts_waitcnt lgkmcnt(1)\n\tv_mov_b32_e32 v0, v5\n"):
         assert len(reads_touched_too_early(read + early)[1]) == 1
+    acc = read.replace("v[4:7]", "a[4:7]")
+    assert reads_touched_too_early(acc + "\ts_waitcnt lgkmcnt(0)\n\tv_accvgpr_read_b32 v0, a5\n", "a") == (1, [])
+    for early in ("\tv_accvgpr_read_b32 v0, a5\n", "\tv_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], a[4:7], 0\n", "\ts_branch .LBB0_1\n"):
+        assert len(reads_touched_too_early(acc + early, "a")[1]) == 1
