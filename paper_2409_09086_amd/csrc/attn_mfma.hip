@@ -1002,7 +1002,9 @@ ScorePlan score_plan(const Geometry& g, int ncol, int lq, bool has_part)
         // 2760 columns 18.5 / 16.0, 300 rows 21.5 / 18.8, 420 rows 24.4 / 22.3; 20 heads, 400 rows, 2000 columns 19.4 / 16.8)
         if (rsplit == 2 && g.d == 128 && niter < 8 && wgs256 >= 128) rsplit = 1;
     }
-    const bool wide = wgsw >= 200 || rsplit > 1;
+    // 256 columns only while they make one round: 288 workgroups of 256 columns / 160 of 512 (32 heads, 2075 to 2300 columns), us: 208 rows
+    // 19.9 / 15.4, 400 rows 26.7 / 20.5, 700 rows 35.3 / 26.6; 256 / 128 (1800 columns) 12.3 / 15.3, 15.9 / 20.2, 20.6 / 26.3.
+    const bool wide = (g.d == 128 && wgs256 > 256) || rsplit > 1;
     return ScorePlan{false, wide, wide ? nxw : (ncol + 255) / 256, rsplit};
 }
 

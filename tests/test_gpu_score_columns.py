@@ -22,6 +22,7 @@ pytestmark = pytest.mark.gpu
     (24, 24, 128, 1500, 300, 191, 0, "score_kernel"),         # six: two
     (24, 24, 128, 1500, 300, 223, 0, "score_kernel"),         # seven: three
     (40, 40, 128, 2900, 400, 159, 0, "score_kernel"),         # 512 columns per workgroup
+    (32, 32, 128, 2300, 500, 208, 0, "score_kernel"),         # 288 blocks of 256 columns are more than a round: 512 here too
     (3, 3, 128, 9000, 700, 543, 2, "score_kernel, sliced"),   # the last slice ends with one block
 ])
 def test_scores_of_candidates_in_stream_order(heads, kv, d, budget, recent, L, decoded, kernel):
