@@ -25,6 +25,7 @@ struct RowsArgsT {
     int pos0;
     int t, L, tc, Hq, Hkv, G, cap, max_chunk, ks, nsplit;
     int rg0;                   // first row group of the launch (attn_f32)
+    int beside;                // attn_rows: the row groups of a key are numbered beside each other, so many; 0: not
     uint32_t inv_g;            // see rows_token
     float c;                   // scale * log2(e); fp32: scale
 };

@@ -47,17 +47,17 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
     // several rounds of the chip, over more keys and values than the L2s hold (32 MB); they then get neighbouring ids of one residue
     // class mod 8, i.e. one XCD at one time, so that a key comes into its L2 once.  us with the merge: 64 tokens over 8256 rows of 32
     // heads, 134 MB, 384 workgroups 48.0 -> 43.5; 40 over 8232 46.1 -> 42.9; not where they fit: 64 over 2112 of 32 heads 26.6 / 26.9, 34
-    // tokens of 32 heads on 8 over 4130 30.1 / 31.4.
+    // tokens of 32 heads on 8 over 4130 30.1 / 31.4.  (The host says so: the grid's size is a trip to memory ahead of the first keys.)
     const int t = a.t;
     int sp = blockIdx.x, h = blockIdx.y, rg = blockIdx.z;
     if constexpr (NRB == 2) {
-        const unsigned pairs = gridDim.x * gridDim.y;
-        if (pairs * gridDim.z > (D == 64 ? 512u : 256u) && (pairs & 7) == 0 && (uint64_t)(t + a.L) * a.Hkv * (D * 4) > (48u << 20)) {
-            const unsigned id = blockIdx.x + gridDim.x * blockIdx.y + pairs * blockIdx.z, li = id >> 3;
-            const unsigned pair = li / gridDim.z * 8 + (id & 7);
-            rg = (int)(li % gridDim.z);
-            h = (int)(pair / gridDim.x);
-            sp = (int)(pair % gridDim.x);
+        if (a.beside) {                                        // row groups of the launch
+            const unsigned ns = (unsigned)a.nsplit, groups = (unsigned)a.beside;
+            const unsigned id = blockIdx.x + ns * (blockIdx.y + (unsigned)a.Hkv * blockIdx.z), li = id >> 3;
+            const unsigned pair = li / groups * 8 + (id & 7);
+            rg = (int)(li % groups);
+            h = (int)(pair / ns);
+            sp = (int)(pair % ns);
         }
     }
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
@@ -254,6 +254,30 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
     sweep(std::false_type{});
     if constexpr (APPEND)
         append_share(ap, sp + gridDim.x * (h + gridDim.y * rg), gridDim.x * gridDim.y * gridDim.z, tid, RW_NT);
+    // ---- decoding: tokens sp, sp + nsplit, .. become cache rows (read from the chunk tensors by everyone).  Where the last workgroup
+    // of a kv-head merges the pieces there is time for it while the partials are on their way, and the wavefront with the fewest
+    // keys does it first (ahead of the merge of the wavefronts 24 tokens after a prompt took 234.2 instead of 230.7 us); whole rows
+    // have gone to out by then, and the caller keeps out off k and v where the keys make one piece.  Groups of 32 rows are merged
+    // by a second launch, which waits for all of it: there it comes ahead (29 tokens of 8 x 64 heads on 2 over 3829 rows 12.9 against 13.2 us).
+    auto append_tokens = [&]() __attribute__((always_inline)) {
+        if (!a.pos || rg != 0 || sp >= a.L) return;
+        constexpr int VPR = D / 8;
+        const int from_last = NRB == 1 ? tid ^ (RW_NT - 64) : tid;
+        for (int i = sp + a.nsplit * (from_last / VPR); i < a.L; i += a.nsplit * (RW_NT / VPR)) {
+            const int x = from_last % VPR;
+            const size_t dst = ((size_t)h * a.cap + t + i) * D + x * 8, src = (size_t)i * runs.crs + x * 8;
+            *(u32x4*)(a.K + dst) = *(const u32x4*)(runs.kch + src);
+            *(u32x4*)(a.V + dst) = *(const u32x4*)(runs.vch + src);
+            if (x == 0) {
+                const size_t at = (size_t)h * a.cap + t + i;
+                a.pos[at] = a.pos0 + i;
+                a.score[at] = __builtin_inff();
+                a.rank[at] = t + i;                            // the newest tokens, in the next free physical rows
+                a.row[at] = t + i;
+            }
+        }
+    };
+    if constexpr (NRB == 2) append_tokens();
     // ---- merge the wavefronts: lane (row c16, group g4) holds O[row][16b + 4 g4 + i]
     // wavefront w's share: 16-byte piece p of row r in slot p ^ ((r ^ w) & 7) of the row, which keeps both eight rows and
     // eight wavefronts apart in the banks; rows that do not exist are left out
@@ -307,27 +331,7 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
             leave_row<D>(a, h, sp, row0 + r, d, add_tree(ps));
         }
     }
-    // ---- decoding: tokens sp, sp + nsplit, .. become cache rows (read from the chunk tensors by everyone).  There is time for
-    // it while the partials are on their way, and the wavefront with the fewest keys does it first (ahead of the merge of the
-    // wavefronts 24 tokens after a prompt took 234.2 instead of 230.7 us).  Whole rows have gone to out by then: the caller
-    // keeps out off k and v where the keys make one piece.
-    if (a.pos && rg == 0 && sp < a.L) {
-        constexpr int VPR = D / 8;
-        const int from_last = tid ^ (RW_NT - 64);
-        for (int i = sp + a.nsplit * (from_last / VPR); i < a.L; i += a.nsplit * (RW_NT / VPR)) {
-            const int x = from_last % VPR;
-            const size_t dst = ((size_t)h * a.cap + t + i) * D + x * 8, src = (size_t)i * runs.crs + x * 8;
-            *(u32x4*)(a.K + dst) = *(const u32x4*)(runs.kch + src);
-            *(u32x4*)(a.V + dst) = *(const u32x4*)(runs.vch + src);
-            if (x == 0) {
-                const size_t at = (size_t)h * a.cap + t + i;
-                a.pos[at] = a.pos0 + i;
-                a.score[at] = __builtin_inff();
-                a.rank[at] = t + i;                            // the newest tokens, in the next free physical rows
-                a.row[at] = t + i;
-            }
-        }
-    }
+    if constexpr (NRB == 1) append_tokens();
     if (a.nsplit == 1 || !a.arrived) return;
     if constexpr (NRB == 1) {                                  // tickets are given out with a single row group only
         // Every workgroup waits until its own partials have been written through, then takes a ticket; the one of this
@@ -392,10 +396,13 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
 }
 
 template <int D, int NRB, bool EXACT>
-void launch_rows_cfg(const RowsArgs& a, const AppendJob& ap, hipStream_t st)
+void launch_rows_cfg(RowsArgs a, const AppendJob& ap, hipStream_t st)
 {
     constexpr int ROWS = 16 * NRB;
     const dim3 grid((unsigned)a.nsplit, (unsigned)a.Hkv, (unsigned)((a.L * a.G + ROWS - 1) / ROWS));
+    const unsigned pairs = grid.x * grid.y;
+    a.beside = NRB == 2 && pairs * grid.z > (D == 64 ? 512u : 256u) && pairs % 8 == 0 && (uint64_t)(a.t + a.L) * a.Hkv * (D * 4) > (48u << 20)
+                   ? (int)grid.z : 0;
     if constexpr (!EXACT)
         if (ap.k) {
             hipLaunchKernelGGL((attn_rows_kernel<D, NRB, false, true>), grid, dim3(RW_NT), 0, st, a, ap);
