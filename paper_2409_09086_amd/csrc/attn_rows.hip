@@ -355,8 +355,8 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
         };
         constexpr int DIRECT = 4, PER_ROW = D / 4 * RW_CLASSES;
         static_assert(PER_ROW % RW_NT == 0 || RW_NT % PER_ROW == 0, "a row takes whole rounds of the threads, or a round whole rows");
-        if (a.nsplit <= RW_CLASSES && M <= DIRECT) {
-            constexpr int U = DIRECT * PER_ROW / RW_NT;
+        auto direct = [&](auto rounds) __attribute__((always_inline)) {   // of the threads over the rows
+            constexpr int U = decltype(rounds)::value;
             const int c = tid % RW_CLASSES, cc = min(c, a.nsplit - 1);
             const auto src = __builtin_amdgcn_make_buffer_rsrc((void*)(a.part_o + at * D), 0, parts * D * 4, 0x00020000);
             float2 ml[U];
@@ -376,6 +376,12 @@ attn_rows_kernel(RowsArgs a, AppendJob ap)
                 ps.add_lanes<RW_CLASSES>();
                 if (c == 0) store_row(r, 4 * (x % (D / 4)), ps);
             }
+        };
+        if (a.nsplit <= RW_CLASSES && M <= DIRECT) {
+            constexpr int ALL = DIRECT * PER_ROW / RW_NT;
+            if (M * PER_ROW <= RW_NT) direct(std::integral_constant<int, 1>{});
+            else if (ALL > 2 && M * PER_ROW <= 2 * RW_NT) direct(std::integral_constant<int, 2>{});
+            else direct(std::integral_constant<int, ALL>{});
             return;
         }
         static_assert(RW_TICKET_PARTS * D * 4 <= RW_NW * C::STAGE && RW_TICKET_PARTS <= RW_NT, "the partials reuse the buffers of the tiles");
