@@ -675,8 +675,10 @@ static int decode_some(infmllm_stream* s, const void* q, const void* k, const vo
     hipError_t e;
     CacheView att = s->cache;
     const bool rope = s->rope_base > 0.0, in_place = !s->mfma() || (aligned16(k) && aligned16(v) && over < (t + T <= s->dec_keys ? 1 : 2));
-    if (rope || !in_place)
-        if ((e = launch_append(append_job(s->g, s->cache, k, v, t, T, s->streamed, nullptr, nullptr), s->st)) != hipSuccess) return fail_hip(e, "decode: append");
+    if (rope || !in_place) {
+        e = launch_append(append_job(s->g, s->cache, k, v, t, T, s->streamed, nullptr, nullptr), s->st);
+        if (e != hipSuccess) return fail_hip(e, "decode: append");
+    }
     if (rope) {
         // the tokens' rows enter the cache as given; the decoding kernels see the turned copies (and put the
         // turned keys at rows t.. of K_rot themselves)

@@ -998,8 +998,9 @@ ScorePlan score_plan(const Geometry& g, int ncol, int lq, bool has_part)
         if (rsplit > 4) rsplit = 4;
         if (rsplit > niter / 2) rsplit = niter / 2;
         if (rsplit < 1 || !has_part || wgsw * rsplit * (wcols / 256) > SCORE_SPLIT_WGS) rsplit = 1;
-        // two slices of few rows: their sums cost more than the narrower columns, if those fill half the chip (us, two slices / none, 32 heads on 16, 193 rows and
-        // 2760 columns 18.5 / 16.0, 300 rows 21.5 / 18.8, 420 rows 24.4 / 22.3; 20 heads, 400 rows, 2000 columns 19.4 / 16.8)
+        // two slices of few rows: their sums cost more than the narrower columns, if those fill half the chip (us, two slices /
+        // none, 32 heads on 16, 193 rows and 2760 columns 18.5 / 16.0, 300 rows 21.5 / 18.8, 420 rows 24.4 / 22.3; 20 heads, 400
+        // rows, 2000 columns 19.4 / 16.8)
         if (rsplit == 2 && g.d == 128 && niter < 8 && wgs256 >= 128) rsplit = 1;
     }
     // 256 columns only while they make one round: 288 workgroups of 256 columns / 160 of 512 (32 heads, 2075 to 2300 columns), us: 208 rows

@@ -27,8 +27,7 @@
 // wait for those that see most keys.  Every key range is then cut in two pieces, which two workgroups go through; the one that
 // arrives last adds the other's (o, m, l), 132 KB, in registers, as they were left: 16-byte stores and loads of whole
 // kilobytes that bypass the L2 caches (stored four bytes a lane, and always by both pieces, the exchange took 23 us; now about 5).
-// Launch, us, before (attn_fwd) and after: 32 heads on 8, 1024 rows on 5120 keys 90.5 -> 79.9; 32 heads, 576 rows on 4672
-// 74.8 -> 69.3.
+// Launch, us, before (attn_fwd) and after: 32 heads on 8, 1024 rows on 5120 keys 90 -> 80; 32 heads, 576 rows on 4672 73 -> 69.
 //
 // Under the causal mask the chunk's later rows see more keys.  A wavefront's two blocks are therefore one from
 // the front and one from the back of the head's rows, which gives every wavefront the same number of (row, key)
@@ -673,8 +672,9 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
 
     // ---- normalise and store: lane (row l32, half hh) holds O[row][32b + 8(i/4) + 4hh + i%4] in o[x][b][i] ----
     // Through LDS, so that a store takes four whole rows: eight bytes of 32 rows each, straight from the registers, took
-    // 3.4 us, so 2.1 (both together: 275 -> 272 us a launch of 2048 rows on 8192 + 2048 keys of 32 heads).  The tiles' buffers are free (the loads still in flight go to the scratch area); a wavefront has
-    // 16 KB of them to itself.  Piece p (eight columns) of row r lies in slot p ^ (r & 15).
+    // 3.4 us, so 2.1 (with the queries' way in, 1 % of a launch of 2048 rows on 8192 + 2048 keys of 32 heads: 275 -> 272 us).
+    // The tiles' buffers are free (the loads still in flight go to the scratch area); a wavefront has 16 KB of them to itself.
+    // Piece p (eight columns) of row r lies in slot p ^ (r & 15).
     char* const olds = smem + wave * (64 * ROWB);
     int el = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));   // the lane
     asm volatile("" : "+v"(el));                             // the compiler would keep what the prologue made of it through the loop
@@ -716,7 +716,8 @@ attn_fwd64_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K
                         __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(o[x][b][4 * q4]), __float_as_uint(o[x][b][4 * q4 + 1]),
                                                                      __float_as_uint(o[x][b][4 * q4 + 2]), __float_as_uint(o[x][b][4 * q4 + 3])},
                                                                dst, voff, soff + (16 * x + 4 * b + q4) * 1024, 16 /* sc1 */);
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(m_ref[0]), __float_as_uint(ltot[0]), __float_as_uint(m_ref[1]), __float_as_uint(ltot[1])},
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(m_ref[0]), __float_as_uint(ltot[0]),
+                                                         __float_as_uint(m_ref[1]), __float_as_uint(ltot[1])},
                                                    dst, voff, soff + (VECS - 1) * 1024, 16);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
@@ -801,7 +802,8 @@ hipError_t launch_attn_mfma64(const Geometry& g, const CacheView& c, const KeySo
 #define INFMLLM_FWD64(P)                                                                                                   \
     hipLaunchKernelGGL(attn_fwd64_kernel<P>, dim3(units * P), dim3(w64::NT), 0, st, (const uint16_t*)q, (const uint16_t*)c.K, \
                        (const uint16_t*)c.V, (const uint16_t*)ks.k, (const uint16_t*)ks.v, ks.rows, (uint16_t*)out, lse, t, L, \
-                       g.Hq, g.G, g.cap, g.max_chunk, hpw, ntile, ny, (float)(g.scale * (double)LOG2E), sc.part, sc.arrived, g.cut_hold, sc.arrived + sc.units, ap)
+                       g.Hq, g.G, g.cap, g.max_chunk, hpw, ntile, ny, (float)(g.scale * (double)LOG2E), sc.part, sc.arrived, \
+                       g.cut_hold, sc.arrived + sc.units, ap)
     if (pieces == 2) INFMLLM_FWD64(2);
     else INFMLLM_FWD64(1);
 #undef INFMLLM_FWD64
